@@ -7,7 +7,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["api.hip", "assemble.hip", "apply.hip", "gemm.hip", "learned.hip", "learned_api.hip", "plgf.hip", "hmat.hip",
+SOURCES = ["api.hip", "assemble.hip", "apply.hip", "gemm.hip", "gemm_table.hip", "learned.hip", "learned_api.hip", "plgf.hip", "hmat.hip",
            "probe.hip", "plan.cpp"]
 LIB = os.path.join(HERE, "libfbc.so")
 

@@ -204,8 +204,15 @@ static void compute_windows(fbc_ctx* c, const std::vector<double>& rho_cut, int 
     const bool dt = is_table_form(c->opt.form);
     for (CellPlan& p : c->cells) {
         PlanWindows w;
-        plan_windows(PlanGeom{p.n_i, p.n_b, p.cols_i.data(), p.cols_b.data()}, p.nm, p.mp, p.kp, dt, rows_tile,
-                     c->nz_max / p.nz, rho_cut, w);
+        const PlanGeom g{p.n_i, p.n_b, p.cols_i.data(), p.cols_b.data()};
+        if (dt) {
+            std::vector<PlanRange> tiles, chunks;
+            for (int b = 0; b < p.n_b; b += TAB_COLS) tiles.push_back({b, std::min(p.n_b, b + TAB_COLS)});
+            for (int i = 0; i < p.n_i; i += TAB_COLS) chunks.push_back({i, std::min(p.n_i, i + TAB_COLS)});
+            plan_windows_ranges(g, p.nm, tiles, chunks, c->nz_max / p.nz, rho_cut, w);
+        } else {
+            plan_windows(g, p.nm, p.mp, p.kp, false, rows_tile, c->nz_max / p.nz, rho_cut, w);
+        }
         p.n_tiles = w.n_tiles;
         p.n_chunks = w.n_chunks;
         p.win_start.swap(w.win_start);
@@ -286,8 +293,11 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
         // than the 21 of 2 GiB, within 1 % of 80 or 171)
         c->gen_modes = (int)std::max<int64_t>(1, std::min<int64_t>(T, ((int64_t)4 << 30) / std::max<int64_t>(1, n_off * 96)));
         if (c->opt.gen_modes > 0) c->gen_modes = std::min(c->opt.gen_modes, T);
-        if ((s = dev_alloc(c, (void**)&c->gen, (int64_t)c->gen_modes * n_off * 96)) != FBC_OK) return s;
-        c->scratch_bytes += (int64_t)c->gen_modes * n_off * 96;
+        // one record of zeros behind the slices stands for every offset that is not generated
+        const int64_t gen_bytes = (int64_t)c->gen_modes * n_off * 96;
+        if ((s = dev_alloc(c, (void**)&c->gen, gen_bytes + 96)) != FBC_OK) return s;
+        HIPCHK(c, hipMemsetAsync((char*)c->gen + gen_bytes, 0, 96, st));
+        c->scratch_bytes += gen_bytes;
     } else if ((s = talloc((void**)&c->tab, (int64_t)T * n_off * 96)) != FBC_OK) {
         cleanup();
         return s;
@@ -538,7 +548,7 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
 static void product_stats(fbc_ctx* c) {
     const int form = c->opt.form;
     const bool dt = is_table_form(form);
-    const int rows_tile = dt ? 96 : gemm_tile_rows(form, c->ctmax);
+    const int rows_tile = dt ? 3 * TAB_COLS : gemm_tile_rows(form, c->ctmax);
     const double eb = (form == FBC_FORM_FP64) ? 8.0 : 4.0;       // stored bytes per real entry
     const double fb = (form == FBC_FORM_FP64 || dt) ? 16.0 : 8.0; // bytes per complex f^
     double bytes = 0, flops = 0, area = 0, kept = 0;
@@ -550,7 +560,7 @@ static void product_stats(fbc_ctx* c) {
                 const int ws = p.win_start[(size_t)m * p.n_tiles + tl];
                 const int wl = p.win_len[(size_t)m * p.n_tiles + tl];
                 for (int ch = 0; ch < p.n_chunks; ++ch) {
-                    const double kc = dt ? 3.0 * std::max(0, std::min(p.n_i, 8 * (ch + 1)) - 8 * ch)
+                    const double kc = dt ? 3.0 * std::max(0, std::min(p.n_i, TAB_COLS * (ch + 1)) - TAB_COLS * ch)
                                          : (double)std::max(0, std::min(p.K, 32 * (ch + 1)) - 32 * ch);
                     area += rows * kc;
                     if (((ch - ws + p.n_chunks) % p.n_chunks) < wl) {
@@ -597,9 +607,9 @@ static void unit_jobs(const fbc_ctx* c, const Unit& u, int nsplit, std::vector<G
     const int form = c->opt.form;
     const CellPlan& p = c->cells[u.cell];
     const bool dt = is_table_form(form);
-    const int tile_rows = dt ? 96 : gemm_tile_rows(form, c->ctmax);
+    const int tile_rows = dt ? 3 * TAB_COLS : gemm_tile_rows(form, c->ctmax);
     const int tiles = p.mp / tile_rows;
-    const int unit_k = dt ? 8 : 64;
+    const int unit_k = dt ? TAB_COLS : 64;
     for (int ks = 0; ks < nsplit; ++ks)
         for (int tl = 0; tl < tiles; ++tl) {
             // the K slice ks of this tile's window (cyclic; empty slices write zeros)
@@ -634,8 +644,8 @@ static std::vector<GemmJob> build_jobs(const fbc_ctx* c, int nsplit, int order, 
     for (int ci = 0; ci < (int)c->cells.size(); ++ci) {
         const CellPlan& p = c->cells[ci];
         const int mult = c->nz_max / p.nz;
-        const int64_t tile_rows = dt ? 96 : gemm_tile_rows(c->opt.form, c->ctmax);
-        const int64_t unit_k = dt ? 48 : 64;
+        const int64_t tile_rows = dt ? 3 * TAB_COLS : gemm_tile_rows(c->opt.form, c->ctmax);
+        const int64_t unit_k = dt ? 6 * TAB_COLS : 64;
         for (int m = 0; m < p.nm; ++m) {
             int64_t cost = 0;
             for (int tl = 0; tl < p.n_tiles; ++tl) cost += p.win_len[(size_t)m * p.n_tiles + tl];
@@ -675,16 +685,21 @@ static std::vector<GemmJob> build_jobs(const fbc_ctx* c, int nsplit, int order, 
     }
     size_t mx = 0;
     for (auto& v : per_xcd) mx = std::max(mx, v.size());
+    // consecutive work groups go to consecutive XCDs: a work group of the offset-table
+    // products takes four consecutive jobs, one of the dense products one
+    const size_t per_group = dt ? 4 : 1;
+    mx = (mx + per_group - 1) / per_group * per_group;
     out.reserve(mx * 8);
-    for (size_t k = 0; k < mx; ++k)
-        for (int x = 0; x < 8; ++x) {
-            if (k < per_xcd[x].size()) out.push_back(per_xcd[x][k]);
-            else {
-                GemmJob z{};
-                z.mb = 0;      // empty job: every wave returns at once
-                out.push_back(z);
+    for (size_t k0 = 0; k0 < mx; k0 += per_group)
+        for (int x = 0; x < 8; ++x)
+            for (size_t k = k0; k < k0 + per_group; ++k) {
+                if (k < per_xcd[x].size()) out.push_back(per_xcd[x][k]);
+                else {
+                    GemmJob z{};
+                    z.mb = 0;      // empty job: every wave returns at once
+                    out.push_back(z);
+                }
             }
-        }
     return out;
 }
 
@@ -804,8 +819,8 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         p.K = 3 * p.n_i;
         p.M = 3 * p.n_b;
         if (is_table_form(form)) {
-            p.kp = 6 * (int)roundup(p.n_i, 8);       // whole chunks of 8 interface columns
-            p.mp = (int)roundup(p.M, 96);            // whole tiles of 32 pad columns
+            p.kp = 6 * (int)roundup(p.n_i, TAB_COLS);       // whole chunks of 16 interface columns
+            p.mp = 3 * (int)roundup(p.n_b, TAB_COLS);       // whole tiles of 16 pad columns
         } else {
             p.kp = (int)roundup(6 * (int64_t)p.n_i, 64);
             p.mp = (int)roundup(p.M, rows_tile);
@@ -826,7 +841,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         b_off += b_mode_elems(form, p) * p.nm;
         p.c_split = (int64_t)p.nm * p.ct * p.mp * 16;
         if (is_table_form(form)) {
-            tiles_total += (int64_t)p.nm * (p.mp / 96);
+            tiles_total += (int64_t)p.nm * (p.mp / (3 * TAB_COLS));
             kslices_max = std::min(kslices_max, (p.n_i + 7) / 8);
         } else {
             tiles_total += (int64_t)p.nm * (p.mp / rows_tile);
@@ -924,12 +939,6 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         HIPCHK(c, hipMemcpyAsync(p.cols_i_d, p.cols_i.data(), (size_t)p.n_i * 8, hipMemcpyHostToDevice, st));
         HIPCHK(c, hipMemcpyAsync(p.cols_b_d, p.cols_b.data(), (size_t)p.n_b * 8, hipMemcpyHostToDevice, st));
     }
-    {
-        std::vector<CellDev> cd;
-        for (auto& p : c->cells) cd.push_back(CellDev{p.cols_b_d, p.cols_i_d, p.n_b, p.n_i});
-        if ((s = dev_alloc(c, (void**)&c->celldev, (int64_t)cd.size() * sizeof(CellDev))) != FBC_OK) goto fail_out;
-        HIPCHK(c, hipMemcpyAsync(c->celldev, cd.data(), cd.size() * sizeof(CellDev), hipMemcpyHostToDevice, st));
-    }
     HIPCHK(c, hipMemsetAsync(c->bfrag, 0, (size_t)(b_off * b_elem_bytes(form)), st));
     HIPCHK(c, hipMemsetAsync(c->status, 0, 128, st));
     {
@@ -956,6 +965,28 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         }
         (void)hipStreamSynchronize(st);
         (void)hipFree(sn_d);
+    }
+    if (is_table_form(form)) {
+        // column keys of the offset-table products (see CellDev)
+        std::vector<CellDev> cd;
+        std::vector<int32_t> keys;
+        for (auto& p : c->cells) {
+            const int nb = (int)roundup(p.n_b, TAB_COLS), ni = (int)roundup(p.n_i, TAB_COLS);
+            cd.push_back(CellDev{(int64_t)keys.size(), (int64_t)keys.size() + nb});
+            for (int b = 0; b < nb; ++b) {
+                const int q = std::min(b, p.n_b - 1);
+                keys.push_back((p.cols_b[2 * q] - c->d1min) * c->w2 + p.cols_b[2 * q + 1] - c->d2min);
+            }
+            for (int x = 0; x < ni; ++x) {             // [chunk][g][q] holds column 16 chunk + 4 q + g
+                const int q = std::min((x & ~15) + 4 * (x & 3) + ((x >> 2) & 3), p.n_i - 1);
+                keys.push_back(p.cols_i[2 * q] * c->w2 + p.cols_i[2 * q + 1]);
+            }
+        }
+        if ((s = dev_alloc(c, (void**)&c->colkeys, (int64_t)keys.size() * 4)) != FBC_OK) goto fail_out;
+        if ((s = dev_alloc(c, (void**)&c->celldev, (int64_t)cd.size() * sizeof(CellDev))) != FBC_OK) goto fail_out;
+        HIPCHK(c, hipMemcpyAsync(c->colkeys, keys.data(), keys.size() * 4, hipMemcpyHostToDevice, st));
+        HIPCHK(c, hipMemcpyAsync(c->celldev, cd.data(), cd.size() * sizeof(CellDev), hipMemcpyHostToDevice, st));
+        HIPCHK(c, hipStreamSynchronize(st));
     }
     product_stats(c);
     if (form == FBC_FORM_SURROGATE) c->nsplit = 1;     // slices are generated per mode chunk
@@ -1040,19 +1071,20 @@ static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st) {
             ql.nl = 1;
             for (int l = 0; l < 9; ++l) ql.start[l] = j1 - j0;
             ql.start[0] = 0;
-            launch_gemm_dtab(st, c->jobs + j0, j1 - j0, c->ctmax, c->gen, (int64_t)t0 * c->n_offsets * 6,
-                             (const double*)c->bfrag, c->cbuf, c->celldev, c->lut, c->d1min, c->d2min, c->w2,
-                             c->n_need, c->n_offsets, c->job_order == 3 ? &ql : nullptr, c->opt.table_fp32);
+            const TabView tv{c->gen, (int64_t)t0 * c->n_offsets * 6, c->lut, c->colkeys, c->n_need, c->n_offsets,
+                             (int64_t)c->gen_modes * c->n_offsets};
+            launch_gemm_dtab(st, c->jobs + j0, j1 - j0, c->ctmax, tv, (const double*)c->bfrag, c->cbuf, c->celldev,
+                             c->job_order == 3 ? &ql : nullptr, c->opt.table_fp32);
         }
     } else if (form == FBC_FORM_DTABLE_FP64 && c->hmat) {
         const CellPlan& p = c->cells[0];          // one cell (checked when attached)
         hmat_enqueue_pipeline(c->hmat, (const double*)c->bfrag + p.b_off, b_mode_elems(form, p), p.kp,
                               c->cbuf + p.c_off, p.mp, p.nm, p.ct, st);
-    } else if (form == FBC_FORM_DTABLE_FP64)
-        launch_gemm_dtab(st, c->jobs, c->njobs, c->ctmax, c->tab, 0, (const double*)c->bfrag, c->cbuf,
-                         c->celldev, c->lut, c->d1min, c->d2min, c->w2, nullptr, c->n_offsets,
+    } else if (form == FBC_FORM_DTABLE_FP64) {
+        const TabView tv{c->tab, 0, c->lut, c->colkeys, nullptr, c->n_offsets, 0};
+        launch_gemm_dtab(st, c->jobs, c->njobs, c->ctmax, tv, (const double*)c->bfrag, c->cbuf, c->celldev,
                          c->job_order >= 3 ? &c->lists : nullptr, c->opt.table_fp32);
-    else
+    } else
         launch_gemm(st, form, c->jobs, c->njobs, c->ctmax, c->store, c->bfrag, c->cbuf,
                     c->job_order >= 3 ? &c->lists : nullptr, c->variant);
     if (tm) {
@@ -1274,7 +1306,7 @@ static uint64_t tune_key(const fbc_ctx* c) {
         const unsigned char* b = (const unsigned char*)p;
         for (size_t i = 0; i < n; ++i) h = (h ^ b[i]) * 1099511628211ull;
     };
-    const int version = 1;
+    const int version = 2;
     mix(&version, sizeof version);
     mix(&c->opt.form, sizeof c->opt.form);
     mix(&c->opt.skip_tol, sizeof c->opt.skip_tol);
@@ -1590,7 +1622,7 @@ extern "C" fbc_status fbc_get_info(const fbc_ctx* c, fbc_info* info) {
     info->skipped_fraction = c->skipped_fraction;
     info->kernel_variant = c->variant;
     info->n_variants = n_variants(c);
-    const std::string shape = is_table_form(c->opt.form) ? std::string("offset table, 32 pad columns x 8 interface columns per step")
+    const std::string shape = is_table_form(c->opt.form) ? std::string("offset table, 16 pad columns x 16 interface columns per step and wave")
                                                          : gemm_shape(c->opt.form, c->ctmax, c->variant);
     std::snprintf(info->kernel_shape, sizeof info->kernel_shape, "%s", shape.c_str());
     return FBC_OK;

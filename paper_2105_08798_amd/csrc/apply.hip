@@ -197,7 +197,7 @@ __device__ inline float bf2f(unsigned short h) { return __uint_as_float((unsigne
 
 template <int FORM>
 __device__ inline void put_b(void* bm, int n, int kq, int kp, double v) {
-    if (FORM == FBC_FORM_FP64 || FORM == FBC_FORM_DTABLE_FP64) {
+    if (FORM == FBC_FORM_FP64) {
         ((double*)bm)[frag_off_f64(n, kq, kp)] = v;
     } else if (FORM == FBC_FORM_FP32) {
         ((float*)bm)[frag_off_f32(n, kq, kp)] = (float)v;
@@ -221,7 +221,7 @@ __device__ inline void put_b(void* bm, int n, int kq, int kp, double v) {
 // (kq, kq + 4, kq + 8, kq + 12), split units 8 consecutive kq (hi run, lo run 1 KiB on).
 template <int FORM, int NV>
 __device__ inline void put_b_units(void* bm, int n, int kq0, int kp, const double (&v)[NV]) {
-    if constexpr (FORM == FBC_FORM_FP64 || FORM == FBC_FORM_DTABLE_FP64) {
+    if constexpr (FORM == FBC_FORM_FP64) {
         static_assert(NV == 8, "FP64 units cover 8 K' entries");
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -341,6 +341,30 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
         (int64_t)16 * ct * kp * ((FORM == FBC_FORM_SPLIT_BF16 || FORM == FBC_FORM_SPLIT_FP16) ? 2 : 1);
     const int tile = r >> 3, j = r & 7;
     const int nre = 16 * tile + j, nim = nre + 8;
+    if constexpr (FORM == FBC_FORM_DTABLE_FP64) {
+        // offset-table products: one 16-byte pair per entry, four interface columns adjacent
+        const int nch = kp / 96;
+        for (int t = threadIdx.x; t < nm * tc; t += NTH) {
+            const int m = t / tc, c = t - m * tc, k = k0 + c;
+            if (k >= K) continue;
+            const double2 z = lds[(c >> 1) * ss + m];
+            const double2 zn = lds[(c >> 1) * ss + ((nz - m) & (nz - 1))];
+            double fr, fi;
+            if ((c & 1) == 0) {
+                fr = 0.5 * (z.x + zn.x);
+                fi = 0.5 * (z.y - zn.y);
+            } else {
+                fr = 0.5 * (z.y + zn.y);
+                fi = 0.5 * (zn.x - z.x);
+            }
+            if (m == 0 || 2 * m == nz) fi = 0.0;
+            double* bm = (double*)bfrag + m * mode_elems;
+            *(double2*)(bm + tab_frag_off(nre, k, nch)) = make_double2(fr, -fi);
+            *(double2*)(bm + tab_frag_off(nim, k, nch)) = make_double2(fi, fr);
+        }
+        __syncthreads();        // the next chunk overwrites the LDS sequences
+        continue;
+    }
     // G consecutive complex columns per thread, written as whole 16-byte units
     constexpr int G = (FORM == FBC_FORM_FP32) ? 8 : 4;
     if (tc % G == 0) {
@@ -372,7 +396,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
                 vim[2 * q + 1] = fr;
             }
             void* bm;
-            if (FORM == FBC_FORM_FP64 || FORM == FBC_FORM_DTABLE_FP64)
+            if (FORM == FBC_FORM_FP64)
                 bm = (double*)bfrag + m * mode_elems;
             else if (FORM == FBC_FORM_FP32)
                 bm = (float*)bfrag + m * mode_elems;
@@ -399,7 +423,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
         }
         if (m == 0 || 2 * m == nz) fi = 0.0;
         void* bm;
-        if (FORM == FBC_FORM_FP64 || FORM == FBC_FORM_DTABLE_FP64)
+        if (FORM == FBC_FORM_FP64)
             bm = (double*)bfrag + m * mode_elems;
         else if (FORM == FBC_FORM_FP32)
             bm = (float*)bfrag + m * mode_elems;
@@ -461,7 +485,8 @@ void launch_line_rfft(hipStream_t st, int form, const double* f, const double* t
         case FBC_FORM_FP32: RF_LAUNCH(FBC_FORM_FP32); break;
         case FBC_FORM_SPLIT_FP16: RF_LAUNCH(FBC_FORM_SPLIT_FP16); break;
         case FBC_FORM_SPLIT_BF16: RF_LAUNCH(FBC_FORM_SPLIT_BF16); break;
-        default: RF_LAUNCH(FBC_FORM_FP64); break;
+        case FBC_FORM_FP64: RF_LAUNCH(FBC_FORM_FP64); break;
+        default: RF_LAUNCH(FBC_FORM_DTABLE_FP64); break;      // the offset-table forms
     }
 #undef RF_LAUNCH
 }
@@ -1408,6 +1433,8 @@ void apply_kernels_init() {
     {
         const int lim = 160 * 1024;
         (void)hipFuncSetAttribute((const void*)k_line_rfft<FBC_FORM_FP64, 1024>, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
+        (void)hipFuncSetAttribute((const void*)k_line_rfft<FBC_FORM_DTABLE_FP64, 1024>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, lim);
         (void)hipFuncSetAttribute((const void*)k_line_rfft<FBC_FORM_FP32, 1024>, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
         (void)hipFuncSetAttribute((const void*)k_line_rfft<FBC_FORM_SPLIT_BF16, 1024>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lim);

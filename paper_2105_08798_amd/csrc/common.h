@@ -98,7 +98,7 @@ struct GemmJob {
     int32_t rb0;     // first row block of this tile
     int32_t ct;      // column tiles (8 RHS each)
     int32_t cell;    // cell index (offset form)
-    // K' range [k0, k1) (dense forms) or interface columns [k0, k1) (offset forms); the
+    // K' range [k0, k1) (dense forms) or interface columns [k0, k1) (offset forms, multiples of 16); the
     // range is cyclic: indices at or beyond the padded K wrap to its start (windows around
     // the non-negligible blocks of a tile may straddle the end); k0 == k1: empty (zeros)
     int32_t k0, k1;
@@ -121,11 +121,34 @@ struct PqLists {
 // Physical index of a step of a cyclic K range (idx < 2 n).
 __host__ __device__ inline int wrap_k(int idx, int n) { return idx >= n ? idx - n : idx; }
 
-// Per-cell device view used by the offset-table product kernel.
+// B fragments of the offset-table products, in the K order of their kernel (chunks of 16
+// interface columns; column 16 chunk + 4 q + g in lane group g): per column tile and chunk
+// 12 steps (q, d) of 64 units (Re- and Im-part operand), column n's four units of a step
+// adjacent as in the dense forms (bpos).  Element offset of the pair for B column n and
+// complex column k = 3 i + d; nch chunks.
+__host__ __device__ inline int64_t tab_frag_off(int n, int k, int nch) {
+    const int i = k / 3, d = k - 3 * i;
+    const int64_t step = ((int64_t)(n >> 4) * nch + (i >> 4)) * 12 + 3 * ((i >> 2) & 3) + d;
+    return (step * 64 + (((n & 15) << 2) | (i & 3))) << 1;
+}
+
+// Per-cell device view used by the offset-table product kernel: the column keys n1 w2 + n2
+// (their differences index the offset lookup), pad columns up to whole tiles of 16 (the last
+// column repeated), interface columns up to whole chunks of 16 in the order [chunk][g][q].
 struct CellDev {
-    const int32_t* cols_b;   // [n_b][2]
-    const int32_t* cols_i;   // [n_i][2]
-    int32_t n_b, n_i;
+    int64_t key_b, key_i;    // offsets into TabView::keys
+};
+
+// The table of an offset-table product: `tab` starts at element a_base of the whole table
+// (generated tables hold a few modes at a time); need (or NULL): offsets present per table
+// mode, every other one reads as the record zero_rec of `tab`.
+struct TabView {
+    const double2* tab;
+    int64_t a_base;
+    const int32_t* lut;      // offset number by key difference
+    const int32_t* keys;     // column keys of every cell (CellDev)
+    const int32_t* need;
+    int64_t n_off, zero_rec;
 };
 
 // Device-side status latch bits

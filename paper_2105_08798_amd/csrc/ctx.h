@@ -63,6 +63,7 @@ struct fbc_ctx {
     int32_t* lut = nullptr;
     int d1min = 0, d2min = 0, w2 = 0;
     CellDev* celldev = nullptr;
+    int32_t* colkeys = nullptr;     // column keys of the offset-table products (see CellDev)
     // surrogate form: ragged exact table, offsets by increasing distance, generated slices
     const fbc_sur* sur = nullptr;
     double2* exact_tab = nullptr;    // mode t: the first n_exact[t] offsets at ex_off[t] (x 6)

@@ -16,10 +16,9 @@
 #include <cstdint>
 
 #include "kernels.h"
+#include "pq.h"
 
 #include <algorithm>
-#include <map>
-#include <mutex>
 
 static __device__ inline void store_c_f64(double* __restrict__ c, const GemmJob& jb, int rb,
                                           int ctile, int lane, const d4_t& acc) {
@@ -58,64 +57,13 @@ __device__ inline float4 ld_stream(const float4* p) {
 __device__ inline bf8_t ld_stream(const bf8_t* p) { return __builtin_nontemporal_load(p); }
 __device__ inline h8_t ld_stream(const h8_t* p) { return __builtin_nontemporal_load(p); }
 
-// Persistent work-queue form of the product kernels: as many work groups as fit on the
-// chip at once, each taking the next job of its list from a device counter until the
+// Persistent work-queue form of the product kernels (pq.h): as many work groups as fit on
+// the chip at once, each taking the next job of its list from a device counter until the
 // lists are exhausted (with a list longest first, the groups that finish early take the
 // short jobs: dynamic longest-processing-time scheduling of uneven jobs).  With one list
 // per XCD (PqLists), the groups of an XCD work through consecutive row tiles of the same
 // mode together, so the f^ fragments of their overlapping K windows are fetched into that
 // XCD's L2 once; a group whose list is exhausted takes jobs from the other lists in turn.
-// The last group to leave sets the counters back to zero for the next launch (so the
-// launch can be replayed from a graph).  `cur` (thread 0's) counts the lists this group
-// has exhausted; every group leaves once it has drawn past the end of all of them.
-__device__ inline int pq_next(const PqLists& q, int* slot, int& cur) {
-    if (threadIdx.x == 0) {
-        const int home = q.nl > 1 ? (int)(blockIdx.x % q.nl) : 0;
-        int j = 0x7fffffff;
-        while (cur < q.nl) {
-            const int l = (home + cur) % q.nl;
-            const int s = atomicAdd(&q.ctr[l], 1);
-            if (s < q.start[l + 1] - q.start[l]) {
-                j = q.start[l] + s;
-                break;
-            }
-            ++cur;
-        }
-        *slot = j;
-    }
-    __syncthreads();
-    const int j = __builtin_amdgcn_readfirstlane(*slot);   // uniform: the job fields go to SGPRs
-    __syncthreads();                     // every thread has read the slot; LDS of the last job free
-    return j;
-}
-__device__ inline void pq_done(const PqLists& q) {
-    if (threadIdx.x == 0) {
-        __threadfence();
-        if (atomicAdd(&q.ctr[8], 1) == (int)gridDim.x - 1) {
-            for (int l = 0; l < q.nl; ++l) atomicExch(&q.ctr[l], 0);
-            atomicExch(&q.ctr[8], 0);
-        }
-    }
-}
-
-// Work groups of a persistent launch: the kernel's occupancy per CU times the CUs
-// (queried once per kernel and cached; the library runs on one device type per process).
-template <typename K>
-static int pq_groups_of(K kernel, int threads) {
-    static std::mutex mu;
-    static std::map<const void*, int> cache;
-    std::lock_guard<std::mutex> lock(mu);
-    const void* key = (const void*)kernel;
-    auto it = cache.find(key);
-    if (it != cache.end()) return it->second;
-    int per_cu = 0, dev = 0, cus = 0;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0);
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    const int g = std::max(1, per_cu) * std::max(1, cus);
-    cache[key] = g;
-    return g;
-}
 
 // ------------------------------- FP64 ---------------------------------------------
 // Branch-free main loop: the planner pads rows to whole work-group tiles (zero rows),
@@ -727,270 +675,4 @@ void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int c
 #undef GEMM_CASE8
 #undef GEMM_PICK
 #undef GEMM_CASE
-}
-
-// ------------------------------- offset table (FP64) ------------------------------
-// No dense store: the blocks G^(m; n_b - n_i) are gathered from the table of distinct
-// column offsets (six symmetric complex components per offset, 96 bytes) into LDS, in
-// the FP64 MFMA fragment order, chunk by chunk of 8 interface columns (48 real k').  A
-// work group of two waves owns 32 pad columns (96 rows = 6 row blocks, 3 per wave) of
-// one mode; the B fragments of the chunk are staged in LDS once for both waves.
-#define DT_TB 32
-#define DT_TI 8
-// Register-prefetch pipeline: the gathers of chunk i+1 are issued right after chunk i has
-// been written to LDS, so their latency hides behind the MFMAs of chunk i.  jb.ct_active
-// column tiles carry RHS of this cell; the others are skipped.
-// F32 (jobs with jb.prec = 1): the same gathered values rounded to FP32 on FP32 MFMA
-// 16x16x4 (same operand lanes as the FP64 one), accumulated in FP32 over a chunk of 48
-// k' and in FP64 across chunks.
-// LDS of the offset-table product, declared once by each kernel and shared by both
-// precisions: the A chunk in natural order [row][k'] with an odd row stride (the gathering
-// threads' 8-byte writes and the MFMA lanes' 8-byte reads both fall into distinct banks);
-// for CT > 2 the chunk's B fragments, staged once for both waves (CT <= 2: each wave keeps
-// them in registers, so four work groups fit per CU); the tile's pad columns.
-#define DT_AS 49
-template <int CT>
-struct DtabLds {
-    double As[96 * DT_AS];
-    double Bs[(CT <= 2 ? 1 : CT * 6 * 128)];   // [ct][p][lane][2]
-    int scb[2 * DT_TB];
-};
-// One job of the offset-table product.  Every thread of the work group calls it with the
-// same job (its barriers are uniform); it leaves LDS free for the next job once a barrier
-// has followed it.
-template <int CT, bool F32>
-__device__ inline void dtab_job(DtabLds<CT>& sh, const GemmJob& jb, const double2* __restrict__ tab, int64_t a_base,
-                                const double* __restrict__ B, double* __restrict__ C,
-                                const CellDev* __restrict__ cells, const int32_t* __restrict__ lut,
-                                int d1min, int d2min, int w2, const int32_t* __restrict__ need,
-                                int64_t n_off) {
-    constexpr int AS = DT_AS;
-    double* As = sh.As;
-    double* Bs = sh.Bs;
-    int* scb = sh.scb;
-    if (jb.mb == 0) return;
-    const CellDev cd = cells[jb.cell];
-    const int nca = jb.ct_active;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int b0 = (jb.rb0 / 6) * DT_TB;
-    if (tid < DT_TB) {
-        const int b = b0 + tid;
-        scb[2 * tid] = b < cd.n_b ? cd.cols_b[2 * b] : 0;
-        scb[2 * tid + 1] = b < cd.n_b ? cd.cols_b[2 * b + 1] : 0;
-    }
-    const double2* tm = tab + (jb.a_off - a_base);
-    // generated tables (surrogate form) hold only the first need[t] offsets of table mode t;
-    // the rest are zero by definition and are not read
-    const int64_t o_lim = need ? (int64_t)need[jb.a_off / (6 * n_off)] : INT64_MAX;
-    const double* bm = B + jb.b_off;
-    const int kp8 = jb.kp >> 3;
-    d4_t acc[3][CT];
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) acc[r][c] = (d4_t){0, 0, 0, 0};
-    __syncthreads();
-    double2 va[2][6];
-    double2 vb[CT <= 2 ? 6 : 1][CT <= 2 ? CT : 1];    // next chunk's B fragments (CT <= 2)
-    double2 bcur[CT <= 2 ? 6 : 1][CT <= 2 ? CT : 1];  // this chunk's
-    const int ni8 = jb.kp / 6;                  // interface columns rounded up to 8
-    auto prefetch = [&](int i0u) {
-        const int i0 = wrap_k(i0u, ni8);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int q = tid + 128 * h;
-            const int bl = q >> 3, il = q & 7;
-            const int b = b0 + bl, i = i0 + il;
-            if (b < cd.n_b && i < cd.n_i) {
-                const int d1 = scb[2 * bl] - cd.cols_i[2 * i] - d1min;
-                const int d2 = scb[2 * bl + 1] - cd.cols_i[2 * i + 1] - d2min;
-                const int64_t o = lut[(int64_t)d1 * w2 + d2];
-                if (o < o_lim) {
-                    const double2* src = tm + o * 6;
-#pragma unroll
-                    for (int s = 0; s < 6; ++s) va[h][s] = src[s];
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 6; ++s) va[h][s] = make_double2(0, 0);
-                }
-            } else {
-#pragma unroll
-                for (int s = 0; s < 6; ++s) va[h][s] = make_double2(0, 0);
-            }
-        }
-        if constexpr (CT <= 2) {
-            const int p0 = (6 * i0) >> 3;      // physical chunk (i0 wrapped above)
-#pragma unroll
-            for (int p = 0; p < 6; ++p)
-#pragma unroll
-                for (int c = 0; c < CT; ++c)
-                    vb[p][c] = (c < nca) ? *(const double2*)&bm[((int64_t)c * kp8 + p0 + p) * 128 + 2 * bpos(lane)]
-                                         : make_double2(0.0, 0.0);
-        }
-    };
-    prefetch(jb.k0);
-    for (int i0 = jb.k0; i0 < jb.k1; i0 += DT_TI) {
-        __syncthreads();                          // the previous chunk's MFMAs are done
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int q = tid + 128 * h;
-            const int bl = q >> 3, il = q & 7;
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const double2 x = va[h][sym_idx(c, d)];
-                    const int row = 3 * bl + c, kq = 6 * il + 2 * d;
-                    As[row * AS + kq] = x.x;
-                    As[row * AS + kq + 1] = x.y;
-                }
-        }
-        if constexpr (CT <= 2) {
-#pragma unroll
-            for (int p = 0; p < 6; ++p)
-#pragma unroll
-                for (int c = 0; c < CT; ++c) bcur[p][c] = vb[p][c];
-        } else {
-            const int p0 = (6 * wrap_k(i0, ni8)) >> 3;
-            for (int e = tid; e < CT * 768; e += 128) {      // LDS in lane order
-                const int ct = e / 768, x = e - ct * 768;
-                const int pl = x >> 7, l = (x >> 1) & 63, hh = x & 1;
-                Bs[e] = (ct < nca) ? bm[((int64_t)ct * kp8 + p0 + pl) * 128 + 2 * bpos(l) + hh] : 0.0;
-            }
-        }
-        if (i0 + DT_TI < jb.k1) prefetch(i0 + DT_TI);
-        __syncthreads();
-        f4_t a32[3][CT];
-        if constexpr (F32) {
-#pragma unroll
-            for (int r = 0; r < 3; ++r)
-#pragma unroll
-                for (int c = 0; c < CT; ++c) a32[r][c] = (f4_t){0, 0, 0, 0};
-        }
-#pragma unroll
-        for (int p = 0; p < 6; ++p) {
-            double2 av[3], bv[CT];
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                // lane l holds A[16 rb + l%16][8 p + 4 h + l/16], h = 0, 1 (FP64 16x16x4 order)
-                const double* ap = &As[(16 * (3 * wave + r) + (lane & 15)) * AS + 8 * p + (lane >> 4)];
-                av[r] = make_double2(ap[0], ap[4]);
-            }
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                if constexpr (CT <= 2) bv[c] = bcur[p][c];
-                else bv[c] = *(const double2*)&Bs[(c * 6 + p) * 128 + 2 * lane];
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int r = 0; r < 3; ++r)
-#pragma unroll
-                    for (int c = 0; c < CT; ++c)
-                        if (c < nca) {
-                            if constexpr (F32)
-                                a32[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                    (float)(h ? av[r].y : av[r].x), (float)(h ? bv[c].y : bv[c].x), a32[r][c], 0, 0,
-                                    0);
-                            else
-                                acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(h ? av[r].y : av[r].x,
-                                                                                 h ? bv[c].y : bv[c].x,
-                                                                                 acc[r][c], 0, 0, 0);
-                        }
-        }
-        if constexpr (F32) {
-#pragma unroll
-            for (int r = 0; r < 3; ++r)
-#pragma unroll
-                for (int c = 0; c < CT; ++c)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[r][c][j] += (double)a32[r][c][j];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-            if (c < nca) {
-                if constexpr (F32) store_c_f32acc(C, jb, jb.rb0 + 3 * wave + r, c, lane, acc[r][c]);
-                else store_c_f64(C, jb, jb.rb0 + 3 * wave + r, c, lane, acc[r][c]);
-            }
-}
-
-// MIX = 0: every job on FP64 MFMA; MIX = 1 (options.table_fp32): each job in its own
-// precision (jb.prec).  Separate instantiations, so that the FP64 kernel keeps its own
-// register allocation.
-template <int CT, int MIX>
-__device__ inline void dtab_any(DtabLds<CT>& sh, const GemmJob& jb, const double2* __restrict__ tab, int64_t a_base,
-                                const double* __restrict__ B, double* __restrict__ C,
-                                const CellDev* __restrict__ cells, const int32_t* __restrict__ lut, int d1min,
-                                int d2min, int w2, const int32_t* __restrict__ need, int64_t n_off) {
-    if (MIX && jb.prec) dtab_job<CT, true>(sh, jb, tab, a_base, B, C, cells, lut, d1min, d2min, w2, need, n_off);
-    else dtab_job<CT, false>(sh, jb, tab, a_base, B, C, cells, lut, d1min, d2min, w2, need, n_off);
-}
-
-// One work group per job, in list order.
-template <int CT, int MIX>
-__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(CT == 2 ? 2 : 1)))
-k_gemm_dtab(const GemmJob* __restrict__ jobs, const double2* __restrict__ tab, int64_t a_base,
-            const double* __restrict__ B, double* __restrict__ C, const CellDev* __restrict__ cells,
-            const int32_t* __restrict__ lut, int d1min, int d2min, int w2,
-            const int32_t* __restrict__ need, int64_t n_off) {
-    __shared__ DtabLds<CT> sh;
-    const GemmJob jb = jobs[blockIdx.x];
-    dtab_any<CT, MIX>(sh, jb, tab, a_base, B, C, cells, lut, d1min, d2min, w2, need, n_off);
-}
-
-// Persistent form (work queue as for the dense products).
-template <int CT, int MIX>
-__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(CT == 2 ? 2 : 1)))
-k_gemm_dtab_pq(const GemmJob* __restrict__ jobs, int njobs, PqLists q,
-               const double2* __restrict__ tab, int64_t a_base, const double* __restrict__ B,
-               double* __restrict__ C, const CellDev* __restrict__ cells,
-               const int32_t* __restrict__ lut, int d1min, int d2min, int w2,
-               const int32_t* __restrict__ need, int64_t n_off) {
-    __shared__ int slot;
-    __shared__ DtabLds<CT> sh;
-    int cur = 0;
-    for (int j = pq_next(q, &slot, cur); j < njobs; j = pq_next(q, &slot, cur)) {
-        const GemmJob jb = jobs[j];
-        dtab_any<CT, MIX>(sh, jb, tab, a_base, B, C, cells, lut, d1min, d2min, w2, need, n_off);
-    }
-    pq_done(q);
-}
-
-void launch_gemm_dtab(hipStream_t st, const GemmJob* jobs, int njobs, int ct, const double2* tab,
-                      int64_t a_base, const double* b, double* c, const CellDev* cells,
-                      const int32_t* lut, int d1min, int d2min, int w2, const int32_t* need,
-                      int64_t n_off, const PqLists* q, int mixed) {
-    if (njobs <= 0) return;
-    dim3 blk(128);
-    if (q) {
-#define PQ_CASE(CT, MIX)                                                                             \
-    hipLaunchKernelGGL((k_gemm_dtab_pq<CT, MIX>), dim3(std::min(njobs, pq_groups_of(k_gemm_dtab_pq<CT, MIX>, 128))), blk, 0, \
-                       st, jobs, njobs, *q, tab, a_base, b, c, cells, lut, d1min, d2min, w2, need, n_off)
-#define PQ_CT(CT) do { if (mixed) PQ_CASE(CT, 1); else PQ_CASE(CT, 0); } while (0)
-        switch (ct) {
-            case 1: PQ_CT(1); break;
-            case 2: PQ_CT(2); break;
-            case 4: PQ_CT(4); break;
-            default: PQ_CT(8); break;
-        }
-#undef PQ_CT
-#undef PQ_CASE
-        return;
-    }
-    dim3 grid(njobs);
-#define DT_CASE(CT, MIX)                                                                              \
-    hipLaunchKernelGGL((k_gemm_dtab<CT, MIX>), grid, blk, 0, st, jobs, tab, a_base, b, c, cells, lut, d1min, d2min, \
-                       w2, need, n_off)
-#define DT_CT(CT) do { if (mixed) DT_CASE(CT, 1); else DT_CASE(CT, 0); } while (0)
-    switch (ct) {
-        case 1: DT_CT(1); break;
-        case 2: DT_CT(2); break;
-        case 4: DT_CT(4); break;
-        default: DT_CT(8); break;
-    }
-#undef DT_CT
-#undef DT_CASE
 }

@@ -71,8 +71,8 @@ __device__ inline double2 cmul(double2 a, double2 b) {
 
 // Operands of the product: either the plain layouts of fbc_hmat_apply (x [mode][3 n_i][R],
 // y [mode][3 n_b][R], complex) or, inside a context's apply pipeline, the context's own
-// ones: x read from the forward transform's FP64 B fragments (RHS r = 8 tile + j: column
-// 16 tile + j holds Re f^ at K' = 2k, column 16 tile + j + 8 holds Im f^ there) and y
+// ones: x read from the forward transform's offset-table B fragments (RHS r = 8 tile + j:
+// column 16 tile + j holds Re f^, column 16 tile + j + 8 holds Im f^) and y
 // written as the product records the inverse transform reads ([tile][row][mode][16]:
 // Re of the tile's 8 RHS, then Im), every RHS slot of the tiles written (zeros past R).
 struct HIo {
@@ -99,8 +99,9 @@ __global__ void __launch_bounds__(NTH) k_hmat_x(HIo io, int n_i, int R, double2*
     for (int e = blockIdx.x * NTH + threadIdx.x; e < 3 * n_i * R; e += gridDim.x * NTH) {
         const int col = e / R, r = e - col * R;
         const int tile = r >> 3, j = r & 7;
-        x[(int64_t)m * 3 * n_i * R + e] = make_double2(b[frag_off_f64(16 * tile + j, 2 * col, io.kp)],
-                                                       b[frag_off_f64(16 * tile + j + 8, 2 * col, io.kp)]);
+        const int nch = io.kp / 96;
+        x[(int64_t)m * 3 * n_i * R + e] = make_double2(b[tab_frag_off(16 * tile + j, col, nch)],
+                                                       b[tab_frag_off(16 * tile + j + 8, col, nch)]);
     }
 }
 

@@ -51,12 +51,11 @@ void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int c
                  const PqLists* q, int variant);   // q != NULL: persistent work-queue kernel on these lists
 int gemm_variants(int form, int ctmax);
 std::string gemm_shape(int form, int ctmax, int variant);
-// Offset-table form: 32 pad columns x all interface columns per work group, table
-// entries gathered into LDS in MFMA fragment order.
-void launch_gemm_dtab(hipStream_t st, const GemmJob* jobs, int njobs, int ct, const double2* tab,
-                      int64_t a_base, const double* b, double* c, const CellDev* cells,
-                      const int32_t* lut, int d1min, int d2min, int w2, const int32_t* need,
-                      int64_t n_off, const PqLists* q, int mixed = 0);   // q != NULL: persistent work-queue kernel
+// Offset-table forms (gemm_table.hip): one job per wave, 16 pad columns over a window of
+// interface columns.  q != NULL: persistent work-queue kernel; mixed: jobs carry their precision.
+#define TAB_COLS 16
+void launch_gemm_dtab(hipStream_t st, const GemmJob* jobs, int njobs, int ct, const TabView& tv, const double* b,
+                      double* c, const CellDev* cells, const PqLists* q, int mixed);
 // H-matrix product step (hmat.hip): B fragments of one FP64 cell in, product records out
 void hmat_enqueue_pipeline(fbc_hmat* h, const double* bfrag, int64_t bf_mode, int kp, double* rec, int mp, int nm,
                            int ct, hipStream_t st);

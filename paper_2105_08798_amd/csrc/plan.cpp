@@ -61,27 +61,33 @@ double plan_pair_rho(int32_t a1, int32_t a2, int32_t b1, int32_t b2) {
 
 void plan_windows(const PlanGeom& p, int nm, int mp, int kp, bool dt, int rows_tile, int mult,
                   const std::vector<double>& rho_cut, PlanWindows& out) {
-    out.n_tiles = dt ? mp / 96 : mp / rows_tile;
-    out.n_chunks = dt ? (p.n_i + 7) / 8 : kp / 64;
+    const int nt = dt ? mp / 96 : mp / rows_tile;
+    const int nc = dt ? (p.n_i + 7) / 8 : kp / 64;
+    std::vector<PlanRange> tiles, chunks;
+    for (int tl = 0; tl < nt; ++tl) {
+        if (dt) tiles.push_back({32 * tl, std::min(p.n_b, 32 * tl + 32)});
+        else tiles.push_back({(tl * rows_tile) / 3, std::min(p.n_b, ((tl + 1) * rows_tile + 2) / 3)});
+    }
+    for (int ch = 0; ch < nc; ++ch) {
+        if (dt) chunks.push_back({8 * ch, std::min(p.n_i, 8 * ch + 8)});
+        else chunks.push_back({(32 * ch) / 3, std::min(p.n_i, (32 * (ch + 1) + 2) / 3)});
+    }
+    plan_windows_ranges(p, nm, tiles, chunks, mult, rho_cut, out);
+}
+
+void plan_windows_ranges(const PlanGeom& p, int nm, const std::vector<PlanRange>& tiles,
+                         const std::vector<PlanRange>& chunks, int mult, const std::vector<double>& rho_cut,
+                         PlanWindows& out) {
+    out.n_tiles = (int)tiles.size();
+    out.n_chunks = (int)chunks.size();
     const int NT_ = out.n_tiles, NC = out.n_chunks;
-    // pad columns of a tile and interface columns of a chunk
     auto tile_cols = [&](int tl, int& b0, int& b1) {
-        if (dt) {
-            b0 = 32 * tl;
-            b1 = std::min(p.n_b, b0 + 32);
-        } else {
-            b0 = (tl * rows_tile) / 3;
-            b1 = std::min(p.n_b, ((tl + 1) * rows_tile + 2) / 3);
-        }
+        b0 = tiles[tl].lo;
+        b1 = tiles[tl].hi;
     };
     auto chunk_cols = [&](int ch, int& i0, int& i1) {
-        if (dt) {
-            i0 = 8 * ch;
-            i1 = std::min(p.n_i, i0 + 8);
-        } else {
-            i0 = (32 * ch) / 3;
-            i1 = std::min(p.n_i, (32 * (ch + 1) + 2) / 3);
-        }
+        i0 = chunks[ch].lo;
+        i1 = chunks[ch].hi;
     };
     std::vector<float> rmin((size_t)NT_ * NC, INFINITY);
     std::vector<uint8_t> real_chunk(NC, 0);

@@ -41,6 +41,13 @@ struct PlanWindows {
     std::vector<int32_t> win_start, win_len;   // [nm][n_tiles]
     std::vector<uint8_t> mode_skips;           // [nm]
 };
+// The same for row tiles and K chunks given by their column ranges [lo, hi) (a chunk with lo >= hi is padding).
+struct PlanRange {
+    int lo, hi;
+};
+void plan_windows_ranges(const PlanGeom& g, int nm, const std::vector<PlanRange>& tiles,
+                         const std::vector<PlanRange>& chunks, int mult, const std::vector<double>& rho_cut,
+                         PlanWindows& out);
 void plan_windows(const PlanGeom& g, int nm, int mp, int kp, bool table_form, int rows_tile, int mult,
                   const std::vector<double>& rho_cut, PlanWindows& out);
 
