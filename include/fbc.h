@@ -77,13 +77,15 @@ typedef enum {
 
 /* How G^(m) is stored and applied (the per-mode product, Section 3.2 in spectral form). */
 typedef enum {
-    FBC_FORM_FP64 = 0,        /* dense FP64 complex blocks, FP64 MFMA                        */
+    FBC_FORM_FP64 = 0,        /* FP64: blocks gathered from the table of distinct column
+                                 offsets (FBC_FORM_DTABLE_FP64's product), FP64 MFMA         */
     FBC_FORM_FP32 = 1,        /* dense FP32 complex blocks, FP32 MFMA, FP64 across K chunks   */
     FBC_FORM_SPLIT_BF16 = 2,  /* dense split-BF16 (hi+lo) blocks, BF16 MFMA with FP32
                                  accumulation inside K chunks and FP64 across them            */
-    FBC_FORM_DTABLE_FP64 = 3, /* no dense store: FP64 table over distinct column offsets
-                                 (entries depend on n_b - n_i only), gathered into LDS
-                                 tiles and applied on FP64 MFMA                               */
+    FBC_FORM_DTABLE_FP64 = 3, /* FP64 table over distinct column offsets (entries depend on
+                                 n_b - n_i only), gathered into the operands of FP64 MFMA;
+                                 the form that table_fp32, fbc_hmat_* and
+                                 fbc_sur_training_set take                                    */
     FBC_FORM_SURROGATE = 4,   /* offset-table product whose table is generated per mode
                                  chunk before each product: exact lattice values (kept,
                                  FP64) near the source, beyond them the continuum Green

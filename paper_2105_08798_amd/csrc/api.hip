@@ -138,8 +138,8 @@ static void twiddles(int n, std::vector<double2>& out) {
     if (n / 2 == 0) out[0] = make_double2(1.0, 0.0);
 }
 
-static bool is_table_form(int form) {
-    return form == FBC_FORM_DTABLE_FP64 || form == FBC_FORM_SURROGATE;
+static bool is_table_form(int form) {        // products over the FP64 offset table
+    return form == FBC_FORM_FP64 || form == FBC_FORM_DTABLE_FP64 || form == FBC_FORM_SURROGATE;
 }
 
 // Row gauge: reduced dense forms store G^_bi(m) - mean_i G^_bi(m) (smaller dynamic range
@@ -151,7 +151,7 @@ static bool row_gauge_active(const fbc_ctx* c) {
 }
 
 static int64_t store_elem_bytes(int form) {
-    return form == FBC_FORM_FP64 ? 8 : (form == FBC_FORM_FP32 ? 4 : 2);
+    return form == FBC_FORM_FP32 ? 4 : 2;
 }
 // Store elements (of the store type) of one chunk-tile of the compact dense store:
 // rows_tile rows x 64 K' (x2 for the hi and lo parts of the split forms).
@@ -162,7 +162,7 @@ static int64_t b_mode_elems(int form, const CellPlan& p) {
     return (int64_t)16 * p.ct * p.kp * (is_split16(form) ? 2 : 1);
 }
 static int64_t b_elem_bytes(int form) {
-    return (form == FBC_FORM_FP64 || is_table_form(form)) ? 8 : (form == FBC_FORM_FP32 ? 4 : 2);
+    return is_table_form(form) ? 8 : (form == FBC_FORM_FP32 ? 4 : 2);
 }
 
 // ----------------------------------------------------------------------------------
@@ -282,7 +282,7 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
     };
     fbc_status s;
     int32_t *d1_d, *d2_d;
-    const bool keep = (form == FBC_FORM_DTABLE_FP64);
+    const bool keep = is_table_form(form) && !sur;
     if ((s = dev_alloc(c, (void**)&c->lut, (int64_t)os.lut.size() * 4)) != FBC_OK) return s;
     if (keep) {
         if ((s = dev_alloc(c, (void**)&c->tab, (int64_t)T * n_off * 96)) != FBC_OK) return s;
@@ -549,8 +549,8 @@ static void product_stats(fbc_ctx* c) {
     const int form = c->opt.form;
     const bool dt = is_table_form(form);
     const int rows_tile = dt ? 3 * TAB_COLS : gemm_tile_rows(form, c->ctmax);
-    const double eb = (form == FBC_FORM_FP64) ? 8.0 : 4.0;       // stored bytes per real entry
-    const double fb = (form == FBC_FORM_FP64 || dt) ? 16.0 : 8.0; // bytes per complex f^
+    const double eb = 4.0;                       // stored bytes per real entry
+    const double fb = dt ? 16.0 : 8.0;           // bytes per complex f^
     double bytes = 0, flops = 0, area = 0, kept = 0;
     for (const CellPlan& p : c->cells) {
         for (int m = 0; m < p.nm; ++m) {
@@ -685,21 +685,16 @@ static std::vector<GemmJob> build_jobs(const fbc_ctx* c, int nsplit, int order, 
     }
     size_t mx = 0;
     for (auto& v : per_xcd) mx = std::max(mx, v.size());
-    // consecutive work groups go to consecutive XCDs: a work group of the offset-table
-    // products takes four consecutive jobs, one of the dense products one
-    const size_t per_group = dt ? 4 : 1;
-    mx = (mx + per_group - 1) / per_group * per_group;
     out.reserve(mx * 8);
-    for (size_t k0 = 0; k0 < mx; k0 += per_group)
-        for (int x = 0; x < 8; ++x)
-            for (size_t k = k0; k < k0 + per_group; ++k) {
-                if (k < per_xcd[x].size()) out.push_back(per_xcd[x][k]);
-                else {
-                    GemmJob z{};
-                    z.mb = 0;      // empty job: every wave returns at once
-                    out.push_back(z);
-                }
+    for (size_t k = 0; k < mx; ++k)
+        for (int x = 0; x < 8; ++x) {
+            if (k < per_xcd[x].size()) out.push_back(per_xcd[x][k]);
+            else {
+                GemmJob z{};
+                z.mb = 0;      // empty job: every wave returns at once
+                out.push_back(z);
             }
+        }
     return out;
 }
 
@@ -770,7 +765,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         return fail(nullptr, FBC_E_ARG, "the surrogate form needs an fbc_sur with MLP weights");
     if (opt->gen_modes < 0) return fail(nullptr, FBC_E_ARG, "gen_modes must be >= 0");
     if (opt->table_fp32 != 0 && opt->table_fp32 != 1) return fail(nullptr, FBC_E_ARG, "table_fp32 must be 0 or 1");
-    if (opt->table_fp32 && !is_table_form(opt->form))
+    if (opt->table_fp32 && opt->form != FBC_FORM_DTABLE_FP64 && opt->form != FBC_FORM_SURROGATE)
         return fail(nullptr, FBC_E_ARG, "table_fp32 applies to the offset-table forms (FP64 table, surrogate)");
     if (!is_pow2(opt->bz_m1) || !is_pow2(opt->bz_m2) || opt->bz_m1 < 8 || opt->bz_m2 < 8 ||
         opt->bz_m1 > 4096 || opt->bz_m2 > 4096)
@@ -809,6 +804,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     int rhs0 = 0;
     int64_t tiles_total = 0;   // (cell, mode, row tile) work items before the K split
     int kslices_max = 1 << 30;
+    int chunks_min = 1 << 30;  // offset tables: chunks of interface columns of the smallest cell
     for (int i = 0; i < n_cells; ++i) {
         CellPlan p{};
         p.nz = cells[i].nz;
@@ -843,6 +839,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         if (is_table_form(form)) {
             tiles_total += (int64_t)p.nm * (p.mp / (3 * TAB_COLS));
             kslices_max = std::min(kslices_max, (p.n_i + 7) / 8);
+            chunks_min = std::min(chunks_min, (p.n_i + TAB_COLS - 1) / TAB_COLS);
         } else {
             tiles_total += (int64_t)p.nm * (p.mp / rows_tile);
             kslices_max = std::min(kslices_max, p.kp / 64);
@@ -855,8 +852,14 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     // K slices: enough work items for several rounds of the resident work groups
     // (256 CUs x 3 groups), so the last round leaves little of the chip idle
     {
-        const int64_t want = 6 * 768;
+        // offset tables: one job for each of the 2048 waves that are resident at once (two per
+        // SIMD), in slices of two chunks of 16 interface columns or more -- shorter ones spend
+        // their time filling the pipeline, and every slice costs the inverse transform a read (32
+        // layers, 301 / 613 columns, 3 RHS: 4 slices 77 us per call, 1 or 8 slices 79 and 86; 8
+        // layers, 96 / 192 columns: 2 or 4 slices 44 and 45 us, 8 slices 50)
+        const int64_t want = is_table_form(form) ? 2048 : 6 * 768;
         int ks = (int)std::min<int64_t>((want + tiles_total - 1) / tiles_total, kslices_max);
+        if (is_table_form(form)) ks = std::min(ks, chunks_min / 2);
         c->nsplit = std::max(1, std::min(ks, 8));
         // room for up to 8 slices within 4 GiB of partial outputs (the autotuner may pick more)
         int64_t per_split = 0;
@@ -990,10 +993,11 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     }
     product_stats(c);
     if (form == FBC_FORM_SURROGATE) c->nsplit = 1;     // slices are generated per mode chunk
-    // default lists: mode-major for the offset table, mode-major chunks consumed by the
-    // persistent kernel for the surrogate (1 % faster on the long workload), XCD-grouped
-    // for the dense stores
-    if ((s = upload_jobs(c, c->nsplit, form == FBC_FORM_SURROGATE ? 3 : is_table_form(form) ? 1 : 0, st)) != FBC_OK)
+    // default lists: longest job first for the offset table (0.89 ms, mode-major 0.99, persistent
+    // 0.94 at 128 layers, 1024 / 2048 columns, 8 RHS; eight uneven cells 3.74 against 3.95 and 3.77),
+    // mode-major chunks consumed by the persistent kernel for the surrogate, XCD-grouped for the
+    // dense stores
+    if ((s = upload_jobs(c, c->nsplit, form == FBC_FORM_SURROGATE ? 3 : is_table_form(form) ? 2 : 0, st)) != FBC_OK)
         goto fail_out;
     if ((s = dev_alloc(c, (void**)&c->fprev, c->f_elems * 8)) != FBC_OK) goto fail_out;
     HIPCHK(c, hipStreamSynchronize(st));
@@ -1074,16 +1078,16 @@ static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st) {
             const TabView tv{c->gen, (int64_t)t0 * c->n_offsets * 6, c->lut, c->colkeys, c->n_need, c->n_offsets,
                              (int64_t)c->gen_modes * c->n_offsets};
             launch_gemm_dtab(st, c->jobs + j0, j1 - j0, c->ctmax, tv, (const double*)c->bfrag, c->cbuf, c->celldev,
-                             c->job_order == 3 ? &ql : nullptr, c->opt.table_fp32);
+                             c->job_order == 3 ? &ql : nullptr, c->opt.table_fp32, 0);
         }
     } else if (form == FBC_FORM_DTABLE_FP64 && c->hmat) {
         const CellPlan& p = c->cells[0];          // one cell (checked when attached)
         hmat_enqueue_pipeline(c->hmat, (const double*)c->bfrag + p.b_off, b_mode_elems(form, p), p.kp,
                               c->cbuf + p.c_off, p.mp, p.nm, p.ct, st);
-    } else if (form == FBC_FORM_DTABLE_FP64) {
+    } else if (is_table_form(form)) {
         const TabView tv{c->tab, 0, c->lut, c->colkeys, nullptr, c->n_offsets, 0};
         launch_gemm_dtab(st, c->jobs, c->njobs, c->ctmax, tv, (const double*)c->bfrag, c->cbuf, c->celldev,
-                         c->job_order >= 3 ? &c->lists : nullptr, c->opt.table_fp32);
+                         c->job_order >= 3 ? &c->lists : nullptr, c->opt.table_fp32, c->variant);
     } else
         launch_gemm(st, form, c->jobs, c->njobs, c->ctmax, c->store, c->bfrag, c->cbuf,
                     c->job_order >= 3 ? &c->lists : nullptr, c->variant);
@@ -1193,7 +1197,10 @@ extern "C" fbc_status fbc_apply_graph(fbc_ctx* c, const double* f, double* u, do
     return FBC_OK;
 }
 
-static int n_variants(const fbc_ctx* c) { return is_table_form(c->opt.form) ? 1 : gemm_variants(c->opt.form, c->ctmax); }
+static int n_variants(const fbc_ctx* c) {
+    if (c->opt.form == FBC_FORM_DTABLE_FP64 || c->opt.form == FBC_FORM_SURROGATE) return 1;
+    return c->opt.form == FBC_FORM_FP64 ? 2 : gemm_variants(c->opt.form, c->ctmax);
+}
 
 extern "C" fbc_status fbc_autotune(fbc_ctx* c, const double* f, double* w, int reps,
                                    fbc_tune_result* out, void* stream) {
@@ -1622,7 +1629,7 @@ extern "C" fbc_status fbc_get_info(const fbc_ctx* c, fbc_info* info) {
     info->skipped_fraction = c->skipped_fraction;
     info->kernel_variant = c->variant;
     info->n_variants = n_variants(c);
-    const std::string shape = is_table_form(c->opt.form) ? std::string("offset table, 16 pad columns x 16 interface columns per step and wave")
+    const std::string shape = is_table_form(c->opt.form) ? std::string("offset table, 16 pad columns x 16 interface columns per step and wave, waves=") + (c->variant ? "4" : "1")
                                                          : gemm_shape(c->opt.form, c->ctmax, c->variant);
     std::snprintf(info->kernel_shape, sizeof info->kernel_shape, "%s", shape.c_str());
     return FBC_OK;
@@ -1634,58 +1641,30 @@ extern "C" fbc_status fbc_copy_block_rows(fbc_ctx* c, int cell, int m, int b0, i
     const CellPlan& p = c->cells[cell];
     if (m < 0 || m >= p.nm || b0 < 0 || b1 > p.n_b || b0 >= b1) return fail(c, FBC_E_ARG, "range");
     if (c->opt.form == FBC_FORM_SURROGATE) return fail(c, FBC_E_UNSUPPORTED, "no stored table in the surrogate form");
-    if (c->opt.form == FBC_FORM_DTABLE_FP64) {
-        // reconstruct the block rows from the offset table
-        const int mult = c->nz_max / p.nz;
-        HIPCHK(c, hipDeviceSynchronize());
-        std::vector<double2> tabm((size_t)c->n_offsets * 6);
-        HIPCHK(c, hipMemcpy(tabm.data(), c->tab + (int64_t)m * mult * c->n_offsets * 6,
-                            tabm.size() * 16, hipMemcpyDeviceToHost));
-        OffsetSet os = offsets_of(c->cells);
-        for (int b = b0; b < b1; ++b)
-            for (int i = 0; i < p.n_i; ++i) {
-                const int x = p.cols_b[2 * b] - p.cols_i[2 * i] - os.d1min;
-                const int y = p.cols_b[2 * b + 1] - p.cols_i[2 * i + 1] - os.d2min;
-                const int64_t o = os.lut[(size_t)x * os.w2 + y];
-                for (int cc = 0; cc < 3; ++cc)
-                    for (int d = 0; d < 3; ++d) {
-                        const double2 v = tabm[o * 6 + sym_idx(cc, d)];
-                        double* dst = out + ((int64_t)(3 * (b - b0) + cc) * 6 * p.n_i + 2 * (3 * i + d));
-                        dst[0] = v.x;
-                        dst[1] = v.y;
-                    }
-            }
-        return FBC_OK;
-    }
-    if (c->opt.form != FBC_FORM_FP64) return fail(c, FBC_E_UNSUPPORTED, "FP64 forms only");
-    // compact store: the row tiles covering the rows, their windows at mode m; blocks
-    // outside a window are the product's zeros
-    const int rows_tile = gemm_tile_rows(c->opt.form, c->ctmax);
-    const int64_t cte = chunk_tile_elems(c->opt.form, rows_tile);
-    const int trb = rows_tile / 16;
-    const int rows = 3 * (b1 - b0);
-    std::fill(out, out + (int64_t)rows * 6 * p.n_i, 0.0);
+    if (!is_table_form(c->opt.form)) return fail(c, FBC_E_UNSUPPORTED, "FP64 forms only");
+    // the block rows from the offset table; in the FP64 form, blocks outside the window of their
+    // tile are the product's zeros
+    const bool windows = c->opt.form == FBC_FORM_FP64;
+    const int mult = c->nz_max / p.nz;
     HIPCHK(c, hipDeviceSynchronize());
-    std::vector<double> reg;
-    for (int tl = (3 * b0) / rows_tile; tl <= (3 * b1 - 1) / rows_tile; ++tl) {
-        const int r = m * p.n_tiles + tl;
-        const int ws = p.win_start[r], wl = p.win_len[r];
-        if (wl == 0) continue;
-        reg.resize((size_t)wl * cte);
-        HIPCHK(c, hipMemcpy(reg.data(), (double*)c->store + p.a_off + p.reg_pre[r] * cte, reg.size() * 8,
-                            hipMemcpyDeviceToHost));
-        for (int row = std::max(3 * b0, tl * rows_tile); row < std::min(3 * b1, (tl + 1) * rows_tile); ++row) {
-            const int rr = row - tl * rows_tile, blk = rr >> 4;
-            for (int j = 0; j < wl; ++j) {
-                const int ch = (ws + j) % p.n_chunks;
-                for (int x = 0; x < 64; ++x) {
-                    const int k = 64 * ch + x;
-                    if (k >= 6 * p.n_i) break;
-                    const int lane = ((x & 3) << 4) | (rr & 15);
-                    const int64_t el = (int64_t)j * cte + ((((x >> 3) * trb + blk) * 64 + lane) << 1) + ((x >> 2) & 1);
-                    out[(int64_t)(row - 3 * b0) * 6 * p.n_i + k] = reg[el];
+    std::vector<double2> tabm((size_t)c->n_offsets * 6);
+    HIPCHK(c, hipMemcpy(tabm.data(), c->tab + (int64_t)m * mult * c->n_offsets * 6, tabm.size() * 16,
+                        hipMemcpyDeviceToHost));
+    OffsetSet os = offsets_of(c->cells);
+    for (int b = b0; b < b1; ++b) {
+        const size_t r = (size_t)m * p.n_tiles + b / TAB_COLS;
+        for (int i = 0; i < p.n_i; ++i) {
+            const int x = p.cols_b[2 * b] - p.cols_i[2 * i] - os.d1min;
+            const int y = p.cols_b[2 * b + 1] - p.cols_i[2 * i + 1] - os.d2min;
+            const int64_t o = os.lut[(size_t)x * os.w2 + y];
+            const bool in = !windows || (i / TAB_COLS - p.win_start[r] + p.n_chunks) % p.n_chunks < p.win_len[r];
+            for (int cc = 0; cc < 3; ++cc)
+                for (int d = 0; d < 3; ++d) {
+                    const double2 v = in ? tabm[o * 6 + sym_idx(cc, d)] : make_double2(0.0, 0.0);
+                    double* dst = out + ((int64_t)(3 * (b - b0) + cc) * 6 * p.n_i + 2 * (3 * i + d));
+                    dst[0] = v.x;
+                    dst[1] = v.y;
                 }
-            }
         }
     }
     return FBC_OK;

@@ -197,9 +197,7 @@ __device__ inline float bf2f(unsigned short h) { return __uint_as_float((unsigne
 
 template <int FORM>
 __device__ inline void put_b(void* bm, int n, int kq, int kp, double v) {
-    if (FORM == FBC_FORM_FP64) {
-        ((double*)bm)[frag_off_f64(n, kq, kp)] = v;
-    } else if (FORM == FBC_FORM_FP32) {
+    if (FORM == FBC_FORM_FP32) {
         ((float*)bm)[frag_off_f32(n, kq, kp)] = (float)v;
     } else if (FORM == FBC_FORM_SPLIT_FP16) {        // v already scaled by 2^e
         const _Float16 hi = f64_to_f16(v);
@@ -217,16 +215,11 @@ __device__ inline void put_b(void* bm, int n, int kq, int kp, double v) {
 }
 
 // Whole 16-byte fragment units of one B column n for the 2G consecutive K' entries
-// kq0 .. kq0 + 2G - 1 (kq0 a multiple of 2G): FP64 units hold (kq, kq + 4), FP32 units
+// kq0 .. kq0 + 2G - 1 (kq0 a multiple of 2G): FP32 units hold
 // (kq, kq + 4, kq + 8, kq + 12), split units 8 consecutive kq (hi run, lo run 1 KiB on).
 template <int FORM, int NV>
 __device__ inline void put_b_units(void* bm, int n, int kq0, int kp, const double (&v)[NV]) {
-    if constexpr (FORM == FBC_FORM_FP64) {
-        static_assert(NV == 8, "FP64 units cover 8 K' entries");
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            *(double2*)((double*)bm + frag_off_f64(n, kq0 + j, kp)) = make_double2(v[j], v[j + 4]);
-    } else if constexpr (FORM == FBC_FORM_FP32) {
+    if constexpr (FORM == FBC_FORM_FP32) {
         static_assert(NV == 16, "FP32 units cover 16 K' entries");
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -396,9 +389,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
                 vim[2 * q + 1] = fr;
             }
             void* bm;
-            if (FORM == FBC_FORM_FP64)
-                bm = (double*)bfrag + m * mode_elems;
-            else if (FORM == FBC_FORM_FP32)
+            if (FORM == FBC_FORM_FP32)
                 bm = (float*)bfrag + m * mode_elems;
             else
                 bm = (unsigned short*)bfrag + m * mode_elems;
@@ -423,9 +414,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
         }
         if (m == 0 || 2 * m == nz) fi = 0.0;
         void* bm;
-        if (FORM == FBC_FORM_FP64)
-            bm = (double*)bfrag + m * mode_elems;
-        else if (FORM == FBC_FORM_FP32)
+        if (FORM == FBC_FORM_FP32)
             bm = (float*)bfrag + m * mode_elems;
         else
             bm = (unsigned short*)bfrag + m * mode_elems;
@@ -485,7 +474,6 @@ void launch_line_rfft(hipStream_t st, int form, const double* f, const double* t
         case FBC_FORM_FP32: RF_LAUNCH(FBC_FORM_FP32); break;
         case FBC_FORM_SPLIT_FP16: RF_LAUNCH(FBC_FORM_SPLIT_FP16); break;
         case FBC_FORM_SPLIT_BF16: RF_LAUNCH(FBC_FORM_SPLIT_BF16); break;
-        case FBC_FORM_FP64: RF_LAUNCH(FBC_FORM_FP64); break;
         default: RF_LAUNCH(FBC_FORM_DTABLE_FP64); break;      // the offset-table forms
     }
 #undef RF_LAUNCH
@@ -1432,7 +1420,6 @@ void apply_kernels_init() {
     if (!done.insert(dev).second) return;
     {
         const int lim = 160 * 1024;
-        (void)hipFuncSetAttribute((const void*)k_line_rfft<FBC_FORM_FP64, 1024>, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
         (void)hipFuncSetAttribute((const void*)k_line_rfft<FBC_FORM_DTABLE_FP64, 1024>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lim);
         (void)hipFuncSetAttribute((const void*)k_line_rfft<FBC_FORM_FP32, 1024>, hipFuncAttributeMaxDynamicSharedMemorySize, lim);

@@ -256,7 +256,6 @@ __device__ inline double dense_value(int row, int kq, int m, int mode_mult,
 // holds win_len[r] chunk-tiles from reg_pre[r] on, the window position j holding the
 // cyclic chunk (win_start[r] + j) mod n_chunks.  Inside a chunk-tile the MFMA fragment
 // order of the product kernels, K-major across the tile's row blocks:
-//   FP64  [8 steps of 8 k'][row block][lane][2]
 //   FP32  [4 steps of 16 k'][row block][lane][4]
 //   split [2 steps of 32 k'][row block][hi, lo][lane][8]
 // One work group per chunk-tile.
@@ -287,14 +286,7 @@ __global__ void __launch_bounds__(256) k_build_dense(int form, void* __restrict_
         if (ch >= n_chunks) ch -= n_chunks;
         const int row0 = tl * tile_rows, k0 = 64 * ch;
         for (int64_t x = threadIdx.x; x < ce; x += blockDim.x) {
-            if (form == FBC_FORM_FP64) {
-                const int sub = (int)(x & 1), lane = (int)((x >> 1) & 63);
-                const int rest = (int)(x >> 7);
-                const int blk = rest % trb, st = rest / trb;
-                const int row = row0 + 16 * blk + (lane & 15), kq = k0 + 8 * st + 4 * sub + (lane >> 4);
-                ((double*)store)[g * ce + x] = dense_value(row, kq, m, mode_mult, tab, rowmean, n_off, n_b, n_i,
-                                                           cols_b, cols_i, lut, d1min, d2min, w2);
-            } else if (form == FBC_FORM_FP32) {
+            if (form == FBC_FORM_FP32) {
                 const int sub = (int)(x & 3), lane = (int)((x >> 2) & 63);
                 const int rest = (int)(x >> 8);
                 const int blk = rest % trb, st = rest / trb;

@@ -51,11 +51,6 @@ __device__ inline _Float16 f64_to_f16(double x) {
     asm volatile("" : "+v"(f));
     return (_Float16)f;
 }
-__host__ __device__ inline int64_t frag_off_f64(int64_t r, int64_t k, int64_t kp) {
-    int64_t blk = r >> 4, rr = r & 15;
-    int64_t lane = ((k & 3) << 4) | rr;
-    return (((blk * (kp >> 3) + (k >> 3)) * 64 + bpos((int)lane)) << 1) + ((k >> 2) & 1);
-}
 __host__ __device__ inline int64_t frag_off_f32(int64_t r, int64_t k, int64_t kp) {
     int64_t blk = r >> 4, rr = r & 15;
     int64_t lane = ((k & 3) << 4) | rr;
@@ -67,15 +62,6 @@ __host__ __device__ inline int64_t frag_off_bf16(int64_t r, int64_t k, int64_t k
     int64_t kk = k & 31;
     int64_t lane = ((kk >> 3) << 4) | rr;
     return ((((blk * (kp >> 5) + (k >> 5)) * 2) * 64 + bpos((int)lane)) << 3) + (kk & 7);
-}
-
-// The dense G^ stores use the same lane map but are K-major across row blocks,
-// [k step][row block][lane], so the work groups of one mode, which advance through K at
-// about the same rate, read neighbouring addresses at any moment.
-__host__ __device__ inline int64_t frag_off_f64_km(int64_t r, int64_t k, int64_t mp) {
-    int64_t blk = r >> 4, rr = r & 15;
-    int64_t lane = ((k & 3) << 4) | rr;
-    return ((((k >> 3) * (mp >> 4) + blk) * 64 + lane) << 1) + ((k >> 2) & 1);
 }
 
 // Symmetric 3x3 component index: xx yy zz xy xz yz

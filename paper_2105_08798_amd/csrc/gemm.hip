@@ -20,16 +20,6 @@
 
 #include <algorithm>
 
-static __device__ inline void store_c_f64(double* __restrict__ c, const GemmJob& jb, int rb,
-                                          int ctile, int lane, const d4_t& acc) {
-    const int64_t mp = (int64_t)jb.mb * 16;
-    const int col = lane & 15;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int row = 16 * rb + 4 * j + (lane >> 4);      // FP64 16x16x4 output order
-        c[jb.c_off + ((int64_t)ctile * mp + row) * jb.crs + col] = acc[j];
-    }
-}
 static __device__ inline void store_c_f32acc(double* __restrict__ c, const GemmJob& jb, int rb,
                                              int ctile, int lane, const d4_t& acc) {
     const int64_t mp = (int64_t)jb.mb * 16;
@@ -45,11 +35,6 @@ static __device__ inline void store_c_f32acc(double* __restrict__ c, const GemmJ
 // nontemporal (streaming) loads and do not push the f^ fragments, the partial outputs and
 // the caller's arrays out of L2 and the Infinity Cache (measured on MI355X: the products
 // run 8-11 % faster than with ordinary loads).
-__device__ inline double2 ld_stream(const double2* p) {
-    typedef double dv2_t __attribute__((ext_vector_type(2)));
-    const dv2_t v = __builtin_nontemporal_load((const dv2_t*)p);
-    return make_double2(v[0], v[1]);
-}
 __device__ inline float4 ld_stream(const float4* p) {
     const f4_t v = __builtin_nontemporal_load((const f4_t*)p);
     return make_float4(v[0], v[1], v[2], v[3]);
@@ -64,95 +49,6 @@ __device__ inline h8_t ld_stream(const h8_t* p) { return __builtin_nontemporal_l
 // per XCD (PqLists), the groups of an XCD work through consecutive row tiles of the same
 // mode together, so the f^ fragments of their overlapping K windows are fetched into that
 // XCD's L2 once; a group whose list is exhausted takes jobs from the other lists in turn.
-
-// ------------------------------- FP64 ---------------------------------------------
-// Branch-free main loop: the planner pads rows to whole work-group tiles (zero rows),
-// K' to a multiple of 64 and gives every cell of a context the same column-tile count,
-// so every wave runs full RB x CT tiles over the whole K; the prefetch index is clamped
-// to the last step instead of being predicated.
-template <int RB, int CT, int PF>
-__device__ inline void gemm_f64_job(const GemmJob& jb,
-                                                  const double* __restrict__ A,
-                                                  const double* __restrict__ B,
-                                                  double* __restrict__ C) {
-    // the main loop runs whole ring passes: the ring must divide the 8 steps of a 64-k' chunk
-    static_assert(8 % PF == 0, "ring depth must divide the steps of a chunk");
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int rbw = jb.rb0 + wave * RB;
-    if (rbw >= jb.mb) return;
-    const int kp8 = jb.kp >> 3;
-    const int pb = jb.k0 >> 3, pe = jb.k1 >> 3;
-    constexpr int TRB = 4 * RB;          // row blocks of the tile: the A step stride
-    const double2* a = (const double2*)(A + jb.a_off) + (int64_t)(wave * RB) * 64 + lane;
-    const double2* b = (const double2*)(B + jb.b_off) + bpos(lane);
-    d4_t acc[RB][CT];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) acc[r][c] = (d4_t){0, 0, 0, 0};
-    if (pe <= pb) {              // empty K slice: its partial output is zero
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-#pragma unroll
-            for (int c = 0; c < CT; ++c) store_c_f64(C, jb, rbw + r, c, lane, acc[r][c]);
-        return;
-    }
-    double2 ab[PF][RB], bb[PF][CT];
-#pragma unroll
-    for (int u = 0; u < PF; ++u) {
-        const int pw = wrap_k(pb + u, kp8);
-        const int pa = min(u, pe - pb - 1);       // A: step inside the job's stored run
-#pragma unroll
-        for (int r = 0; r < RB; ++r) ab[u][r] = ld_stream(a + (((int64_t)pa * TRB + r) * 64));
-#pragma unroll
-        for (int c = 0; c < CT; ++c) bb[u][c] = b[((int64_t)c * kp8 + pw) * 64];
-
-        // keeps the ring's loads in slot order (slot 0 first), so the first wait of the main
-        // loop leaves the later slots in flight instead of draining every load
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    for (int p0 = pb; p0 < pe; p0 += PF) {
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int r = 0; r < RB; ++r)
-#pragma unroll
-                    for (int c = 0; c < CT; ++c)
-                        acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                            h ? ab[u][r].y : ab[u][r].x, h ? bb[u][c].y : bb[u][c].x, acc[r][c], 0, 0, 0);
-            const int pl = min(p0 + u + PF, pe - 1);
-            const int pn = wrap_k(pl, kp8);
-#pragma unroll
-            for (int r = 0; r < RB; ++r) ab[u][r] = ld_stream(a + (((int64_t)(pl - pb) * TRB + r) * 64));
-#pragma unroll
-            for (int c = 0; c < CT; ++c) bb[u][c] = b[((int64_t)c * kp8 + pn) * 64];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) store_c_f64(C, jb, rbw + r, c, lane, acc[r][c]);
-}
-
-template <int RB, int CT, int PF>
-__global__ void __launch_bounds__(256) k_gemm_f64(const GemmJob* __restrict__ jobs, const double* __restrict__ A,
-        const double* __restrict__ B, double* __restrict__ C) {
-    const GemmJob jb = jobs[blockIdx.x];
-    gemm_f64_job<RB, CT, PF>(jb, A, B, C);
-}
-template <int RB, int CT, int PF>
-__global__ void __launch_bounds__(256) k_gemm_f64_pq(const GemmJob* __restrict__ jobs, int njobs, PqLists q,
-        const double* __restrict__ A, const double* __restrict__ B, double* __restrict__ C) {
-    __shared__ int slot;
-    int cur = 0;
-    for (int j = pq_next(q, &slot, cur); j < njobs; j = pq_next(q, &slot, cur)) {
-        const GemmJob jb = jobs[j];
-        gemm_f64_job<RB, CT, PF>(jb, A, B, C);
-    }
-    pq_done(q);
-}
 
 // ------------------------------- FP32 ---------------------------------------------
 // FP32 MFMA with FP32 accumulation inside chunks of KCH*16 real k, FP64 across chunks.
@@ -563,10 +459,9 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_split_lds_pq(const GemmJob* __
 static int gemm_rb(int form, int ctmax) {
     // one column tile: 2 row blocks per wave for the FP32 and split products (128-row work
     // groups: finer negligible-block windows and more work groups; measured 3 % faster
-    // than 4 on the medium workload), 4 for FP64
-    if (form == FBC_FORM_SPLIT_BF16 || form == FBC_FORM_SPLIT_FP16 || form == FBC_FORM_FP32)
-        return ctmax <= 1 ? 2 : ctmax <= 2 ? 4 : 2;
-    return ctmax <= 2 ? 4 : 2;
+    // than 4 on the medium workload)
+    (void)form;
+    return ctmax == 2 ? 4 : 2;
 }
 // Waves per work group (every product kernel as launched runs four).
 static int gemm_waves(int, int) { return 4; }
@@ -589,7 +484,7 @@ static void launch_dense(void (*kn)(const GemmJob*, const TA*, const TA*, double
 // Kernel variants of a product class (form, column tiles) that the autotuner may choose
 // from.  They share the tile height (the compact store is laid out in tiles) and the
 // arithmetic order, so every variant gives bitwise the same result: variant 0 is the
-// default; variant 1 changes the depth of the prefetch ring (FP64, FP32) or the K steps
+// default; variant 1 changes the depth of the prefetch ring (FP32) or the K steps
 // per barrier (split products staging B in LDS); variant 2 of those splits the column
 // tiles between two halves of eight waves (two waves per SIMD).  The split products with one or two
 // column tiles have one variant: their main loop runs whole ring passes, and a 64-k'
@@ -605,10 +500,7 @@ std::string gemm_shape(int form, int ctmax, int variant) {
     const int ct = ctmax <= 1 ? 1 : ctmax <= 2 ? 2 : ctmax <= 4 ? 4 : 8;
     const bool alt = variant == 1;
     char buf[96];
-    if (form == FBC_FORM_FP64) {
-        const int rb = ct <= 2 ? 4 : 2, pf = (ct <= 2) != alt ? 4 : 2;
-        snprintf(buf, sizeof buf, "f64 RB=%d CT=%d PF=%d waves=4", rb, ct, pf);
-    } else if (form == FBC_FORM_FP32) {
+    if (form == FBC_FORM_FP32) {
         const int rb = ct == 2 ? 4 : 2, pf = (ct <= 2) != alt ? 4 : 2;
         snprintf(buf, sizeof buf, "f32 RB=%d CT=%d PF=%d KCH=16 waves=4", rb, ct, pf);
     } else if (ct <= 2) {
@@ -636,13 +528,7 @@ void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int c
 #define GEMM_CASE8(KERN, ...)                                                                  \
     launch_dense<TA>(KERN<__VA_ARGS__, 8, 2>, KERN##_pq<__VA_ARGS__, 8, 2>, st, jobs, njobs, a, b, c, q, 512)
 #define GEMM_PICK3(DEF, ALT, CS) do { if (variant == 2) CS; else if (variant == 1) ALT; else DEF; } while (0)
-    if (form == FBC_FORM_FP64) {
-        typedef double TA;
-        if (ctmax <= 1) GEMM_PICK(GEMM_CASE(k_gemm_f64, 4, 1, 4), GEMM_CASE(k_gemm_f64, 4, 1, 2));
-        else if (ctmax <= 2) GEMM_PICK(GEMM_CASE(k_gemm_f64, 4, 2, 4), GEMM_CASE(k_gemm_f64, 4, 2, 2));
-        else if (ctmax <= 4) GEMM_PICK(GEMM_CASE(k_gemm_f64, 2, 4, 2), GEMM_CASE(k_gemm_f64, 2, 4, 4));
-        else GEMM_PICK(GEMM_CASE(k_gemm_f64, 2, 8, 2), GEMM_CASE(k_gemm_f64, 2, 8, 4));
-    } else if (form == FBC_FORM_FP32) {
+    if (form == FBC_FORM_FP32) {
         typedef float TA;
         if (ctmax <= 1) GEMM_PICK(GEMM_CASE(k_gemm_f32, 2, 1, 4, 16), GEMM_CASE(k_gemm_f32, 2, 1, 2, 16));
         else if (ctmax <= 2) GEMM_PICK(GEMM_CASE(k_gemm_f32, 4, 2, 4, 16), GEMM_CASE(k_gemm_f32, 4, 2, 2, 16));

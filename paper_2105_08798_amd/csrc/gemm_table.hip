@@ -180,13 +180,13 @@ __device__ inline void tab_any(const GemmJob& jb, const TabView& tv, const doubl
     else tab_job<CT, DB, false>(jb, tv, B, C, cells);
 }
 
-// Four waves per work group, each on its own job; MIX: each job in its own precision
-// (options.table_fp32).
+// Each wave of a work group (one, or four: variant 1) on its own job; MIX: each job in its
+// own precision (options.table_fp32).
 template <int CT, int MIX>
 __global__ void __launch_bounds__(256, CT <= 2 ? 2 : 1)
 k_tab(const GemmJob* __restrict__ jobs, int njobs, TabView tv, const double* __restrict__ B, double* __restrict__ C,
       const CellDev* __restrict__ cells) {
-    const int j = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    const int j = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
     if (j >= njobs) return;
     const GemmJob jb = jobs[j];
     if (jb.mb == 0) return;
@@ -206,16 +206,20 @@ k_tab_pq(const GemmJob* __restrict__ jobs, int njobs, PqLists q, TabView tv, con
 }
 
 void launch_gemm_dtab(hipStream_t st, const GemmJob* jobs, int njobs, int ct, const TabView& tv, const double* b,
-                      double* c, const CellDev* cells, const PqLists* q, int mixed) {
+                      double* c, const CellDev* cells, const PqLists* q, int mixed, int variant) {
     if (njobs <= 0) return;
-    const int groups = (njobs + 3) / 4;
-#define TAB_CASE(CT, MIX)                                                                              \
-    do {                                                                                                   \
-        if (q)                                                                                             \
-            hipLaunchKernelGGL((k_tab_pq<CT, MIX>), dim3(std::min(groups, pq_groups_of(k_tab_pq<CT, MIX>, 256))), \
-                               dim3(256), 0, st, jobs, njobs, *q, tv, b, c, cells);                        \
-        else                                                                                               \
-            hipLaunchKernelGGL((k_tab<CT, MIX>), dim3(groups), dim3(256), 0, st, jobs, njobs, tv, b, c, cells); \
+    // one wave per work group: a finished job frees its place at once, where a group of four
+    // waits for its longest (128 layers, 1024 / 2048 columns, 8 RHS: 0.89 against 0.92 ms; 32
+    // layers, 301 / 613 columns, 3 RHS: 47 against 49 us)
+    const int waves = variant == 1 ? 4 : 1, groups = (njobs + waves - 1) / waves;
+#define TAB_CASE(CT, MIX)                                                                                     \
+    do {                                                                                                      \
+        if (q)                                                                                                \
+            hipLaunchKernelGGL((k_tab_pq<CT, MIX>),                                                           \
+                               dim3(std::min(groups, 4 / waves * pq_groups_of(k_tab_pq<CT, MIX>, 256))),      \
+                               dim3(64 * waves), 0, st, jobs, njobs, *q, tv, b, c, cells);                    \
+        else                                                                                                  \
+            hipLaunchKernelGGL((k_tab<CT, MIX>), dim3(groups), dim3(64 * waves), 0, st, jobs, njobs, tv, b, c, cells); \
     } while (0)
 #define TAB_CT(CT) do { if (mixed) TAB_CASE(CT, 1); else TAB_CASE(CT, 0); } while (0)
     switch (ct) {

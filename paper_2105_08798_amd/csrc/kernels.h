@@ -52,10 +52,11 @@ void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int c
 int gemm_variants(int form, int ctmax);
 std::string gemm_shape(int form, int ctmax, int variant);
 // Offset-table forms (gemm_table.hip): one job per wave, 16 pad columns over a window of
-// interface columns.  q != NULL: persistent work-queue kernel; mixed: jobs carry their precision.
+// interface columns.  q != NULL: persistent work-queue kernel; mixed: jobs carry their precision;
+// variant 1: work groups of four waves instead of one (bitwise the same result).
 #define TAB_COLS 16
 void launch_gemm_dtab(hipStream_t st, const GemmJob* jobs, int njobs, int ct, const TabView& tv, const double* b,
-                      double* c, const CellDev* cells, const PqLists* q, int mixed);
+                      double* c, const CellDev* cells, const PqLists* q, int mixed, int variant);
 // H-matrix product step (hmat.hip): B fragments of one FP64 cell in, product records out
 void hmat_enqueue_pipeline(fbc_hmat* h, const double* bfrag, int64_t bf_mode, int kp, double* rec, int mp, int nm,
                            int ct, hipStream_t st);
