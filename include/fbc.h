@@ -302,7 +302,8 @@ fbc_status fbc_sync_status(fbc_ctx* ctx, void* stream);
 typedef struct {
     int n_cells;
     int total_rhs;
-    int64_t store_bytes;       /* bytes of the G^ store (dense tiles or offset table)     */
+    int64_t store_bytes;       /* bytes of the G^ store (offset table; reduced forms: the
+                                  blocks stored and the table of the gathered ones)       */
     int64_t scratch_bytes;     /* bytes of scratch owned by the context                   */
     int64_t f_elems, u_elems;  /* doubles expected in f and u                             */
     int64_t n_offsets;         /* distinct column offsets over all cells                  */

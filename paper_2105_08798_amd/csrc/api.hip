@@ -460,6 +460,56 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
         }
         const int rows_tile = gemm_tile_rows(form, c->ctmax);
         compute_windows(c, rho_cut, rows_tile);
+        if (!is_table_form(form)) {
+            // modes whose rows carry no gauge depend on the offset alone: gathered from the reduced
+            // table (n1 in [d1min, d1max], s = n1 + 2 n2 in [smin, smax]) where the boxes of a tile's
+            // rows fit (columns in the order of a ring or another neighbourly one) -- unless the
+            // table takes more memory than the blocks it stands for
+            const int64_t tile_bytes = chunk_tile_elems(form, rows_tile) * store_elem_bytes(form);
+            int64_t blocks = 0;
+            for (CellPlan& p : c->cells) {
+                const int sub = rows_tile / JOB_ROWS;
+                PlanBoxes pb;
+                plan_boxes(PlanGeom{p.n_i, p.n_b, p.cols_i.data(), p.cols_b.data()}, p.mp / JOB_ROWS, JOB_ROWS, p.kp / 64, pb);
+                std::vector<uint8_t> fits(p.n_tiles, 1);
+                for (int q = 0; q < p.mp / JOB_ROWS; ++q) fits[q / sub] &= pb.largest[q] <= G_CAP;
+                p.gather.assign((size_t)p.nm * p.n_tiles, 0);
+                for (int m = 0; m < p.nm; ++m)
+                    for (int tl = 0; tl < p.n_tiles; ++tl)
+                        if (fits[tl] && (p.mode_skips[m] || !row_gauge_active(c))) {
+                            p.gather[(size_t)m * p.n_tiles + tl] = 1;
+                            blocks += p.win_len[(size_t)m * p.n_tiles + tl] * tile_bytes;
+                        }
+            }
+            int64_t smin = INT64_MAX, smax = INT64_MIN, d1max = INT64_MIN;
+            for (int64_t o = 0; o < n_off; ++o) {
+                const int64_t sv = os.d1[o] + 2 * (int64_t)os.d2[o];
+                smin = std::min(smin, sv);
+                smax = std::max(smax, sv);
+                d1max = std::max<int64_t>(d1max, os.d1[o]);
+            }
+            RBox& box = c->rbox;
+            box.w = (smax - smin) / 2 + 2;             // neighbouring n1 stay more than one key apart
+            box.base = (2 * box.w * os.d1min + smin) & ~(int64_t)1;
+            box.mode_bytes = (((2 * box.w * d1max + smax - box.base) >> 1) + 1) * 64;
+            if (blocks == 0 || box.mode_bytes > ((int64_t)1 << 31) || T * box.mode_bytes > std::max<int64_t>(blocks, 64 << 20) ||
+                2 * box.w * (std::max(std::abs(d1max), std::abs((int64_t)os.d1min)) + 2) > (1 << 30)) {
+                box.mode_bytes = 0;
+                for (CellPlan& p : c->cells) std::fill(p.gather.begin(), p.gather.end(), 0);
+            }
+            // offsets within reach of each table mode (for the product's byte count)
+            std::vector<int64_t> cum(4097, 0);
+            double rmax = 0.0;
+            std::vector<double> rho(n_off);
+            for (int64_t o = 0; o < n_off; ++o) {
+                rho[o] = plan_pair_rho(os.d1[o], os.d2[o], 0, 0);
+                rmax = std::max(rmax, rho[o]);
+            }
+            for (int64_t o = 0; o < n_off; ++o) ++cum[1 + (int)std::min(4095.0, 4096.0 * rho[o] / (rmax + 1e-9))];
+            for (int b = 0; b < 4096; ++b) cum[b + 1] += cum[b];
+            c->rtab_need.assign(T, 0);
+            for (int t = 0; t < T; ++t) c->rtab_need[t] = cum[(int)std::min(4096.0, 1.0 + 4096.0 * rho_cut[t] / (rmax + 1e-9))];
+        }
     }
     if (!keep && !sur) {
         if (form == FBC_FORM_SPLIT_FP16) {
@@ -495,7 +545,7 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
         for (CellPlan& p : c->cells) {
             const int nreg = p.nm * p.n_tiles;
             p.reg_pre.assign((size_t)nreg + 1, 0);
-            for (int r = 0; r < nreg; ++r) p.reg_pre[r + 1] = p.reg_pre[r] + p.win_len[r];
+            for (int r = 0; r < nreg; ++r) p.reg_pre[r + 1] = p.reg_pre[r] + (p.gather[r] ? 0 : p.win_len[r]);
             p.n_ct = p.reg_pre[nreg];
             p.a_off = a_tot;
             a_tot += p.n_ct * cte;
@@ -506,6 +556,19 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
             cleanup();
             return fail(c, FBC_E_NOMEM, "dense store of " + std::to_string(c->store_bytes) +
                                             " B (the blocks inside the negligible-block windows): " + c->err);
+        }
+        if (c->rbox.mode_bytes > 0) {
+            const RBox& box = c->rbox;
+            unsigned long long* amax_t;
+            if ((s = dev_alloc(c, (void**)&c->rtab, T * box.mode_bytes)) != FBC_OK ||
+                (s = talloc((void**)&amax_t, (int64_t)T * 8)) != FBC_OK) {
+                cleanup();
+                return s;
+            }
+            c->store_bytes += T * box.mode_bytes;
+            launch_tab_absmax(st, c->tab, T, n_off, amax_t);
+            launch_build_rtab(st, form, c->tab, T, n_off, d1_d, d2_d, box, amax_t, c->rtab);
+            HIPCHK(c, hipGetLastError());
         }
         int64_t* reg_d;
         int32_t* ws_d;
@@ -566,11 +629,19 @@ static void product_stats(fbc_ctx* c) {
                     if (((ch - ws + p.n_chunks) % p.n_chunks) < wl) {
                         kept += rows * kc;
                         flops += 8.0 * rows * kc * p.R;
-                        if (!dt) bytes += (double)rows_tile * 64.0 * eb;
+                        if (!dt && !p.gather[(size_t)m * p.n_tiles + tl]) bytes += (double)rows_tile * 64.0 * eb;
                     }
                 }
             }
         }
+    }
+    if (!dt) {
+        std::vector<uint8_t> seen(c->nz_max / 2 + 1, 0);
+        for (const CellPlan& p : c->cells)
+            for (int m = 0; m < p.nm; ++m)
+                if (std::count(&p.gather[(size_t)m * p.n_tiles], &p.gather[(size_t)m * p.n_tiles] + p.n_tiles, 1) &&
+                    !seen[(size_t)m * (c->nz_max / p.nz)]++)
+                    bytes += 64.0 * c->rtab_need[(size_t)m * (c->nz_max / p.nz)];
     }
     if (form == FBC_FORM_SURROGATE) {
         for (int t : c->n_need_h) bytes += t * 96.0;     // generated slices, read once
@@ -633,8 +704,29 @@ static void unit_jobs(const fbc_ctx* c, const Unit& u, int nsplit, std::vector<G
             // FP32 MFMA only at modes whose far blocks are skipped: a mode without skipping
             // (mode 0 among them) keeps its whole long-range part, gauge constant included,
             // which FP32 rounding of the blocks would not carry to 1e-6
+            if (!dt) {
+                j.gather = p.gather[(size_t)u.m * p.n_tiles + tl];
+                if (j.gather) j.a_off = (int64_t)u.t * c->rbox.mode_bytes;
+                j.win_len = wl;
+                j.win_a = a;
+                j.vs = nsplit == c->nsplit_def ? c->vslices : nsplit;
+            }
             j.prec = (dt && c->opt.table_fp32 && p.mode_skips[u.m]) ? 1 : 0;
-            out.push_back(j);
+            if (dt) {
+                out.push_back(j);
+                continue;
+            }
+            // JOB_ROWS rows at a time; the store's row blocks of a K step follow one another
+            const int64_t blk = (int64_t)16 * (form == FBC_FORM_FP32 ? 16 : 64);      // elements
+            for (int r0 = 0; r0 < tile_rows; r0 += JOB_ROWS) {
+                GemmJob h = j;
+                h.rb0 += r0 / 16;
+                if (!h.gather) h.a_off += r0 / 16 * blk;
+                for (int c0 = 0; c0 < p.ctr; c0 += gemm_job_tiles(c->ctmax)) {     // (tiles past ctr hold no RHS)
+                    h.c0 = c0;
+                    out.push_back(h);
+                }
+            }
         }
 }
 
@@ -648,7 +740,10 @@ static std::vector<GemmJob> build_jobs(const fbc_ctx* c, int nsplit, int order, 
         const int64_t unit_k = dt ? 6 * TAB_COLS : 64;
         for (int m = 0; m < p.nm; ++m) {
             int64_t cost = 0;
-            for (int tl = 0; tl < p.n_tiles; ++tl) cost += p.win_len[(size_t)m * p.n_tiles + tl];
+            for (int tl = 0; tl < p.n_tiles; ++tl) {
+                const size_t r = (size_t)m * p.n_tiles + tl;
+                cost += p.win_len[r] * (dt || p.gather[r] ? 1 : 3);     // a streamed block takes about three times as long
+            }
             units.push_back({ci, m, m * mult, cost * tile_rows * unit_k});
         }
     }
@@ -789,6 +884,11 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     c->lat = *lat;
     c->sur = opt->surrogate;
     (void)hipGetDevice(&c->device);
+    if (!is_table_form(opt->form)) {
+        int ct = 1;
+        for (int i = 0; i < n_cells; ++i) ct = std::max(ct, (cells[i].n_rhs + 7) / 8);
+        gemm_kernels_init(opt->form, ct);
+    }
     apply_kernels_init();            // dynamic-LDS limits of the long-line transforms, before any capture
     hipStream_t st = (hipStream_t)stream;
     const int form = opt->form;
@@ -861,6 +961,19 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         int ks = (int)std::min<int64_t>((want + tiles_total - 1) / tiles_total, kslices_max);
         if (is_table_form(form)) ks = std::min(ks, chunks_min / 2);
         c->nsplit = std::max(1, std::min(ks, 8));
+        c->vslices = c->nsplit;
+        if (!is_table_form(form)) {
+            // jobs of 128 rows are many; every slice costs the inverse transform a read and the pipeline
+            // a fill.  Two slices up to 3000 jobs (call, 1 / 2 / 4 slices: 627 jobs 110, 104, 107 us;
+            // 1560 jobs 256, 238, 296; 2720 jobs 210, 202, -; 3120 jobs 674, 732, 925), four where two
+            // would leave half of the CUs idle.  FP32 sums still end where the slices counted above
+            // would (GemmJob::vs), so their number must divide those.
+            const int64_t jobs1 = tiles_total * (gemm_tile_rows(form, c->ctmax) / JOB_ROWS);
+            int r = jobs1 >= 3000 ? 1 : jobs1 >= 128 ? 2 : 4;
+            while (c->vslices % r) r /= 2;
+            c->nsplit = r;
+        }
+        c->nsplit_def = c->nsplit;
         // room for up to 8 slices within 4 GiB of partial outputs (the autotuner may pick more)
         int64_t per_split = 0;
         for (auto& p : c->cells) per_split += p.c_split * 8;
@@ -969,20 +1082,53 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         (void)hipStreamSynchronize(st);
         (void)hipFree(sn_d);
     }
-    if (is_table_form(form)) {
-        // column keys of the offset-table products (see CellDev)
+    {
+        // column keys of the offset-table products and of the gather jobs (see CellDev)
         std::vector<CellDev> cd;
         std::vector<int32_t> keys;
         for (auto& p : c->cells) {
+            if (!is_table_form(form)) {
+                CellDev v{};
+                const int tiles = p.mp / JOB_ROWS, chunks = p.kp / 64;
+                PlanBoxes pb;
+                plan_boxes(PlanGeom{p.n_i, p.n_b, p.cols_i.data(), p.cols_b.data()}, tiles, JOB_ROWS, chunks, pb);
+                if (keys.size() & 1) keys.push_back(0);           // pairs are read as such
+                v.rkey_i = (int64_t)keys.size();
+                for (int i = 0; i < (32 * chunks) / 3 + 12; ++i)
+                    for (int a = 0; a < 2; ++a) keys.push_back(p.cols_i[2 * std::min(i, p.n_i - 1) + a]);
+                v.rchunk = (int64_t)keys.size();
+                keys.insert(keys.end(), pb.chunk.begin(), pb.chunk.end());
+                v.rbox = (int64_t)keys.size();
+                keys.insert(keys.end(), pb.box.begin(), pb.box.end());
+                v.rrow = (int64_t)keys.size();
+                for (int tl = 0; tl < tiles; ++tl) {
+                    const int b0 = tl * JOB_ROWS / 3, nb = ((tl + 1) * JOB_ROWS - 1) / 3 - b0 + 1;
+                    const int32_t* bx = &pb.box[4 * tl];
+                    std::vector<std::pair<int64_t, int>> order(nb);      // place in the box, pad column
+                    for (int x = 0; x < nb; ++x) {
+                        const int32_t* cb = &p.cols_b[2 * std::min(b0 + x, p.n_b - 1)];
+                        order[x] = {(int64_t)bx[3] * (cb[0] - bx[0]) + cb[1] - bx[2], b0 + x};
+                    }
+                    std::sort(order.begin(), order.end());
+                    for (int cc = 0; cc < 3; ++cc)
+                        for (const auto& o : order) {
+                            const int y = 3 * o.second + cc - tl * JOB_ROWS;
+                            // (places past 16 bits: only tiles whose boxes do not fit, never gathered)
+                            if (y >= 0 && y < JOB_ROWS) keys.push_back(y | (int32_t)((o.first & 0x7fff) << 16));
+                        }
+                }
+                cd.push_back(v);
+                continue;
+            }
             const int nb = (int)roundup(p.n_b, TAB_COLS), ni = (int)roundup(p.n_i, TAB_COLS);
-            cd.push_back(CellDev{(int64_t)keys.size(), (int64_t)keys.size() + nb});
+            cd.push_back(CellDev{(int64_t)keys.size(), (int64_t)keys.size() + nb, 0, 0, 0, 0});
             for (int b = 0; b < nb; ++b) {
                 const int q = std::min(b, p.n_b - 1);
-                keys.push_back((p.cols_b[2 * q] - c->d1min) * c->w2 + p.cols_b[2 * q + 1] - c->d2min);
+                keys.push_back((int32_t)(((int64_t)p.cols_b[2 * q] - c->d1min) * c->w2 + p.cols_b[2 * q + 1] - c->d2min));
             }
             for (int x = 0; x < ni; ++x) {             // [chunk][g][q] holds column 16 chunk + 4 q + g
                 const int q = std::min((x & ~15) + 4 * (x & 3) + ((x >> 2) & 3), p.n_i - 1);
-                keys.push_back(p.cols_i[2 * q] * c->w2 + p.cols_i[2 * q + 1]);
+                keys.push_back((int32_t)((int64_t)p.cols_i[2 * q] * c->w2 + p.cols_i[2 * q + 1]));
             }
         }
         if ((s = dev_alloc(c, (void**)&c->colkeys, (int64_t)keys.size() * 4)) != FBC_OK) goto fail_out;
@@ -993,12 +1139,18 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     }
     product_stats(c);
     if (form == FBC_FORM_SURROGATE) c->nsplit = 1;     // slices are generated per mode chunk
-    // default lists: longest job first for the offset table (0.89 ms, mode-major 0.99, persistent
-    // 0.94 at 128 layers, 1024 / 2048 columns, 8 RHS; eight uneven cells 3.74 against 3.95 and 3.77),
-    // mode-major chunks consumed by the persistent kernel for the surrogate, XCD-grouped for the
-    // dense stores
-    if ((s = upload_jobs(c, c->nsplit, form == FBC_FORM_SURROGATE ? 3 : is_table_form(form) ? 2 : 0, st)) != FBC_OK)
-        goto fail_out;
+    // default lists: longest unit first (offset table: 0.89 ms, mode-major 0.99, persistent 0.94 at
+    // 128 layers, 1024 / 2048 columns, 8 RHS; eight uneven cells 3.74 against 3.95 and 3.77.  Reduced
+    // forms: 5.5 ms, XCD-grouped 5.7, mode-major 5.7, persistent 5.6 at 1024 layers, 2048 / 4096
+    // columns, 16 RHS); per-XCD lists for long split lists of four or eight column tiles, whose f^
+    // fragments then stay in one L2 (3.80 ms against 3.96 at 256 layers, 2048 / 4096 columns, 64 RHS,
+    // 0.83 against 0.86 at 12480 jobs; from 3000 jobs down the queue costs as much as it saves);
+    // mode-major chunks consumed by the persistent kernel for the surrogate
+    {
+        const int64_t njobs = (int64_t)build_jobs(c, c->nsplit, 2).size();
+        const int order = form == FBC_FORM_SURROGATE ? 3 : is_split16(form) && c->ctmax > 2 && njobs >= 6000 ? 4 : 2;
+        if ((s = upload_jobs(c, c->nsplit, order, st)) != FBC_OK) goto fail_out;
+    }
     if ((s = dev_alloc(c, (void**)&c->fprev, c->f_elems * 8)) != FBC_OK) goto fail_out;
     HIPCHK(c, hipStreamSynchronize(st));
     HIPCHK(c, hipGetLastError());
@@ -1089,8 +1241,8 @@ static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st) {
         launch_gemm_dtab(st, c->jobs, c->njobs, c->ctmax, tv, (const double*)c->bfrag, c->cbuf, c->celldev,
                          c->job_order >= 3 ? &c->lists : nullptr, c->opt.table_fp32, c->variant);
     } else
-        launch_gemm(st, form, c->jobs, c->njobs, c->ctmax, c->store, c->bfrag, c->cbuf,
-                    c->job_order >= 3 ? &c->lists : nullptr, c->variant);
+        launch_gemm(st, form, c->jobs, c->njobs, c->ctmax, c->store, RTabView{c->rtab, c->colkeys, (int)(2 * c->rbox.w), (int)c->rbox.base, (int)(c->rbox.mode_bytes / 64)}, c->bfrag, c->cbuf,
+                    c->celldev, c->job_order >= 3 ? &c->lists : nullptr, c->variant);
     if (tm) {
         (void)hipEventRecord(c->ev[2 * c->n_timed + 1], st);
         ++c->n_timed;

@@ -401,3 +401,54 @@ void launch_build_dense(hipStream_t st, int form, void* store, const double2* ta
                        reg_pre, win_start, nm * n_tiles, n_tiles, n_chunks, tile_rows, n_ct, mode_mult, n_off,
                        n_b, n_i, cols_b, cols_i, lut, d1min, d2min, w2, amax);
 }
+
+void launch_tab_absmax(hipStream_t st, const double2* tab, int T, int64_t n_off, unsigned long long* amax) {
+    hipLaunchKernelGGL(k_zero_u64, dim3((T + 255) / 256), dim3(256), 0, st, amax, T);
+    const int sl = (int)std::min<int64_t>(64, (n_off * 6 + 255) / 256);
+    hipLaunchKernelGGL(k_tab_absmax, dim3(sl, T), dim3(256), 0, st, tab, 1, n_off, amax);
+}
+
+// Records of the reduced forms' table (RTabView), rounded exactly as the compact store's
+// entries without a row gauge.  One thread per (offset, table mode).
+__global__ void __launch_bounds__(256) k_build_rtab(int form, const double2* __restrict__ tab, int64_t n_off,
+                                                    const int32_t* __restrict__ d1, const int32_t* __restrict__ d2,
+                                                    RBox box, const unsigned long long* __restrict__ amax,
+                                                    char* __restrict__ rtab) {
+    const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int t = blockIdx.y;
+    if (o >= n_off) return;
+    const int64_t at = (2 * box.w * d1[o] + d1[o] + 2 * (int64_t)d2[o] - box.base) >> 1;
+    const double2* src = tab + ((int64_t)t * n_off + o) * 6;
+    uint2* dst = (uint2*)(rtab + (int64_t)t * box.mode_bytes + at * 64);
+    const int comp[6] = {0, 3, 4, 5, 1, 2};          // xx xy xz yz yy zz of xx yy zz xy xz yz
+    for (int c = 0; c < 6; ++c) {
+        const double2 v = src[comp[c]];
+        if (form == FBC_FORM_FP32) {
+            dst[c] = make_uint2(__float_as_uint((float)v.x), __float_as_uint((float)v.y));
+            continue;
+        }
+        unsigned hi = 0, lo = 0;
+        for (int p = 0; p < 2; ++p) {
+            const double x = p ? v.y : v.x;
+            unsigned short h, l;
+            if (form == FBC_FORM_SPLIT_FP16) {
+                const double xs = ldexp(x, split16_exp_a(amax[t]));
+                const _Float16 fh = f64_to_f16(xs);
+                h = __builtin_bit_cast(unsigned short, fh);
+                l = __builtin_bit_cast(unsigned short, f64_to_f16(xs - (double)fh));
+            } else {
+                h = f32_to_bf16_rne((float)x);
+                l = f32_to_bf16_rne((float)(x - (double)bf16_to_f32(h)));
+            }
+            hi |= (unsigned)h << (16 * p);
+            lo |= (unsigned)l << (16 * p);
+        }
+        dst[c] = make_uint2(hi, lo);
+    }
+}
+
+void launch_build_rtab(hipStream_t st, int form, const double2* tab, int T, int64_t n_off, const int32_t* d1,
+                       const int32_t* d2, const RBox& box, const unsigned long long* amax, char* rtab) {
+    hipLaunchKernelGGL(k_build_rtab, dim3((unsigned)((n_off + 255) / 256), T), dim3(256), 0, st, form, tab, n_off, d1,
+                       d2, box, amax, rtab);
+}

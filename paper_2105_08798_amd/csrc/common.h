@@ -91,6 +91,11 @@ struct GemmJob {
     int32_t ct_active;  // column tiles holding RHS of this cell (offset form skips the rest)
     int32_t crs;        // output row stride (doubles): the modes of a row are adjacent
     int32_t prec;       // offset forms: 1 = this job on FP32 MFMA (options.table_fp32), 0 = FP64
+    // reduced forms: 1 = blocks gathered from the reduced table (a_off: byte offset of its mode),
+    // 0 = streamed from the compact store; the (mode, tile)'s window has win_len chunks of 64 k',
+    // this job starts at chunk win_a of it, and FP32 sums end where vs equal slices of it do
+    int32_t gather, win_len, win_a, vs;
+    int32_t c0;         // reduced forms: first column tile of the job
 };
 
 // Work lists of a persistent product launch: one list consumed by every work group (the
@@ -118,11 +123,38 @@ __host__ __device__ inline int64_t tab_frag_off(int n, int k, int nch) {
     return (step * 64 + (((n & 15) << 2) | (i & 3))) << 1;
 }
 
+// Read-only data that a whole wave reads at one address: through the constant address space the
+// loads are scalar whatever the kernel stores.
+typedef const __attribute__((address_space(4))) int uniform_int;
+
 // Per-cell device view used by the offset-table product kernel: the column keys n1 w2 + n2
 // (their differences index the offset lookup), pad columns up to whole tiles of 16 (the last
 // column repeated), interface columns up to whole chunks of 16 in the order [chunk][g][q].
 struct CellDev {
     int64_t key_b, key_i;    // offsets into TabView::keys
+    // reduced forms, offsets into RTabView::keys: interface columns (n1, n2) in natural order, the last
+    // one repeated past the end; per chunk of 64 k' the smallest and largest n1 and the largest n2 of
+    // its columns (four ints); per JOB_ROWS rows the smallest n1, the range of n1, the smallest n2
+    // and the row length of their pad columns' boxes (four ints); and these rows by component,
+    // then (n1, n2): row - first row | place of the pad column in the box << 16
+    int64_t rkey_i, rchunk, rbox, rrow;
+};
+
+// Rows of a job of the reduced forms, and the largest box of a chunk (records) that a job gathers.
+#define JOB_ROWS 128
+#define G_CAP 384
+
+// The reduced forms' table of distinct column offsets: records of 64 bytes (16 of padding) in the
+// order xx xy xz yz yy zz, each component eight bytes -- split forms: (re, im) hi halves, (re, im) lo
+// halves; FP32: re, im.  Record of offset (d1, d2): (2 W d1 + (d1 + 2 d2) - base) >> 1, so
+// consecutive d2 are consecutive records and the offsets' disc fills most of the array.
+struct RTabView {
+    const char* tab;
+    const int32_t* keys;
+    int w2, base, nrec;            // 2 W, and the number of records
+};
+struct RBox {
+    int64_t w, base, mode_bytes;   // half range of n1 + 2 n2, smallest index, bytes per table mode
 };
 
 // The table of an offset-table product: `tab` starts at element a_base of the whole table
@@ -165,8 +197,10 @@ struct CellPlan {
     int n_tiles = 0, n_chunks = 0;
     std::vector<int32_t> win_start, win_len;   // [nm][n_tiles]
     std::vector<uint8_t> mode_skips;           // [nm]: some chunk of this mode is skipped
-    // Compact dense store: region r = m n_tiles + tl holds the win_len[r] chunk-tiles of
-    // that window from chunk-tile reg_pre[r] on (cell-local); n_ct = reg_pre[nm n_tiles].
+    std::vector<uint8_t> gather;               // [nm][n_tiles]: reduced forms: blocks from the reduced table (RTabView)
+    // Compact dense store of the tiles that are not gathered: region r = m n_tiles + tl holds the
+    // win_len[r] chunk-tiles of that window from chunk-tile reg_pre[r] on (cell-local); n_ct =
+    // reg_pre[nm n_tiles].
     std::vector<int64_t> reg_pre;
     int64_t n_ct = 0;
 };

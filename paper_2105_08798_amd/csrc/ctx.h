@@ -63,6 +63,11 @@ struct fbc_ctx {
     int32_t* lut = nullptr;
     int d1min = 0, d2min = 0, w2 = 0;
     CellDev* celldev = nullptr;
+    char* rtab = nullptr;           // reduced forms: table of the modes without a row gauge (RTabView)
+    RBox rbox{};
+    std::vector<int64_t> rtab_need; // offsets within reach of each table mode
+    int vslices = 1;                // reduced forms: slices of a window at whose ends FP32 sums end (FlushAt)
+    int nsplit_def = 1;             // K slices after assembly
     int32_t* colkeys = nullptr;     // column keys of the offset-table products (see CellDev)
     // surrogate form: ragged exact table, offsets by increasing distance, generated slices
     const fbc_sur* sur = nullptr;

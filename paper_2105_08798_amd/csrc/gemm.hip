@@ -5,20 +5,23 @@
 // columns (Re f, -Im f) and (Im f, Re f), so a 16-column output tile carries the real
 // parts of 8 RHS in columns 0..7 and their imaginary parts in columns 8..15.
 //
-// A is streamed once from HBM in MFMA fragment order (each wave-wide 16-byte load is
-// 1 KiB contiguous, no LDS) from the compact store: a job's stored blocks are the K
-// chunks of its (mode, row tile) window, one contiguous run, K-major across the tile's
-// row blocks, so a work group streams one sequential region; B fragments are re-read by
-// every row tile of the same mode and stay in L2 because the job list gives all tiles
-// of a mode to one XCD.
-// Each work group is 4 waves; a wave owns RB row blocks (16 rows each) of one mode and
-// all column tiles of that mode, over the whole K.  Loads run PF steps ahead.
+// Two kinds of jobs share a launch, 128 rows of one (cell, mode) each:
+//  * stream: the tile's blocks are stored (compact store: the K chunks of its window, one
+//    contiguous run in MFMA fragment order, each wave-wide 16-byte load 1 KiB contiguous) and
+//    streamed once from HBM.  Only modes whose rows carry a row gauge take it (the
+//    subtracted mean makes an entry depend on the pad column, not on the offset alone).
+//  * gather: every other mode reads the table of distinct column offsets in the form's
+//    precision: the records of a K chunk's box of offsets are staged through LDS and read back as
+//    fragments (gather_job).
+// Both run the same MFMAs on the same operand values in the same order, FP32 sums over the
+// same K chunks and FP64 across them, so a result does not depend on the kind of its job.
 #include <cstdint>
 
 #include "kernels.h"
 #include "pq.h"
 
 #include <algorithm>
+#include <type_traits>
 
 static __device__ inline void store_c_f32acc(double* __restrict__ c, const GemmJob& jb, int rb,
                                              int ctile, int lane, const d4_t& acc) {
@@ -27,7 +30,7 @@ static __device__ inline void store_c_f32acc(double* __restrict__ c, const GemmJ
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int row = 16 * rb + 4 * (lane >> 4) + j;      // FP32-accumulator output order
-        c[jb.c_off + ((int64_t)ctile * mp + row) * jb.crs + col] = acc[j];
+        c[jb.c_off + ((int64_t)(jb.c0 + ctile) * mp + row) * jb.crs + col] = acc[j];
     }
 }
 
@@ -50,23 +53,46 @@ __device__ inline h8_t ld_stream(const h8_t* p) { return __builtin_nontemporal_l
 // mode together, so the f^ fragments of their overlapping K windows are fetched into that
 // XCD's L2 once; a group whose list is exhausted takes jobs from the other lists in turn.
 
+// Where the FP32 sums go into the FP64 accumulators: after every KC chunks of 64 k', counted
+// from the start of a slice, and at a slice's end.  The slices are those of the window cut
+// into jb.vs parts (at least the job's own K slices): the sums then do not depend on how many
+// of them one job runs through.
+struct FlushAt {
+    int w, seg0, seg1, v, wl, vs;
+    __device__ explicit FlushAt(const GemmJob& jb) : w(jb.win_a), seg0(0), seg1(0), v(-1), wl(jb.win_len), vs(jb.vs) {
+        while (seg1 <= w && v + 1 < vs) next();
+    }
+    __device__ void next() {
+        ++v;
+        seg0 = seg1;
+        seg1 = (int)((unsigned)(wl * (v + 1)) / (unsigned)vs);
+    }
+    // one more chunk done: true when the sums are due
+    template <int KC>
+    __device__ bool step() {
+        ++w;
+        const bool due = ((w - seg0) & (KC - 1)) == 0 || w == seg1;
+        while (w == seg1 && v + 1 < vs) next();
+        return due;
+    }
+};
+
 // ------------------------------- FP32 ---------------------------------------------
 // FP32 MFMA with FP32 accumulation inside chunks of KCH*16 real k, FP64 across chunks.
-template <int RB, int CT, int PF, int KCH>
+template <int TRB, int RB, int CT, int PF, int KC>
 __device__ inline void gemm_f32_job(const GemmJob& jb,
                                                   const float* __restrict__ A,
                                                   const float* __restrict__ B,
                                                   double* __restrict__ C) {
     static_assert(4 % PF == 0, "ring depth must divide the 4 steps of a 64-k' chunk");
-    static_assert(KCH % PF == 0, "FP32 chunks are whole ring passes");
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int rbw = jb.rb0 + wave * RB;
     if (rbw >= jb.mb) return;
+    FlushAt fl(jb);
     const int kq = jb.kp >> 4;
     const int qb = jb.k0 >> 4, qe = jb.k1 >> 4;
-    constexpr int TRB = 4 * RB;          // row blocks of the tile: the A step stride
     const float4* a = (const float4*)(A + jb.a_off) + (int64_t)(wave * RB) * 64 + lane;
-    const float4* b = (const float4*)(B + jb.b_off) + bpos(lane);
+    const float4* b = (const float4*)(B + jb.b_off) + (int64_t)jb.c0 * kq * 64 + bpos(lane);
     d4_t acc[RB][CT];
     f4_t ac32[RB][CT];
 #pragma unroll
@@ -119,7 +145,8 @@ __device__ inline void gemm_f32_job(const GemmJob& jb,
 
             __builtin_amdgcn_sched_barrier(0);     // the same order in every ring pass
         }
-        if (((q0 - qb + PF) % KCH) == 0 || q0 + PF >= qe) {
+        const bool chunk_end = ((q0 - qb + PF) & 3) == 0;
+        if (chunk_end && (fl.template step<KC>() || q0 + PF >= qe)) {
 #pragma unroll
             for (int r = 0; r < RB; ++r)
 #pragma unroll
@@ -136,24 +163,6 @@ __device__ inline void gemm_f32_job(const GemmJob& jb,
         for (int c = 0; c < CT; ++c) store_c_f32acc(C, jb, rbw + r, c, lane, acc[r][c]);
 }
 
-template <int RB, int CT, int PF, int KCH>
-__global__ void __launch_bounds__(256) k_gemm_f32(const GemmJob* __restrict__ jobs, const float* __restrict__ A,
-        const float* __restrict__ B, double* __restrict__ C) {
-    const GemmJob jb = jobs[blockIdx.x];
-    gemm_f32_job<RB, CT, PF, KCH>(jb, A, B, C);
-}
-template <int RB, int CT, int PF, int KCH>
-__global__ void __launch_bounds__(256) k_gemm_f32_pq(const GemmJob* __restrict__ jobs, int njobs, PqLists q,
-        const float* __restrict__ A, const float* __restrict__ B, double* __restrict__ C) {
-    __shared__ int slot;
-    int cur = 0;
-    for (int j = pq_next(q, &slot, cur); j < njobs; j = pq_next(q, &slot, cur)) {
-        const GemmJob jb = jobs[j];
-        gemm_f32_job<RB, CT, PF, KCH>(jb, A, B, C);
-    }
-    pq_done(q);
-}
-
 // ------------------------------- split BF16 ---------------------------------------
 // G ~ G_hi + G_lo, f ~ f_hi + f_lo; products lo*hi + hi*lo + hi*hi on BF16 MFMA with
 // FP32 accumulation inside chunks of KCH*32 real k, FP64 across chunks.
@@ -166,20 +175,19 @@ __device__ inline f4_t mfma_16x16x32(h8_t a, h8_t b, f4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-template <typename VT, int RB, int CT, int PF, int KCH>
+template <typename VT, int TRB, int RB, int CT, int PF, int KC>
 __device__ inline void gemm_split_job(const GemmJob& jb,
                                                     const unsigned short* __restrict__ A,
                                                     const unsigned short* __restrict__ B,
                                                     double* __restrict__ C) {
-    static_assert(2 % PF == 0, "ring depth must divide the 2 steps of a 64-k' chunk");
-    static_assert(KCH % PF == 0, "FP32 chunks are whole ring passes");
+    static_assert(PF == 2, "a ring pass is the 2 steps of a 64-k' chunk");
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int rbw = jb.rb0 + wave * RB;
     if (rbw >= jb.mb) return;
+    FlushAt fl(jb);
     const int kt = jb.kp >> 5;
     const int tb = jb.k0 >> 5, te = jb.k1 >> 5;
     // 16-byte units: per (block, t): hi run of 64 units then lo run of 64 units
-    constexpr int TRB = 4 * RB;          // row blocks of the tile: the A step stride
     const VT* a = (const VT*)(A + jb.a_off) + (int64_t)(wave * RB) * 128 + lane;
     const VT* b = (const VT*)(B + jb.b_off) + bpos(lane);
     d4_t acc[RB][CT];
@@ -249,7 +257,7 @@ __device__ inline void gemm_split_job(const GemmJob& jb,
             }
             __builtin_amdgcn_sched_barrier(0);     // the same order in every ring pass
         }
-        if (((t0 - tb + PF) % KCH) == 0 || t0 + PF >= te) {
+        if (fl.template step<KC>() || t0 + PF >= te) {
 #pragma unroll
             for (int r = 0; r < RB; ++r)
 #pragma unroll
@@ -266,24 +274,6 @@ __device__ inline void gemm_split_job(const GemmJob& jb,
         for (int c = 0; c < CT; ++c) store_c_f32acc(C, jb, rbw + r, c, lane, acc[r][c]);
 }
 
-template <typename VT, int RB, int CT, int PF, int KCH>
-__global__ void __launch_bounds__(256) k_gemm_split(const GemmJob* __restrict__ jobs, const unsigned short* __restrict__ A,
-        const unsigned short* __restrict__ B, double* __restrict__ C) {
-    const GemmJob jb = jobs[blockIdx.x];
-    gemm_split_job<VT, RB, CT, PF, KCH>(jb, A, B, C);
-}
-template <typename VT, int RB, int CT, int PF, int KCH>
-__global__ void __launch_bounds__(256) k_gemm_split_pq(const GemmJob* __restrict__ jobs, int njobs, PqLists q,
-        const unsigned short* __restrict__ A, const unsigned short* __restrict__ B, double* __restrict__ C) {
-    __shared__ int slot;
-    int cur = 0;
-    for (int j = pq_next(q, &slot, cur); j < njobs; j = pq_next(q, &slot, cur)) {
-        const GemmJob jb = jobs[j];
-        gemm_split_job<VT, RB, CT, PF, KCH>(jb, A, B, C);
-    }
-    pq_done(q);
-}
-
 // Variant for 4 or 8 column tiles (many RHS): the B fragments of a K step are the same
 // for the NW waves of a work group, so they are loaded once per work group into LDS
 // (double buffered) instead of once per wave from L2, and the group meets at one barrier
@@ -295,47 +285,34 @@ __global__ void __launch_bounds__(256) k_gemm_split_pq(const GemmJob* __restrict
 // otherwise also wait for every A load issued before it, and cut the effective depth of
 // the A ring down to the distance at which B was fetched.  K windows and slices hold an
 // even number of steps, so S = 2 needs no tail.
-// CH = 2 splits the column tiles between two halves of the waves (eight waves: four row
-// groups x two column halves, the same 128-row tile): each wave holds the accumulators of
-// half the tiles, so two waves fit per SIMD; the two waves of a row group read the same A
-// (ordinary loads, so the second finds it in L2).  Every output tile sees the same
-// sequence of MFMAs, so the result is bitwise that of CH = 1.
-template <typename VT, int RB, int CT, int PFA, int KCH, int S, int NW, int CH = 1>
-__device__ inline void gemm_split_lds_job(const GemmJob& jb,
-                                                        const unsigned short* __restrict__ A,
-                                                        const unsigned short* __restrict__ B,
-                                                        double* __restrict__ C) {
+template <typename VT, int RB, int CT, int PFA, int KC, int S, int NW>
+__device__ inline void gemm_split_lds_job(const GemmJob& jb, const unsigned short* __restrict__ A,
+                                          const unsigned short* __restrict__ B, double* __restrict__ C, char* smem) {
     static_assert(CT >= 2 && (CT % 2) == 0, "B staging assumes an even tile count");
-    static_assert(CH == 1 || CH == 2, "one or two column halves");
-    static_assert(NW % CH == 0 && ((CT / CH) % 2) == 0, "column halves of an even tile count");
     static_assert(S == 1 || S == 2, "one or two K steps per barrier");
-    constexpr int RG = NW / CH;              // row groups of the tile
-    constexpr int CTW = CT / CH;             // column tiles per wave
     static_assert(PFA >= 2 * S && (PFA % (2 * S)) == 0, "ring depth must be a multiple of 2 S");
     constexpr int NTH = 64 * NW;             // threads of the work group
     constexpr int STEP_UNITS = CT * 128;     // 16-byte units of B per step (hi and lo runs)
     static_assert(STEP_UNITS % NTH == 0, "B units must spread evenly over the threads");
     constexpr int NU = STEP_UNITS / NTH;     // per thread and step
-    __shared__ VT bs[2][STEP_UNITS * S];
+    VT* bs = (VT*)smem;                      // [2][STEP_UNITS * S]
     if (jb.rb0 >= jb.mb) return;             // whole work group (empty job)
+    FlushAt fl(jb);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int rg = wave % RG, c0w = (wave / RG) * CTW;
-    const int rbw = jb.rb0 + rg * RB;
+    const int rbw = jb.rb0 + wave * RB;
     const int kt = jb.kp >> 5;
     const int tb = jb.k0 >> 5, te = jb.k1 >> 5;    // te - tb is even (K slices of 64 k')
-    constexpr int TRB = RG * RB;         // row blocks of the tile: the A step stride
-    const VT* a = (const VT*)(A + jb.a_off) + (int64_t)(rg * RB) * 128 + lane;
-    const VT* b = (const VT*)(B + jb.b_off);
-    auto lda = [](const VT* p) -> VT {
-        if constexpr (CH == 1) return ld_stream(p);
-        else return *p;
-    };
-    d4_t acc[RB][CTW];
-    f4_t ac32[RB][CTW];
+    constexpr int TRB = NW * RB;         // row blocks of the tile: the A step stride
+    const VT* a = (const VT*)(A + jb.a_off) + (int64_t)(wave * RB) * 128 + lane;
+    const VT* b = (const VT*)(B + jb.b_off) + (int64_t)jb.c0 * kt * 128;
+    // (two jobs of an 8-tile row block read the same A: ordinary loads, the second finds it in a
+    // cache)
+    d4_t acc[RB][CT];
+    f4_t ac32[RB][CT];
 #pragma unroll
     for (int r = 0; r < RB; ++r)
 #pragma unroll
-        for (int c = 0; c < CTW; ++c) {
+        for (int c = 0; c < CT; ++c) {
             acc[r][c] = (d4_t){0, 0, 0, 0};
             ac32[r][c] = (f4_t){0, 0, 0, 0};
         }
@@ -343,7 +320,7 @@ __device__ inline void gemm_split_lds_job(const GemmJob& jb,
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int c = 0; c < CTW; ++c) store_c_f32acc(C, jb, rbw + r, c0w + c, lane, acc[r][c]);
+            for (int c = 0; c < CT; ++c) store_c_f32acc(C, jb, rbw + r, c, lane, acc[r][c]);
         return;
     }
     // this thread's share of B for step t: LDS in lane order, global in column-run order
@@ -357,7 +334,7 @@ __device__ inline void gemm_split_lds_job(const GemmJob& jb,
     };
     auto store_b = [&](int buf, int sidx, const VT (&src)[NU]) {
 #pragma unroll
-        for (int j = 0; j < NU; ++j) bs[buf][sidx * STEP_UNITS + tid + NTH * j] = src[j];
+        for (int j = 0; j < NU; ++j) bs[(buf * S + sidx) * STEP_UNITS + tid + NTH * j] = src[j];
     };
     // rings: PFA steps of A and of this thread's share of B in flight
     VT ah[PFA][RB], al[PFA][RB], br[PFA][NU];
@@ -366,8 +343,8 @@ __device__ inline void gemm_split_lds_job(const GemmJob& jb,
         const int tl = min(tb + u, te - 1);
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
-            ah[u][r] = lda(a + (((int64_t)(tl - tb) * TRB + r) * 128));
-            al[u][r] = lda(a + (((int64_t)(tl - tb) * TRB + r) * 128 + 64));
+            ah[u][r] = a[((int64_t)(tl - tb) * TRB + r) * 128];
+            al[u][r] = a[((int64_t)(tl - tb) * TRB + r) * 128 + 64];
         }
         load_b(br[u], tl);
     }
@@ -381,13 +358,13 @@ __device__ inline void gemm_split_lds_job(const GemmJob& jb,
             if (t >= te) break;                    // same for every wave of the group
             const int sidx = u % S;                // step inside the group of S
             const int buf = (u / S) & 1;           // groups of S alternate (PFA / S even)
-            const VT* bb = bs[buf] + sidx * STEP_UNITS;
+            const VT* bb = bs + (buf * S + sidx) * STEP_UNITS;
             // two column tiles at a time, the three products of a tile interleaved with
             // the other tile's, so dependent MFMAs are 2 RB instructions apart
 #pragma unroll
-            for (int c = 0; c < CTW; c += 2) {
-                const VT bh0 = bb[(c0w + c) * 128 + lane], bl0 = bb[(c0w + c) * 128 + 64 + lane];
-                const VT bh1 = bb[(c0w + c + 1) * 128 + lane], bl1 = bb[(c0w + c + 1) * 128 + 64 + lane];
+            for (int c = 0; c < CT; c += 2) {
+                const VT bh0 = bb[c * 128 + lane], bl0 = bb[c * 128 + 64 + lane];
+                const VT bh1 = bb[(c + 1) * 128 + lane], bl1 = bb[(c + 1) * 128 + 64 + lane];
 #pragma unroll
                 for (int r = 0; r < RB; ++r) {
                     ac32[r][c] = mfma_16x16x32(al[u][r], bh0, ac32[r][c]);
@@ -408,15 +385,15 @@ __device__ inline void gemm_split_lds_job(const GemmJob& jb,
             const int tl = min(t + PFA, te - 1);
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
-                ah[u][r] = lda(a + (((int64_t)(tl - tb) * TRB + r) * 128));
-                al[u][r] = lda(a + (((int64_t)(tl - tb) * TRB + r) * 128 + 64));
+                ah[u][r] = a[((int64_t)(tl - tb) * TRB + r) * 128];
+                al[u][r] = a[((int64_t)(tl - tb) * TRB + r) * 128 + 64];
             }
             load_b(br[u], tl);
-            if (((t - tb + 1) % KCH) == 0 || t + 1 == te) {
+            if (((t - tb) & 1) && (fl.template step<KC>() || t + 1 == te)) {
 #pragma unroll
                 for (int r = 0; r < RB; ++r)
 #pragma unroll
-                    for (int c = 0; c < CTW; ++c) {
+                    for (int c = 0; c < CT; ++c) {
 #pragma unroll
                         for (int j = 0; j < 4; ++j) acc[r][c][j] += (double)ac32[r][c][j];
                         ac32[r][c] = (f4_t){0, 0, 0, 0};
@@ -434,131 +411,393 @@ __device__ inline void gemm_split_lds_job(const GemmJob& jb,
 #pragma unroll
     for (int r = 0; r < RB; ++r)
 #pragma unroll
-        for (int c = 0; c < CTW; ++c) store_c_f32acc(C, jb, rbw + r, c0w + c, lane, acc[r][c]);
+        for (int c = 0; c < CT; ++c) store_c_f32acc(C, jb, rbw + r, c, lane, acc[r][c]);
 }
 
-template <typename VT, int RB, int CT, int PFA, int KCH, int S, int NW, int CH = 1>
-__global__ void __launch_bounds__(64 * NW) k_gemm_split_lds(const GemmJob* __restrict__ jobs, const unsigned short* __restrict__ A,
-        const unsigned short* __restrict__ B, double* __restrict__ C) {
-    const GemmJob jb = jobs[blockIdx.x];
-    gemm_split_lds_job<VT, RB, CT, PFA, KCH, S, NW, CH>(jb, A, B, C);
+typedef unsigned u4_t __attribute__((ext_vector_type(4)));
+
+// ------------------------------- gather jobs --------------------------------------
+// The blocks come from the table of distinct column offsets.  A job's 128 rows belong to 43 or
+// 44 pad columns, a chunk of 64 k' to 11 or 12 interface columns (the first and last maybe in
+// part): some 500 pairs, but on neighbouring columns only about a hundred distinct offsets, all
+// of them in a box of n1 x n2 of two hundred or so.  So the box, not the pairs, is read per
+// chunk: while the group computes a chunk, its threads load the records of the next chunk's box
+// into registers, then store them to LDS in three planes of 16 bytes (components xx xy | xz yz |
+// yy zz, eight bytes each); the chunk's B fragments and the places of its columns go the same
+// way.  One buffer and several work groups per CU rather than two buffers: their load, store and
+// compute phases overlap.
+// A record has 64 bytes (16 of padding): the address unit takes a quad of lanes a clock where
+// their 16-byte accesses fill one aligned 64-byte block, and one lane a clock otherwise.
+// A fragments are read component by component, at the place of the pad column plus that of the
+// interface column (n1 x n2 is linear in both).  The rows are taken in the order of their
+// Cartesian component, then of (n1, n2) (rows may be permuted freely, the K order may not).  The
+// column and the component of k' depend on the lane only through its group g and the chunk
+// number mod 3, so they come from three per-lane constants each.
+// bytes of a plane: 48 modulo 128, so that the three parts of consecutive records fall into
+// distinct banks
+constexpr int G_PL = G_CAP * 16 + 48;
+constexpr int G_COLS = (3 * G_PL + 127) / 128 * 128;      // places of the chunk's columns
+constexpr int G_B = G_COLS + 128;                         // B fragments, 4 KiB per column tile
+constexpr int gather_lds(int ct) { return G_B + 4096 * ct; }
+
+// STG: records of a box that go through registers; of a larger box (up to G_CAP) the rest is
+// copied while the chunk is stored.
+template <typename VT, int CT, int RG, int KC, int STG>
+__device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const void* __restrict__ Bv,
+                                  double* __restrict__ C, const CellDev* __restrict__ cells, char* smem) {
+    constexpr bool F32 = sizeof(VT) == 4;                         // VT = float: FP32, else the split halves
+    constexpr int NTH = 64 * RG, RB = JOB_ROWS / 16 / RG;
+    constexpr int NR = 4 * STG / NTH;
+    static_assert(4 * STG % NTH == 0 && STG <= G_CAP, "whole rounds of units");
+    constexpr int NBU = CT * 256 / NTH;                           // 16-byte B units per thread
+    static_assert(CT * 256 % NTH == 0, "B units must spread evenly over the threads");
+    if (jb.rb0 >= jb.mb) return;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4;
+    const int nch = jb.kp >> 6, first = jb.k0 >> 6, n = (jb.k1 - jb.k0) >> 6;
+    const CellDev cd = cells[jb.cell];
+    const int row0 = 16 * jb.rb0, tile = row0 / JOB_ROWS;
+    // the rows in the order used here: row - row0, place of the pad column in the box << 16
+    const int32_t* rows = tv.keys + cd.rrow + tile * JOB_ROWS;
+    d4_t acc[RB][CT];
+    f4_t ac32[RB][CT];
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            acc[r][c] = (d4_t){0, 0, 0, 0};
+            ac32[r][c] = (f4_t){0, 0, 0, 0};
+        }
+    if (n > 0) {
+        FlushAt fl(jb);
+        // this lane's complex column is a + 4 g (split; a + g / 2 for FP32, whose steps hold two
+        // columns), a the same for every lane, am = a mod 3: its interface column, and the LDS
+        // address of its rows' component at the pad column's place
+        const int gg = F32 ? g >> 1 : g;
+        int base[RB][3], il4[3];
+#pragma unroll
+        for (int am = 0; am < 3; ++am) il4[am] = G_COLS + 4 * ((am + (F32 ? gg : 4 * gg)) / 3);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int e = rows[16 * (wave * RB + r) + (lane & 15)];
+            const int c = (row0 + (e & 0xffff)) % 3;
+#pragma unroll
+            for (int am = 0; am < 3; ++am) {
+                const int d = (am + gg) % 3, lo = min(c, d), hi = max(c, d);
+                // slots: xx 0, xy 1, xz 2, yz 3, yy 4, zz 5
+                const int slot = lo == 0 ? hi : lo == 1 ? (hi == 1 ? 4 : 3) : 5;
+                base[r][am] = (slot >> 1) * G_PL + (slot & 1) * 8 + (e >> 16) * 16 + (F32 ? (g & 1) * 4 : 0);
+            }
+        }
+        const uniform_int* box = (const uniform_int*)(tv.keys + cd.rbox + 4 * tile);
+        const int tn1 = box[0], tspan = box[1], tn2 = box[2], L = box[3];   // smallest n1, range of n1, smallest n2
+        const uniform_int* chunks = (const uniform_int*)(tv.keys + cd.rchunk);
+        const int2* cols = (const int2*)(tv.keys + cd.rkey_i);
+        // this thread's units: quarter of a record, and the record's number relative to the box's first
+        const int part = tid & 3;
+        auto relative = [&](int p) {
+            const int r = p / L;
+            return r * tv.w2 + r + 2 * (p - r * L);
+        };
+        int rel[NR];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) rel[k] = relative((tid + NTH * k) >> 2);
+        const int at = part * G_PL + (tid >> 2) * 16;
+        const char* tm = tv.tab + jb.a_off;
+        const u4_t* bsrc = (const u4_t*)Bv + (F32 ? jb.b_off >> 2 : jb.b_off >> 3);
+        u4_t st[NR], sb[NBU];
+        int2 xc = make_int2(0, 0);
+        auto chunk_at = [&](int t) { return wrap_k(first + t, nch); };
+        int cmin1, cmax1, cmax2, pmax1 = 0, pmax2 = 0;            // of the chunk to load, of the chunk loaded
+        auto look = [&](int ch) {
+            cmin1 = chunks[4 * ch];
+            cmax1 = chunks[4 * ch + 1];
+            cmax2 = chunks[4 * ch + 2];
+        };
+        int nu = 0, org = 0;                                      // units of the box loaded, its first record
+        auto unit = [&](int rl) {                                 // (records of no offset are read too, inside the table)
+            const int rec = max(0, min((rl + org) >> 1, tv.nrec - 1));
+            return *(const u4_t*)(tm + (unsigned)(rec * 64 + part * 16));
+        };
+        auto load = [&](int ch) {
+            nu = 4 * L * (tspan + cmax1 - cmin1 + 1);
+            const int d1 = tn1 - cmax1, d2 = tn2 - cmax2;         // the box's first offset
+            org = d1 * tv.w2 + d1 + 2 * d2 - tv.base;
+#pragma unroll
+            for (int k = 0; k < NR; ++k) st[k] = unit(rel[k]);
+#pragma unroll
+            for (int j = 0; j < NBU; ++j) {
+                const int u = tid + NTH * j, c = u >> 8, e = u & 255;       // lane order from column-run order
+                sb[j] = bsrc[(unsigned)((jb.c0 + c) * jb.kp * 4 + (e & ~63) + bpos(e & 63)) + (unsigned)(256 * ch)];
+            }
+            if (tid < 12) xc = cols[(32 * ch) / 3 + tid];
+            pmax1 = cmax1;
+            pmax2 = cmax2;
+        };
+        auto store = [&]() {
+            if (part < 3) {
+#pragma unroll
+                for (int k = 0; k < NR; ++k) *(u4_t*)(smem + at + NTH * k * 4) = st[k];
+                if constexpr (STG < G_CAP)
+                    for (int u = NTH * NR + tid; u < nu; u += NTH)
+                        *(u4_t*)(smem + at + (u - tid) * 4) = unit(relative(u >> 2));
+            }
+#pragma unroll
+            for (int j = 0; j < NBU; ++j) *(u4_t*)(smem + G_B + (tid + NTH * j) * 16) = sb[j];
+            if (tid < 12) *(int*)(smem + G_COLS + 4 * tid) = 16 * (L * (pmax1 - xc.x) + pmax2 - xc.y);
+        };
+        auto compute = [&](auto phase) {
+            constexpr int PH = decltype(phase)::value;
+            const char* bl = smem + G_B + lane * 16;
+            if constexpr (F32) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float4 bb[CT];
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) bb[c] = *(const float4*)(bl + (c * 4 + q) * 1024);
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        constexpr int A0 = 32 * PH;
+                        const int a = A0 + 8 * q + 2 * h;
+                        const int pl = *(const int*)(smem + il4[a % 3] + 4 * (a / 3 - A0 / 3));
+                        float av[RB];
+#pragma unroll
+                        for (int r = 0; r < RB; ++r) av[r] = *(const float*)(smem + base[r][a % 3] + pl);
+#pragma unroll
+                        for (int r = 0; r < RB; ++r)
+#pragma unroll
+                            for (int c = 0; c < CT; ++c) {
+                                const float bv = h == 0 ? bb[c].x : h == 1 ? bb[c].y : h == 2 ? bb[c].z : bb[c].w;
+                                ac32[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r], bv, ac32[r][c], 0, 0, 0);
+                            }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    VT ah[RB], al[RB];
+                    int pl[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        constexpr int A0 = 32 * PH;
+                        const int a = A0 + 16 * s + j;
+                        pl[j] = *(const int*)(smem + il4[a % 3] + 4 * (a / 3 - A0 / 3));
+                    }
+#pragma unroll
+                    for (int r = 0; r < RB; ++r) {
+                        u4_t h4, l4;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const uint2 v = *(const uint2*)(smem + base[r][(32 * PH + 16 * s + j) % 3] + pl[j]);
+                            h4[j] = v.x;
+                            l4[j] = v.y;
+                        }
+                        ah[r] = __builtin_bit_cast(VT, h4);
+                        al[r] = __builtin_bit_cast(VT, l4);
+                    }
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) {
+                        const VT bh = *(const VT*)(bl + (c * 4 + 2 * s) * 1024);
+                        const VT bo = *(const VT*)(bl + (c * 4 + 2 * s + 1) * 1024);
+#pragma unroll
+                        for (int r = 0; r < RB; ++r) ac32[r][c] = mfma_16x16x32(al[r], bh, ac32[r][c]);
+#pragma unroll
+                        for (int r = 0; r < RB; ++r) ac32[r][c] = mfma_16x16x32(ah[r], bo, ac32[r][c]);
+#pragma unroll
+                        for (int r = 0; r < RB; ++r) ac32[r][c] = mfma_16x16x32(ah[r], bh, ac32[r][c]);
+                    }
+                }
+            }
+        };
+        int ch = chunk_at(0);
+        look(ch);
+        load(ch);
+        look(chunk_at(min(1, n - 1)));
+        store();
+        __syncthreads();
+        for (int t = 0; t < n; ++t) {
+            const int nx = chunk_at(min(t + 1, n - 1));
+            if (t + 1 < n) load(nx);
+            const int ph = ch % 3;
+            if (ph == 0) compute(std::integral_constant<int, 0>());
+            else if (ph == 1) compute(std::integral_constant<int, 1>());
+            else compute(std::integral_constant<int, 2>());
+            if (fl.template step<KC>() || t + 1 == n) {
+#pragma unroll
+                for (int r = 0; r < RB; ++r)
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) acc[r][c][j] += (double)ac32[r][c][j];
+                        ac32[r][c] = (f4_t){0, 0, 0, 0};
+                    }
+            }
+            __syncthreads();                       // the chunk has been read
+            if (t + 1 < n) {
+                look(chunk_at(min(t + 2, n - 1)));
+                store();
+            }
+            __syncthreads();
+            ch = nx;
+        }
+    }
+    const int64_t mp = (int64_t)jb.mb * 16;
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t row = row0 + (rows[16 * (wave * RB + r) + 4 * g + j] & 0xffff);
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+                C[jb.c_off + ((jb.c0 + c) * mp + row) * jb.crs + (lane & 15)] = acc[r][c][j];
+        }
 }
-template <typename VT, int RB, int CT, int PFA, int KCH, int S, int NW, int CH = 1>
-__global__ void __launch_bounds__(64 * NW) k_gemm_split_lds_pq(const GemmJob* __restrict__ jobs, int njobs, PqLists q,
-        const unsigned short* __restrict__ A, const unsigned short* __restrict__ B, double* __restrict__ C) {
+
+// ------------------------------- kernels ------------------------------------------
+// Shape of a product class and variant: TRB row blocks per tile of the compact store, RG row
+// groups (waves) on a job's 128 rows, CT column tiles, KC chunks of 64 k' per FP32 sum, OCC work groups per CU, STG staged records, and the stream jobs' ring (PF, or PFA
+// and K steps per barrier S).
+template <typename VT_, int TRB_, int CT_, int RG_, int KC_, int OCC_, int STG_, int PF_, int S_ = 0>
+struct Shape {
+    using VT = VT_;
+    static constexpr int TRB = TRB_, CT = CT_, RG = RG_, KC = KC_, PF = PF_, S = S_, OCC = OCC_, STG = STG_;
+    static constexpr int NTH = 64 * RG_, RB = JOB_ROWS / 16 / RG_;
+    static constexpr int LDS = S_ == 0 ? gather_lds(CT_) : std::max(gather_lds(CT_), 2 * S_ * CT_ * 2048);
+    static constexpr int WPE = std::max(1, OCC_ * RG_ / 4);      // waves per SIMD
+};
+
+template <typename SH>
+__device__ inline void any_job(const GemmJob& jb, const void* __restrict__ A, const RTabView& tv,
+                               const void* __restrict__ B, double* __restrict__ C,
+                               const CellDev* __restrict__ cells, char* smem) {
+    using VT = typename SH::VT;
+    if (jb.gather) {
+        gather_job<VT, SH::CT, SH::RG, SH::KC, SH::STG>(jb, tv, B, C, cells, smem);
+    } else if constexpr (sizeof(VT) == 4) {
+        gemm_f32_job<SH::TRB, SH::RB, SH::CT, SH::PF, SH::KC>(jb, (const float*)A, (const float*)B, C);
+    } else if constexpr (SH::S == 0) {
+        gemm_split_job<VT, SH::TRB, SH::RB, SH::CT, SH::PF, SH::KC>(
+            jb, (const unsigned short*)A, (const unsigned short*)B, C);
+    } else {
+        gemm_split_lds_job<VT, SH::RB, SH::CT, SH::PF, SH::KC, SH::S, SH::RG>(
+            jb, (const unsigned short*)A, (const unsigned short*)B, C, smem);
+    }
+}
+
+// A job, loaded into scalar registers (the persistent kernels' own stores would otherwise make
+// every load of the list a vector load).
+__device__ inline GemmJob job_at(const GemmJob* __restrict__ jobs, int j) {
+    GemmJob jb;
+    const uniform_int* src = (const uniform_int*)(jobs + j);
+    int* dst = (int*)&jb;
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(GemmJob) / 4); ++k) dst[k] = src[k];
+    return jb;
+}
+
+template <typename SH>
+__global__ void __launch_bounds__(SH::NTH, SH::WPE) k_gemm(const GemmJob* __restrict__ jobs, const void* __restrict__ A,
+                                                  RTabView tv, const void* __restrict__ B, double* __restrict__ C,
+                                                  const CellDev* __restrict__ cells) {
+    extern __shared__ __attribute__((aligned(128))) char gsm[];
+    const GemmJob jb = job_at(jobs, blockIdx.x);
+    any_job<SH>(jb, A, tv, B, C, cells, gsm);
+}
+template <typename SH>
+__global__ void __launch_bounds__(SH::NTH, SH::WPE) k_gemm_pq(const GemmJob* __restrict__ jobs, int njobs, PqLists q,
+                                                     const void* __restrict__ A, RTabView tv,
+                                                     const void* __restrict__ B, double* __restrict__ C,
+                                                     const CellDev* __restrict__ cells) {
+    extern __shared__ __attribute__((aligned(128))) char gsm[];
     __shared__ int slot;
     int cur = 0;
     for (int j = pq_next(q, &slot, cur); j < njobs; j = pq_next(q, &slot, cur)) {
-        const GemmJob jb = jobs[j];
-        gemm_split_lds_job<VT, RB, CT, PFA, KCH, S, NW, CH>(jb, A, B, C);
+        const GemmJob jb = job_at(jobs, j);
+        any_job<SH>(jb, A, tv, B, C, cells, gsm);
     }
     pq_done(q);
 }
 
-// Row blocks per wave for a given column-tile count (register budget per lane).
-static int gemm_rb(int form, int ctmax) {
-    // one column tile: 2 row blocks per wave for the FP32 and split products (128-row work
-    // groups: finer negligible-block windows and more work groups; measured 3 % faster
-    // than 4 on the medium workload)
-    (void)form;
-    return ctmax == 2 ? 4 : 2;
-}
-// Waves per work group (every product kernel as launched runs four).
-static int gemm_waves(int, int) { return 4; }
-// Rows of a work group's tile (16 per row block): the planner pads rows to whole tiles,
-// K' to a multiple of 64, and lays the compact store out in tiles of this height.
-int gemm_tile_rows(int form, int ctmax) { return 16 * gemm_rb(form, ctmax) * gemm_waves(form, ctmax); }
-
-template <typename TA>
-static void launch_dense(void (*kn)(const GemmJob*, const TA*, const TA*, double*),
-                         void (*kp)(const GemmJob*, int, PqLists, const TA*, const TA*, double*),
-                         hipStream_t st, const GemmJob* jobs, int njobs, const void* a, const void* b,
-                         double* c, const PqLists* q, int threads = 256) {
-    if (q)
-        hipLaunchKernelGGL(kp, dim3(std::min(njobs, pq_groups_of(kp, threads))), dim3(threads), 0, st, jobs, njobs,
-                           *q, (const TA*)a, (const TA*)b, c);
-    else
-        hipLaunchKernelGGL(kn, dim3(njobs), dim3(threads), 0, st, jobs, (const TA*)a, (const TA*)b, c);
-}
+// Rows of a tile (16 per row block): the planner pads rows to whole tiles, K' to a multiple of
+// 64, takes the windows per tile and lays the compact store out in tiles of this height.  256
+// rows at two column tiles, 128 at the others; a job is 128 rows of a tile (JOB_ROWS).
+int gemm_tile_rows(int, int ctmax) { return ctmax == 2 ? 256 : 128; }
 
 // Kernel variants of a product class (form, column tiles) that the autotuner may choose
-// from.  They share the tile height (the compact store is laid out in tiles) and the
-// arithmetic order, so every variant gives bitwise the same result: variant 0 is the
-// default; variant 1 changes the depth of the prefetch ring (FP32) or the K steps
-// per barrier (split products staging B in LDS); variant 2 of those splits the column
-// tiles between two halves of eight waves (two waves per SIMD).  The split products with one or two
-// column tiles have one variant: their main loop runs whole ring passes, and a 64-k'
-// chunk is two of their steps, so the ring cannot be deeper than two steps.
+// from.  They share the tile height and the arithmetic order, so every variant gives bitwise
+// the same result: variant 0 is the default; variant 1 changes the depth of the stream jobs'
+// prefetch ring (FP32) or their K steps per barrier (split products with four or eight column
+// tiles; variant 2: half the ring besides).
 int gemm_variants(int form, int ctmax) {
     if (form == FBC_FORM_SPLIT_FP16 || form == FBC_FORM_SPLIT_BF16) return ctmax <= 2 ? 1 : 3;
     return 2;
 }
 
-// Readable shape of a variant: kernel, row blocks per wave, column tiles, ring depth,
-// FP32 chunk (K steps), K steps per barrier, waves per group.
-std::string gemm_shape(int form, int ctmax, int variant) {
-    const int ct = ctmax <= 1 ? 1 : ctmax <= 2 ? 2 : ctmax <= 4 ? 4 : 8;
-    const bool alt = variant == 1;
-    char buf[96];
+// Column tiles of a job: contexts of eight tiles run each row tile as two jobs of four.
+int gemm_job_tiles(int ctmax) { return std::min(ctmax, 4); }
+
+// Calls fn(Shape) for a product class and variant.  FP32 sums: 2 chunks of 64 k' for split FP16
+// (its representation error is ~2^-23, so the FP32 sums must not dominate; 1 chunk at one or
+// two column tiles), 4 for split BF16 and FP32.
+template <typename F>
+static void with_shape(int form, int ctmax, int variant, F&& fn) {
+#define SPLIT_SHAPES(VT, KC12, KC48, OCC2, STG2)                                               \
+    if (ctmax <= 1) fn(Shape<VT, 8, 1, 4, KC12, 4, G_CAP, 2>());                               \
+    else if (ctmax <= 2) fn(Shape<VT, 16, 2, 4, KC12, OCC2, STG2, 2>());                       \
+    else if (variant == 2) fn(Shape<VT, 8, 4, 4, KC48, 2, G_CAP, 2, 1>());                     \
+    else if (variant == 1) fn(Shape<VT, 8, 4, 4, KC48, 2, G_CAP, 4, 1>());                     \
+    else fn(Shape<VT, 8, 4, 4, KC48, 2, G_CAP, 4, 2>());
     if (form == FBC_FORM_FP32) {
-        const int rb = ct == 2 ? 4 : 2, pf = (ct <= 2) != alt ? 4 : 2;
-        snprintf(buf, sizeof buf, "f32 RB=%d CT=%d PF=%d KCH=16 waves=4", rb, ct, pf);
-    } else if (ct <= 2) {
-        const bool f16 = form == FBC_FORM_SPLIT_FP16;
-        snprintf(buf, sizeof buf, "split %s RB=%d CT=%d PF=2 KCH=%d waves=4", f16 ? "f16" : "bf16", ct == 2 ? 4 : 2,
-                 ct, f16 ? 2 : 8);
+        if (ctmax <= 1) {
+            if (variant) fn(Shape<float, 8, 1, 4, 4, 4, G_CAP, 2>());
+            else fn(Shape<float, 8, 1, 4, 4, 4, G_CAP, 4>());
+        } else if (ctmax <= 2) {
+            if (variant) fn(Shape<float, 16, 2, 4, 4, 3, G_CAP, 2>());
+            else fn(Shape<float, 16, 2, 4, 4, 3, G_CAP, 4>());
+        } else {
+            if (variant) fn(Shape<float, 8, 4, 4, 4, 2, G_CAP, 4>());
+            else fn(Shape<float, 8, 4, 4, 4, 2, G_CAP, 2>());
+        }
+    } else if (form == FBC_FORM_SPLIT_FP16) {
+        SPLIT_SHAPES(h8_t, 1, 2, 4, 256)
     } else {
-        const bool f16 = form == FBC_FORM_SPLIT_FP16;
-        if (variant == 2)
-            snprintf(buf, sizeof buf, "split_lds %s RB=2 CT=%d PFA=4 KCH=%d S=2 waves=8 (column halves)",
-                     f16 ? "f16" : "bf16", ct, f16 ? 4 : 8);
-        else
-            snprintf(buf, sizeof buf, "split_lds %s RB=2 CT=%d PFA=4 KCH=%d S=%d waves=4", f16 ? "f16" : "bf16", ct,
-                     f16 ? 4 : 8, alt ? 1 : 2);
+        SPLIT_SHAPES(bf8_t, 4, 4, 3, G_CAP)
     }
+#undef SPLIT_SHAPES
+}
+
+// Readable shape of a variant.
+std::string gemm_shape(int form, int ctmax, int variant) {
+    char buf[96];
+    with_shape(form, ctmax, variant, [&](auto sh) {
+        using SH = decltype(sh);
+        snprintf(buf, sizeof buf, "%s rows=%d CT=%d waves=%d KC=%d ring=%d S=%d, gather + stream",
+                 form == FBC_FORM_FP32 ? "f32" : form == FBC_FORM_SPLIT_FP16 ? "f16" : "bf16", JOB_ROWS, SH::CT,
+                 SH::RG, SH::KC, SH::PF, SH::S);
+    });
     return buf;
 }
 
-void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int ctmax,
-                 const void* a, const void* b, double* c, const PqLists* q, int variant) {
+// Raises the dynamic-LDS limit of the product kernels of a class on the current device (call
+// outside stream capture, e.g. at context creation).
+void gemm_kernels_init(int form, int ctmax) {
+    for (int v = 0; v < gemm_variants(form, ctmax); ++v)
+        with_shape(form, ctmax, v, [&](auto sh) {
+            using SH = decltype(sh);
+            (void)hipFuncSetAttribute((const void*)k_gemm<SH>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS);
+            (void)hipFuncSetAttribute((const void*)k_gemm_pq<SH>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS);
+        });
+    (void)hipGetLastError();
+}
+
+void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int ctmax, const void* a,
+                 const RTabView& tv, const void* b, double* c, const CellDev* cells, const PqLists* q, int variant) {
     if (njobs <= 0) return;
-#define GEMM_CASE(KERN, RB, CT, ...)                                                           \
-    launch_dense<TA>(KERN<RB, CT, __VA_ARGS__>, KERN##_pq<RB, CT, __VA_ARGS__>, st, jobs, njobs, a, b, c, q)
-#define GEMM_PICK(DEF, ALT) do { if (variant == 1) ALT; else DEF; } while (0)
-#define GEMM_CASE8(KERN, ...)                                                                  \
-    launch_dense<TA>(KERN<__VA_ARGS__, 8, 2>, KERN##_pq<__VA_ARGS__, 8, 2>, st, jobs, njobs, a, b, c, q, 512)
-#define GEMM_PICK3(DEF, ALT, CS) do { if (variant == 2) CS; else if (variant == 1) ALT; else DEF; } while (0)
-    if (form == FBC_FORM_FP32) {
-        typedef float TA;
-        if (ctmax <= 1) GEMM_PICK(GEMM_CASE(k_gemm_f32, 2, 1, 4, 16), GEMM_CASE(k_gemm_f32, 2, 1, 2, 16));
-        else if (ctmax <= 2) GEMM_PICK(GEMM_CASE(k_gemm_f32, 4, 2, 4, 16), GEMM_CASE(k_gemm_f32, 4, 2, 2, 16));
-        else if (ctmax <= 4) GEMM_PICK(GEMM_CASE(k_gemm_f32, 2, 4, 2, 16), GEMM_CASE(k_gemm_f32, 2, 4, 4, 16));
-        else GEMM_PICK(GEMM_CASE(k_gemm_f32, 2, 8, 2, 16), GEMM_CASE(k_gemm_f32, 2, 8, 4, 16));
-    } else if (form == FBC_FORM_SPLIT_FP16) {
-        // shorter FP32 chunks: the representation error is ~2^-23, so the FP32 sums must
-        // not dominate
-        typedef unsigned short TA;
-        if (ctmax <= 1) GEMM_CASE(k_gemm_split, h8_t, 2, 1, 2, 2);
-        else if (ctmax <= 2) GEMM_CASE(k_gemm_split, h8_t, 4, 2, 2, 2);
-        else if (ctmax <= 4)
-            GEMM_PICK3(GEMM_CASE(k_gemm_split_lds, h8_t, 2, 4, 4, 4, 2, 4), GEMM_CASE(k_gemm_split_lds, h8_t, 2, 4, 4, 4, 1, 4),
-                       GEMM_CASE8(k_gemm_split_lds, h8_t, 2, 4, 4, 4, 2));
+    with_shape(form, ctmax, variant, [&](auto sh) {
+        using SH = decltype(sh);
+        if (q)
+            hipLaunchKernelGGL(k_gemm_pq<SH>, dim3(std::min(njobs, SH::OCC * device_cus())),
+                               dim3(SH::NTH), SH::LDS, st, jobs, njobs, *q, a, tv, b, c, cells);
         else
-            GEMM_PICK3(GEMM_CASE(k_gemm_split_lds, h8_t, 2, 8, 4, 4, 2, 4), GEMM_CASE(k_gemm_split_lds, h8_t, 2, 8, 4, 4, 1, 4),
-                       GEMM_CASE8(k_gemm_split_lds, h8_t, 2, 8, 4, 4, 2));
-    } else {
-        typedef unsigned short TA;
-        if (ctmax <= 1) GEMM_CASE(k_gemm_split, bf8_t, 2, 1, 2, 8);
-        else if (ctmax <= 2) GEMM_CASE(k_gemm_split, bf8_t, 4, 2, 2, 8);
-        else if (ctmax <= 4)
-            GEMM_PICK3(GEMM_CASE(k_gemm_split_lds, bf8_t, 2, 4, 4, 8, 2, 4), GEMM_CASE(k_gemm_split_lds, bf8_t, 2, 4, 4, 8, 1, 4),
-                       GEMM_CASE8(k_gemm_split_lds, bf8_t, 2, 4, 4, 8, 2));
-        else
-            GEMM_PICK3(GEMM_CASE(k_gemm_split_lds, bf8_t, 2, 8, 4, 8, 2, 4), GEMM_CASE(k_gemm_split_lds, bf8_t, 2, 8, 4, 8, 1, 4),
-                       GEMM_CASE8(k_gemm_split_lds, bf8_t, 2, 8, 4, 8, 2));
-    }
-#undef GEMM_PICK3
-#undef GEMM_CASE8
-#undef GEMM_PICK
-#undef GEMM_CASE
+            hipLaunchKernelGGL(k_gemm<SH>, dim3(njobs), dim3(SH::NTH), SH::LDS, st, jobs, a, tv, b, c, cells);
+    });
 }

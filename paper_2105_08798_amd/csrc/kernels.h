@@ -36,6 +36,12 @@ void launch_build_dense(hipStream_t st, int form, void* store, const double2* ta
                         int64_t n_off, int n_b, int n_i, const int32_t* cols_b, const int32_t* cols_i,
                         const int32_t* lut, int d1min, int d2min, int w2, unsigned long long* amax);
 
+// Table of the reduced forms (RTabView): records of every table mode; amax: largest magnitude per
+// table mode (split FP16: its scale).
+void launch_build_rtab(hipStream_t st, int form, const double2* tab, int T, int64_t n_off, const int32_t* d1,
+                       const int32_t* d2, const RBox& box, const unsigned long long* amax, char* rtab);
+void launch_tab_absmax(hipStream_t st, const double2* tab, int T, int64_t n_off, unsigned long long* amax);
+
 // ---- apply (Section 2.3.2 update in line-mode form) ----
 // Per-layer sums sums[r][n0][6] (net force, absolute force), cell totals tot[r][3] with
 // the net-force check, and (shat != NULL) the line transform of the per-layer net force.
@@ -45,10 +51,12 @@ void launch_netforce(hipStream_t st, const double* f, double* sums, double* tot,
 void launch_line_rfft(hipStream_t st, int form, const double* f, const double* tot, int project,
                       void* bfrag, int R, int nz, int n_i, int kp, int ct, const double2* tw,
                       const int* bexp);
-// variant: one of gemm_variants(form, ctmax) kernel instantiations (bitwise the same result)
-void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int ctmax,
-                 const void* a, const void* b, double* c,
-                 const PqLists* q, int variant);   // q != NULL: persistent work-queue kernel on these lists
+// Reduced forms.  variant: one of gemm_variants(form, ctmax) kernel instantiations (bitwise the
+// same result); q != NULL: persistent work-queue kernel on these lists.
+void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int ctmax, const void* a,
+                 const RTabView& tv, const void* b, double* c, const CellDev* cells, const PqLists* q, int variant);
+void gemm_kernels_init(int form, int ctmax);
+int gemm_job_tiles(int ctmax);
 int gemm_variants(int form, int ctmax);
 std::string gemm_shape(int form, int ctmax, int variant);
 // Offset-table forms (gemm_table.hip): one job per wave, 16 pad columns over a window of

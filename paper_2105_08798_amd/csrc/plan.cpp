@@ -156,6 +156,43 @@ void plan_windows_ranges(const PlanGeom& p, int nm, const std::vector<PlanRange>
     }
 }
 
+void plan_boxes(const PlanGeom& p, int n_tiles, int rows, int n_chunks, PlanBoxes& out) {
+    auto span = [](const int32_t* cols, int n, int lo, int hi, int32_t (&r)[4]) {     // min, max of n1, n2
+        for (int k = lo; k <= hi; ++k) {
+            const int32_t* c = cols + 2 * std::min(k, n - 1);
+            for (int a = 0; a < 2; ++a) {
+                r[2 * a] = k == lo ? c[a] : std::min(r[2 * a], c[a]);
+                r[2 * a + 1] = k == lo ? c[a] : std::max(r[2 * a + 1], c[a]);
+            }
+        }
+    };
+    out.chunk.assign((size_t)n_chunks * 4, 0);
+    std::vector<int32_t> r2(n_chunks);
+    int32_t r[4];
+    for (int ch = 0; ch < n_chunks; ++ch) {
+        span(p.cols_i, p.n_i, (32 * ch) / 3, (32 * ch + 31) / 3, r);
+        out.chunk[4 * ch] = r[0];
+        out.chunk[4 * ch + 1] = r[1];
+        out.chunk[4 * ch + 2] = r[3];
+        r2[ch] = r[3] - r[2];
+    }
+    out.box.assign((size_t)n_tiles * 4, 0);
+    out.largest.assign(n_tiles, 0);
+    for (int tl = 0; tl < n_tiles; ++tl) {
+        span(p.cols_b, p.n_b, (tl * rows) / 3, ((tl + 1) * rows - 1) / 3, r);
+        int64_t len = 0, d1 = 0;
+        for (int ch = 0; ch < n_chunks; ++ch) {
+            len = std::max<int64_t>(len, (int64_t)r[3] - r[2] + r2[ch] + 1);
+            d1 = std::max<int64_t>(d1, (int64_t)r[1] - r[0] + out.chunk[4 * ch + 1] - out.chunk[4 * ch] + 1);
+        }
+        out.box[4 * tl] = r[0];
+        out.box[4 * tl + 1] = r[1] - r[0];
+        out.box[4 * tl + 2] = r[2];
+        out.box[4 * tl + 3] = (int32_t)len;
+        out.largest[tl] = len * d1;
+    }
+}
+
 int plan_tree(std::vector<PlanNode>& nodes, const std::vector<int32_t>& cols, std::vector<int> idx, int b_min) {
     PlanNode h;
     h.n = (long long)idx.size();

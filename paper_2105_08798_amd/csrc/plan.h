@@ -51,6 +51,18 @@ void plan_windows_ranges(const PlanGeom& g, int nm, const std::vector<PlanRange>
 void plan_windows(const PlanGeom& g, int nm, int mp, int kp, bool table_form, int rows_tile, int mult,
                   const std::vector<double>& rho_cut, PlanWindows& out);
 
+// Boxes of column offsets of the reduced forms' gather jobs.  chunk [n_chunks][4]: smallest and
+// largest n1 and largest n2 of the interface columns that a chunk of 32 complex columns (three per
+// interface column) touches, one unused; box [n_tiles][4]: smallest n1, range of n1, smallest n2
+// of the pad columns that a tile of `rows` rows touches, and the length of a box row (the largest
+// range of d2 over the chunks, plus one); largest [n_tiles]: records of the tile's largest box
+// (range of d1 plus one, times the row length).  Columns past the last count as the last.
+struct PlanBoxes {
+    std::vector<int32_t> chunk, box;
+    std::vector<int64_t> largest;
+};
+void plan_boxes(const PlanGeom& g, int n_tiles, int rows, int n_chunks, PlanBoxes& out);
+
 // Cluster tree node: columns in tree order and the bounding box in the integer coordinates
 // X = n1, Y = n1 + 2 n2 (in-plane x = X / 2, y = Y / (2 sqrt 2)).
 struct PlanNode {

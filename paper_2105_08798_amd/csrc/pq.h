@@ -51,6 +51,17 @@ __device__ inline void pq_done(const PqLists& q) {
     if (threadIdx.x == 0) pq_leave(q, (int)gridDim.x);
 }
 
+// Compute units of the current device (one device type per process).
+static inline int device_cus() {
+    static const int n = [] {
+        int dev = 0, cus = 0;
+        (void)hipGetDevice(&dev);
+        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        return std::max(1, cus);
+    }();
+    return n;
+}
+
 // Work groups of a persistent launch: the kernel's occupancy per CU times the CUs
 // (queried once per kernel and cached; the library runs on one device type per process).
 template <typename K>
@@ -61,11 +72,9 @@ static int pq_groups_of(K kernel, int threads) {
     const void* key = (const void*)kernel;
     auto it = cache.find(key);
     if (it != cache.end()) return it->second;
-    int per_cu = 0, dev = 0, cus = 0;
+    int per_cu = 0;
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0);
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    const int g = std::max(1, per_cu) * std::max(1, cus);
+    const int g = std::max(1, per_cu) * device_cus();
     cache[key] = g;
     return g;
 }
