@@ -37,8 +37,8 @@ void launch_cgf_points(hipStream_t st, const CgfView& v, const double* theta0, c
 int64_t mlp_workspace_floats(int n);
 void launch_mlp_forward(hipStream_t st, const float* params, const float* x, int n, float* ws,
                         float* y);
-void launch_mlp_loss_grad(hipStream_t st, const float* params, const float* x, const float* t,
-                          const float* w, int n, float* ws, float* grad, float* loss);
+void launch_mlp_loss_grad(hipStream_t st, const float* params, const float* x, const float* t, int n, float* ws,
+                          float* grad, float* loss);
 void launch_adam(hipStream_t st, float* p, const float* g, float* m, float* v, int n, float lr,
                  int step);
 

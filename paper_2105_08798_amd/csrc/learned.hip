@@ -5,6 +5,7 @@
 // backward, Adam) and the on-the-fly table generator of the surrogate form.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "elastic.h"
@@ -221,122 +222,308 @@ void launch_cgf_build(hipStream_t st, const CgfConst& k, const double* cpsi, con
 // ----------------------------------------------------------------------------------
 // MLP 8 -> 128 -> 128 -> 128 -> 12, SiLU, FP32 training kernels.
 // Parameter layout: per layer W [out][in] row-major, then b [out].
+//
+// A work group takes MT samples through every layer and, for training, back: the contractions
+// over a layer run on FP32 MFMA (FP32 operands and sums, as scalar FMAs would), a wave for each 16
+// rows of a layer and all MT samples, activations in LDS, z in registers between the two passes.
+// Weights go from L2 straight to registers (35k of them, the same for every group).  Weight
+// gradients, sums over all samples, are FP64 MFMA products of the stored activations and dz, in
+// chunks whose partial sums are added in fixed order.  8192 samples: 8 us each of FP32 and of FP64
+// MFMA; loss and gradient in three launches 83 us a call (26, 24 and 4 of kernels), with scalar FMAs
+// in a launch per layer and step 782.
 // ----------------------------------------------------------------------------------
+typedef float f4v_t __attribute__((ext_vector_type(4)));
+typedef double d4v_t __attribute__((ext_vector_type(4)));
+
 __device__ inline float silu(float z) { return z / (1.0f + expf(-z)); }
 __device__ inline float silu_d(float z) {
     const float s = 1.0f / (1.0f + expf(-z));
     return s * (1.0f + z * (1.0f - s));
 }
 
-// out[s][o] = b[o] + sum_i in[s][i] W[o][i]; z stored, a = silu(z) unless last.
-// A block takes FWD_S samples: W (transposed, [i][o]) and the input rows are staged in
-// LDS, then each thread forms outputs (s, o) with o running fastest across the wave.
-#define FWD_S 32
-__global__ void __launch_bounds__(NTL) k_dense_fwd(const float* __restrict__ in, int n, int ni, int no,
-                                                   const float* __restrict__ W,
-                                                   const float* __restrict__ b,
-                                                   float* __restrict__ z, float* __restrict__ a,
-                                                   int last) {
-    __shared__ float wt[MLP_H * MLP_H];
-    __shared__ float xs[FWD_S * MLP_H];
-    const int s0 = blockIdx.x * FWD_S;
-    const int ns = min(FWD_S, n - s0);
-    for (int e = threadIdx.x; e < ni * no; e += NTL) {
-        const int o = e / ni, i = e - o * ni;
-        wt[i * no + o] = W[e];
+// Offset of a layer's weights in the parameters; its biases follow them.
+__host__ __device__ constexpr int layer_off(int l) {
+    return l == 0 ? 0 : MLP_H * (MLP_IN + 1) + (l - 1) * MLP_H * (MLP_H + 1);
+}
+static_assert(layer_off(3) + MLP_OUT * (MLP_H + 1) == MLP_NPARAMS, "layers end to end");
+
+#define MT 32                       // samples of a work group
+#define MT_LD (MLP_H + 4)           // row of a sample in LDS: 16-byte reads of 16 samples spread over the banks
+#define OUT_LD 16                   // row of dz of the last layer (12 outputs, zeros)
+
+// Training workspace: a and dz of the three hidden layers, dz of the last (n samples), the loss
+// partials of the work groups, the chunks' partial gradients.
+struct MlpWs {
+    float *a[3], *dz[4];
+    double *loss, *part;
+};
+static const int kMaxChunks = 23;
+static int mlp_groups(int n) { return (n + MT - 1) / MT; }
+int64_t mlp_workspace_floats(int n) {
+    return (int64_t)n * (6 * MLP_H + OUT_LD) + 4LL * mlp_groups(n) + 2LL * kMaxChunks * MLP_NPARAMS;
+}
+static MlpWs mlp_ws(float* ws, int n) {
+    MlpWs w;
+    double* d = (double*)ws;                      // the doubles first
+    w.part = d;
+    w.loss = d + (int64_t)kMaxChunks * MLP_NPARAMS;
+    float* p = (float*)(w.loss + 2 * mlp_groups(n));
+    for (int l = 0; l < 3; ++l) {
+        w.a[l] = p + (int64_t)l * n * MLP_H;
+        w.dz[l] = p + (int64_t)(3 + l) * n * MLP_H;
     }
-    for (int e = threadIdx.x; e < ns * ni; e += NTL) xs[e] = in[(int64_t)s0 * ni + e];
-    __syncthreads();
-    for (int e = threadIdx.x; e < ns * no; e += NTL) {
-        const int sl = e / no, o = e - sl * no;
-        float acc = b[o];
-        const float* x = xs + sl * ni;
-        for (int i = 0; i < ni; ++i) acc = fmaf(x[i], wt[i * no + o], acc);
-        const int64_t idx = (int64_t)(s0 + sl) * no + o;
-        z[idx] = acc;
-        a[idx] = last ? acc : silu(acc);
-    }
+    w.dz[3] = p + (int64_t)6 * n * MLP_H;
+    return w;
 }
 
-// dz = da * silu'(z) (or da for the last layer).
-__global__ void __launch_bounds__(NTL) k_dense_dz(const float* __restrict__ da,
-                                                  const float* __restrict__ z, int64_t total,
-                                                  float* __restrict__ dz, int last) {
-    const int64_t idx = (int64_t)blockIdx.x * NTL + threadIdx.x;
-    if (idx < total) dz[idx] = last ? da[idx] : da[idx] * silu_d(z[idx]);
-}
-// din[s][i] = sum_o dz[s][o] W[o][i].
-__global__ void __launch_bounds__(NTL) k_dense_bwd_x(const float* __restrict__ dz, int n, int ni, int no,
-                                                     const float* __restrict__ W,
-                                                     float* __restrict__ din) {
-    const int64_t idx = (int64_t)blockIdx.x * NTL + threadIdx.x;
-    if (idx >= (int64_t)n * ni) return;
-    const int s = (int)(idx / ni), i = (int)(idx - (int64_t)s * ni);
-    float acc = 0.0f;
-    const float* g = dz + (int64_t)s * no;
-    for (int o = 0; o < no; ++o) acc = fmaf(g[o], W[(int64_t)o * ni + i], acc);
-    din[idx] = acc;
-}
-// dW[o][i] = sum_s dz[s][o] in[s][i]; db[o] = sum_s dz[s][o].  The samples are cut into
-// gridDim.y chunks; each chunk's FP64 partial sum goes to part[chunk][o * (ni + 1) + i],
-// and k_dense_bwd_sum adds the chunks in fixed order (deterministic result).
-__global__ void __launch_bounds__(NTL) k_dense_bwd_w(const float* __restrict__ dz,
-                                                     const float* __restrict__ in, int n, int ni,
-                                                     int no, int chunk, double* __restrict__ part) {
-    const int idx = blockIdx.x * NTL + threadIdx.x;
-    const int nw = no * (ni + 1);
-    if (idx >= nw) return;
-    const int o = idx / (ni + 1), i = idx - o * (ni + 1);
-    const int sa = blockIdx.y * chunk, sb = min(n, sa + chunk);
-    double acc = 0.0;
-    if (i < ni)
-        for (int s = sa; s < sb; ++s) acc += (double)dz[(int64_t)s * no + o] * in[(int64_t)s * ni + i];
-    else
-        for (int s = sa; s < sb; ++s) acc += dz[(int64_t)s * no + o];
-    part[(int64_t)blockIdx.y * nw + idx] = acc;
-}
-__global__ void __launch_bounds__(NTL) k_dense_bwd_sum(const double* __restrict__ part, int nchunk, int ni,
-                                                       int no, float* __restrict__ dW,
-                                                       float* __restrict__ db) {
-    const int idx = blockIdx.x * NTL + threadIdx.x;
-    const int nw = no * (ni + 1);
-    if (idx >= nw) return;
-    double acc = 0.0;
-    for (int c = 0; c < nchunk; ++c) acc += part[(int64_t)c * nw + idx];
-    const int o = idx / (ni + 1), i = idx - o * (ni + 1);
-    if (i < ni) dW[(int64_t)o * ni + i] = (float)acc;
-    else db[o] = (float)acc;
-}
-#define BWD_CHUNKS 64
+// Output row block wave, samples 16 sb + (lane & 15): D register j is output 16 wave + 4 g + j
+// (g = lane >> 4).  K steps take inputs 16 q + 4 g + j, so both operands are 16-byte reads.
+template <bool TRAIN>
+__global__ void __launch_bounds__(512) k_mlp(const float* __restrict__ par, const float* __restrict__ x,
+                                             const float* __restrict__ t, int n, float* __restrict__ y, MlpWs ws) {
+    __shared__ __attribute__((aligned(16))) float act[2][MT * MT_LD];
+    __shared__ __attribute__((aligned(16))) float dzo[MT * (OUT_LD + 4)];
+    constexpr int SB = MT / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int col = lane & 15, g = lane >> 4, row = 16 * wave + col, o4 = 16 * wave + 4 * g;
+    const int s0 = blockIdx.x * MT;
+    // forward operand of hidden layer l: its rows' weights along the inputs; backward: along the outputs
+    auto load_w = [&](f4v_t (&w)[8], int l) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w[q] = *(const f4v_t*)(par + layer_off(l) + row * MLP_H + 16 * q + 4 * g);
+    };
+    auto load_wt = [&](f4v_t (&w)[8], int l) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[q][j] = par[layer_off(l) + (16 * q + 4 * g + j) * MLP_H + row];
+    };
+    auto product = [&](f4v_t (&acc)[SB], const f4v_t (&w)[8], const float* in) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            f4v_t b[SB];
+#pragma unroll
+            for (int sb = 0; sb < SB; ++sb) b[sb] = *(const f4v_t*)(in + (16 * sb + col) * MT_LD + 16 * q + 4 * g);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int sb = 0; sb < SB; ++sb)
+                    acc[sb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[q][j], b[sb][j], acc[sb], 0, 0, 0);
+        }
+    };
+    // a value of this wave's rows for the next layer (LDS) and for the weight gradients
+    auto keep = [&](float* out, float* glob, int sb, const f4v_t& v) {
+        const int s = 16 * sb + col;
+        if (out) *(f4v_t*)(out + s * MT_LD + o4) = v;
+        if (TRAIN && s0 + s < n) *(f4v_t*)(glob + (int64_t)(s0 + s) * MLP_H + o4) = v;
+    };
+    auto bias = [&](int l, int ni) { return *(const f4v_t*)(par + layer_off(l) + MLP_H * ni + o4); };
 
-// Loss: mean over samples of sum over outputs of (w (y - t))^2; dy = 2 w^2 (y - t) / n.
-__global__ void __launch_bounds__(NTL) k_loss(const float* __restrict__ y, const float* __restrict__ t,
-                                              const float* __restrict__ wt, int n, int no,
-                                              float* __restrict__ dy, double* __restrict__ part) {
-    __shared__ double red[NTL];
-    double acc = 0.0;
-    for (int64_t idx = (int64_t)blockIdx.x * NTL + threadIdx.x; idx < (int64_t)n * no;
-         idx += (int64_t)gridDim.x * NTL) {
-        const int s = (int)(idx / no);
-        const float w = wt ? wt[s] : 1.0f;
-        const float d = y[idx] - t[idx];
-        dy[idx] = 2.0f * w * w * d / n;
-        acc += (double)(w * d) * (w * d);
+    f4v_t w[8], wn[8], z[3][SB];
+    load_w(w, 1);
+    {
+        float w0[2], xv[SB][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            w0[j] = par[row * MLP_IN + 2 * g + j];
+#pragma unroll
+            for (int sb = 0; sb < SB; ++sb) {
+                const int s = s0 + 16 * sb + col;
+                const float v = x[(int64_t)min(s, n - 1) * MLP_IN + 2 * g + j];
+                xv[sb][j] = s < n ? v : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb) {
+            z[0][sb] = bias(0, MLP_IN);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                z[0][sb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[j], xv[sb][j], z[0][sb], 0, 0, 0);
+        }
     }
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int st = NTL / 2; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb) {
+            f4v_t v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = silu(z[l][sb][j]);
+            keep(act[l & 1], ws.a[l], sb, v);
+        }
         __syncthreads();
+        if (l == 2) break;
+        if (l == 0) load_w(wn, 2);
+        const f4v_t b0 = bias(l + 1, MLP_H);
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb) z[l + 1][sb] = b0;
+        product(z[l + 1], l == 0 ? w : wn, act[l & 1]);
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    if (TRAIN) load_wt(w, 2);
+    // last layer: a wave for 16 samples, rows 12 .. 15 zero
+    if (wave < SB) {
+        f4v_t acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (4 * g + j < MLP_OUT) acc[j] = par[layer_off(3) + MLP_OUT * MLP_H + 4 * g + j];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            f4v_t wv = *(const f4v_t*)(par + layer_off(3) + min(col, MLP_OUT - 1) * MLP_H + 16 * q + 4 * g);
+            const f4v_t b = *(const f4v_t*)(act[0] + (16 * wave + col) * MT_LD + 16 * q + 4 * g);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(col < MLP_OUT ? wv[j] : 0.0f, b[j], acc, 0, 0, 0);
+        }
+        const int s = s0 + 16 * wave + col;
+        const bool on = s < n && g < 3;
+        if constexpr (!TRAIN) {
+            if (on)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) y[(int64_t)s * MLP_OUT + 4 * g + j] = acc[j];
+        } else {
+            // loss: mean over samples of the sum over outputs of (y - t)^2; dy = 2 (y - t) / n
+            f4v_t dy = {0, 0, 0, 0};
+            double loss = 0.0;
+            if (on)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float d = acc[j] - t[(int64_t)s * MLP_OUT + 4 * g + j];
+                    dy[j] = 2.0f * d / n;
+                    loss += (double)d * d;
+                }
+            for (int m = 32; m > 0; m >>= 1) loss += __shfl_xor(loss, m);
+            if (lane == 0) ws.loss[(int64_t)blockIdx.x * SB + wave] = loss;
+            *(f4v_t*)(dzo + (16 * wave + col) * (OUT_LD + 4) + 4 * g) = dy;
+            if (s < n) *(f4v_t*)(ws.dz[3] + (int64_t)s * OUT_LD + 4 * g) = dy;
+        }
+    }
+    if constexpr (TRAIN) {
+        __syncthreads();
+        f4v_t da[SB];
+        float w3[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float v = par[layer_off(3) + min(4 * g + j, MLP_OUT - 1) * MLP_H + row];
+            w3[j] = g < 3 ? v : 0.0f;
+        }
+        load_wt(wn, 1);
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb) {
+            const f4v_t b = *(const f4v_t*)(dzo + (16 * sb + col) * (OUT_LD + 4) + 4 * g);
+            da[sb] = (f4v_t){0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) da[sb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w3[j], b[j], da[sb], 0, 0, 0);
+        }
+#pragma unroll
+        for (int l = 2; l >= 0; --l) {
+#pragma unroll
+            for (int sb = 0; sb < SB; ++sb) {
+                f4v_t v;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = da[sb][j] * silu_d(z[l][sb][j]);
+                keep(l ? act[(l + 1) & 1] : nullptr, ws.dz[l], sb, v);
+                da[sb] = (f4v_t){0, 0, 0, 0};
+            }
+            if (l == 0) break;
+            __syncthreads();
+            product(da, l == 2 ? w : wn, act[(l + 1) & 1]);
+        }
+    }
 }
-__global__ void k_loss_final(const double* __restrict__ part, int np, int n, float* __restrict__ loss) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < np; ++i) s += part[i];
-        *loss = (float)(s / n);
+
+// Partial gradients of a chunk of samples: dW[o][i] = sum_s dz[s][o] in[s][i], db[o] = sum_s
+// dz[s][o], in FP64.  A wave takes 16 outputs x 64 inputs (all 8 of the first layer); the four
+// waves of a group share rows or columns.  Column lane & 15 of block c is input 4 (lane & 15) + c,
+// so a lane's four operands are one 16-byte load (the input of the network may lie at any float).
+#define GRAD_TILES (8 + 16 + 16 + 2)
+__global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ x, int n, int chunk, MlpWs ws) {
+    const int tile = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (tile >= GRAD_TILES) return;
+    const int sa = blockIdx.y * chunk, sb = min(n, sa + chunk);
+    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int l = tile < 16 ? 1 : tile < 32 ? 2 : tile < 40 ? 0 : 3;
+    const int ob = l == 1 ? tile >> 1 : l == 2 ? (tile - 16) >> 1 : l == 0 ? tile - 32 : 0;
+    const int half = l == 0 ? 0 : tile & 1;
+    const int no = l == 3 ? MLP_OUT : MLP_H, ni = l == 0 ? MLP_IN : MLP_H;
+    const int ldo = l == 3 ? OUT_LD : MLP_H;
+    const float* dz = ws.dz[l] + 16 * ob + col;
+    const float* in = l == 0 ? x + 4 * min(col, MLP_IN / 4 - 1) : ws.a[l - 1] + 64 * half + 4 * col;
+    d4v_t acc[4] = {};
+    double db = 0.0;
+    auto run = [&](auto aligned) {
+        constexpr int U = 8;
+        float a[U];
+        f4v_t b[U];
+        auto load = [&](int s) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t q = min(s + 4 * u + g, sb - 1);
+                a[u] = dz[q * ldo];
+                if constexpr (decltype(aligned)::value)
+                    b[u] = *(const f4v_t*)(in + q * MLP_H);
+                else
+                    for (int c = 0; c < 4; ++c) b[u][c] = in[q * MLP_IN + c];
+            }
+        };
+        load(sa);
+        for (int s = sa; s < sb; s += 4 * U) {
+            float av[U];
+            f4v_t bv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool on = s + 4 * u + g < sb;
+                av[u] = on ? a[u] : 0.0f;
+                for (int c = 0; c < 4; ++c) bv[u][c] = on ? b[u][c] : 0.0f;
+            }
+            load(s + 4 * U);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                db += av[u];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[u], (double)bv[u][c], acc[c], 0, 0, 0);
+            }
+        }
+    };
+    if (l == 0) run(std::false_type());
+    else run(std::true_type());
+    double* part = ws.part + (int64_t)blockIdx.y * MLP_NPARAMS + layer_off(l);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int o = 16 * ob + 4 * j + g, i = 64 * half + 4 * col + c;      // FP64-accumulator output order
+            if (o < no && i < ni) part[o * ni + i] = acc[c][j];
+        }
+    if (half == 0) {
+        db += __shfl_xor(db, 16);
+        db += __shfl_xor(db, 32);
+        const int o = 16 * ob + col;
+        if (g == 0 && o < no) part[no * ni + o] = db;
     }
+}
+
+// Adds the chunks in fixed order; the last work group adds the loss partials.
+__global__ void __launch_bounds__(NTL) k_mlp_sum(int nchunk, int nloss, int n, MlpWs ws, float* __restrict__ grad,
+                                                 float* __restrict__ loss) {
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ double red[NTL];
+        double s = 0.0;
+        for (int i = threadIdx.x; i < nloss; i += NTL) s += ws.loss[i];
+        red[threadIdx.x] = s;
+        __syncthreads();
+        for (int st = NTL / 2; st > 0; st >>= 1) {
+            if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *loss = (float)(red[0] / n);
+        return;
+    }
+    const int idx = blockIdx.x * NTL + threadIdx.x;
+    if (idx >= MLP_NPARAMS) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < nchunk; ++c) s += ws.part[(int64_t)c * MLP_NPARAMS + idx];
+    grad[idx] = (float)s;
 }
 
 __global__ void __launch_bounds__(NTL) k_adam(float* __restrict__ p, const float* __restrict__ g,
@@ -353,82 +540,25 @@ __global__ void __launch_bounds__(NTL) k_adam(float* __restrict__ p, const float
     p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-static const int MLP_SIZES[5] = {MLP_IN, MLP_H, MLP_H, MLP_H, MLP_OUT};
-
-static int64_t layer_off(int l) {
-    int64_t off = 0;
-    for (int k = 0; k < l; ++k) off += (int64_t)MLP_SIZES[k + 1] * MLP_SIZES[k] + MLP_SIZES[k + 1];
-    return off;
-}
-
-// Workspace: activations z_l, a_l for l = 1..4 and gradients, n samples.
-int64_t mlp_workspace_floats(int n) {
-    int64_t t = 0;
-    for (int l = 1; l <= 4; ++l) t += 4 * (int64_t)n * MLP_SIZES[l];   // z, a, dz, da
-    // loss partials (256 doubles) and the weight-gradient chunk partials (doubles)
-    return t + (int64_t)n * MLP_H + 4096 + 2LL * BWD_CHUNKS * MLP_H * (MLP_H + 1);
-}
-
 void launch_mlp_forward(hipStream_t st, const float* params, const float* x, int n, float* ws,
                         float* y) {
-    const float* in = x;
-    float* p = ws;
-    for (int l = 0; l < 4; ++l) {
-        const int ni = MLP_SIZES[l], no = MLP_SIZES[l + 1];
-        float* z = p;
-        float* a = (l == 3 && y) ? y : p + (int64_t)n * no;
-        const int64_t tot = (int64_t)n * no;
-        (void)tot;
-        hipLaunchKernelGGL(k_dense_fwd, dim3((unsigned)((n + FWD_S - 1) / FWD_S)), dim3(NTL), 0, st, in, n, ni,
-                           no, params + layer_off(l), params + layer_off(l) + (int64_t)no * ni, z, a,
-                           l == 3 ? 1 : 0);
-        in = a;
-        p += 4 * (int64_t)n * no;
-    }
+    // samples are read and written group by group: an output over the input goes through the workspace
+    const bool over = y < x + (int64_t)n * MLP_IN && x < y + (int64_t)n * MLP_OUT;
+    hipLaunchKernelGGL(k_mlp<false>, dim3(mlp_groups(n)), dim3(512), 0, st, params, x, nullptr, n, over ? ws : y, MlpWs{});
+    if (over) (void)hipMemcpyAsync(y, ws, (int64_t)n * MLP_OUT * 4, hipMemcpyDeviceToDevice, st);
 }
 
-void launch_mlp_loss_grad(hipStream_t st, const float* params, const float* x, const float* t,
-                          const float* w, int n, float* ws, float* grad, float* loss) {
-    launch_mlp_forward(st, params, x, n, ws, nullptr);
-    // pointers per layer
-    float* zl[4];
-    float* al[4];
-    float* dzl[4];
-    float* dal[4];
-    float* p = ws;
-    for (int l = 0; l < 4; ++l) {
-        const int no = MLP_SIZES[l + 1];
-        zl[l] = p;
-        al[l] = p + (int64_t)n * no;
-        dzl[l] = p + 2 * (int64_t)n * no;
-        dal[l] = p + 3 * (int64_t)n * no;
-        p += 4 * (int64_t)n * no;
-    }
-    double* part = (double*)(p + (int64_t)n * MLP_H);
-    double* wpart = part + 2048;              // after the 4096 floats of loss partials
-    const int nb = 256;
-    hipLaunchKernelGGL(k_loss, dim3(nb), dim3(NTL), 0, st, al[3], t, w, n, MLP_OUT, dal[3], part);
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, st, part, nb, n, loss);
-    for (int l = 3; l >= 0; --l) {
-        const int ni = MLP_SIZES[l], no = MLP_SIZES[l + 1];
-        const float* Wl = params + layer_off(l);
-        const int64_t tot = (int64_t)n * no;
-        hipLaunchKernelGGL(k_dense_dz, dim3((unsigned)((tot + NTL - 1) / NTL)), dim3(NTL), 0, st, dal[l],
-                           zl[l], tot, dzl[l], l == 3 ? 1 : 0);
-        const float* in = (l == 0) ? x : al[l - 1];
-        const int nw = no * (ni + 1);
-        const int chunk = std::max(64, (n + BWD_CHUNKS - 1) / BWD_CHUNKS);
-        const int nchunk = (n + chunk - 1) / chunk;
-        hipLaunchKernelGGL(k_dense_bwd_w, dim3((nw + NTL - 1) / NTL, nchunk), dim3(NTL), 0, st, dzl[l], in, n,
-                           ni, no, chunk, wpart);
-        hipLaunchKernelGGL(k_dense_bwd_sum, dim3((nw + NTL - 1) / NTL), dim3(NTL), 0, st, wpart, nchunk, ni, no,
-                           grad + layer_off(l), grad + layer_off(l) + (int64_t)no * ni);
-        if (l > 0) {
-            const int64_t ti = (int64_t)n * ni;
-            hipLaunchKernelGGL(k_dense_bwd_x, dim3((unsigned)((ti + NTL - 1) / NTL)), dim3(NTL), 0, st, dzl[l],
-                               n, ni, no, Wl, dal[l - 1]);
-        }
-    }
+void launch_mlp_loss_grad(hipStream_t st, const float* params, const float* x, const float* t, int n, float* ws,
+                          float* grad, float* loss) {
+    const MlpWs w = mlp_ws(ws, n);
+    // chunks of 32 samples or more; 23 of them at most are a work group for each CU (8192 samples: 24.5
+    // us; 32 chunks 27.2, the last round nearly empty; 46 chunks 23.4, but 2 us more to add them up)
+    const int chunk = std::max(32, ((n + kMaxChunks - 1) / kMaxChunks + 3) & ~3);
+    const int nchunk = (n + chunk - 1) / chunk;
+    hipLaunchKernelGGL(k_mlp<true>, dim3(mlp_groups(n)), dim3(512), 0, st, params, x, t, n, nullptr, w);
+    hipLaunchKernelGGL(k_mlp_grad, dim3((GRAD_TILES + 3) / 4, nchunk), dim3(256), 0, st, x, n, chunk, w);
+    hipLaunchKernelGGL(k_mlp_sum, dim3((MLP_NPARAMS + NTL - 1) / NTL + 1), dim3(NTL), 0, st, nchunk,
+                       mlp_groups(n) * (MT / 16), n, w, grad, loss);
 }
 
 void launch_adam(hipStream_t st, float* p, const float* g, float* m, float* v, int n, float lr, int step) {

@@ -359,7 +359,7 @@ extern "C" fbc_status fbc_mlp_loss_grad(fbc_mlp* m, const float* x, const float*
                                         float* loss_dev, void* stream) {
     if (!m || !x || !t) return lfail(nullptr, FBC_E_ARG, "null argument");
     if (n < 1 || n > m->max_batch) return lfail(&m->err, FBC_E_ARG, "batch size out of range");
-    launch_mlp_loss_grad((hipStream_t)stream, m->params, x, t, nullptr, n, m->ws, m->grad,
+    launch_mlp_loss_grad((hipStream_t)stream, m->params, x, t, n, m->ws, m->grad,
                          loss_dev ? loss_dev : m->loss);
     LCHK(&m->err, hipGetLastError());
     return FBC_OK;
@@ -383,15 +383,14 @@ extern "C" fbc_status fbc_mlp_forward(fbc_mlp* m, const float* x, float* y, int 
 
 // ----------------------------------------------------------------------------------
 // Forward pass without device allocation, for callers that cannot allocate (code under
-// HIP graph capture, serving loops): the layer activations go to a file-scope device
-// array instead of the network's workspace.  Each GPU the library runs on holds its own
+// HIP graph capture, serving loops): what the pass stages (an output that overlaps the
+// input) goes to a file-scope device array instead of the network's workspace.  Each GPU the library runs on holds its own
 // copy of the array until the process ends; every call on that GPU shares it.
 // ----------------------------------------------------------------------------------
 static constexpr int64_t kNoAllocBytes = (int64_t)64 << 20;
 static __device__ __align__(256) float scratch[kNoAllocBytes / 4];
 
-// Floats of the forward workspace for n rows (z and a of every layer in the layout of
-// launch_mlp_forward, 4 n x width per layer).
+// Rows are limited to those whose z, a and gradients of every layer the array could hold.
 static int64_t forward_ws_floats(int64_t n) { return 4 * n * (3 * MLP_H + MLP_OUT); }
 static const int kNoAllocRows = (int)(kNoAllocBytes / 4 / forward_ws_floats(1));
 
@@ -431,7 +430,6 @@ extern "C" fbc_status fbc_mlp_forward_noalloc(const fbc_mlp* m, const float* x, 
     float* ws = nullptr;
     fbc_status s = scratch_address(dev, &ws);
     if (s != FBC_OK) return s;
-    // every workspace value is written before it is read: nothing needs clearing
     launch_mlp_forward((hipStream_t)stream, m->params, x, n, ws, y);
     LCHK(nullptr, hipGetLastError());
     return FBC_OK;
