@@ -126,6 +126,14 @@ __host__ __device__ inline int64_t tab_frag_off(int n, int k, int nch) {
 // Read-only data that a whole wave reads at one address: through the constant address space the
 // loads are scalar whatever the kernel stores.
 typedef const __attribute__((address_space(4))) int uniform_int;
+template <typename T>
+__device__ inline T uniform_at(const T* p) {
+    T v;
+    const uniform_int* src = (const uniform_int*)p;
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(T) / 4); ++k) ((int*)&v)[k] = src[k];
+    return v;
+}
 
 // Per-cell device view used by the offset-table product kernel: the column keys n1 w2 + n2
 // (their differences index the offset lookup), pad columns up to whole tiles of 16 (the last

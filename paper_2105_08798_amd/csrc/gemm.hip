@@ -683,23 +683,12 @@ __device__ inline void any_job(const GemmJob& jb, const void* __restrict__ A, co
     }
 }
 
-// A job, loaded into scalar registers (the persistent kernels' own stores would otherwise make
-// every load of the list a vector load).
-__device__ inline GemmJob job_at(const GemmJob* __restrict__ jobs, int j) {
-    GemmJob jb;
-    const uniform_int* src = (const uniform_int*)(jobs + j);
-    int* dst = (int*)&jb;
-#pragma unroll
-    for (int k = 0; k < (int)(sizeof(GemmJob) / 4); ++k) dst[k] = src[k];
-    return jb;
-}
-
 template <typename SH>
 __global__ void __launch_bounds__(SH::NTH, SH::WPE) k_gemm(const GemmJob* __restrict__ jobs, const void* __restrict__ A,
                                                   RTabView tv, const void* __restrict__ B, double* __restrict__ C,
                                                   const CellDev* __restrict__ cells) {
     extern __shared__ __attribute__((aligned(128))) char gsm[];
-    const GemmJob jb = job_at(jobs, blockIdx.x);
+    const GemmJob jb = uniform_at(jobs + blockIdx.x);
     any_job<SH>(jb, A, tv, B, C, cells, gsm);
 }
 template <typename SH>
@@ -711,7 +700,7 @@ __global__ void __launch_bounds__(SH::NTH, SH::WPE) k_gemm_pq(const GemmJob* __r
     __shared__ int slot;
     int cur = 0;
     for (int j = pq_next(q, &slot, cur); j < njobs; j = pq_next(q, &slot, cur)) {
-        const GemmJob jb = job_at(jobs, j);
+        const GemmJob jb = uniform_at(jobs + j);     // scalar loads, whatever the kernel stores
         any_job<SH>(jb, A, tv, B, C, cells, gsm);
     }
     pq_done(q);

@@ -86,33 +86,26 @@ struct HIo {
     int r_out;             // RHS slots written per row: R (plain) or 8 x tiles (records)
 };
 
-template <bool PIPE>
-__device__ inline double2 xval(const HIo& io, int m, int col, int r, int n_i, int R) {
-    return io.x[((int64_t)m * 3 * n_i + col) * R + r];
-}
+// Right-hand sides per group of the products; x and T hold whole groups, zeros past R.
+#define HR 8
 
-// The pipeline's input in the plain layout x [mode][3 n_i][R] (one pass over the
-// fragments; the products then read x with unit stride over the right-hand sides).
-__global__ void __launch_bounds__(NTH) k_hmat_x(HIo io, int n_i, int R, double2* __restrict__ x) {
+// The products' input x [mode][3 n_i][Rp], from the fragments or the plain input.
+template <bool PIPE>
+__global__ void __launch_bounds__(NTH) k_hmat_x(HIo io, int n_i, int R, int Rp, double2* __restrict__ x) {
     const int m = blockIdx.y;
-    const double* b = io.bf + (int64_t)m * io.bf_mode;
-    for (int e = blockIdx.x * NTH + threadIdx.x; e < 3 * n_i * R; e += gridDim.x * NTH) {
-        const int col = e / R, r = e - col * R;
+    const double* b = PIPE ? io.bf + (int64_t)m * io.bf_mode : nullptr;
+    for (int e = blockIdx.x * NTH + threadIdx.x; e < 3 * n_i * Rp; e += gridDim.x * NTH) {
+        const int col = e / Rp, r = e - col * Rp;
         const int tile = r >> 3, j = r & 7;
         const int nch = io.kp / 96;
-        x[(int64_t)m * 3 * n_i * R + e] = make_double2(b[tab_frag_off(16 * tile + j, col, nch)],
-                                                       b[tab_frag_off(16 * tile + j + 8, col, nch)]);
-    }
-}
-
-template <bool PIPE>
-__device__ inline void yput(const HIo& io, int m, int row, int r, int n_b, int R, double2 v) {
-    if constexpr (!PIPE) {
-        io.y[((int64_t)m * 3 * n_b + row) * R + r] = v;
-    } else {
-        double* rec = io.rec + (((int64_t)(r >> 3) * io.mp + row) * io.nm + m) * 16;
-        rec[r & 7] = v.x;
-        rec[8 + (r & 7)] = v.y;
+        double2 v = make_double2(0, 0);
+        if (r < R) {
+            if constexpr (PIPE)
+                v = make_double2(b[tab_frag_off(16 * tile + j, col, nch)], b[tab_frag_off(16 * tile + j + 8, col, nch)]);
+            else
+                v = io.x[((int64_t)m * 3 * n_i + col) * R + r];
+        }
+        x[(int64_t)m * 3 * n_i * Rp + e] = v;
     }
 }
 
@@ -276,31 +269,56 @@ __global__ void __launch_bounds__(NTH) k_hmat_aca(const HBlk* __restrict__ blks,
     if (threadIdx.x == 0) rank[(int64_t)m * n_lr + li] = (result < 0) ? -1 : k;
 }
 
-// T[lr][l][r] = sum_j V[l][j] x[col_j][r] for the low-rank blocks, Rp columns per l (the
-// columns from R on zero, so the y kernel runs whole groups of HR right-hand sides).
-template <bool PIPE>
+// Complex products on FP64 MFMA: columns 0..7 hold the real parts of HR right-hand sides (A re with
+// x re, A im with -x im), 8..15 the imaginary ones (A re with x im, A im with x re).
+__device__ inline double re_im(double2 x, int col) { return col < 8 ? x.x : x.y; }
+__device__ inline double i_re_im(double2 x, int col) { return col < 8 ? -x.y : x.x; }
+
+// T[lr][l][r] = sum_j V[l][j] x[col_j][r] for the low-rank blocks.  One work group per (block,
+// mode); 16 terms x HR right-hand sides at a time on MFMA, a fourth of the columns per wave.
+// Bound by the reads of V.  64 layers, 1024 / 2048 columns, 8 RHS: 73 us; a thread per term
+// and right-hand side, each reading a row of V, 325.
 __global__ void __launch_bounds__(NTH) k_hmat_vt(const HBlk* __restrict__ blks, const int* __restrict__ lr_ids,
                                                  const int32_t* __restrict__ scols, const double2* __restrict__ V,
                                                  int64_t v_mode, const int* __restrict__ rank, int n_lr,
-                                                 int max_rank, HIo io, int n_i, int R, int Rp,
+                                                 int max_rank, const double2* __restrict__ x, int n_i, int Rp,
                                                  double2* __restrict__ T) {
+    __shared__ double red[4][256];
     const int li = blockIdx.x, m = blockIdx.y;
     const int k = rank[(int64_t)m * n_lr + li];
     if (k <= 0) return;
     const HBlk b = blks[lr_ids[li]];
-    const int nc = 3 * b.ns;
-    const double2* Vb = V + (int64_t)m * v_mode + b.v_off;
-    double2* Tb = T + ((int64_t)m * n_lr + li) * max_rank * Rp;
-    for (int e = threadIdx.x; e < k * Rp; e += NTH) {
-        const int l = e / Rp, r = e - l * Rp;
-        double2 acc = make_double2(0, 0);
-        if (r < R)
-            for (int j = 0; j < nc; ++j) {
-                const double2 p = cmul(Vb[(int64_t)l * nc + j], xval<PIPE>(io, m, gcol(scols, b.s_off, j), r, n_i, R));
-                acc.x += p.x;
-                acc.y += p.y;
+    const int nc = 3 * b.ns, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const double2* xm = x + (int64_t)m * 3 * n_i * Rp + (col & 7);
+    double* Tb = (double*)(T + ((int64_t)m * n_lr + li) * max_rank * Rp);
+    for (int l0 = 0; l0 < k; l0 += 16) {
+        const double2* Vl = V + (int64_t)m * v_mode + b.v_off + (int64_t)min(l0 + col, k - 1) * nc;
+        for (int r0 = 0; r0 < Rp; r0 += HR) {
+            d4_t acc = {0, 0, 0, 0};
+            for (int j0 = 16 * wave; j0 < nc; j0 += 64) {
+                double2 v[4], xv[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const int j = min(j0 + 4 * s + g, nc - 1);
+                    v[s] = Vl[j];
+                    xv[s] = xm[(int64_t)gcol(scols, b.s_off, j) * Rp + r0];
+                    if (j0 + 4 * s + g >= nc) xv[s] = make_double2(0, 0);
+                }
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[s].x, re_im(xv[s], col), acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[s].y, i_re_im(xv[s], col), acc, 0, 0, 0);
+                }
             }
-        Tb[(int64_t)l * Rp + r] = acc;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) red[wave][16 * (4 * j + g) + col] = acc[j];
+            __syncthreads();
+            const int l = l0 + (threadIdx.x >> 4), c = threadIdx.x & 15;
+            double t = 0.0;
+            for (int w = 0; w < 4; ++w) t += red[w][threadIdx.x];
+            if (l < k) Tb[2 * ((int64_t)l * Rp + r0 + (c & 7)) + (c >> 3)] = t;
+            __syncthreads();
+        }
     }
 }
 
@@ -327,85 +345,121 @@ __global__ void __launch_bounds__(NTH) k_hmat_dense(const HBlk* __restrict__ blk
 
 // y rows of one pad leaf: sum over the blocks that cover it (low rank: U rows times T;
 // dense leaves: their stored entries times x; low-rank blocks over the rank bound: the
-// offset table's entries times x).  One wave per (leaf, mode), four modes per work group;
-// a lane owns one row of the leaf (rows past 64 in further passes) and HR right-hand sides
-// at a time, so each factor or stored entry is read once per HR of them, and the lanes
-// read consecutive rows of U and of the dense entries.  The RHS slots from R to
-// io.r_out are written as zeros.
-#define HR 8
+// offset table's entries times x).  One work group per (leaf, mode), on MFMA: 16 pad columns x HR
+// right-hand sides, an accumulator for each Cartesian row of the columns.  The four waves take the
+// blocks in turn, of a block over the rank bound every fourth step of four interface columns, and
+// add up through LDS.  Such a block reads a record of the table per pair of columns (a lane per
+// pair; six components serve the nine entries), its place in the table looked up a step ahead.
+// Blocks over the bound are most of the work near the zone boundary, where little compresses; the
+// gathers of records bound it (a lane a clock), then MFMA.  The RHS slots from R to io.r_out are
+// written as zeros.  64 layers, 1024 / 2048 columns, 8 RHS, 0.4 G entries, 2374 of 15708 blocks
+// over the bound: 620 us; a row per lane, its entries looked up one by one, 3850.
 template <bool PIPE>
-__global__ void __launch_bounds__(NTH) k_hmat_y(const HBlk* __restrict__ blks, const int32_t* __restrict__ scols,
-                                                const int32_t* __restrict__ leaf_cols,
-                                                const int* __restrict__ leaf_off,
-                                                const HContrib* __restrict__ contrib,
-                                                const int* __restrict__ contrib_off, HStore st,
-                                                const double2* __restrict__ U, int64_t u_mode,
-                                                const double2* __restrict__ D, int64_t d_mode,
-                                                const double2* __restrict__ T, const int* __restrict__ rank,
-                                                int n_lr, int max_rank, HIo io, int n_i,
-                                                int n_b, int R, int Rp, int nm) {
-    const int leaf = blockIdx.x, lane = threadIdx.x & 63;
-    const int m = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6));
-    if (m >= nm) return;
-    const int c0 = leaf_off[leaf], nrow = 3 * (leaf_off[leaf + 1] - c0);
-    for (int rl = lane; rl - lane < nrow; rl += 64) {          // every lane runs every pass
-        const bool live = rl < nrow;
-        const int grow = live ? 3 * leaf_cols[c0 + rl / 3] + rl % 3 : 0;
+__global__ void __launch_bounds__(NTH, 4) k_hmat_y(const HBlk* __restrict__ blks, const int32_t* __restrict__ scols,
+                                                   const int2* __restrict__ skeys,
+                                                   const int32_t* __restrict__ leaf_cols,
+                                                   const int* __restrict__ leaf_off,
+                                                   const HContrib* __restrict__ contrib,
+                                                   const int* __restrict__ contrib_off, HStore st,
+                                                   const double2* __restrict__ U, int64_t u_mode,
+                                                   const double2* __restrict__ D, int64_t d_mode,
+                                                   const double2* __restrict__ T, const int* __restrict__ rank,
+                                                   int n_lr, int max_rank, const double2* __restrict__ x, HIo io,
+                                                   int n_i, int n_b, int R, int Rp) {
+    __shared__ double red[4][3][256];
+    const int leaf = blockIdx.x, m = gridDim.y - 1 - blockIdx.y;      // high modes first: the longest
+    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c0 = leaf_off[leaf], ncol = leaf_off[leaf + 1] - c0;
+    const uniform_int* ranks = (const uniform_int*)(rank + (int64_t)m * n_lr);
+    const double2* tab = st.tab + (int64_t)m * st.n_off * 6;
+    for (int p0 = 0; p0 < ncol; p0 += 16) {
+        const int lc = min(p0 + col, ncol - 1), ib = leaf_cols[c0 + lc];
+        const int bkey = (st.cols_b[2 * ib] - st.d1min) * st.w2 + st.cols_b[2 * ib + 1] - st.d2min;
         for (int r0 = 0; r0 < io.r_out; r0 += HR) {
-            const int nr_here = min(HR, R - r0);                  // <= 0: zero slots only
-            double2 acc[HR];
+            const double2* xm = x + (int64_t)m * 3 * n_i * Rp + r0 + (col & 7);
+            d4_t acc[3] = {};
+            int turn = 0;
+            for (int q2 = contrib_off[leaf]; q2 < contrib_off[leaf + 1] && r0 < R; ++q2) {
+                const HContrib cb = uniform_at(contrib + q2);
+                const HBlk b = uniform_at(blks + cb.blk);
+                const int k = (b.kind == 1) ? ranks[b.lr] : 0;
+                if (k < 0) {
+                    const int2* sk = skeys + b.s_off;
+                    const int steps = (b.ns + 3) >> 2;
+                    auto key_at = [&](int t) { return sk[min(4 * t + g, b.ns - 1)]; };
+                    int2 kc = key_at(wave), kn = key_at(wave + 4);
+                    int o = st.lut[bkey - kc.y];
+                    for (int t = wave; t < steps; t += 4) {
+                        double2 a[6], xv[3];
 #pragma unroll
-            for (int q = 0; q < HR; ++q) acc[q] = make_double2(0, 0);
-            for (int q2 = contrib_off[leaf]; q2 < contrib_off[leaf + 1] && nr_here > 0 && live; ++q2) {
-                const HContrib cb = contrib[q2];
-                const HBlk b = blks[cb.blk];
-                const int br = cb.row0 + rl;                 // row within the block
-                const int nr = 3 * b.nt;
-                const int k = (b.kind == 1) ? rank[(int64_t)m * n_lr + b.lr] : -1;
-                if (k >= 0) {
-                    // T holds Rp >= r0 + HR columns, zeros past R: no per-RHS test
-                    const double2* Ub = U + (int64_t)m * u_mode + b.u_off + br;
-                    const double2* Tb = T + ((int64_t)m * n_lr + b.lr) * max_rank * Rp + r0;
-                    for (int l = 0; l < k; ++l) {
-                        const double2 u = Ub[(int64_t)l * nr];
+                        for (int e = 0; e < 6; ++e) a[e] = tab[(int64_t)o * 6 + e];
 #pragma unroll
-                        for (int q = 0; q < HR; ++q) {
-                            const double2 t = Tb[(int64_t)l * Rp + q];
-                            acc[q].x += u.x * t.x - u.y * t.y;
-                            acc[q].y += u.x * t.y + u.y * t.x;
+                        for (int d = 0; d < 3; ++d) xv[d] = xm[(int64_t)(3 * kc.x + d) * Rp];
+                        kc = kn;
+                        o = st.lut[bkey - kc.y];
+                        kn = key_at(t + 8);
+                        if (4 * t + g >= b.ns)
+                            for (int d = 0; d < 3; ++d) xv[d] = make_double2(0, 0);
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) {
+                            const double br = re_im(xv[d], col), bi = i_re_im(xv[d], col);
+#pragma unroll
+                            for (int c = 0; c < 3; ++c)
+                                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[sym_idx(c, d)].x, br, acc[c], 0, 0, 0);
+#pragma unroll
+                            for (int c = 0; c < 3; ++c)
+                                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[sym_idx(c, d)].y, bi, acc[c], 0, 0, 0);
                         }
                     }
-                } else {
-                    const double2* Db = (b.kind == 0) ? D + (int64_t)m * d_mode + b.d_off + br : nullptr;
-                    if (nr_here == HR) {
-                        for (int j = 0; j < 3 * b.ns; ++j) {
-                            const int gc = gcol(scols, b.s_off, j);
-                            const double2 a = Db ? Db[(int64_t)j * nr] : entry(st, m, grow, gc);
+                    continue;
+                }
+                if ((turn++ & 3) != wave) continue;
+                // rows of the factor U, or of the stored entries, 3 nt of them per term
+                const int nr = 3 * b.nt, n = b.kind == 1 ? k : 3 * b.ns;
+                const double2* Ab = (b.kind == 1 ? U + (int64_t)m * u_mode + b.u_off : D + (int64_t)m * d_mode + b.d_off) +
+                                    cb.row0 + 3 * lc;
+                const double2* Tb = T + ((int64_t)m * n_lr + b.lr) * max_rank * Rp + r0 + (col & 7);
+                for (int l0 = 0; l0 < n; l0 += 8) {
+                    double2 a[2][3], bv[2];
 #pragma unroll
-                            for (int q = 0; q < HR; ++q) {
-                                const double2 x = xval<PIPE>(io, m, gc, r0 + q, n_i, R);
-                                acc[q].x += a.x * x.x - a.y * x.y;
-                                acc[q].y += a.x * x.y + a.y * x.x;
-                            }
-                        }
-                    } else {
-                        for (int j = 0; j < 3 * b.ns; ++j) {
-                            const int gc = gcol(scols, b.s_off, j);
-                            const double2 a = Db ? Db[(int64_t)j * nr] : entry(st, m, grow, gc);
-                            for (int q = 0; q < nr_here; ++q) {
-                                const double2 x = xval<PIPE>(io, m, gc, r0 + q, n_i, R);
-                                acc[q].x += a.x * x.x - a.y * x.y;
-                                acc[q].y += a.x * x.y + a.y * x.x;
-                            }
-                        }
+                    for (int s = 0; s < 2; ++s) {
+                        const int l = min(l0 + 4 * s + g, n - 1);
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) a[s][c] = Ab[(int64_t)l * nr + c];
+                        bv[s] = b.kind == 1 ? Tb[(int64_t)l * Rp] : xm[(int64_t)gcol(scols, b.s_off, l) * Rp];
+                        if (l0 + 4 * s + g >= n) bv[s] = make_double2(0, 0);
+                    }
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) {
+                        const double br = re_im(bv[s], col), bi = i_re_im(bv[s], col);
+#pragma unroll
+                        for (int c = 0; c < 3; ++c)
+                            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][c].x, br, acc[c], 0, 0, 0);
+#pragma unroll
+                        for (int c = 0; c < 3; ++c)
+                            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][c].y, bi, acc[c], 0, 0, 0);
                     }
                 }
             }
-            if (live) {
 #pragma unroll
-                for (int q = 0; q < HR; ++q)
-                    if (r0 + q < io.r_out) yput<PIPE>(io, m, grow, r0 + q, n_b, R, acc[q]);
-            }
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) red[wave][c][16 * (4 * j + g) + col] = acc[c][j];
+            __syncthreads();
+            const int lb = p0 + (threadIdx.x >> 4), cc = threadIdx.x & 15, r = r0 + (cc & 7);
+            if (lb < ncol && r < io.r_out)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    double v = red[0][c][threadIdx.x];
+                    for (int w = 1; w < 4; ++w) v += red[w][c][threadIdx.x];
+                    const int64_t row = 3 * leaf_cols[c0 + lb] + c;
+                    if constexpr (PIPE)
+                        io.rec[(((int64_t)(r0 >> 3) * io.mp + row) * io.nm + m) * 16 + cc] = v;
+                    else
+                        ((double*)io.y)[2 * (((int64_t)m * 3 * n_b + row) * R + r) + (cc >> 3)] = v;
+                }
+            __syncthreads();
         }
     }
 }
@@ -427,10 +481,11 @@ struct fbc_hmat {
     int* lr_ids = nullptr;
     int* d_ids_d = nullptr;
     int32_t *tcols = nullptr, *scols = nullptr, *leaf_cols = nullptr;
+    int2* skeys = nullptr;                // per entry of scols: column, n1 w2 + n2
     int *leaf_off = nullptr, *contrib_off = nullptr;
     HContrib* contrib = nullptr;
     double2 *U = nullptr, *V = nullptr, *T = nullptr, *D = nullptr;
-    double2* xbuf = nullptr;              // pipeline input in the plain layout
+    double2* xbuf = nullptr;              // input of the products (k_hmat_x)
     int64_t d_mode = 0;
     int* rank = nullptr;
     double stored = 0, dense_total = 0;
@@ -493,7 +548,7 @@ extern "C" fbc_status fbc_hmat_create(const fbc_ctx* ctx, const fbc_hmat_opts* o
     plan_tree(ti, p.cols_i, all_i, o->b_min);
     std::vector<HPart> part;
     plan_partition(tb, ti, 0, 0, o->gamma, part);
-    std::vector<int32_t> tcols, scols;
+    std::vector<int32_t> tcols, scols, skeys;
     std::vector<int> lr_ids, d_ids;
     int64_t u_mode = 0, v_mode = 0, d_mode = 0;
     for (const HPart& q : part) {
@@ -505,6 +560,10 @@ extern "C" fbc_status fbc_hmat_create(const fbc_ctx* ctx, const fbc_hmat_opts* o
         b.ns = (int)ti[q.s].idx.size();
         tcols.insert(tcols.end(), tb[q.t].idx.begin(), tb[q.t].idx.end());
         scols.insert(scols.end(), ti[q.s].idx.begin(), ti[q.s].idx.end());
+        for (int i : ti[q.s].idx) {
+            skeys.push_back(i);
+            skeys.push_back(p.cols_i[2 * i] * ctx->w2 + p.cols_i[2 * i + 1]);
+        }
         h->part_stream.push_back(q.kind);
         h->part_stream.push_back(b.nt);
         h->part_stream.push_back(b.ns);
@@ -564,6 +623,7 @@ extern "C" fbc_status fbc_hmat_create(const fbc_ctx* ctx, const fbc_hmat_opts* o
         (s = halloc(h, &h->lr_ids, (int64_t)lr_ids.size() * 4)) != FBC_OK ||
         (s = halloc(h, &h->tcols, (int64_t)tcols.size() * 4)) != FBC_OK ||
         (s = halloc(h, &h->scols, (int64_t)scols.size() * 4)) != FBC_OK ||
+        (s = halloc(h, &h->skeys, (int64_t)skeys.size() * 4)) != FBC_OK ||
         (s = halloc(h, &h->leaf_cols, (int64_t)leaf_cols.size() * 4)) != FBC_OK ||
         (s = halloc(h, &h->leaf_off, (int64_t)leaf_off.size() * 4)) != FBC_OK ||
         (s = halloc(h, &h->contrib, (int64_t)contrib.size() * sizeof(HContrib))) != FBC_OK ||
@@ -571,7 +631,7 @@ extern "C" fbc_status fbc_hmat_create(const fbc_ctx* ctx, const fbc_hmat_opts* o
         (s = halloc(h, &h->U, (int64_t)p.nm * u_mode * 16)) != FBC_OK ||
         (s = halloc(h, &h->V, (int64_t)p.nm * v_mode * 16)) != FBC_OK ||
         (s = halloc(h, &h->T, t_elems * 16)) != FBC_OK ||
-        (s = halloc(h, &h->xbuf, (int64_t)p.nm * 3 * p.n_i * p.R * 16)) != FBC_OK ||
+        (s = halloc(h, &h->xbuf, (int64_t)p.nm * 3 * p.n_i * (HR * ((p.R + HR - 1) / HR)) * 16)) != FBC_OK ||
         (s = halloc(h, &h->D, (int64_t)p.nm * d_mode * 16)) != FBC_OK ||
         (s = halloc(h, &h->d_ids_d, (int64_t)d_ids.size() * 4)) != FBC_OK ||
         (s = halloc(h, &h->rank, (int64_t)p.nm * std::max(h->n_lr, 1) * 4)) != FBC_OK) {
@@ -587,6 +647,7 @@ extern "C" fbc_status fbc_hmat_create(const fbc_ctx* ctx, const fbc_hmat_opts* o
     up(h->d_ids_d, d_ids.data(), d_ids.size() * 4);
     up(h->tcols, tcols.data(), tcols.size() * 4);
     up(h->scols, scols.data(), scols.size() * 4);
+    up(h->skeys, skeys.data(), skeys.size() * 4);
     up(h->leaf_cols, leaf_cols.data(), leaf_cols.size() * 4);
     up(h->leaf_off, leaf_off.data(), leaf_off.size() * 4);
     up(h->contrib, contrib.data(), contrib.size() * sizeof(HContrib));
@@ -674,27 +735,17 @@ extern "C" fbc_status fbc_hmat_ranks(const fbc_hmat* h, int32_t* out) {
 }
 
 template <bool PIPE>
-static void hmat_launch_t(fbc_hmat* h, const HIo& io, hipStream_t sm) {
-    const int Rp = HR * ((h->R + HR - 1) / HR);
-    if (h->n_lr > 0)
-        hipLaunchKernelGGL(k_hmat_vt<PIPE>, dim3(h->n_lr, h->nm), dim3(NTH), 0, sm, h->blk_d, h->lr_ids, h->scols,
-                           h->V, h->v_mode, h->rank, h->n_lr, h->max_rank, io, h->n_i, h->R, Rp, h->T);
-    hipLaunchKernelGGL(k_hmat_y<PIPE>, dim3(h->n_leaves, (h->nm + 3) / 4), dim3(NTH), 0, sm, h->blk_d, h->scols,
-                       h->leaf_cols, h->leaf_off, h->contrib, h->contrib_off, h->st, h->U, h->u_mode, h->D,
-                       h->d_mode, h->T, h->rank, h->n_lr, h->max_rank, io, h->n_i, h->n_b, h->R, Rp, h->nm);
-}
-
 static void hmat_launch(fbc_hmat* h, const HIo& io, hipStream_t sm) {
-    if (io.x) {
-        hmat_launch_t<false>(h, io, sm);
-        return;
-    }
-    HIo pio = io;
-    pio.x = h->xbuf;
-    const int n = 3 * h->n_i * h->R;
-    hipLaunchKernelGGL(k_hmat_x, dim3((unsigned)std::min(1024, (n + NTH - 1) / NTH), h->nm), dim3(NTH), 0, sm, io,
-                       h->n_i, h->R, h->xbuf);
-    hmat_launch_t<true>(h, pio, sm);
+    const int Rp = HR * ((h->R + HR - 1) / HR);
+    const int n = 3 * h->n_i * Rp;
+    hipLaunchKernelGGL(k_hmat_x<PIPE>, dim3((unsigned)std::min(1024, (n + NTH - 1) / NTH), h->nm), dim3(NTH), 0, sm, io,
+                       h->n_i, h->R, Rp, h->xbuf);
+    if (h->n_lr > 0)
+        hipLaunchKernelGGL(k_hmat_vt, dim3(h->n_lr, h->nm), dim3(NTH), 0, sm, h->blk_d, h->lr_ids, h->scols, h->V,
+                           h->v_mode, h->rank, h->n_lr, h->max_rank, h->xbuf, h->n_i, Rp, h->T);
+    hipLaunchKernelGGL(k_hmat_y<PIPE>, dim3(h->n_leaves, h->nm), dim3(NTH), 0, sm, h->blk_d, h->scols, h->skeys,
+                       h->leaf_cols, h->leaf_off, h->contrib, h->contrib_off, h->st, h->U, h->u_mode, h->D, h->d_mode, h->T,
+                       h->rank, h->n_lr, h->max_rank, h->xbuf, io, h->n_i, h->n_b, h->R, Rp);
 }
 
 extern "C" fbc_status fbc_hmat_apply(fbc_hmat* h, const double* fhat, double* what, void* stream) {
@@ -704,7 +755,7 @@ extern "C" fbc_status fbc_hmat_apply(fbc_hmat* h, const double* fhat, double* wh
     io.x = (const double2*)fhat;
     io.y = (double2*)what;
     io.r_out = h->R;
-    hmat_launch(h, io, (hipStream_t)stream);
+    hmat_launch<false>(h, io, (hipStream_t)stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hfail(FBC_E_DEVICE, std::string("launch: ") + hipGetErrorString(e));
     return FBC_OK;
@@ -722,7 +773,7 @@ void hmat_enqueue_pipeline(fbc_hmat* h, const double* bfrag, int64_t bf_mode, in
     io.mp = mp;
     io.nm = nm;
     io.r_out = 8 * ct;
-    hmat_launch(h, io, st);
+    hmat_launch<true>(h, io, st);
 }
 
 const fbc_ctx* hmat_context(const fbc_hmat* h) { return h->ctx; }
