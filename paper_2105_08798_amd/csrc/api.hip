@@ -1109,13 +1109,30 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
                         const int32_t* cb = &p.cols_b[2 * std::min(b0 + x, p.n_b - 1)];
                         order[x] = {(int64_t)bx[3] * (cb[0] - bx[0]) + cb[1] - bx[2], b0 + x};
                     }
-                    std::sort(order.begin(), order.end());
-                    for (int cc = 0; cc < 3; ++cc)
+                    // by component; within one, of the rows left, one whose place has a residue
+                    // modulo 16 (LDS bank pair) that its group of 16 rows does not hold yet, from
+                    // the most frequent such residue
+                    for (int cc = 0; cc < 3; ++cc) {
+                        std::vector<int32_t> left[16];
                         for (const auto& o : order) {
                             const int y = 3 * o.second + cc - tl * JOB_ROWS;
                             // (places past 16 bits: only tiles whose boxes do not fit, never gathered)
-                            if (y >= 0 && y < JOB_ROWS) keys.push_back(y | (int32_t)((o.first & 0x7fff) << 16));
+                            if (y >= 0 && y < JOB_ROWS) left[o.first & 15].push_back(y | (int32_t)((o.first & 0x7fff) << 16));
                         }
+                        unsigned held = 0;
+                        for (;;) {
+                            if ((keys.size() - v.rrow) % 16 == 0) held = 0;
+                            int best = -1;
+                            for (int r = 0; r < 16; ++r)
+                                if (!left[r].empty() && (best < 0 || std::make_pair(!(held >> r & 1), left[r].size()) >
+                                                                         std::make_pair(!(held >> best & 1), left[best].size())))
+                                    best = r;
+                            if (best < 0) break;
+                            keys.push_back(left[best].back());
+                            left[best].pop_back();
+                            held |= 1u << best;
+                        }
+                    }
                 }
                 cd.push_back(v);
                 continue;

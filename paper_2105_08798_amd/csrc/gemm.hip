@@ -415,6 +415,7 @@ __device__ inline void gemm_split_lds_job(const GemmJob& jb, const unsigned shor
 }
 
 typedef unsigned u4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u2_t __attribute__((ext_vector_type(2)));
 
 // ------------------------------- gather jobs --------------------------------------
 // The blocks come from the table of distinct column offsets.  A job's 128 rows belong to 43 or
@@ -422,21 +423,23 @@ typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 // part): some 500 pairs, but on neighbouring columns only about a hundred distinct offsets, all
 // of them in a box of n1 x n2 of two hundred or so.  So the box, not the pairs, is read per
 // chunk: while the group computes a chunk, its threads load the records of the next chunk's box
-// into registers, then store them to LDS in three planes of 16 bytes (components xx xy | xz yz |
-// yy zz, eight bytes each); the chunk's B fragments and the places of its columns go the same
-// way.  One buffer and several work groups per CU rather than two buffers: their load, store and
+// into registers, then store them to LDS in six planes of eight bytes (xx xy xz yz yy zz); the
+// chunk's B fragments and the places of its columns go the same way.  One buffer and several work groups per CU rather than two buffers: their load, store and
 // compute phases overlap.
 // A record has 64 bytes (16 of padding): the address unit takes a quad of lanes a clock where
 // their 16-byte accesses fill one aligned 64-byte block, and one lane a clock otherwise.
 // A fragments are read component by component, at the place of the pad column plus that of the
-// interface column (n1 x n2 is linear in both).  The rows are taken in the order of their
-// Cartesian component, then of (n1, n2) (rows may be permuted freely, the K order may not).  The
-// column and the component of k' depend on the lane only through its group g and the chunk
-// number mod 3, so they come from three per-lane constants each.
-// bytes of a plane: 48 modulo 128, so that the three parts of consecutive records fall into
-// distinct banks
-constexpr int G_PL = G_CAP * 16 + 48;
-constexpr int G_COLS = (3 * G_PL + 127) / 128 * 128;      // places of the chunk's columns
+// interface column (n1 x n2 is linear in both).  The rows are taken in the order of their Cartesian
+// component and, within one, so that the 16 of a fragment fall into distinct banks wherever the
+// chunk's columns shift them (rows may be permuted freely, the K order may not).  The column and
+// the component of k' depend on the lane only through its group g and the chunk number mod 3, so
+// they come from three per-lane constants each.  Bound by LDS, the vector operations and MFMA about
+// equally (1024 layers, 2048 / 4096 columns, 16 RHS, two column tiles, gathered modes alone: busy
+// 59, 50 and 32 % of 2.8 ms; with 16-byte planes and rows by place 65 % of 3.1).
+// Bytes of a plane: 16 modulo 64, so that the three pairs of planes that a quad of lanes writes
+// fall into distinct banks.
+constexpr int G_PL = G_CAP * 8 + 16;
+constexpr int G_COLS = (6 * G_PL + 127) / 128 * 128;      // places of the chunk's columns
 constexpr int G_B = G_COLS + 128;                         // B fragments, 4 KiB per column tile
 constexpr int gather_lds(int ct) { return G_B + 4096 * ct; }
 
@@ -485,7 +488,7 @@ __device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const v
                 const int d = (am + gg) % 3, lo = min(c, d), hi = max(c, d);
                 // slots: xx 0, xy 1, xz 2, yz 3, yy 4, zz 5
                 const int slot = lo == 0 ? hi : lo == 1 ? (hi == 1 ? 4 : 3) : 5;
-                base[r][am] = (slot >> 1) * G_PL + (slot & 1) * 8 + (e >> 16) * 16 + (F32 ? (g & 1) * 4 : 0);
+                base[r][am] = slot * G_PL + (e >> 16) * 8 + (F32 ? (g & 1) * 4 : 0);
             }
         }
         const uniform_int* box = (const uniform_int*)(tv.keys + cd.rbox + 4 * tile);
@@ -501,7 +504,7 @@ __device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const v
         int rel[NR];
 #pragma unroll
         for (int k = 0; k < NR; ++k) rel[k] = relative((tid + NTH * k) >> 2);
-        const int at = part * G_PL + (tid >> 2) * 16;
+        const int at = 2 * part * G_PL + (tid >> 2) * 8;
         const char* tm = tv.tab + jb.a_off;
         const u4_t* bsrc = (const u4_t*)Bv + (F32 ? jb.b_off >> 2 : jb.b_off >> 3);
         u4_t st[NR], sb[NBU];
@@ -533,17 +536,21 @@ __device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const v
             pmax1 = cmax1;
             pmax2 = cmax2;
         };
+        auto put = [](char* p, u4_t v) {
+            *(u2_t*)p = v.xy;
+            *(u2_t*)(p + G_PL) = v.zw;
+        };
         auto store = [&]() {
             if (part < 3) {
 #pragma unroll
-                for (int k = 0; k < NR; ++k) *(u4_t*)(smem + at + NTH * k * 4) = st[k];
+                for (int k = 0; k < NR; ++k) put(smem + at + NTH * k * 2, st[k]);
                 if constexpr (STG < G_CAP)
                     for (int u = NTH * NR + tid; u < nu; u += NTH)
-                        *(u4_t*)(smem + at + (u - tid) * 4) = unit(relative(u >> 2));
+                        put(smem + at + (u - tid) * 2, unit(relative(u >> 2)));
             }
 #pragma unroll
             for (int j = 0; j < NBU; ++j) *(u4_t*)(smem + G_B + (tid + NTH * j) * 16) = sb[j];
-            if (tid < 12) *(int*)(smem + G_COLS + 4 * tid) = 16 * (L * (pmax1 - xc.x) + pmax2 - xc.y);
+            if (tid < 12) *(int*)(smem + G_COLS + 4 * tid) = 8 * (L * (pmax1 - xc.x) + pmax2 - xc.y);
         };
         auto compute = [&](auto phase) {
             constexpr int PH = decltype(phase)::value;
