@@ -1208,14 +1208,12 @@ static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st) {
         double* sums = c->sums + sums_off;
         double* tot = c->ftot + 3 * p.rhs0;
         int* bexp = f16 ? c->bexp + p.rhs0 : nullptr;
-        if (c->opt.check_netforce || c->opt.project_netforce || comp || f16)
-            launch_netforce(st, fc, sums, tot, comp ? c->shat + c->shat_off[ci] : nullptr,
-                            comp ? c->shat_on + p.rhs0 : nullptr, p.R, p.nz, p.n_i, c->opt.netforce_tol,
-                            c->opt.check_netforce, c->opt.project_netforce, c->tw + p.tw_off, bexp,
-                            c->status);
         void* bm = (char*)c->bfrag + p.b_off * b_elem_bytes(form);
-        launch_line_rfft(st, form, fc, tot, c->opt.project_netforce, bm, p.R, p.nz, p.n_i, p.kp,
-                         p.ct, c->tw + p.tw_off, bexp);
+        launch_forward(st, form, fc, sums, tot, comp ? c->shat + c->shat_off[ci] : nullptr,
+                       comp ? c->shat_on + p.rhs0 : nullptr,
+                       c->opt.check_netforce || c->opt.project_netforce || comp || f16, c->opt.netforce_tol,
+                       c->opt.check_netforce, c->opt.project_netforce, bm, p.R, p.nz, p.n_i, p.kp, p.ct,
+                       c->tw + p.tw_off, bexp, c->status);
         sums_off += (int64_t)p.R * p.nz * 8;
     }
     const bool tm = c->timing && c->n_timed < kMaxTimed;
@@ -1280,32 +1278,29 @@ static void enqueue_update(fbc_ctx* c, double* u, double alpha, bool mean_remova
         const int* be = f16 ? c->bexp + p.rhs0 : nullptr;
         int tr, pp;
         if (!update_shape(p.nz, p.M, p.ctr, &tr, &pp)) {
-            // lines outside 16..1024 layers: inverse transform into w, then the tiled transpose-update,
+            // lines outside 4..1024 layers: inverse transform into w, then the tiled transpose-update,
             // which also removes the mean (known beforehand, as for the fused update)
             double* uc = u + p.u_off;
             double* sp = c->sum_part + c->sum_part_off[ci];
-            double* mu = nullptr;
-            if (mean_removal) {
-                mu = c->mean + 3 * p.rhs0;
-                launch_update_mean(st, uc, c->cbuf + p.c_off, sp, p.R, p.nz, p.mp, p.M, c->nsplit, p.c_split, rm,
-                                   sh, so, am, be, alpha, mu, c->status);
-            }
+            MeanIn mean{};
+            if (mean_removal)
+                mean = launch_update_mean(st, uc, c->cbuf + p.c_off, sp, p.R, p.nz, p.mp, p.M, c->nsplit, p.c_split, rm,
+                                          sh, so, am, be, alpha, c->mean + 3 * p.rhs0, c->status);
             launch_line_irfft(st, c->cbuf + p.c_off, c->wbuf + p.w_off, c->wmax_part + c->wmax_off[ci], p.R,
                               p.nz, p.mp, p.M, p.ct, p.ctr, c->tw + p.tw_off, c->nsplit, p.c_split, rm, sh,
                               so, am, be, nullptr);
             if (!mean_removal) launch_fill(st, uc, (int64_t)p.R * p.nz * p.M, 0.0);
             // the mean is known beforehand: no partial sums
-            launch_axpy(st, c->wbuf + p.w_off, uc, p.R, p.nz, p.M, alpha, nullptr, c->status, mu);
+            launch_axpy(st, c->wbuf + p.w_off, uc, p.R, p.nz, p.M, alpha, nullptr, c->status, mean);
             continue;
         }
-        double* mu = nullptr;
-        if (mean_removal) {
-            mu = c->mean + 3 * p.rhs0;
-            launch_update_mean(st, u + p.u_off, c->cbuf + p.c_off, c->sum_part + c->sum_part_off[ci], p.R,
-                               p.nz, p.mp, p.M, c->nsplit, p.c_split, rm, sh, so, am, be, alpha, mu, c->status);
-        }
+        MeanIn mean{};
+        if (mean_removal)
+            mean = launch_update_mean(st, u + p.u_off, c->cbuf + p.c_off, c->sum_part + c->sum_part_off[ci], p.R, p.nz,
+                                      p.mp, p.M, c->nsplit, p.c_split, rm, sh, so, am, be, alpha,
+                                      c->mean + 3 * p.rhs0, c->status);
         launch_irfft_update(st, c->cbuf + p.c_off, u + p.u_off, p.R, p.nz, p.mp, p.M, p.ctr,
-                            c->tw + p.tw_off, c->nsplit, p.c_split, rm, sh, so, am, be, alpha, mu,
+                            c->tw + p.tw_off, c->nsplit, p.c_split, rm, sh, so, am, be, alpha, mean,
                             mean_removal ? 1 : 0, c->status);
     }
 }
@@ -1668,10 +1663,11 @@ static void enqueue_relax(fbc_ctx* c, const double* f_in, double* u, fbc_relax_o
         if (c->ropt.du_max <= 0.0 && c->npart_update[ci] > 0) {
             // no step bound: the step factors are known before w, so the fused inverse
             // transform and update takes them, and leaves the maxima of |w| for step_inf
-            launch_update_mean(st, uc, c->cbuf + p.c_off, c->sum_part + c->sum_part_off[ci], p.R, p.nz, p.mp,
-                               p.M, c->nsplit, p.c_split, rm, sh, so, am, be, 0.0, mu, c->status, c->alpha + p.rhs0);
+            const MeanIn mean =
+                launch_update_mean(st, uc, c->cbuf + p.c_off, c->sum_part + c->sum_part_off[ci], p.R, p.nz, p.mp, p.M,
+                                   c->nsplit, p.c_split, rm, sh, so, am, be, 0.0, mu, c->status, c->alpha + p.rhs0);
             launch_irfft_update(st, c->cbuf + p.c_off, uc, p.R, p.nz, p.mp, p.M, p.ctr, c->tw + p.tw_off, c->nsplit,
-                                p.c_split, rm, sh, so, am, be, 0.0, mu, 1, c->status, c->alpha + p.rhs0, wm);
+                                p.c_split, rm, sh, so, am, be, 0.0, mean, 1, c->status, c->alpha + p.rhs0, wm);
             launch_relax_clamp(st, wm, c->npart_update[ci], c->alpha + p.rhs0, c->stepinf + p.rhs0, p.R,
                                c->ropt.du_max, kdev, c->ropt.relax);
             continue;
@@ -1680,9 +1676,10 @@ static void enqueue_relax(fbc_ctx* c, const double* f_in, double* u, fbc_relax_o
         enqueue_to_w(c, ci, st);
         launch_relax_clamp(st, wm, c->npart_irfft[ci], c->alpha + p.rhs0, c->stepinf + p.rhs0, p.R,
                            c->ropt.du_max, kdev, c->ropt.relax);
-        launch_update_mean(st, uc, c->cbuf + p.c_off, c->sum_part + c->sum_part_off[ci], p.R, p.nz, p.mp, p.M,
-                           c->nsplit, p.c_split, rm, sh, so, am, be, 0.0, mu, c->status, c->alpha + p.rhs0);
-        launch_axpy(st, c->wbuf + p.w_off, uc, p.R, p.nz, p.M, 0.0, c->alpha + p.rhs0, c->status, mu);
+        const MeanIn mean =
+            launch_update_mean(st, uc, c->cbuf + p.c_off, c->sum_part + c->sum_part_off[ci], p.R, p.nz, p.mp, p.M,
+                               c->nsplit, p.c_split, rm, sh, so, am, be, 0.0, mu, c->status, c->alpha + p.rhs0);
+        launch_axpy(st, c->wbuf + p.w_off, uc, p.R, p.nz, p.M, 0.0, c->alpha + p.rhs0, c->status, mean);
     }
     launch_relax_finish(st, c->alpha, c->finf, c->stepinf, c->rmean, out, c->total_rhs, kdev, c->ropt.tol_f);
 }

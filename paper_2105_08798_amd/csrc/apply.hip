@@ -93,25 +93,6 @@ __global__ void __launch_bounds__(NT) k_netforce(const double* __restrict__ f,
     }
 }
 
-// Split-FP16 form: scale exponent of the force operand of each RHS (one work group per
-// RHS), from a bound on its transformed forces, |f^(m)| <= sum_n0 |f(n0)| <= Nz max|f|
-// (twice that after the projection), so that the scaled values stay below 2^14.  One
-// exponent per RHS: a RHS far smaller than another of the same cell (a converged one
-// beside one that is not) keeps its full 22-bit split instead of falling into subnormals.
-__global__ void __launch_bounds__(NT) k_bexp(const double* __restrict__ sums, int nz,
-                                             int* __restrict__ bexp) {
-    __shared__ double red[NT];
-    const int r = blockIdx.x;
-    double mx[1] = {0.0};
-    for (int n0 = threadIdx.x; n0 < nz; n0 += NT)
-        mx[0] = fmax(mx[0], sums[((int64_t)r * nz + n0) * NF_STRIDE + 6]);
-    block_max<1>(mx, red);
-    if (threadIdx.x == 0) {
-        const double bound = 2.0 * nz * mx[0];
-        bexp[r] = (bound > 0.0 && isfinite(bound)) ? 13 - ilogb(bound) : 0;
-    }
-}
-
 // Net force of the whole cell per RHS and component (sum over layers in fixed order):
 // tot[r][c].  Only this total enters the gauge (line mode 0); the check compares it with
 // the total absolute force.  With shat != NULL the same block then transforms the
@@ -121,26 +102,46 @@ __global__ void __launch_bounds__(NT) k_bexp(const double* __restrict__ sums, in
 // force lies within the rounding bound of its own summation, |s_c| <= n_i 2^-52 sum|f_c|,
 // is indistinguishable from a balanced one and enters as exactly zero; shat_on[r] = 0 then
 // records that the whole transform vanishes, so the compensation can be skipped.
-__global__ void __launch_bounds__(NT) k_netforce_total(const double* __restrict__ sums, int nz, int logn,
-                                                       int n_i, double tol, int check, int project,
-                                                       double* __restrict__ tot,
-                                                       const double2* __restrict__ tw,
-                                                       double2* __restrict__ shat,
-                                                       int* __restrict__ shat_on,
-                                                       int* __restrict__ status) {
-    extern __shared__ double2 lds[];             // 3 Nz (line transforms); >= 6 NT doubles
-    const int r = blockIdx.x;
+//
+// Split-FP16 form (bexp != NULL): also the scale exponent of the force operand of each RHS,
+// from a bound on its transformed forces, |f^(m)| <= sum_n0 |f(n0)| <= Nz max|f| (twice that
+// after the projection), so that the scaled values stay below 2^14.  One exponent per RHS:
+// a RHS far smaller than another of the same cell (a converged one beside one that is not)
+// keeps its full 22-bit split instead of falling into subnormals.
+struct NfTotal {
+    const double* sums;
+    double tol;
+    int check, project;
+    double* tot;
+    double2* shat;
+    int *shat_on, *bexp, *status;
+};
+// One work group of NT threads; lds: 3 Nz complex values and at least 6 NT doubles.
+__device__ inline void netforce_total(const NfTotal& a, int r, int nz, int logn, int n_i,
+                                      const double2* __restrict__ tw, double2* lds) {
+    const double* __restrict__ sums = a.sums;
+    double2* __restrict__ shat = a.shat;
+    const int project = a.project;
+    if (a.bexp) {
+        double mx[1] = {0.0};
+        for (int n0 = threadIdx.x; n0 < nz; n0 += NT) mx[0] = fmax(mx[0], sums[((int64_t)r * nz + n0) * NF_STRIDE + 6]);
+        block_max<1>(mx, (double*)lds);
+        if (threadIdx.x == 0) {
+            const double bound = 2.0 * nz * mx[0];
+            a.bexp[r] = (bound > 0.0 && isfinite(bound)) ? 13 - ilogb(bound) : 0;
+        }
+    }
     double v[6] = {0, 0, 0, 0, 0, 0};
     for (int n0 = threadIdx.x; n0 < nz; n0 += NT)
         for (int c = 0; c < 6; ++c) v[c] += sums[((int64_t)r * nz + n0) * NF_STRIDE + c];
     block_sum<6>(v, (double*)lds);
     if (threadIdx.x == 0) {
-        for (int c = 0; c < 3; ++c) tot[r * 3 + c] = v[c];
-        if (check && !project) {
+        for (int c = 0; c < 3; ++c) a.tot[r * 3 + c] = v[c];
+        if (a.check && !project) {
             int bits = 0;
             for (int c = 0; c < 3; ++c)
-                if (fabs(v[c]) > tol * v[3 + c]) bits |= ST_NETFORCE;
-            if (bits) atomicOr(status, bits);
+                if (fabs(v[c]) > a.tol * v[3 + c]) bits |= ST_NETFORCE;
+            if (bits) atomicOr(a.status, bits);
         }
     }
     if (!shat) return;
@@ -166,20 +167,15 @@ __global__ void __launch_bounds__(NT) k_netforce_total(const double* __restrict_
         any |= (z.x != 0.0 || z.y != 0.0);
     }
     any = __syncthreads_or(any);
-    if (threadIdx.x == 0) shat_on[r] = any;     // 0: s^ = 0 exactly, the compensation adds 0
+    if (threadIdx.x == 0) a.shat_on[r] = any;   // 0: s^ = 0 exactly, the compensation adds 0
+}
+__global__ void __launch_bounds__(NT) k_netforce_total(NfTotal a, int nz, int logn, int n_i,
+                                                       const double2* __restrict__ tw) {
+    extern __shared__ double2 lds[];
+    netforce_total(a, blockIdx.x, nz, logn, n_i, tw, lds);
 }
 
-void launch_netforce(hipStream_t st, const double* f, double* sums, double* tot, double2* shat,
-                     int* shat_on, int R, int nz, int n_i, double tol, int check, int project,
-                     const double2* tw, int* bexp, int* status) {
-    int logn = 0;
-    while ((1 << logn) < nz) ++logn;
-    hipLaunchKernelGGL(k_netforce, dim3(nz, R), dim3(NT), 0, st, f, sums, nz, n_i, check, status);
-    const size_t lds = std::max((size_t)3 * nz * sizeof(double2), (size_t)6 * NT * sizeof(double));
-    hipLaunchKernelGGL(k_netforce_total, dim3(R), dim3(NT), lds, st, sums, nz, logn, n_i, tol, check, project, tot,
-                       tw, shat, shat_on, status);
-    if (bexp) hipLaunchKernelGGL(k_bexp, dim3(R), dim3(NT), 0, st, sums, nz, bexp);
-}
+static size_t nf_lds(int nz) { return std::max((size_t)3 * nz * sizeof(double2), (size_t)6 * NT * sizeof(double)); }
 
 // ----------------------------------------------------------------------------------
 // rFFT along the line for every (RHS, column component), written straight into the
@@ -256,8 +252,13 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
                                                   void* __restrict__ bfrag, int nz, int logn,
                                                   int n_i, int kp, int ct, int tc,
                                                   const double2* __restrict__ tw, double inv_cnt,
-                                                  const int* __restrict__ bexp, int pairs) {
+                                                  const int* __restrict__ bexp, int pairs, NfTotal nf, int ny) {
     extern __shared__ double2 lds[];
+    if constexpr (NTH == NT)
+        if ((int)blockIdx.y >= ny) {        // one work group more per RHS: its net-force totals
+            netforce_total(nf, blockIdx.x, nz, logn, n_i, tw, lds);
+            return;
+        }
     // RHS fastest across blocks: the 8 RHS of a column tile, whose 64-byte column runs
     // fill the same 1 KiB fragment blocks, are written by neighbouring blocks close in time
     const int r = blockIdx.x;
@@ -267,7 +268,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
     const int ss = nz + 1;                  // sequence stride (complex values)
     const int nchunk = (K + tc - 1) / tc;
     double* ldsd = (double*)lds;
-    for (int cy = blockIdx.y; cy < nchunk; cy += gridDim.y) {     // column chunks (grid-stride)
+    for (int cy = blockIdx.y; cy < nchunk; cy += ny) {     // column chunks (grid-stride)
     const int k0 = cy * tc;
     // loads issued in batches of 8 per thread before their LDS stores (latency hiding);
     // the forces are read once per update: nontemporal loads keep them from displacing
@@ -429,9 +430,9 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
 
 
 
-void launch_line_rfft(hipStream_t st, int form, const double* f, const double* tot, int project,
-                      void* bfrag, int R, int nz, int n_i, int kp, int ct, const double2* tw,
-                      const int* bexp) {
+void launch_forward(hipStream_t st, int form, const double* f, double* sums, double* tot, double2* shat, int* shat_on,
+                    bool statistics, double tol, int check, int project, void* bfrag, int R, int nz, int n_i, int kp,
+                    int ct, const double2* tw, int* bexp, int* status) {
     int logn = 0;
     while ((1 << logn) < nz) ++logn;
     const int K = 3 * n_i;
@@ -456,18 +457,31 @@ void launch_line_rfft(hipStream_t st, int form, const double* f, const double* t
     const int kk = (K + 1) & ~1;
     if (tc > kk) tc = kk;
     tc &= ~1;
-    dim3 grid(R, (unsigned)std::min((K + tc - 1) / tc, 65535));
+    const int ny = std::min((K + tc - 1) / tc, 65534);
+    dim3 grid(R, ny);
     const int pairs = ((K & 1) == 0 && ((uintptr_t)f & 15) == 0) ? 1 : 0;
-    const size_t lds = (size_t)(nz + 1) * tc * sizeof(double);
+    size_t lds = (size_t)(nz + 1) * tc * sizeof(double);
+    // the totals: in the transform's launch where it does not read them (no projection, no operand
+    // scale) -- a launch less, 4.5 us where those are what an update costs
+    const NfTotal nf{sums, tol, check, project, tot, shat, shat_on, bexp, status};
+    if (statistics) {
+        hipLaunchKernelGGL(k_netforce, dim3(nz, R), dim3(NT), 0, st, f, sums, nz, n_i, check, status);
+        if (project || bexp || wide) {
+            hipLaunchKernelGGL(k_netforce_total, dim3(R), dim3(NT), nf_lds(nz), st, nf, nz, logn, n_i, tw);
+        } else {
+            grid.y += 1;
+            lds = std::max(lds, nf_lds(nz));
+        }
+    }
     const double inv_cnt = 1.0 / ((double)n_i * nz);
 #define RF_LAUNCH(FM)                                                                                       \
     do {                                                                                                    \
         if (wide) {                                                                                         \
             hipLaunchKernelGGL((k_line_rfft<FM, 1024>), grid, dim3(1024), lds, st, f, tot, project, bfrag, nz, logn, \
-                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs);                                  \
+                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs, nf, ny);                          \
         } else {                                                                                            \
             hipLaunchKernelGGL((k_line_rfft<FM, NT>), grid, dim3(NT), lds, st, f, tot, project, bfrag, nz, logn, \
-                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs);                                  \
+                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs, nf, ny);                          \
         }                                                                                                   \
     } while (0)
     switch (form) {
@@ -764,6 +778,27 @@ void launch_line_irfft(hipStream_t st, const double* c, double* w, double* wmax_
     if (n_part_out) *n_part_out = n_rg;
 }
 
+// Means still to be formed (MeanIn::nbr > 0) of RHS r0 .. r0 + n - 1, n <= 2, from the MEAN_INLINE
+// or fewer partial sums of each, in a fixed tree: smu[3 q + cc], and to mean.mu if `put`.  The
+// caller's next barrier covers smu.
+__device__ inline void form_means(const MeanIn& mean, int r0, int n, double alpha, const double* __restrict__ alpha_d,
+                                  bool put, double* smu) {
+    const int v = threadIdx.x / MEAN_INLINE, b = threadIdx.x % MEAN_INLINE;
+    if (v >= 3 * n) return;
+    const int r = r0 + v / 3, cc = v % 3;
+    const double* p = mean.part + ((int64_t)r * mean.nbr + min(b, mean.nbr - 1)) * 6 + cc;
+    double su = b < mean.nbr ? p[0] : 0.0, sw = b < mean.nbr ? p[3] : 0.0;
+    for (int m = MEAN_INLINE / 2; m > 0; m >>= 1) {
+        su += __shfl_xor(su, m);
+        sw += __shfl_xor(sw, m);
+    }
+    if (b == 0) {
+        const double a = alpha_d ? alpha_d[r] : alpha;
+        smu[v] = (su - a * sw) * mean.inv_n;
+        if (put) mean.mu[3 * r + cc] = smu[v];
+    }
+}
+
 // ----------------------------------------------------------------------------------
 // Fused inverse transform and pad update (the update step of Algorithm 1):
 //   u[r][n0][row] <- (read_u ? u : 0) - alpha * w[r][row][n0] - mu[r][row % 3]
@@ -779,10 +814,10 @@ void launch_line_irfft(hipStream_t st, const double* c, double* w, double* wmax_
 //  3. per thread four consecutive bit-reversed slots of one sequence: the stages of half
 //     length 2 and 1 in registers, then four layers n0 = bitrev(slot) of u, rows fastest
 //     across threads (runs of tr values of u per layer).
-// mu (mean of the updated u, from k_update_mean) may be NULL (no mean removal).  alpha_d:
+// mu (mean of the updated u, from k_update_mean or form_means) may be NULL (no mean removal).  alpha_d:
 // per-RHS step factors on the device in place of alpha (the relaxation step without its
 // bound); wmax_part (one RHS pair per group): per RHS and row group the largest |w|.
-// Skipped entirely when a data check has latched an error.  Needs Nz >= 16.
+// Skipped entirely when a data check has latched an error.  Needs Nz >= 4.
 // ----------------------------------------------------------------------------------
 template <int NSM, int NTH>
 __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__ c,
@@ -796,10 +831,11 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
                                                      const unsigned long long* __restrict__ amax,
                                                      const int* __restrict__ bexp, double alpha,
                                                      const double* __restrict__ alpha_d,
-                                                     const double* __restrict__ mu, int read_u,
+                                                     MeanIn mean, int read_u,
                                                      double* __restrict__ wmax_part,
                                                      const int* __restrict__ status) {
     extern __shared__ double2 lds[];
+    __shared__ double smu[6];
     if (status && *status) return;
     int tile, rg, pg;
     if (!xcd_unit(n_units, n_rg, 4 / pp, tile, rg, pg)) return;
@@ -807,6 +843,10 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
     const int ss = nz + 1;
     const int nm = (nz >> 1) + 1;
     const int nseq = tr * pp;
+    // (pp = 1) the means of the pair, read after step 1's barrier
+    const int ra0 = 8 * tile + 2 * pair0, nra = min(2, R - ra0);
+    if (mean.nbr > 0) form_means(mean, ra0, nra, alpha, alpha_d, rg == 0, smu);
+    else if (mean.mu && (int)threadIdx.x < 3 * nra) smu[threadIdx.x] = mean.mu[3 * ra0 + threadIdx.x];
     // 0. row-gauge compensation (pairs with per-layer net force only): the terms of every
     //    (row, mode) staged in the LDS slots of the mode and its mirror, the s^ of a mode
     //    loaded once per 4 rows and all loads of a thread issued before any is used
@@ -933,8 +973,8 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
             const int row = row0 + trr;
             const int ra = 8 * tile + 2 * (pair0 + pj);
             const bool live = t < nitem && row < M;
-            ma[k] = (mu && live && ra < R) ? mu[ra * 3 + row % 3] : 0.0;
-            mb[k] = (mu && live && ra + 1 < R) ? mu[(ra + 1) * 3 + row % 3] : 0.0;
+            ma[k] = (mean.mu && live && ra < R) ? smu[row % 3] : 0.0;
+            mb[k] = (mean.mu && live && ra + 1 < R) ? smu[3 + row % 3] : 0.0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 oa[k][e] = ob[k][e] = 0.0;
@@ -982,11 +1022,11 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
                 }
                 if (ra < R) {
                     const double x = oa[k][e] - aa * wa;
-                    u[((int64_t)ra * nz + n0) * M + row] = mu ? x - ma[k] : x;
+                    u[((int64_t)ra * nz + n0) * M + row] = mean.mu ? x - ma[k] : x;
                 }
                 if (ra + 1 < R) {
                     const double x = ob[k][e] - ab * wb;
-                    u[((int64_t)(ra + 1) * nz + n0) * M + row] = mu ? x - mb[k] : x;
+                    u[((int64_t)(ra + 1) * nz + n0) * M + row] = mean.mu ? x - mb[k] : x;
                 }
             }
         }
@@ -1009,8 +1049,10 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
 // threads per group (sixteen waves on the CU it fills): on the long workload 2.8-3.4 ms
 // against 4.3 ms for the inverse transform into w and the transpose-update, where 256
 // threads took 3.9-4.4 ms, 4 or 2 rows 4.2-7.9 ms, and 4 rows with 512 or 1024 threads (two
-// groups per CU) 4.2-5.1 ms; at Nz = 256, 1024 or 512 threads are 9-40 % slower than 256.  Returns false outside 16 <= Nz <= 1024: the update then
-// goes through the w scratch and the tiled transpose.
+// groups per CU) 4.2-5.1 ms; at Nz = 256, 1024 or 512 threads are 9-40 % slower than 256.  Lines below 64 layers: more rows, so that a
+// group's loads fill its threads (8 layers, 96 / 192 columns, 1 RHS: 6.7 us, the inverse
+// transform into w and the transpose 13.4 + 4.0).  Returns false outside 4 <= Nz <= 1024: the
+// update then goes through the w scratch and the tiled transpose.
 static int update_groups(int tr, int pp, int M, int ct_grid) {
     return xcd_groups(ct_grid * ((M + tr - 1) / tr), 4 / pp);
 }
@@ -1019,15 +1061,15 @@ bool update_shape(int nz, int M, int ct_grid, int* tr, int* pp) {
     (void)M;
     (void)ct_grid;
     *pp = 1;
-    *tr = 8;
-    return nz >= 16 && nz <= 1024;
+    *tr = nz >= 64 ? 8 : nz >= 32 ? 16 : nz >= 16 ? 32 : 64;
+    return nz >= 4 && nz <= 1024;
 }
 
 void launch_irfft_update(hipStream_t st, const double* c, double* u, int R, int nz, int mp, int M,
                          int ct_grid, const double2* tw, int nsplit, int64_t split_stride,
                          const double2* rowmean, const double2* shat, const int* shat_on,
                          const unsigned long long* amax, const int* bexp, double alpha,
-                         const double* mu, int read_u, const int* status, const double* alpha_d,
+                         const MeanIn& mean, int read_u, const int* status, const double* alpha_d,
                          double* wmax_part) {
     int logn = 0;
     while ((1 << logn) < nz) ++logn;
@@ -1047,11 +1089,11 @@ void launch_irfft_update(hipStream_t st, const double* c, double* u, int R, int 
     if (nz > 256) {                                                                                   \
         hipLaunchKernelGGL((k_irfft_update<NS, 1024>), dim3(nblk), dim3(1024), lds, st, c, u, R, nz, logn, mp, \
                            M, tr, pp, n_rg, n_units, tw, nsplit, split_stride, rowmean, shat, shat_on, amax, \
-                           bexp, alpha, alpha_d, mu, read_u, wmax_part, status);                      \
+                           bexp, alpha, alpha_d, mean, read_u, wmax_part, status);                    \
     } else {                                                                                          \
         hipLaunchKernelGGL((k_irfft_update<NS, NT>), dim3(nblk), dim3(NT), lds, st, c, u, R, nz, logn, mp, M, \
                            tr, pp, n_rg, n_units, tw, nsplit, split_stride, rowmean, shat, shat_on, amax, \
-                           bexp, alpha, alpha_d, mu, read_u, wmax_part, status);                      \
+                           bexp, alpha, alpha_d, mean, read_u, wmax_part, status);                    \
     }                                                                                                 \
 } while (0)
     if (nsplit <= 1) UPD_CASE(1);
@@ -1067,7 +1109,8 @@ void launch_irfft_update(hipStream_t st, const double* c, double* u, int R, int 
 // where sum_n0 w[row][n0] is the line mode 0 of the row (the inverse transform's
 // constant term), so sum w needs only the mode-0 records.  k_mean_parts: partial sums
 // of u and of the mode-0 values over a fixed partition (nbr blocks per RHS);
-// k_update_mean: one block per RHS adds the partials in fixed order.
+// k_update_mean: one block per RHS adds the partials in fixed order.  With MEAN_INLINE or fewer of
+// them the kernel that updates u does that itself (form_means) instead.
 // ----------------------------------------------------------------------------------
 __global__ void __launch_bounds__(NT) k_mean_parts(const double* __restrict__ u, const double* __restrict__ c,
                                                    int64_t per_rhs, int nbr, int R, int nz, int mp, int M,
@@ -1124,9 +1167,13 @@ __global__ void __launch_bounds__(NT) k_mean_parts(const double* __restrict__ u,
         for (int k = 0; k < 6; ++k) part[((int64_t)r * nbr + b) * 6 + k] = v[k];
 }
 
+// Blocks of 8192 values, of 2048 where that makes no more than MEAN_INLINE (a thread's chain of
+// loads is what they cost then).
 int mean_blocks(int64_t per_rhs) {
+    const int64_t s = (per_rhs + (int64_t)NT * 8 - 1) / ((int64_t)NT * 8);
+    if (s <= MEAN_INLINE) return (int)std::max<int64_t>(1, s);
     const int64_t b = (per_rhs + (int64_t)NT * 32 - 1) / ((int64_t)NT * 32);
-    return (int)std::max<int64_t>(1, std::min<int64_t>(1024, b));
+    return (int)std::max<int64_t>(MEAN_INLINE, std::min<int64_t>(1024, b));
 }
 
 __global__ void __launch_bounds__(NT) k_update_mean(const double* __restrict__ part, int nbr, int nz, int n_b,
@@ -1147,7 +1194,7 @@ __global__ void __launch_bounds__(NT) k_update_mean(const double* __restrict__ p
     }
 }
 
-void launch_update_mean(hipStream_t st, const double* u, const double* c, double* part, int R, int nz,
+MeanIn launch_update_mean(hipStream_t st, const double* u, const double* c, double* part, int R, int nz,
                         int mp, int M, int nsplit, int64_t split_stride, const double2* rowmean,
                         const double2* shat, const int* shat_on, const unsigned long long* amax,
                         const int* bexp, double alpha, double* mu, const int* status,
@@ -1156,7 +1203,9 @@ void launch_update_mean(hipStream_t st, const double* u, const double* c, double
     const int nbr = mean_blocks(per_rhs);
     hipLaunchKernelGGL(k_mean_parts, dim3(nbr, R), dim3(NT), 0, st, u, c, per_rhs, nbr, R, nz, mp, M, nsplit,
                        split_stride, rowmean, shat, shat_on, amax, bexp, part, status);
+    if (nbr <= MEAN_INLINE) return MeanIn{mu, part, nbr, 1.0 / ((double)nz * (M / 3))};
     hipLaunchKernelGGL(k_update_mean, dim3(R), dim3(NT), 0, st, part, nbr, nz, M / 3, alpha, alpha_d, mu, status);
+    return MeanIn{mu, nullptr, 0, 0.0};
 }
 
 // ----------------------------------------------------------------------------------
@@ -1172,18 +1221,18 @@ void launch_update_mean(hipStream_t st, const double* u, const double* c, double
 
 __global__ void __launch_bounds__(NT) k_axpy(const double* __restrict__ w, double* __restrict__ u, int nz,
                                              int M, double alpha, const double* __restrict__ alpha_d,
-                                             const double* __restrict__ mu, int vec,
+                                             MeanIn mean, int vec,
                                              const int* __restrict__ status) {
     __shared__ double tile[AX_TR][AX_TN + 1];
+    __shared__ double smu[6];
     if (status && *status) return;
     const int r = blockIdx.z;
     const int row0 = blockIdx.x * AX_TR, n00 = blockIdx.y * AX_TN;
     const double a = alpha_d ? alpha_d[r] : alpha;
     const double* wr = w + (int64_t)r * M * nz;
     double* ur = u + (int64_t)r * nz * M;
-    double m3[3] = {0.0, 0.0, 0.0};
-    if (mu)
-        for (int cc = 0; cc < 3; ++cc) m3[cc] = mu[r * 3 + cc];
+    if (mean.nbr > 0) form_means(mean, r, 1, alpha, alpha_d, blockIdx.x == 0 && blockIdx.y == 0, smu);
+    else if (mean.mu && threadIdx.x < 3) smu[threadIdx.x] = mean.mu[r * 3 + threadIdx.x];
     // old u: rows 2 tx, 2 tx + 1 of layers ty + 8 k
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     const int row = row0 + 2 * tx;
@@ -1237,7 +1286,7 @@ __global__ void __launch_bounds__(NT) k_axpy(const double* __restrict__ w, doubl
         for (int e = 0; e < 2; ++e) {
             const int rr = row + e;
             x[e] = uo[k][e] - a * tile[2 * tx + e][ty + 8 * k];
-            if (mu) x[e] -= m3[rr % 3];
+            if (mean.mu) x[e] -= smu[rr % 3];
         }
         double* p = ur + (int64_t)n0 * M + row;
         if (vec && row + 1 < M) {
@@ -1250,11 +1299,11 @@ __global__ void __launch_bounds__(NT) k_axpy(const double* __restrict__ w, doubl
 }
 
 void launch_axpy(hipStream_t st, const double* w, double* u, int R, int nz, int M, double alpha,
-                 const double* alpha_d, const int* status, const double* mu) {
+                 const double* alpha_d, const int* status, const MeanIn& mean) {
     dim3 grid((M + AX_TR - 1) / AX_TR, (nz + AX_TN - 1) / AX_TN, R);
     // 16-byte accesses: every row pair of u and layer pair of w starts 16-byte aligned
     const int vec = ((M & 1) == 0 && (nz & 1) == 0 && ((uintptr_t)u & 15) == 0 && ((uintptr_t)w & 15) == 0) ? 1 : 0;
-    hipLaunchKernelGGL(k_axpy, grid, dim3(NT), 0, st, w, u, nz, M, alpha, alpha_d, mu, vec, status);
+    hipLaunchKernelGGL(k_axpy, grid, dim3(NT), 0, st, w, u, nz, M, alpha, alpha_d, mean, vec, status);
 }
 
 // ----------------------------------------------------------------------------------

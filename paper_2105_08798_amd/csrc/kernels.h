@@ -45,12 +45,11 @@ void launch_tab_absmax(hipStream_t st, const double2* tab, int T, int64_t n_off,
 // ---- apply (Section 2.3.2 update in line-mode form) ----
 // Per-layer sums sums[r][n0][6] (net force, absolute force), cell totals tot[r][3] with
 // the net-force check, and (shat != NULL) the line transform of the per-layer net force.
-void launch_netforce(hipStream_t st, const double* f, double* sums, double* tot, double2* shat,
-                     int* shat_on, int R, int nz, int n_i, double tol, int check, int project,
-                     const double2* tw, int* bexp, int* status);
-void launch_line_rfft(hipStream_t st, int form, const double* f, const double* tot, int project,
-                      void* bfrag, int R, int nz, int n_i, int kp, int ct, const double2* tw,
-                      const int* bexp);
+// launch_forward: these (if `statistics`; bexp: also the operand scale of split FP16), then the
+// transforms of f into the product's B fragments.
+void launch_forward(hipStream_t st, int form, const double* f, double* sums, double* tot, double2* shat, int* shat_on,
+                    bool statistics, double tol, int check, int project, void* bfrag, int R, int nz, int n_i, int kp,
+                    int ct, const double2* tw, int* bexp, int* status);
 // Reduced forms.  variant: one of gemm_variants(form, ctmax) kernel instantiations (bitwise the
 // same result); q != NULL: persistent work-queue kernel on these lists.
 void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int ctmax, const void* a,
@@ -78,9 +77,18 @@ void launch_line_irfft(hipStream_t st, const double* c, double* w, double* wmax_
 // Raises the dynamic-LDS limit of the 1024-thread line-transform kernels on the current
 // device (once per device; call outside stream capture, e.g. at context creation).
 void apply_kernels_init();
+// The mean that an update removes, mu[r][3] (mu NULL: none).  nbr > 0: the kernel that updates u
+// still has to form it, from nbr <= MEAN_INLINE partial sums per RHS, and to write it.
+#define MEAN_INLINE 32
+struct MeanIn {
+    double* mu;
+    const double* part;
+    int nbr;
+    double inv_n;
+};
 // u <- u - alpha_r w - mu_r (mu optional) through a tiled transpose
 void launch_axpy(hipStream_t st, const double* w, double* u, int R, int nz, int M, double alpha,
-                 const double* alpha_d, const int* status, const double* mu);
+                 const double* alpha_d, const int* status, const MeanIn& mean);
 // fused inverse transform + update (fbc_apply, fbc_green_apply, the relaxation step without
 // a step bound), and the mean it removes; update_shape is false where the line is too long
 // for the fused kernel.  alpha_d: per-RHS step factors on the device (else alpha);
@@ -90,10 +98,10 @@ void launch_irfft_update(hipStream_t st, const double* c, double* u, int R, int 
                          int ct_grid, const double2* tw, int nsplit, int64_t split_stride,
                          const double2* rowmean, const double2* shat, const int* shat_on,
                          const unsigned long long* amax, const int* bexp, double alpha,
-                         const double* mu, int read_u, const int* status,
+                         const MeanIn& mean, int read_u, const int* status,
                          const double* alpha_d = nullptr, double* wmax_part = nullptr);
 int mean_blocks(int64_t per_rhs);
-void launch_update_mean(hipStream_t st, const double* u, const double* c, double* part, int R, int nz,
+MeanIn launch_update_mean(hipStream_t st, const double* u, const double* c, double* part, int R, int nz,
                         int mp, int M, int nsplit, int64_t split_stride, const double2* rowmean,
                         const double2* shat, const int* shat_on, const unsigned long long* amax,
                         const int* bexp, double alpha, double* mu, const int* status,
