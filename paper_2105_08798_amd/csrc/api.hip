@@ -1016,7 +1016,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
             c->npart_update.push_back(np_up);
             wmax_n += (int64_t)p.R * std::max(np_ir, np_up);
             sp_n += (int64_t)p.R * mean_blocks((int64_t)p.nz * p.M) * 6;
-            rp_n += (int64_t)p.R * 64 * 3;
+            rp_n += (int64_t)p.R * p.nz * 3;
         }
         if ((s = dev_alloc(c, (void**)&c->sums, sums_n * 8)) != FBC_OK) goto fail_out;
         if ((s = dev_alloc(c, (void**)&c->ftot, (int64_t)c->total_rhs * 3 * 8)) != FBC_OK) goto fail_out;
@@ -1197,7 +1197,8 @@ static void enqueue_to_w(fbc_ctx* c, size_t ci, hipStream_t st) {
                       f16 ? c->bexp + p.rhs0 : nullptr, nullptr);
 }
 
-static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st) {
+// relax: the step factors of a relaxation step as well.
+static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st, bool relax = false) {
     const int form = c->opt.form;
     int64_t sums_off = 0;
     const bool comp = row_gauge_active(c);
@@ -1213,7 +1214,10 @@ static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st) {
                        comp ? c->shat_on + p.rhs0 : nullptr,
                        c->opt.check_netforce || c->opt.project_netforce || comp || f16, c->opt.netforce_tol,
                        c->opt.check_netforce, c->opt.project_netforce, bm, p.R, p.nz, p.n_i, p.kp, p.ct,
-                       c->tw + p.tw_off, bexp, c->status);
+                       c->tw + p.tw_off, bexp, c->status,
+                       relax ? RelaxIn{c->fprev + p.f_off, c->rpart + c->rpart_off[ci], c->alpha + p.rhs0,
+                                       c->finf + p.rhs0, c->status + 4, c->ropt.relax, c->ropt.alpha_min}
+                             : RelaxIn{});
         sums_off += (int64_t)p.R * p.nz * 8;
     }
     const bool tm = c->timing && c->n_timed < kMaxTimed;
@@ -1638,14 +1642,7 @@ extern "C" fbc_status fbc_relax_begin(fbc_ctx* c, const fbc_relax_opts* o, void*
 // One relaxation step, enqueued; the iteration index is read and advanced on the device.
 static void enqueue_relax(fbc_ctx* c, const double* f_in, double* u, fbc_relax_out* out, hipStream_t st) {
     int* kdev = c->status + 4;
-    for (size_t ci = 0; ci < c->cells.size(); ++ci) {
-        auto& p = c->cells[ci];
-        const int64_t per_rhs = (int64_t)p.nz * p.K;
-        launch_relax_alpha(st, f_in + p.f_off, c->fprev + p.f_off, c->rpart + c->rpart_off[ci],
-                           c->alpha + p.rhs0, c->finf + p.rhs0, p.R, per_rhs, kdev, c->ropt.relax,
-                           c->ropt.alpha_min);
-    }
-    enqueue_forward(c, f_in, st);
+    enqueue_forward(c, f_in, st, true);
     const bool comp = row_gauge_active(c);
     const bool f16 = (c->opt.form == FBC_FORM_SPLIT_FP16);
     for (size_t ci = 0; ci < c->cells.size(); ++ci) {
@@ -1668,17 +1665,17 @@ static void enqueue_relax(fbc_ctx* c, const double* f_in, double* u, fbc_relax_o
                                    c->nsplit, p.c_split, rm, sh, so, am, be, 0.0, mu, c->status, c->alpha + p.rhs0);
             launch_irfft_update(st, c->cbuf + p.c_off, uc, p.R, p.nz, p.mp, p.M, p.ctr, c->tw + p.tw_off, c->nsplit,
                                 p.c_split, rm, sh, so, am, be, 0.0, mean, 1, c->status, c->alpha + p.rhs0, wm);
-            launch_relax_clamp(st, wm, c->npart_update[ci], c->alpha + p.rhs0, c->stepinf + p.rhs0, p.R,
-                               c->ropt.du_max, kdev, c->ropt.relax);
+            launch_relax_clamp(st, RelaxClamp{wm, c->npart_update[ci], c->alpha + p.rhs0, c->stepinf + p.rhs0,
+                                              c->ropt.du_max, kdev, c->ropt.relax}, p.R);
             continue;
         }
         // the step bound needs the whole of w first
         enqueue_to_w(c, ci, st);
-        launch_relax_clamp(st, wm, c->npart_irfft[ci], c->alpha + p.rhs0, c->stepinf + p.rhs0, p.R,
-                           c->ropt.du_max, kdev, c->ropt.relax);
+        const RelaxClamp clamp{wm, c->npart_irfft[ci], c->alpha + p.rhs0, c->stepinf + p.rhs0,
+                               c->ropt.du_max, kdev, c->ropt.relax};
         const MeanIn mean =
             launch_update_mean(st, uc, c->cbuf + p.c_off, c->sum_part + c->sum_part_off[ci], p.R, p.nz, p.mp, p.M,
-                               c->nsplit, p.c_split, rm, sh, so, am, be, 0.0, mu, c->status, c->alpha + p.rhs0);
+                               c->nsplit, p.c_split, rm, sh, so, am, be, 0.0, mu, c->status, c->alpha + p.rhs0, &clamp);
         launch_axpy(st, c->wbuf + p.w_off, uc, p.R, p.nz, p.M, 0.0, c->alpha + p.rhs0, c->status, mean);
     }
     launch_relax_finish(st, c->alpha, c->finf, c->stepinf, c->rmean, out, c->total_rhs, kdev, c->ropt.tol_f);

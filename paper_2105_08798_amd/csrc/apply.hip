@@ -50,25 +50,91 @@ __device__ inline void block_max(double (&v)[NV], double* red) {
 #define NF_STRIDE 8
 
 // ----------------------------------------------------------------------------------
-// Net force per layer and component, and the finiteness check of the forces.
+// Relax (Algorithm 2) on raw residuals, per RHS.  Stage 1 (k_netforce): per layer
+// <f_k, f_{k+1} - f_k>, ||f_{k+1} - f_k||^2 and ||f_{k+1}||_inf.  Stage 2 (work groups of the
+// forward transform's launch): one block per RHS reduces them in fixed order and sets
+// alpha_{k+1} (alpha = 1 before the third iteration or without relaxation; alpha < 0 -> 1;
+// zero denominator keeps alpha_k).  The iteration index k lives in device memory (kdev), read
+// by the kernels and advanced by the step's last one, so a step captured into a graph replays
+// with the current k.
 // ----------------------------------------------------------------------------------
+__device__ inline int relax_on(const int* __restrict__ kdev, int relax) { return (relax && *kdev >= 2) ? 1 : 0; }
+__device__ inline void relax_alpha(const RelaxIn& a, int nz, int r, double* red) {
+    const int use_relax = relax_on(a.kdev, a.relax);
+    double v[2] = {0, 0};
+    double mx[1] = {0};
+    for (int n0 = threadIdx.x; n0 < nz; n0 += NT) {
+        const double* p = a.part + ((int64_t)r * nz + n0) * 3;
+        v[0] += p[0];
+        v[1] += p[1];
+        mx[0] = fmax(mx[0], p[2]);
+    }
+    block_sum<2>(v, red);
+    block_max<1>(mx, red);
+    if (threadIdx.x == 0) {
+        a.finf[r] = mx[0];
+        double al = 1.0;
+        if (use_relax) {
+            const double prev = a.alpha[r];
+            al = prev;
+            if (v[1] > 0.0) al = -prev * v[0] / v[1];
+            if (al < 0.0) al = 1.0;
+            if (a.alpha_min > 0.0) al = fmax(al, a.alpha_min);   // Remark in Section 2.3.3
+        }
+        a.alpha[r] = al;
+    }
+}
+
+// Step bound (the optional bound on the step in Algorithm 2) from the per-block maxima of |w|.
+__device__ inline void relax_clamp(const RelaxClamp& a, int r, double* red) {
+    const int use_bound = relax_on(a.kdev, a.relax);
+    double mx[1] = {0};
+    for (int b = threadIdx.x; b < a.n_part; b += NT) mx[0] = fmax(mx[0], a.wmax_part[(int64_t)r * a.n_part + b]);
+    block_max<1>(mx, red);
+    if (threadIdx.x == 0) {
+        double al = a.alpha[r];
+        if (use_bound && a.du_max > 0.0 && al * mx[0] > a.du_max) al = a.du_max / mx[0];
+        a.alpha[r] = al;
+        a.stepinf[r] = al * mx[0];
+    }
+}
+__global__ void __launch_bounds__(NT) k_relax_clamp(RelaxClamp a) {
+    __shared__ double red[NT];
+    relax_clamp(a, blockIdx.x, red);
+}
+
+void launch_relax_clamp(hipStream_t st, const RelaxClamp& a, int R) {
+    hipLaunchKernelGGL(k_relax_clamp, dim3(R), dim3(NT), 0, st, a);
+}
+
+// ----------------------------------------------------------------------------------
+// Net force per layer and component, and the finiteness check of the forces; RELAX: also the
+// relaxation's partials of the layer (f_k read, then f_{k+1} kept for the next step), so a step
+// reads the forces once for both (512 layers, 1500 columns, 12 RHS: 150 us, 44 + 123 apart).
+// ----------------------------------------------------------------------------------
+template <bool RELAX>
 __global__ void __launch_bounds__(NT) k_netforce(const double* __restrict__ f,
                                                  double* __restrict__ sums, int nz, int n_i,
-                                                 int check, int* __restrict__ status) {
+                                                 int check, int* __restrict__ status, RelaxIn rx) {
     __shared__ double red[7 * NT];
     const int n0 = blockIdx.x, r = blockIdx.y;
     const double* row = f + ((int64_t)r * nz + n0) * n_i * 3;
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
+    double* prev = RELAX ? rx.fprev + (row - f) : nullptr;
+    const int use_prev = RELAX ? relax_on(rx.kdev, rx.relax) : 0;
+    double v[7] = {0, 0, 0, 0, 0, 0, 0}, p[2] = {0, 0};
     double mx[1] = {0.0};
     // columns i = tid, tid + NT, ... in order; the loads of LU of them are issued together
     constexpr int LU = 4;
     for (int i0 = threadIdx.x; i0 < n_i; i0 += NT * LU) {
-        double x[LU][3];
+        double x[LU][3], y[LU][3];
 #pragma unroll
         for (int k = 0; k < LU; ++k) {
             const int i = i0 + k * NT;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) x[k][c] = (i < n_i) ? row[3 * i + c] : 0.0;
+            for (int c = 0; c < 3; ++c) {
+                x[k][c] = (i < n_i) ? row[3 * i + c] : 0.0;
+                y[k][c] = (RELAX && use_prev && i < n_i) ? prev[3 * i + c] : 0.0;
+            }
         }
 #pragma unroll
         for (int k = 0; k < LU; ++k) {
@@ -79,11 +145,26 @@ __global__ void __launch_bounds__(NT) k_netforce(const double* __restrict__ f,
                 v[3 + c] += fabs(x[k][c]);
                 mx[0] = fmax(mx[0], fabs(x[k][c]));
                 if (!isfinite(x[k][c])) v[6] = 1.0;
+                if (RELAX && use_prev) {
+                    const double d = x[k][c] - y[k][c];
+                    p[0] += y[k][c] * d;
+                    p[1] += d * d;
+                }
+                if (RELAX) prev[3 * (i0 + k * NT) + c] = x[k][c];
             }
         }
     }
     block_sum<7>(v, red);
     block_max<1>(mx, red);
+    if (RELAX) {
+        block_sum<2>(p, red);
+        if (threadIdx.x == 0) {
+            double* q = rx.part + ((int64_t)r * nz + n0) * 3;
+            q[0] = p[0];
+            q[1] = p[1];
+            q[2] = mx[0];
+        }
+    }
     if (threadIdx.x == 0) {
         double* o = sums + ((int64_t)r * nz + n0) * NF_STRIDE;
         for (int c = 0; c < 6; ++c) o[c] = v[c];
@@ -170,9 +251,10 @@ __device__ inline void netforce_total(const NfTotal& a, int r, int nz, int logn,
     if (threadIdx.x == 0) a.shat_on[r] = any;   // 0: s^ = 0 exactly, the compensation adds 0
 }
 __global__ void __launch_bounds__(NT) k_netforce_total(NfTotal a, int nz, int logn, int n_i,
-                                                       const double2* __restrict__ tw) {
+                                                       const double2* __restrict__ tw, int totals, RelaxIn rx) {
     extern __shared__ double2 lds[];
-    netforce_total(a, blockIdx.x, nz, logn, n_i, tw, lds);
+    if ((int)blockIdx.y < totals) netforce_total(a, blockIdx.x, nz, logn, n_i, tw, lds);
+    else relax_alpha(rx, nz, blockIdx.x, (double*)lds);
 }
 
 static size_t nf_lds(int nz) { return std::max((size_t)3 * nz * sizeof(double2), (size_t)6 * NT * sizeof(double)); }
@@ -252,11 +334,13 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
                                                   void* __restrict__ bfrag, int nz, int logn,
                                                   int n_i, int kp, int ct, int tc,
                                                   const double2* __restrict__ tw, double inv_cnt,
-                                                  const int* __restrict__ bexp, int pairs, NfTotal nf, int ny) {
+                                                  const int* __restrict__ bexp, int pairs, NfTotal nf, int ny, int totals,
+                                                  RelaxIn rx) {
     extern __shared__ double2 lds[];
     if constexpr (NTH == NT)
-        if ((int)blockIdx.y >= ny) {        // one work group more per RHS: its net-force totals
-            netforce_total(nf, blockIdx.x, nz, logn, n_i, tw, lds);
+        if ((int)blockIdx.y >= ny) {        // work groups more per RHS: its net-force totals, its step factor
+            if ((int)blockIdx.y < ny + totals) netforce_total(nf, blockIdx.x, nz, logn, n_i, tw, lds);
+            else relax_alpha(rx, nz, blockIdx.x, (double*)lds);
             return;
         }
     // RHS fastest across blocks: the 8 RHS of a column tile, whose 64-byte column runs
@@ -432,7 +516,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
 
 void launch_forward(hipStream_t st, int form, const double* f, double* sums, double* tot, double2* shat, int* shat_on,
                     bool statistics, double tol, int check, int project, void* bfrag, int R, int nz, int n_i, int kp,
-                    int ct, const double2* tw, int* bexp, int* status) {
+                    int ct, const double2* tw, int* bexp, int* status, const RelaxIn& rx) {
     int logn = 0;
     while ((1 << logn) < nz) ++logn;
     const int K = 3 * n_i;
@@ -457,31 +541,38 @@ void launch_forward(hipStream_t st, int form, const double* f, double* sums, dou
     const int kk = (K + 1) & ~1;
     if (tc > kk) tc = kk;
     tc &= ~1;
-    const int ny = std::min((K + tc - 1) / tc, 65534);
+    const int ny = std::min((K + tc - 1) / tc, 65533);
     dim3 grid(R, ny);
     const int pairs = ((K & 1) == 0 && ((uintptr_t)f & 15) == 0) ? 1 : 0;
     size_t lds = (size_t)(nz + 1) * tc * sizeof(double);
-    // the totals: in the transform's launch where it does not read them (no projection, no operand
-    // scale) -- a launch less, 4.5 us where those are what an update costs
+    // the totals and the step factor: in the transform's launch, the totals where it does not read
+    // them (no projection, no operand scale) -- a launch less each, 4.5 us where those are what an
+    // update costs
     const NfTotal nf{sums, tol, check, project, tot, shat, shat_on, bexp, status};
-    if (statistics) {
-        hipLaunchKernelGGL(k_netforce, dim3(nz, R), dim3(NT), 0, st, f, sums, nz, n_i, check, status);
-        if (project || bexp || wide) {
-            hipLaunchKernelGGL(k_netforce_total, dim3(R), dim3(NT), nf_lds(nz), st, nf, nz, logn, n_i, tw);
-        } else {
-            grid.y += 1;
-            lds = std::max(lds, nf_lds(nz));
-        }
+    const int relax = rx.fprev ? 1 : 0;
+    int totals = statistics ? 1 : 0;
+    if (relax)
+        hipLaunchKernelGGL(k_netforce<true>, dim3(nz, R), dim3(NT), 0, st, f, sums, nz, n_i, check, status, rx);
+    else if (statistics)
+        hipLaunchKernelGGL(k_netforce<false>, dim3(nz, R), dim3(NT), 0, st, f, sums, nz, n_i, check, status, rx);
+    if (wide ? totals + relax : totals && (project || bexp)) {
+        hipLaunchKernelGGL(k_netforce_total, dim3(R, totals + (wide ? relax : 0)), dim3(NT), nf_lds(nz), st, nf, nz,
+                           logn, n_i, tw, totals, rx);
+        totals = 0;
+    }
+    if (!wide && totals + relax) {
+        grid.y += totals + relax;
+        lds = std::max(lds, nf_lds(nz));
     }
     const double inv_cnt = 1.0 / ((double)n_i * nz);
 #define RF_LAUNCH(FM)                                                                                       \
     do {                                                                                                    \
         if (wide) {                                                                                         \
             hipLaunchKernelGGL((k_line_rfft<FM, 1024>), grid, dim3(1024), lds, st, f, tot, project, bfrag, nz, logn, \
-                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs, nf, ny);                          \
+                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs, nf, ny, totals, rx);              \
         } else {                                                                                            \
             hipLaunchKernelGGL((k_line_rfft<FM, NT>), grid, dim3(NT), lds, st, f, tot, project, bfrag, nz, logn, \
-                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs, nf, ny);                          \
+                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs, nf, ny, totals, rx);              \
         }                                                                                                   \
     } while (0)
     switch (form) {
@@ -1121,8 +1212,12 @@ __global__ void __launch_bounds__(NT) k_mean_parts(const double* __restrict__ u,
                                                    const unsigned long long* __restrict__ amax,
                                                    const int* __restrict__ bexp,
                                                    double* __restrict__ part,
-                                                   const int* __restrict__ status) {
+                                                   const int* __restrict__ status, RelaxClamp cl) {
     __shared__ double red[6 * NT];
+    if ((int)blockIdx.x >= nbr) {            // a work group more per RHS: its step bound
+        relax_clamp(cl, blockIdx.y, red);
+        return;
+    }
     if (status && *status) return;
     const int r = blockIdx.y, b = blockIdx.x;
     double v[6] = {0, 0, 0, 0, 0, 0};     // sum u (3), sum w (3)
@@ -1198,11 +1293,12 @@ MeanIn launch_update_mean(hipStream_t st, const double* u, const double* c, doub
                         int mp, int M, int nsplit, int64_t split_stride, const double2* rowmean,
                         const double2* shat, const int* shat_on, const unsigned long long* amax,
                         const int* bexp, double alpha, double* mu, const int* status,
-                        const double* alpha_d) {
+                        const double* alpha_d, const RelaxClamp* clamp) {
     const int64_t per_rhs = (int64_t)nz * M;
     const int nbr = mean_blocks(per_rhs);
-    hipLaunchKernelGGL(k_mean_parts, dim3(nbr, R), dim3(NT), 0, st, u, c, per_rhs, nbr, R, nz, mp, M, nsplit,
-                       split_stride, rowmean, shat, shat_on, amax, bexp, part, status);
+    hipLaunchKernelGGL(k_mean_parts, dim3(nbr + (clamp ? 1 : 0), R), dim3(NT), 0, st, u, c, per_rhs, nbr, R, nz, mp, M,
+                       nsplit, split_stride, rowmean, shat, shat_on, amax, bexp, part, status,
+                       clamp ? *clamp : RelaxClamp{});
     if (nbr <= MEAN_INLINE) return MeanIn{mu, part, nbr, 1.0 / ((double)nz * (M / 3))};
     hipLaunchKernelGGL(k_update_mean, dim3(R), dim3(NT), 0, st, part, nbr, nz, M / 3, alpha, alpha_d, mu, status);
     return MeanIn{mu, nullptr, 0, 0.0};
@@ -1307,127 +1403,27 @@ void launch_axpy(hipStream_t st, const double* w, double* u, int R, int nz, int 
 }
 
 // ----------------------------------------------------------------------------------
-// Relax (Algorithm 2) on raw residuals, per RHS.  Stage 1: block partials of
-// <f_k, f_{k+1} - f_k>, ||f_{k+1} - f_k||^2 and ||f_{k+1}||_inf.  Stage 2: one block per
-// RHS reduces them in fixed order and sets alpha_{k+1} (alpha = 1 before the third
-// iteration or without relaxation; alpha < 0 -> 1; zero denominator keeps alpha_k).
-// The iteration index k lives in device memory (kdev), read by the kernels and advanced
-// by the last one, so a step captured into a graph replays with the current k.
+// Output and end of a relaxation step (its other parts are work groups of the update's own
+// launches, see RelaxIn and RelaxClamp).
 // ----------------------------------------------------------------------------------
-__device__ inline int relax_on(const int* __restrict__ kdev, int relax) { return (relax && *kdev >= 2) ? 1 : 0; }
-#define RELAX_PARTS 64
-__global__ void __launch_bounds__(NT) k_relax_part(const double* __restrict__ fnew, double* fprev,
-                                                   double* __restrict__ part, int64_t per_rhs,
-                                                   const int* __restrict__ kdev, int relax) {
-    __shared__ double red[3 * NT];
-    const int use_prev = relax_on(kdev, relax);
-    const int r = blockIdx.y;
-    const double* a = fnew + (int64_t)r * per_rhs;
-    double* b = fprev + (int64_t)r * per_rhs;     // f_k read, then f_k+1 kept for the next step
-    double v[2] = {0, 0};
-    double mx[1] = {0};
-    for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < per_rhs;
-         e += (int64_t)NT * gridDim.x) {
-        const double x = a[e];
-        mx[0] = fmax(mx[0], fabs(x));
-        if (use_prev) {
-            const double y = b[e];
-            const double d = x - y;
-            v[0] += y * d;
-            v[1] += d * d;
-        }
-        b[e] = x;
-    }
-    block_sum<2>(v, red);
-    block_max<1>(mx, red);
-    if (threadIdx.x == 0) {
-        double* p = part + ((int64_t)r * gridDim.x + blockIdx.x) * 3;
-        p[0] = v[0];
-        p[1] = v[1];
-        p[2] = mx[0];
-    }
-}
-
-__global__ void __launch_bounds__(NT) k_relax_alpha(const double* __restrict__ part, int n_part,
-                                                    double* __restrict__ alpha_d,
-                                                    double* __restrict__ finf_d, const int* __restrict__ kdev,
-                                                    int relax, double alpha_min) {
-    __shared__ double red[2 * NT];
-    const int use_relax = relax_on(kdev, relax);
-    const int r = blockIdx.x;
-    double v[2] = {0, 0};
-    double mx[1] = {0};
-    for (int b = threadIdx.x; b < n_part; b += NT) {
-        v[0] += part[((int64_t)r * n_part + b) * 3 + 0];
-        v[1] += part[((int64_t)r * n_part + b) * 3 + 1];
-        mx[0] = fmax(mx[0], part[((int64_t)r * n_part + b) * 3 + 2]);
-    }
-    block_sum<2>(v, red);
-    block_max<1>(mx, red);
-    if (threadIdx.x == 0) {
-        finf_d[r] = mx[0];
-        double a = 1.0;
-        if (use_relax) {
-            const double prev = alpha_d[r];
-            a = prev;
-            if (v[1] > 0.0) a = -prev * v[0] / v[1];
-            if (a < 0.0) a = 1.0;
-            if (alpha_min > 0.0) a = fmax(a, alpha_min);   // Remark in Section 2.3.3
-        }
-        alpha_d[r] = a;
-    }
-}
-
-void launch_relax_alpha(hipStream_t st, const double* fnew, double* fprev, double* part,
-                        double* alpha_d, double* finf_d, int R, int64_t per_rhs, const int* kdev,
-                        int relax, double alpha_min) {
-    hipLaunchKernelGGL(k_relax_part, dim3(RELAX_PARTS, R), dim3(NT), 0, st, fnew, fprev, part,
-                       per_rhs, kdev, relax);
-    hipLaunchKernelGGL(k_relax_alpha, dim3(R), dim3(NT), 0, st, part, RELAX_PARTS, alpha_d, finf_d,
-                       kdev, relax, alpha_min);
-}
-
-// Step bound (the optional bound on the step in Algorithm 2) from the per-block maxima of |w|.
-__global__ void __launch_bounds__(NT) k_relax_clamp(const double* __restrict__ wmax_part,
-                                                    int n_part, double* __restrict__ alpha_d,
-                                                    double* __restrict__ stepinf_d, double du_max,
-                                                    const int* __restrict__ kdev, int relax) {
-    __shared__ double red[NT];
-    const int use_bound = relax_on(kdev, relax);
-    const int r = blockIdx.x;
-    double mx[1] = {0};
-    for (int b = threadIdx.x; b < n_part; b += NT)
-        mx[0] = fmax(mx[0], wmax_part[(int64_t)r * n_part + b]);
-    block_max<1>(mx, red);
-    if (threadIdx.x == 0) {
-        double a = alpha_d[r];
-        if (use_bound && du_max > 0.0 && a * mx[0] > du_max) a = du_max / mx[0];
-        alpha_d[r] = a;
-        stepinf_d[r] = a * mx[0];
-    }
-}
-
-void launch_relax_clamp(hipStream_t st, const double* wmax_part, int n_part, double* alpha_d,
-                        double* stepinf_d, int R, double du_max, const int* kdev, int relax) {
-    hipLaunchKernelGGL(k_relax_clamp, dim3(R), dim3(NT), 0, st, wmax_part, n_part, alpha_d,
-                       stepinf_d, du_max, kdev, relax);
-}
-
-__global__ void k_relax_out(const double* __restrict__ alpha_d, const double* __restrict__ finf_d,
-                            const double* __restrict__ stepinf_d, const double* __restrict__ mean_d,
-                            fbc_relax_out* __restrict__ out, int R, const int* __restrict__ kdev,
-                            double tol_f) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(1024) k_relax_out(const double* __restrict__ alpha_d,
+                                                    const double* __restrict__ finf_d,
+                                                    const double* __restrict__ stepinf_d,
+                                                    const double* __restrict__ mean_d,
+                                                    fbc_relax_out* __restrict__ out, int R, int* kdev, double tol_f) {
     const int k = *kdev;
-    if (r >= R) return;
-    fbc_relax_out o;
-    o.alpha = alpha_d[r];
-    o.f_inf = finf_d[r];
-    o.step_inf = stepinf_d[r];
-    for (int c = 0; c < 3; ++c) o.mean_removed[c] = mean_d[r * 3 + c];
-    o.converged = finf_d[r] < tol_f ? 1 : 0;
-    o.k = k;
-    out[r] = o;
+    for (int r = threadIdx.x; r < R; r += 1024) {
+        fbc_relax_out o;
+        o.alpha = alpha_d[r];
+        o.f_inf = finf_d[r];
+        o.step_inf = stepinf_d[r];
+        for (int c = 0; c < 3; ++c) o.mean_removed[c] = mean_d[r * 3 + c];
+        o.converged = finf_d[r] < tol_f ? 1 : 0;
+        o.k = k;
+        out[r] = o;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) *kdev = k + 1;
 }
 
 // kdev[0] <- v (v >= 0), or kdev[0] + 1 (v < 0): the iteration index of the relaxation.
@@ -1441,10 +1437,12 @@ void launch_relax_index(hipStream_t st, int* kdev, int v) {
 
 void launch_relax_finish(hipStream_t st, const double* alpha_d, const double* finf_d, const double* stepinf_d,
                          const double* mean_d, fbc_relax_out* out, int R, int* kdev, double tol_f) {
+    // one work group: the index is advanced after every reader of k in this step
     if (out)
-        hipLaunchKernelGGL(k_relax_out, dim3((R + 63) / 64), dim3(64), 0, st, alpha_d, finf_d,
-                           stepinf_d, mean_d, out, R, kdev, tol_f);
-    launch_relax_index(st, kdev, -1);     // after every reader of k in this step
+        hipLaunchKernelGGL(k_relax_out, dim3(1), dim3(1024), 0, st, alpha_d, finf_d, stepinf_d, mean_d, out, R, kdev,
+                           tol_f);
+    else
+        launch_relax_index(st, kdev, -1);
 }
 
 __global__ void k_fill(double* p, int64_t n, double v) {

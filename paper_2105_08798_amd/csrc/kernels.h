@@ -45,11 +45,27 @@ void launch_tab_absmax(hipStream_t st, const double2* tab, int T, int64_t n_off,
 // ---- apply (Section 2.3.2 update in line-mode form) ----
 // Per-layer sums sums[r][n0][6] (net force, absolute force), cell totals tot[r][3] with
 // the net-force check, and (shat != NULL) the line transform of the per-layer net force.
+// Relaxation: the step factors of this step from f_{k+1} and f_k (fprev, then f_{k+1} for the next
+// step; NULL: no relaxation), part [R][nz][3]; the step bound from the maxima of |w|.
+struct RelaxIn {
+    double *fprev, *part, *alpha, *finf;
+    const int* kdev;
+    int relax;
+    double alpha_min;
+};
+struct RelaxClamp {
+    const double* wmax_part;
+    int n_part;
+    double *alpha, *stepinf;
+    double du_max;
+    const int* kdev;
+    int relax;
+};
 // launch_forward: these (if `statistics`; bexp: also the operand scale of split FP16), then the
 // transforms of f into the product's B fragments.
 void launch_forward(hipStream_t st, int form, const double* f, double* sums, double* tot, double2* shat, int* shat_on,
                     bool statistics, double tol, int check, int project, void* bfrag, int R, int nz, int n_i, int kp,
-                    int ct, const double2* tw, int* bexp, int* status);
+                    int ct, const double2* tw, int* bexp, int* status, const RelaxIn& rx);
 // Reduced forms.  variant: one of gemm_variants(form, ctmax) kernel instantiations (bitwise the
 // same result); q != NULL: persistent work-queue kernel on these lists.
 void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int ctmax, const void* a,
@@ -105,16 +121,11 @@ MeanIn launch_update_mean(hipStream_t st, const double* u, const double* c, doub
                         int mp, int M, int nsplit, int64_t split_stride, const double2* rowmean,
                         const double2* shat, const int* shat_on, const unsigned long long* amax,
                         const int* bexp, double alpha, double* mu, const int* status,
-                        const double* alpha_d = nullptr);
+                        const double* alpha_d = nullptr, const RelaxClamp* clamp = nullptr);
 
 // ---- relax (Section 2.3.3, Algorithm 2); kdev: the iteration index on the device ----
-void launch_relax_alpha(hipStream_t st, const double* fnew, double* fprev, double* part,
-                        double* alpha_d, double* finf_d, int R, int64_t per_rhs, const int* kdev, int relax,
-                        double alpha_min);
-void launch_relax_clamp(hipStream_t st, const double* wmax_part, int n_part, double* alpha_d,
-                        double* stepinf_d, int R, double du_max, const int* kdev, int relax);
-// relaxation output and the index advance; the partials kernel (launch_relax_alpha) keeps
-// f_k+1 in fprev for the next step
+void launch_relax_clamp(hipStream_t st, const RelaxClamp& a, int R);
+// relaxation output and the index advance
 void launch_relax_finish(hipStream_t st, const double* alpha_d, const double* finf_d, const double* stepinf_d,
                          const double* mean_d, fbc_relax_out* out, int R, int* kdev, double tol_f);
 // kdev <- v (v >= 0) or kdev + 1 (v < 0)
