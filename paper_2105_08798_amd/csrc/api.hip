@@ -1008,7 +1008,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
             irfft_shape(p.nz, &tr, &pp);
             const int np_ir = (p.M + tr - 1) / tr;
             int np_up = 0;                   // the fused update's row groups (relaxation without a bound)
-            if (update_shape(p.nz, p.M, p.ctr, &tr, &pp)) np_up = (p.M + tr - 1) / tr;
+            if (update_shape(p.nz, &tr)) np_up = (p.M + tr - 1) / tr;
             c->wmax_off.push_back(wmax_n);
             c->sum_part_off.push_back(sp_n);
             c->rpart_off.push_back(rp_n);
@@ -1280,8 +1280,8 @@ static void enqueue_update(fbc_ctx* c, double* u, double alpha, bool mean_remova
         const int* so = comp ? c->shat_on + p.rhs0 : nullptr;
         const unsigned long long* am = f16 ? c->amax + c->amax_off[ci] : nullptr;
         const int* be = f16 ? c->bexp + p.rhs0 : nullptr;
-        int tr, pp;
-        if (!update_shape(p.nz, p.M, p.ctr, &tr, &pp)) {
+        int tr;
+        if (!update_shape(p.nz, &tr)) {
             // lines outside 4..1024 layers: inverse transform into w, then the tiled transpose-update,
             // which also removes the mean (known beforehand, as for the fused update)
             double* uc = u + p.u_off;

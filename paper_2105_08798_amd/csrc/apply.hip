@@ -894,8 +894,8 @@ __device__ inline void form_means(const MeanIn& mean, int r0, int n, double alph
 // Fused inverse transform and pad update (the update step of Algorithm 1):
 //   u[r][n0][row] <- (read_u ? u : 0) - alpha * w[r][row][n0] - mu[r][row % 3]
 // straight from the product output, without the w scratch.  A work group owns tr
-// consecutive rows (one contiguous run of u per layer) and pp RHS pairs of one column
-// tile, placed on the XCDs by xcd_unit: the 4/pp pair groups of a row block run on one
+// consecutive rows (one contiguous run of u per layer) and a RHS pair of one column
+// tile, placed on the XCDs by xcd_unit: the four pair groups of a row block run on one
 // XCD at about the same time and share the product records (128 bytes per row and mode)
 // through its L2.
 //  1. gather: the spectra in natural order (mode fastest across threads, so the LDS
@@ -907,13 +907,13 @@ __device__ inline void form_means(const MeanIn& mean, int r0, int n, double alph
 //     across threads (runs of tr values of u per layer).
 // mu (mean of the updated u, from k_update_mean or form_means) may be NULL (no mean removal).  alpha_d:
 // per-RHS step factors on the device in place of alpha (the relaxation step without its
-// bound); wmax_part (one RHS pair per group): per RHS and row group the largest |w|.
+// bound); wmax_part: per RHS and row group the largest |w|.
 // Skipped entirely when a data check has latched an error.  Needs Nz >= 4.
 // ----------------------------------------------------------------------------------
 template <int NSM, int NTH>
 __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__ c,
                                                      double* __restrict__ u, int R, int nz, int logn,
-                                                     int mp, int M, int tr, int pp, int n_rg,
+                                                     int mp, int M, int ltr, int n_rg,
                                                      int n_units, const double2* __restrict__ tw,
                                                      int nsplit, int64_t split_stride,
                                                      const double2* __restrict__ rowmean,
@@ -929,31 +929,26 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
     __shared__ double smu[6];
     if (status && *status) return;
     int tile, rg, pg;
-    if (!xcd_unit(n_units, n_rg, 4 / pp, tile, rg, pg)) return;
-    const int row0 = rg * tr, pair0 = pg * pp;
+    if (!xcd_unit(n_units, n_rg, 4, tile, rg, pg)) return;
+    const int tr = 1 << ltr, row0 = rg * tr;
+    const int ra = 8 * tile + 2 * pg, nra = min(2, R - ra);     // the pair, and how many of it there are
     const int ss = nz + 1;
     const int nm = (nz >> 1) + 1;
-    const int nseq = tr * pp;
-    // (pp = 1) the means of the pair, read after step 1's barrier
-    const int ra0 = 8 * tile + 2 * pair0, nra = min(2, R - ra0);
-    if (mean.nbr > 0) form_means(mean, ra0, nra, alpha, alpha_d, rg == 0, smu);
-    else if (mean.mu && (int)threadIdx.x < 3 * nra) smu[threadIdx.x] = mean.mu[3 * ra0 + threadIdx.x];
+    // the means of the pair, read after step 1's barrier
+    if (mean.nbr > 0) form_means(mean, ra, nra, alpha, alpha_d, rg == 0, smu);
+    else if (mean.mu && (int)threadIdx.x < 3 * nra) smu[threadIdx.x] = mean.mu[3 * ra + threadIdx.x];
     // 0. row-gauge compensation (pairs with per-layer net force only): the terms of every
     //    (row, mode) staged in the LDS slots of the mode and its mirror, the s^ of a mode
     //    loaded once per 4 rows and all loads of a thread issued before any is used
     //    (computed inside the gather, each term waited for its own loads after the
     //    records': 1.5 ms more per update of the long lines)
-    bool stage = false;                         // the same for the whole work group
-    for (int pj = 0; pj < pp; ++pj) stage = stage || comp_on(8 * tile + 2 * (pair0 + pj), R, rowmean, shat_on);
+    const bool stage = comp_on(ra, R, rowmean, shat_on);      // the same for the whole work group
     if (stage) {
         constexpr int CR = 4;
         const int nch = (tr + CR - 1) / CR;
-        const int n0 = nm * pp * nch;
+        const int n0 = nm * nch;
         for (int t = threadIdx.x; t < n0; t += NTH) {
-            const int mm = t % nm, rest = t / nm;
-            const int pj = rest % pp, ch = rest / pp;
-            const int ra = 8 * tile + 2 * (pair0 + pj);
-            if (!comp_on(ra, R, rowmean, shat_on)) continue;
+            const int mm = t % nm, ch = t / nm;
             double2 sa[3], sb[3], g[CR][3];
             comp_load_s(mm, nm, ra, R, shat, sa, sb);
 #pragma unroll
@@ -971,31 +966,31 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
                 if (trr >= tr || row >= M) continue;
                 double dar, dai, dbr, dbi;
                 comp_core(g[q], sa, sb, dar, dai, dbr, dbi);
-                double2* sq = lds + (pj * tr + trr) * ss;
+                double2* sq = lds + trr * ss;
                 sq[mm] = make_double2(dar, dbr);
                 if (mm > 0 && 2 * mm < nz) sq[nz - mm] = make_double2(dai, dbi);
             }
         }
         __syncthreads();
     }
-    // 1. gather
+    // 1. gather: modes 0 .. Nz/2 - 1 of each row, then the rows' modes Nz/2
     {
         constexpr int LU = NSM >= 8 ? 1 : 8 / NSM;
-        const int nload = nm * nseq;
+        const int lh = logn - 1, nmain = tr << lh, nload = nmain + tr;
+        const double* rec = c + ((int64_t)tile * mp + row0) * nm * 16 + 2 * pg;
         for (int t0 = threadIdx.x; t0 < nload; t0 += NTH * LU) {
             double2 v0[LU][NSM], v1[LU][NSM];
+            int mk[LU], rk[LU];
 #pragma unroll
             for (int k = 0; k < LU; ++k) {
                 const int t = t0 + k * NTH;
-                const int mm = t % nm, rest = t / nm;
-                const int pj = rest % pp, trr = rest / pp;
-                const int row = row0 + trr;
-                const int ja = 2 * (pair0 + pj);
-                const double* src = c + (((int64_t)tile * mp + row) * nm + mm) * 16 + ja;
+                mk[k] = t < nmain ? t & ((1 << lh) - 1) : 1 << lh;
+                rk[k] = t < nmain ? t >> lh : t - nmain;
+                const double* src = rec + (rk[k] * nm + mk[k]) * 16;
 #pragma unroll
                 for (int ks = 0; ks < NSM; ++ks) {
                     v0[k][ks] = v1[k][ks] = make_double2(0, 0);
-                    if (t < nload && row < M && ks < nsplit) {
+                    if (t < nload && row0 + rk[k] < M && ks < nsplit) {
                         v0[k][ks] = *(const double2*)(src + ks * split_stride);
                         v1[k][ks] = *(const double2*)(src + ks * split_stride + 8);
                     }
@@ -1003,12 +998,8 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
             }
 #pragma unroll
             for (int k = 0; k < LU; ++k) {
-                const int t = t0 + k * NTH;
-                if (t >= nload) break;
-                const int mm = t % nm, rest = t / nm;
-                const int pj = rest % pp, trr = rest / pp;
-                const int row = row0 + trr;
-                const int ja = 2 * (pair0 + pj);
+                if (t0 + k * NTH >= nload) break;
+                const int mm = mk[k];
                 double ar = v0[k][0].x, br = v0[k][0].y, ai = v1[k][0].x, bi = v1[k][0].y;
 #pragma unroll
                 for (int ks = 1; ks < NSM; ++ks) {     // K slices in fixed order (zeros past nsplit)
@@ -1020,11 +1011,10 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
                     }
                 }
                 double2 z = make_double2(0, 0), zc = make_double2(0, 0);
-                double2* sq = lds + (pj * tr + trr) * ss;
-                if (row < M) {
-                    const int ra = 8 * tile + ja;
+                double2* sq = lds + rk[k] * ss;
+                if (row0 + rk[k] < M) {
                     mode_scale(mm, ra, R, amax, bexp, ar, br, ai, bi);
-                    if (comp_on(ra, R, rowmean, shat_on)) {     // the terms staged in step 0
+                    if (stage) {                        // the terms staged in step 0
                         const double2 d0 = sq[mm];
                         const double2 d1 = (mm > 0 && 2 * mm < nz) ? sq[nz - mm] : make_double2(0, 0);
                         ar += d0.x;
@@ -1051,73 +1041,70 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
     //    3.4 ms; 256-thread groups, four per CU, load them after the transform)
     constexpr bool early = NTH >= 1024;
     const double scale = 1.0 / nz;
-    const int nq = nz >> 2;
-    const int nitem = nseq * nq;
+    const int nitem = tr * (nz >> 2);
+    // element (n0, row) of a RHS in 32 bits: the product records of 2^32 elements would take 256 GiB
+    double* ua = u + (int64_t)ra * nz * M + row0;
+    double* ub = ua + (int64_t)nz * M;
     constexpr int LV = 2;
     double oa[LV][4], ob[LV][4], ma[LV], mb[LV];
     auto load_old = [&](int t0) {
 #pragma unroll
         for (int k = 0; k < LV; ++k) {
             const int t = t0 + k * NTH;
-            const int trr = t % tr, rest = t / tr;
-            const int g = rest % nq, pj = rest / nq;
+            const int trr = t & (tr - 1), g = t >> ltr;
             const int row = row0 + trr;
-            const int ra = 8 * tile + 2 * (pair0 + pj);
             const bool live = t < nitem && row < M;
-            ma[k] = (mean.mu && live && ra < R) ? smu[row % 3] : 0.0;
-            mb[k] = (mean.mu && live && ra + 1 < R) ? smu[3 + row % 3] : 0.0;
+            ma[k] = (mean.mu && live) ? smu[row % 3] : 0.0;
+            mb[k] = (mean.mu && live) ? smu[3 + row % 3] : 0.0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 oa[k][e] = ob[k][e] = 0.0;
-                if (read_u && t < nitem && row < M) {
-                    const int n0 = (int)bitrev(4 * g + e, logn);
-                    if (ra < R) oa[k][e] = u[((int64_t)ra * nz + n0) * M + row];
-                    if (ra + 1 < R) ob[k][e] = u[((int64_t)(ra + 1) * nz + n0) * M + row];
+                if (read_u && live) {
+                    const unsigned at = bitrev(4 * g + e, logn) * (unsigned)M + (unsigned)trr;
+                    if (nra > 0) oa[k][e] = ua[at];
+                    if (nra > 1) ob[k][e] = ub[at];
                 }
             }
         }
     };
     if (early) load_old(threadIdx.x);
-    lds_fft_dif_s<true>(lds, nseq, ss, logn, 2, tw);
+    lds_fft_dif_s<true>(lds, ltr, ss, logn, 2, tw);
     // 3. last two stages in registers, then the update; with per-RHS step factors alpha_d
     //    (one RHS pair per group then) the group's largest |w| per RHS goes to wmax_part
     const double2 w0 = twid<true>(tw, 0), w1 = twid<true>(tw, nz >> 2);
     double mxw[2] = {0.0, 0.0};
+    const double aa = (alpha_d && nra > 0) ? alpha_d[ra] : alpha;
+    const double ab = (alpha_d && nra > 1) ? alpha_d[ra + 1] : alpha;
     for (int t0 = threadIdx.x; t0 < nitem; t0 += NTH * LV) {
         if (!early || t0 != (int)threadIdx.x) load_old(t0);
 #pragma unroll
         for (int k = 0; k < LV; ++k) {
             const int t = t0 + k * NTH;
             if (t >= nitem) break;
-            const int trr = t % tr, rest = t / tr;
-            const int g = rest % nq, pj = rest / nq;
-            const int row = row0 + trr;
-            if (row >= M) continue;
-            const int ra = 8 * tile + 2 * (pair0 + pj);
-            const double2* sq = lds + (pj * tr + trr) * ss + 4 * g;
+            const int trr = t & (tr - 1), g = t >> ltr;
+            if (row0 + trr >= M) continue;
+            const double2* sq = lds + trr * ss + 4 * g;
             double2 x0 = sq[0], x1 = sq[1], x2 = sq[2], x3 = sq[3];
             dif(x0, x2, w0);
             dif(x1, x3, w1);
             dif(x0, x1, w0);
             dif(x2, x3, w0);
             const double2 xv[4] = {x0, x1, x2, x3};
-            const double aa = (alpha_d && ra < R) ? alpha_d[ra] : alpha;
-            const double ab = (alpha_d && ra + 1 < R) ? alpha_d[ra + 1] : alpha;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int n0 = (int)bitrev(4 * g + e, logn);
+                const unsigned at = bitrev(4 * g + e, logn) * (unsigned)M + (unsigned)trr;
                 const double wa = xv[e].x * scale, wb = xv[e].y * scale;
                 if (wmax_part) {
                     mxw[0] = fmax(mxw[0], fabs(wa));
                     mxw[1] = fmax(mxw[1], fabs(wb));
                 }
-                if (ra < R) {
+                if (nra > 0) {
                     const double x = oa[k][e] - aa * wa;
-                    u[((int64_t)ra * nz + n0) * M + row] = mean.mu ? x - ma[k] : x;
+                    ua[at] = mean.mu ? x - ma[k] : x;
                 }
-                if (ra + 1 < R) {
+                if (nra > 1) {
                     const double x = ob[k][e] - ab * wb;
-                    u[((int64_t)(ra + 1) * nz + n0) * M + row] = mean.mu ? x - mb[k] : x;
+                    ub[at] = mean.mu ? x - mb[k] : x;
                 }
             }
         }
@@ -1125,9 +1112,8 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
     if (wmax_part) {
         __syncthreads();                     // the transform buffer is free again
         block_max<2, NTH>(mxw, (double*)lds);
-        const int ra = 8 * tile + 2 * pair0;
-        if (threadIdx.x == 0 && ra < R) wmax_part[(int64_t)ra * n_rg + rg] = mxw[0];
-        if (threadIdx.x == 0 && ra + 1 < R) wmax_part[(int64_t)(ra + 1) * n_rg + rg] = mxw[1];
+        if (threadIdx.x == 0 && nra > 0) wmax_part[(int64_t)ra * n_rg + rg] = mxw[0];
+        if (threadIdx.x == 0 && nra > 1) wmax_part[(int64_t)(ra + 1) * n_rg + rg] = mxw[1];
     }
 }
 
@@ -1144,14 +1130,9 @@ __global__ void __launch_bounds__(NTH) k_irfft_update(const double* __restrict__
 // group's loads fill its threads (8 layers, 96 / 192 columns, 1 RHS: 6.7 us, the inverse
 // transform into w and the transpose 13.4 + 4.0).  Returns false outside 4 <= Nz <= 1024: the
 // update then goes through the w scratch and the tiled transpose.
-static int update_groups(int tr, int pp, int M, int ct_grid) {
-    return xcd_groups(ct_grid * ((M + tr - 1) / tr), 4 / pp);
-}
+static int update_groups(int tr, int M, int ct_grid) { return xcd_groups(ct_grid * ((M + tr - 1) / tr), 4); }
 
-bool update_shape(int nz, int M, int ct_grid, int* tr, int* pp) {
-    (void)M;
-    (void)ct_grid;
-    *pp = 1;
+bool update_shape(int nz, int* tr) {
     *tr = nz >= 64 ? 8 : nz >= 32 ? 16 : nz >= 16 ? 32 : 64;
     return nz >= 4 && nz <= 1024;
 }
@@ -1164,13 +1145,13 @@ void launch_irfft_update(hipStream_t st, const double* c, double* u, int R, int 
                          double* wmax_part) {
     int logn = 0;
     while ((1 << logn) < nz) ++logn;
-    int tr, pp;
-    update_shape(nz, M, ct_grid, &tr, &pp);
-    if (pp != 1) wmax_part = nullptr;        // the group's maxima are per RHS pair (never taken)
+    int tr, ltr = 0;
+    update_shape(nz, &tr);
+    while ((1 << ltr) < tr) ++ltr;
     const int n_rg = (M + tr - 1) / tr;
     const int n_units = ct_grid * n_rg;
-    const int nblk = update_groups(tr, pp, M, ct_grid);
-    size_t lds = (size_t)tr * pp * (nz + 1) * sizeof(double2);
+    const int nblk = update_groups(tr, M, ct_grid);
+    size_t lds = (size_t)tr * (nz + 1) * sizeof(double2);
     // the maxima of |w| are reduced in the same LDS: 2 values per thread
     const size_t lds_max = 2 * (size_t)(nz > 256 ? 1024 : NT) * sizeof(double);
     if (wmax_part && lds < lds_max) lds = lds_max;
@@ -1179,11 +1160,11 @@ void launch_irfft_update(hipStream_t st, const double* c, double* u, int R, int 
 #define UPD_CASE(NS) do {                                                                              \
     if (nz > 256) {                                                                                   \
         hipLaunchKernelGGL((k_irfft_update<NS, 1024>), dim3(nblk), dim3(1024), lds, st, c, u, R, nz, logn, mp, \
-                           M, tr, pp, n_rg, n_units, tw, nsplit, split_stride, rowmean, shat, shat_on, amax, \
+                           M, ltr, n_rg, n_units, tw, nsplit, split_stride, rowmean, shat, shat_on, amax,   \
                            bexp, alpha, alpha_d, mean, read_u, wmax_part, status);                    \
     } else {                                                                                          \
         hipLaunchKernelGGL((k_irfft_update<NS, NT>), dim3(nblk), dim3(NT), lds, st, c, u, R, nz, logn, mp, M, \
-                           tr, pp, n_rg, n_units, tw, nsplit, split_stride, rowmean, shat, shat_on, amax, \
+                           ltr, n_rg, n_units, tw, nsplit, split_stride, rowmean, shat, shat_on, amax, \
                            bexp, alpha, alpha_d, mean, read_u, wmax_part, status);                    \
     }                                                                                                 \
 } while (0)

@@ -106,7 +106,8 @@ __device__ inline void lds_fft_s(double2* s, int nb, int ss, int logn, const dou
 // 2^stop are left to the caller, who runs them in registers on four consecutive values).
 // A butterfly (x, y) -> (x + y, (x - y) w), w = tw[j n / (2 half)] (conjugate for the
 // inverse).  With an odd stage count the first stage runs alone, then pairs (2h, h) on
-// quartets, neighbouring threads on neighbouring sequences.
+// quartets, neighbouring threads on neighbouring sequences.  2^lnb sequences: a division by their
+// number costs as much as a butterfly.
 __device__ inline void dif(double2& x, double2& y, double2 w) {
     const double2 d = make_double2(x.x - y.x, x.y - y.y);
     x = make_double2(x.x + y.x, x.y + y.y);
@@ -114,14 +115,14 @@ __device__ inline void dif(double2& x, double2& y, double2 w) {
 }
 
 template <bool INV>
-__device__ inline void lds_fft_dif_s(double2* s, int nb, int ss, int logn, int stop,
+__device__ inline void lds_fft_dif_s(double2* s, int lnb, int ss, int logn, int stop,
                                      const double2* __restrict__ tw) {
-    const int n = 1 << logn;
+    const int n = 1 << logn, nb = 1 << lnb;
     int lh = logn - 1;                            // log2 of the current half length
     if ((logn - stop) & 1) {
         const int half = 1 << lh;                 // = n / 2, twiddle index j
         for (int t = threadIdx.x; t < nb * half; t += blockDim.x) {
-            const int seq = t % nb, j = t / nb;
+            const int seq = t & (nb - 1), j = t >> lnb;
             const int a = seq * ss + j;
             double2 x = s[a], y = s[a + half];
             dif(x, y, twid<INV>(tw, j));
@@ -136,7 +137,7 @@ __device__ inline void lds_fft_dif_s(double2* s, int nb, int ss, int logn, int s
         const int nq = n >> 2;
         const int sa = logn - 1 - lh;             // twiddle stride of the 2h stage: n / (4h)
         for (int t = threadIdx.x; t < nb * nq; t += blockDim.x) {
-            const int seq = t % nb, qd = t / nb;
+            const int seq = t & (nb - 1), qd = t >> lnb;
             const int j = qd & (h - 1), grp = qd >> (lh - 1);
             const int a = seq * ss + (grp << (lh + 1)) + j;
             double2 x0 = s[a], x1 = s[a + h], x2 = s[a + 2 * h], x3 = s[a + 3 * h];

@@ -109,7 +109,7 @@ void launch_axpy(hipStream_t st, const double* w, double* u, int R, int nz, int 
 // a step bound), and the mean it removes; update_shape is false where the line is too long
 // for the fused kernel.  alpha_d: per-RHS step factors on the device (else alpha);
 // wmax_part: per RHS and row group (ceil(M / tr) of them) the largest |w|, or NULL.
-bool update_shape(int nz, int M, int ct_grid, int* tr, int* pp);
+bool update_shape(int nz, int* tr);
 void launch_irfft_update(hipStream_t st, const double* c, double* u, int R, int nz, int mp, int M,
                          int ct_grid, const double2* tw, int nsplit, int64_t split_stride,
                          const double2* rowmean, const double2* shat, const int* shat_on,
