@@ -332,7 +332,7 @@ template <int FORM, int NTH>
 __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
                                                   const double* __restrict__ tot, int project,
                                                   void* __restrict__ bfrag, int nz, int logn,
-                                                  int n_i, int kp, int ct, int tc,
+                                                  int n_i, int kp, int ct, int ltc,
                                                   const double2* __restrict__ tw, double inv_cnt,
                                                   const int* __restrict__ bexp, int pairs, NfTotal nf, int ny, int totals,
                                                   RelaxIn rx) {
@@ -348,7 +348,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
     const int r = blockIdx.x;
     const int esc = (FORM == FBC_FORM_SPLIT_FP16) ? bexp[r] : 0;   // power-of-two operand scale
     const int K = 3 * n_i;
-    const int nseq = tc >> 1;
+    const int tc = 1 << ltc;
     const int ss = nz + 1;                  // sequence stride (complex values)
     const int nchunk = (K + tc - 1) / tc;
     double* ldsd = (double*)lds;
@@ -365,7 +365,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
 #pragma unroll
             for (int q = 0; q < LU; ++q) {
                 const int t = t0 + q * NTH;
-                const int n0 = t / hp, k = k0 + 2 * (t - n0 * hp);
+                const int n0 = t >> (ltc - 1), k = k0 + 2 * (t & (hp - 1));
                 v[q] = (t < nz * hp && k < K)
                            ? __builtin_nontemporal_load((const dv2_t*)(f + ((int64_t)r * nz + n0) * K + k))
                            : dv2_t{0.0, 0.0};
@@ -374,7 +374,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
             for (int q = 0; q < LU; ++q) {
                 const int t = t0 + q * NTH;
                 if (t >= nz * hp) break;
-                const int n0 = t / hp, p = t - n0 * hp, k = k0 + 2 * p;
+                const int n0 = t >> (ltc - 1), p = t & (hp - 1), k = k0 + 2 * p;
                 double x0 = v[q].x, x1 = v[q].y;
                 if (k < K) {
                     if (project) {                  // mean over the cell's atoms
@@ -395,14 +395,14 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
 #pragma unroll
         for (int q = 0; q < LU; ++q) {
             const int t = t0 + q * NTH;
-            const int n0 = t / tc, c = t - n0 * tc, k = k0 + c;
+            const int n0 = t >> ltc, c = t & (tc - 1), k = k0 + c;
             v[q] = (t < nz * tc && k < K) ? __builtin_nontemporal_load(&f[((int64_t)r * nz + n0) * K + k]) : 0.0;
         }
 #pragma unroll
         for (int q = 0; q < LU; ++q) {
             const int t = t0 + q * NTH;
             if (t >= nz * tc) break;
-            const int n0 = t / tc, c = t - n0 * tc, k = k0 + c;
+            const int n0 = t >> ltc, c = t & (tc - 1), k = k0 + c;
             double x = v[q];
             if (k < K) {
                 if (project) x -= tot[r * 3 + (k % 3)] * inv_cnt;     // mean over the cell's atoms
@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
         }
     }
     __syncthreads();
-    lds_fft_s<false>(lds, nseq, ss, logn, tw);
+    lds_fft_s<false>(lds, ltc - 1, ss, logn, tw);
     const int nm = (nz >> 1) + 1;
     // per mode: B elements of one mode occupy 16*ct*kp values (x2 for the bf16 split)
     const int64_t mode_elems =
@@ -423,7 +423,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
         // offset-table products: one 16-byte pair per entry, four interface columns adjacent
         const int nch = kp / 96;
         for (int t = threadIdx.x; t < nm * tc; t += NTH) {
-            const int m = t / tc, c = t - m * tc, k = k0 + c;
+            const int m = t >> ltc, c = t & (tc - 1), k = k0 + c;
             if (k >= K) continue;
             const double2 z = lds[(c >> 1) * ss + m];
             const double2 zn = lds[(c >> 1) * ss + ((nz - m) & (nz - 1))];
@@ -445,10 +445,11 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
     }
     // G consecutive complex columns per thread, written as whole 16-byte units
     constexpr int G = (FORM == FBC_FORM_FP32) ? 8 : 4;
-    if (tc % G == 0) {
-        const int ng = tc / G;
+    constexpr int LG = (FORM == FBC_FORM_FP32) ? 3 : 2;
+    if (tc >= G) {
+        const int lng = ltc - LG, ng = 1 << lng;
         for (int t = threadIdx.x; t < nm * ng; t += NTH) {
-            const int m = t / ng, g = t - m * ng;
+            const int m = t >> lng, g = t & (ng - 1);
             const int kb = k0 + g * G;
             if (kb >= K) continue;
             double vre[2 * G], vim[2 * G];
@@ -485,7 +486,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
         continue;
     }
     for (int t = threadIdx.x; t < nm * tc; t += NTH) {
-        const int m = t / tc, c = t - m * tc, k = k0 + c;
+        const int m = t >> ltc, c = t & (tc - 1), k = k0 + c;
         if (k >= K) continue;
         const double2 z = lds[(c >> 1) * ss + m];
         const double2 zn = lds[(c >> 1) * ss + ((nz - m) & (nz - 1))];
@@ -538,9 +539,9 @@ void launch_forward(hipStream_t st, int form, const double* f, double* sums, dou
         tc = 16;
         while (tc > 2 && (size_t)(nz + 1) * tc * sizeof(double) > 160 * 1024) tc >>= 1;   // the CU's LDS
     }
-    const int kk = (K + 1) & ~1;
-    if (tc > kk) tc = kk;
-    tc &= ~1;
+    while (tc > 2 && tc > ((K + 1) & ~1)) tc >>= 1;
+    int ltc = 1;
+    while ((1 << ltc) < tc) ++ltc;
     const int ny = std::min((K + tc - 1) / tc, 65533);
     dim3 grid(R, ny);
     const int pairs = ((K & 1) == 0 && ((uintptr_t)f & 15) == 0) ? 1 : 0;
@@ -569,10 +570,10 @@ void launch_forward(hipStream_t st, int form, const double* f, double* sums, dou
     do {                                                                                                    \
         if (wide) {                                                                                         \
             hipLaunchKernelGGL((k_line_rfft<FM, 1024>), grid, dim3(1024), lds, st, f, tot, project, bfrag, nz, logn, \
-                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs, nf, ny, totals, rx);              \
+                               n_i, kp, ct, ltc, tw, inv_cnt, bexp, pairs, nf, ny, totals, rx);              \
         } else {                                                                                            \
             hipLaunchKernelGGL((k_line_rfft<FM, NT>), grid, dim3(NT), lds, st, f, tot, project, bfrag, nz, logn, \
-                               n_i, kp, ct, tc, tw, inv_cnt, bexp, pairs, nf, ny, totals, rx);              \
+                               n_i, kp, ct, ltc, tw, inv_cnt, bexp, pairs, nf, ny, totals, rx);              \
         }                                                                                                   \
     } while (0)
     switch (form) {
@@ -756,7 +757,7 @@ __device__ inline void gather_inverse(double2* lds, const double* __restrict__ c
         }
     }
     __syncthreads();
-    lds_fft_s<true>(lds, tr * pp, ss, logn, tw);
+    lds_fft_s<true>(lds, 31 - __clz(tr * pp), ss, logn, tw);      // (powers of two)
 }
 
 // Work unit of a work group of the inverse transforms: units (row group rg of column tile

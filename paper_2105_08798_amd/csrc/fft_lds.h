@@ -47,7 +47,8 @@ __device__ inline void lds_fft(double2* s, int nb, int logn, const double2* __re
 // through registers, so every value makes half as many LDS round trips and the block
 // half as many barriers.  The butterflies, their twiddles and their order are those of
 // the radix-2 transform above.  Neighbouring threads work on neighbouring sequences: with
-// ss = n + 1 (odd) their accesses fall in distinct LDS banks at every stage.
+// ss = n + 1 (odd) their accesses fall in distinct LDS banks at every stage.  2^lnb sequences: a
+// division by their number would cost as much as a butterfly.
 __device__ inline void bfly(double2& x, double2& y, double2 w) {
     const double2 t = cmul(y, w);
     y = make_double2(x.x - t.x, x.y - t.y);
@@ -62,13 +63,13 @@ __device__ inline double2 twid(const double2* __restrict__ tw, int i) {
 }
 
 template <bool INV>
-__device__ inline void lds_fft_s(double2* s, int nb, int ss, int logn, const double2* __restrict__ tw) {
-    const int n = 1 << logn;
+__device__ inline void lds_fft_s(double2* s, int lnb, int ss, int logn, const double2* __restrict__ tw) {
+    const int n = 1 << logn, nb = 1 << lnb;
     int lh = 0;
     if (logn & 1) {                              // odd length exponent: one single stage first
         const int hn = n >> 1;
         for (int t = threadIdx.x; t < nb * hn; t += blockDim.x) {
-            const int seq = t % nb, bf = t / nb;
+            const int seq = t & (nb - 1), bf = t >> lnb;
             const int a = seq * ss + 2 * bf;
             double2 x = s[a], y = s[a + 1];
             bfly(x, y, twid<INV>(tw, 0));
@@ -83,7 +84,7 @@ __device__ inline void lds_fft_s(double2* s, int nb, int ss, int logn, const dou
         const int nq = n >> 2;                   // quartets per sequence
         const int t1 = logn - 1 - lh, t2 = logn - 2 - lh;
         for (int t = threadIdx.x; t < nb * nq; t += blockDim.x) {
-            const int seq = t % nb, qd = t / nb;
+            const int seq = t & (nb - 1), qd = t >> lnb;
             const int j = qd & (h - 1), grp = qd >> lh;
             const int a = seq * ss + (grp << (lh + 2)) + j;
             double2 x0 = s[a], x1 = s[a + h], x2 = s[a + 2 * h], x3 = s[a + 3 * h];
@@ -106,8 +107,7 @@ __device__ inline void lds_fft_s(double2* s, int nb, int ss, int logn, const dou
 // 2^stop are left to the caller, who runs them in registers on four consecutive values).
 // A butterfly (x, y) -> (x + y, (x - y) w), w = tw[j n / (2 half)] (conjugate for the
 // inverse).  With an odd stage count the first stage runs alone, then pairs (2h, h) on
-// quartets, neighbouring threads on neighbouring sequences.  2^lnb sequences: a division by their
-// number costs as much as a butterfly.
+// quartets, neighbouring threads on neighbouring sequences.
 __device__ inline void dif(double2& x, double2& y, double2 w) {
     const double2 d = make_double2(x.x - y.x, x.y - y.y);
     x = make_double2(x.x + y.x, x.y + y.y);
