@@ -674,15 +674,22 @@ struct Unit {
     int64_t cost;
 };
 
-static void unit_jobs(const fbc_ctx* c, const Unit& u, int nsplit, std::vector<GemmJob>& out) {
+// pairs: the jobs of a row tile (contexts of eight column tiles: two) next to each other.
+static void unit_jobs(const fbc_ctx* c, const Unit& u, int nsplit, bool pairs, std::vector<GemmJob>& out) {
     const int form = c->opt.form;
     const CellPlan& p = c->cells[u.cell];
     const bool dt = is_table_form(form);
     const int tile_rows = dt ? 3 * TAB_COLS : gemm_tile_rows(form, c->ctmax);
     const int tiles = p.mp / tile_rows;
     const int unit_k = dt ? TAB_COLS : 64;
-    for (int ks = 0; ks < nsplit; ++ks)
-        for (int tl = 0; tl < tiles; ++tl) {
+    // In the persistent lists the two jobs of a row tile, which read the same blocks, are taken by
+    // groups of one XCD one after the other (256 layers, 64 RHS: 3.56 ms, apart 4.05).  Elsewhere jobs
+    // are dealt to the XCDs in turn, and pairs of different length would give half of the XCDs all
+    // the long ones (64 layers, 700 / 1500 columns, 48 RHS in FP32: 0.61 ms, apart 0.51).
+    const int step = dt ? p.ctr : gemm_job_tiles(c->ctmax);
+    for (int ca = 0; ca < (pairs ? 1 : p.ctr); ca += step)
+        for (int ks = 0; ks < nsplit; ++ks)
+            for (int tl = 0; tl < tiles; ++tl) {
             // the K slice ks of this tile's window (cyclic; empty slices write zeros)
             const int ws = p.win_start[(size_t)u.m * p.n_tiles + tl];
             const int wl = p.win_len[(size_t)u.m * p.n_tiles + tl];
@@ -722,7 +729,7 @@ static void unit_jobs(const fbc_ctx* c, const Unit& u, int nsplit, std::vector<G
                 GemmJob h = j;
                 h.rb0 += r0 / 16;
                 if (!h.gather) h.a_off += r0 / 16 * blk;
-                for (int c0 = 0; c0 < p.ctr; c0 += gemm_job_tiles(c->ctmax)) {     // (tiles past ctr hold no RHS)
+                for (int c0 = ca; c0 < (pairs ? p.ctr : ca + 1); c0 += step) {      // (tiles past ctr hold no RHS)
                     h.c0 = c0;
                     out.push_back(h);
                 }
@@ -750,12 +757,12 @@ static std::vector<GemmJob> build_jobs(const fbc_ctx* c, int nsplit, int order, 
     std::vector<GemmJob> out;
     if (order == 1 || (order == 3 && c->opt.form == FBC_FORM_SURROGATE)) {
         std::stable_sort(units.begin(), units.end(), [](const Unit& a, const Unit& b) { return a.t < b.t; });
-        for (const Unit& u : units) unit_jobs(c, u, nsplit, out);
+        for (const Unit& u : units) unit_jobs(c, u, nsplit, order >= 3, out);
         return out;
     }
     std::stable_sort(units.begin(), units.end(), [](const Unit& a, const Unit& b) { return a.cost > b.cost; });
     if (order == 2 || order == 3) {
-        for (const Unit& u : units) unit_jobs(c, u, nsplit, out);
+        for (const Unit& u : units) unit_jobs(c, u, nsplit, order >= 3, out);
         if (order == 3)
             std::stable_sort(out.begin(), out.end(), [](const GemmJob& a, const GemmJob& b) {
                 return (a.k1 - a.k0) > (b.k1 - b.k0);
@@ -767,7 +774,7 @@ static std::vector<GemmJob> build_jobs(const fbc_ctx* c, int nsplit, int order, 
     for (const Unit& u : units) {
         const int x = (int)(std::min_element(load.begin(), load.end()) - load.begin());
         const size_t before = per_xcd[x].size();
-        unit_jobs(c, u, nsplit, per_xcd[x]);
+        unit_jobs(c, u, nsplit, order >= 3, per_xcd[x]);
         load[x] += (int64_t)(per_xcd[x].size() - before) * u.cost / std::max<int64_t>(1, nsplit);
     }
     if (order == 4) {            // the XCD lists back to back
@@ -963,14 +970,23 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         c->nsplit = std::max(1, std::min(ks, 8));
         c->vslices = c->nsplit;
         if (!is_table_form(form)) {
-            // jobs of 128 rows are many; every slice costs the inverse transform a read and the pipeline
-            // a fill.  Two slices up to 3000 jobs (call, 1 / 2 / 4 slices: 627 jobs 110, 104, 107 us;
-            // 1560 jobs 256, 238, 296; 2720 jobs 210, 202, -; 3120 jobs 674, 732, 925), four where two
-            // would leave half of the CUs idle.  FP32 sums still end where the slices counted above
-            // would (GemmJob::vs), so their number must divide those.
-            const int64_t jobs1 = tiles_total * (gemm_tile_rows(form, c->ctmax) / JOB_ROWS);
-            int r = jobs1 >= 3000 ? 1 : jobs1 >= 128 ? 2 : 4;
-            while (c->vslices % r) r /= 2;
+            // jobs of 128 rows are many; every slice costs the inverse transform a read and the
+            // pipeline a fill (some six chunks of 64 K').  As many slices (a divisor: FP32 sums still
+            // end where the slices counted above would, GemmJob::vs) as fill the chip's groups 5/4
+            // times, with long jobs of one or two column tiles twice; 14 chunks a job or more, four
+            // where the jobs are fewer than half of the CUs.
+            // Whole call, 1 / 2 / 4 slices: 300 columns, 10 RHS, 2064 jobs 270, 293, 385 us; 240
+            // columns, 18 RHS, 1419 jobs 339, 370, 458; 500 columns, 12 RHS, 1560 jobs 256, 238, 296;
+            // 777 columns, 13 RHS, 1122 jobs 209, 193, 222; 1213 columns, 28 RHS, 280 jobs 315, 192, 156
+            const int64_t cols = (c->ctmax + gemm_job_tiles(c->ctmax) - 1) / gemm_job_tiles(c->ctmax);
+            const int64_t jobs1 = tiles_total * cols * (gemm_tile_rows(form, c->ctmax) / JOB_ROWS);
+            int chunks = 1;
+            for (const auto& p : c->cells) chunks = std::max(chunks, p.kp / 64);
+            const int64_t slots = 256 * gemm_groups_per_cu(form, c->ctmax);
+            const int64_t enough = c->ctmax <= 2 && chunks >= 40 ? 2 * slots : slots + slots / 4;
+            int r = 1;
+            while (r < 4 && jobs1 * r < enough && c->vslices % (2 * r) == 0 && chunks / (2 * r) >= (jobs1 * r < 128 ? 4 : 14))
+                r *= 2;
             c->nsplit = r;
         }
         c->nsplit_def = c->nsplit;
@@ -1158,14 +1174,14 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     if (form == FBC_FORM_SURROGATE) c->nsplit = 1;     // slices are generated per mode chunk
     // default lists: longest unit first (offset table: 0.89 ms, mode-major 0.99, persistent 0.94 at
     // 128 layers, 1024 / 2048 columns, 8 RHS; eight uneven cells 3.74 against 3.95 and 3.77.  Reduced
-    // forms: 5.5 ms, XCD-grouped 5.7, mode-major 5.7, persistent 5.6 at 1024 layers, 2048 / 4096
-    // columns, 16 RHS); per-XCD lists for long split lists of four or eight column tiles, whose f^
-    // fragments then stay in one L2 (3.80 ms against 3.96 at 256 layers, 2048 / 4096 columns, 64 RHS,
-    // 0.83 against 0.86 at 12480 jobs; from 3000 jobs down the queue costs as much as it saves);
+    // forms: 5.3 ms, XCD-grouped 5.3, mode-major 5.4, persistent 6.7 at 1024 layers, 2048 / 4096
+    // columns, 16 RHS); per-XCD lists for long lists of five to eight column tiles, whose paired jobs
+    // then share blocks and f^ fragments in one L2 (256 layers, 2048 / 4096 columns, 64 RHS 3.56 ms,
+    // longest first 3.86; 128 layers, 40 RHS 0.73, 0.79; 646 jobs at 60 RHS 156 us, 146);
     // mode-major chunks consumed by the persistent kernel for the surrogate
     {
         const int64_t njobs = (int64_t)build_jobs(c, c->nsplit, 2).size();
-        const int order = form == FBC_FORM_SURROGATE ? 3 : is_split16(form) && c->ctmax > 2 && njobs >= 6000 ? 4 : 2;
+        const int order = form == FBC_FORM_SURROGATE ? 3 : !is_table_form(form) && c->ctmax > 4 && njobs >= 2048 ? 4 : 2;
         if ((s = upload_jobs(c, c->nsplit, order, st)) != FBC_OK) goto fail_out;
     }
     if ((s = dev_alloc(c, (void**)&c->fprev, c->f_elems * 8)) != FBC_OK) goto fail_out;

@@ -700,30 +700,35 @@ __device__ inline void mode_value(double2 v0, double2 v1, const double* __restri
     mode_adjust(mm, row, M, nm, ra, R, rowmean, shat, shat_on, amax, bexp, ar, br, ai, bi);
 }
 
-// Gathers the spectra of tr rows x pp RHS pairs of one column tile into LDS (bit-reversed,
+// Gathers the spectra of tr = 2^ltr rows x pp = 2^lpp RHS pairs of one column tile into LDS (bit-reversed,
 // sequence s = pj * tr + trr at s * ss) and inverse-transforms them.  Each (mode, row,
 // pair) of the product output is read once, pair fastest, then mode, then row: the modes
 // of a row are adjacent in the output, so a wave reads one contiguous run; the mirrored
 // half of the spectrum (m > Nz/2) is written from the same values.  The first K slice's
 // loads are issued LU at a time before any is used.
 __device__ inline void gather_inverse(double2* lds, const double* __restrict__ c, int tile, int row0,
-                                      int pair0, int tr, int pp, int ss, int R, int nz, int logn,
+                                      int pair0, int ltr, int lpp, int ss, int R, int nz, int logn,
                                       int mp, int M, const double2* __restrict__ tw, int nsplit,
                                       int64_t split_stride, const double2* __restrict__ rowmean,
                                       const double2* __restrict__ shat, const int* __restrict__ shat_on,
                                       const unsigned long long* __restrict__ amax,
                                       const int* __restrict__ bexp) {
-    const int nm = (nz >> 1) + 1;
+    const int nm = (nz >> 1) + 1, tr = 1 << ltr, pp = 1 << lpp;
     constexpr int LU = 4;
-    const int nload = nm * tr * pp;
+    const int nmain = tr * pp * (nm - 1), nload = nmain + tr * pp;     // the modes Nz/2 last
+    auto split = [&](int t, int& pj, int& mm, int& trr) {
+        pj = t & (pp - 1);                       // (nmain is a multiple of pp)
+        const int rest = t >> lpp;
+        mm = t < nmain ? rest & (nm - 2) : nm - 1;
+        trr = t < nmain ? rest >> (logn - 1) : (t - nmain) >> lpp;
+    };
     for (int t0 = threadIdx.x; t0 < nload; t0 += NT * LU) {
         double2 pv0[LU], pv1[LU];
 #pragma unroll
         for (int q = 0; q < LU; ++q) {
             const int t = t0 + q * NT;
-            const int pj = t % pp;
-            const int rest = t / pp;
-            const int mm = rest % nm, trr = rest / nm;
+            int pj, mm, trr;
+            split(t, pj, mm, trr);
             const int row = row0 + trr;
             const int ja = 2 * (pair0 + pj);
             pv0[q] = pv1[q] = make_double2(0, 0);
@@ -737,9 +742,8 @@ __device__ inline void gather_inverse(double2* lds, const double* __restrict__ c
         for (int q = 0; q < LU; ++q) {
             const int t = t0 + q * NT;
             if (t >= nload) break;
-            const int pj = t % pp;
-            const int rest = t / pp;
-            const int mm = rest % nm, trr = rest / nm;
+            int pj, mm, trr;
+            split(t, pj, mm, trr);
             const int s = pj * tr + trr;
             const int row = row0 + trr;
             const int ja = 2 * (pair0 + pj);
@@ -757,7 +761,7 @@ __device__ inline void gather_inverse(double2* lds, const double* __restrict__ c
         }
     }
     __syncthreads();
-    lds_fft_s<true>(lds, 31 - __clz(tr * pp), ss, logn, tw);      // (powers of two)
+    lds_fft_s<true>(lds, ltr + lpp, ss, logn, tw);
 }
 
 // Work unit of a work group of the inverse transforms: units (row group rg of column tile
@@ -787,7 +791,7 @@ static inline int xcd_groups(int n_units, int npg) { return 8 * npg * ((n_units 
 __global__ void __launch_bounds__(NT) k_line_irfft(const double* __restrict__ c,
                                                    double* __restrict__ w,
                                                    double* __restrict__ wmax_part, int R, int nz,
-                                                   int logn, int mp, int M, int tr, int pp, int n_rg,
+                                                   int logn, int mp, int M, int ltr, int lpp, int n_rg,
                                                    int n_units,
                                                    const double2* __restrict__ tw, int nsplit,
                                                    int64_t split_stride,
@@ -797,19 +801,20 @@ __global__ void __launch_bounds__(NT) k_line_irfft(const double* __restrict__ c,
                                                    const unsigned long long* __restrict__ amax,
                                                    const int* __restrict__ bexp) {
     extern __shared__ double2 lds[];
+    const int tr = 1 << ltr, pp = 1 << lpp;
     int tile, rg, pg;
     if (!xcd_unit(n_units, n_rg, 4 / pp, tile, rg, pg)) return;
     const int row0 = rg * tr;
     const int pair0 = pg * pp;                  // first RHS pair inside the 8-RHS tile
     const int nseq = tr * pp;
     const int ss = nz + 1;
-    gather_inverse(lds, c, tile, row0, pair0, tr, pp, ss, R, nz, logn, mp, M, tw, nsplit, split_stride,
+    gather_inverse(lds, c, tile, row0, pair0, ltr, lpp, ss, R, nz, logn, mp, M, tw, nsplit, split_stride,
                    rowmean, shat, shat_on, amax, bexp);
     const double scale = 1.0 / nz;
     double mx[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // per RHS inside the tile
     for (int t = threadIdx.x; t < nseq * nz; t += NT) {
-        const int s = t / nz, n0 = t - s * nz;
-        const int pj = s / tr, trr = s - pj * tr;
+        const int s = t >> logn, n0 = t & (nz - 1);
+        const int pj = s >> ltr, trr = s & (tr - 1);
         const int row = row0 + trr;
         const int ja = 2 * (pair0 + pj);
         const int ra = 8 * tile + ja;
@@ -860,12 +865,15 @@ void launch_line_irfft(hipStream_t st, const double* c, double* w, double* wmax_
     while ((1 << logn) < nz) ++logn;
     int pp, tr;
     irfft_shape(nz, &tr, &pp);
+    int ltr = 0, lpp = 0;                                       // (powers of two)
+    while ((1 << ltr) < tr) ++ltr;
+    while ((1 << lpp) < pp) ++lpp;
     const int n_rg = (M + tr - 1) / tr;
     const int n_units = ct_grid * n_rg;
     size_t lds = (size_t)tr * pp * (nz + 1) * sizeof(double2);
     if (lds < 8 * NT * sizeof(double)) lds = 8 * NT * sizeof(double);   // reused by the max
     hipLaunchKernelGGL(k_line_irfft, dim3(xcd_groups(n_units, 4 / pp)), dim3(NT), lds, st, c, w, wmax_part,
-                       R, nz, logn, mp, M, tr, pp, n_rg, n_units, tw, nsplit, split_stride, rowmean, shat,
+                       R, nz, logn, mp, M, ltr, lpp, n_rg, n_units, tw, nsplit, split_stride, rowmean, shat,
                        shat_on, amax, bexp);
     if (n_part_out) *n_part_out = n_rg;
 }

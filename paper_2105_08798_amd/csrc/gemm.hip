@@ -78,7 +78,7 @@ struct FlushAt {
 };
 
 // ------------------------------- FP32 ---------------------------------------------
-// FP32 MFMA with FP32 accumulation inside chunks of KCH*16 real k, FP64 across chunks.
+// FP32 MFMA with FP32 accumulation inside KC chunks of 64 real k, FP64 across chunks.
 template <int TRB, int RB, int CT, int PF, int KC>
 __device__ inline void gemm_f32_job(const GemmJob& jb,
                                                   const float* __restrict__ A,
@@ -165,7 +165,7 @@ __device__ inline void gemm_f32_job(const GemmJob& jb,
 
 // ------------------------------- split BF16 ---------------------------------------
 // G ~ G_hi + G_lo, f ~ f_hi + f_lo; products lo*hi + hi*lo + hi*hi on BF16 MFMA with
-// FP32 accumulation inside chunks of KCH*32 real k, FP64 across chunks.
+// FP32 accumulation inside KC chunks of 64 real k, FP64 across chunks.
 // The split-FP16 form runs the same kernel on FP16 MFMA; its operands carry power-of-two
 // scales that the inverse transform removes.
 __device__ inline f4_t mfma_16x16x32(bf8_t a, bf8_t b, f4_t c) {
@@ -189,7 +189,7 @@ __device__ inline void gemm_split_job(const GemmJob& jb,
     const int tb = jb.k0 >> 5, te = jb.k1 >> 5;
     // 16-byte units: per (block, t): hi run of 64 units then lo run of 64 units
     const VT* a = (const VT*)(A + jb.a_off) + (int64_t)(wave * RB) * 128 + lane;
-    const VT* b = (const VT*)(B + jb.b_off) + bpos(lane);
+    const VT* b = (const VT*)(B + jb.b_off) + (int64_t)jb.c0 * kt * 128 + bpos(lane);
     d4_t acc[RB][CT];
     f4_t ac32[RB][CT];
 #pragma unroll
@@ -274,12 +274,10 @@ __device__ inline void gemm_split_job(const GemmJob& jb,
         for (int c = 0; c < CT; ++c) store_c_f32acc(C, jb, rbw + r, c, lane, acc[r][c]);
 }
 
-// Variant for 4 or 8 column tiles (many RHS): the B fragments of a K step are the same
-// for the NW waves of a work group, so they are loaded once per work group into LDS
+// Stream job of four column tiles (more than 16 RHS): the B fragments of a K step are the
+// same for the NW waves of a work group, so they are loaded once per work group into LDS
 // (double buffered) instead of once per wave from L2, and the group meets at one barrier
-// per S steps.  NW waves per group: four at 64 RHS (the FP64 accumulators of 16 output
-// tiles and the A and B rings need more registers than two waves per SIMD leave, so a
-// group of eight waves, which would halve the B fetches per row, spills).  A is streamed from HBM into a register ring PFA steps deep.  Each thread
+// per S steps.  A is streamed from HBM into a register ring PFA steps deep.  Each thread
 // also keeps its share of B for the same PFA steps in a ring of its own: vector-memory
 // loads complete in issue order, so the wait for B before it is copied into LDS would
 // otherwise also wait for every A load issued before it, and cut the effective depth of
@@ -461,6 +459,7 @@ __device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const v
     const int row0 = 16 * jb.rb0, tile = row0 / JOB_ROWS;
     // the rows in the order used here: row - row0, place of the pad column in the box << 16
     const int32_t* rows = tv.keys + cd.rrow + tile * JOB_ROWS;
+    const bool full = CT != 4 || jb.ct_active - jb.c0 != 3;       // else the last tile holds no RHS
     d4_t acc[RB][CT];
     f4_t ac32[RB][CT];
 #pragma unroll
@@ -570,12 +569,13 @@ __device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const v
 #pragma unroll
                         for (int r = 0; r < RB; ++r) av[r] = *(const float*)(smem + base[r][a % 3] + pl);
 #pragma unroll
-                        for (int r = 0; r < RB; ++r)
+                        for (int c = 0; c < CT; ++c) {
+                            if (c == 3 && !full) continue;
+                            const float bv = h == 0 ? bb[c].x : h == 1 ? bb[c].y : h == 2 ? bb[c].z : bb[c].w;
 #pragma unroll
-                            for (int c = 0; c < CT; ++c) {
-                                const float bv = h == 0 ? bb[c].x : h == 1 ? bb[c].y : h == 2 ? bb[c].z : bb[c].w;
+                            for (int r = 0; r < RB; ++r)
                                 ac32[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r], bv, ac32[r][c], 0, 0, 0);
-                            }
+                        }
                     }
                 }
             } else {
@@ -603,6 +603,7 @@ __device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const v
                     }
 #pragma unroll
                     for (int c = 0; c < CT; ++c) {
+                        if (c == 3 && !full) continue;
                         const VT bh = *(const VT*)(bl + (c * 4 + 2 * s) * 1024);
                         const VT bo = *(const VT*)(bl + (c * 4 + 2 * s + 1) * 1024);
 #pragma unroll
@@ -672,20 +673,29 @@ struct Shape {
     static constexpr int WPE = std::max(1, OCC_ * RG_ / 4);      // waves per SIMD
 };
 
-template <typename SH>
+// A job runs the column tiles that hold RHS of its cell, rounded up to a power of two (three of
+// four: the gather jobs leave the fourth out): a cell with few RHS beside one with many, or the
+// second job of five tiles, does not multiply zeros.
+template <typename SH, int CT = SH::CT>
 __device__ inline void any_job(const GemmJob& jb, const void* __restrict__ A, const RTabView& tv,
                                const void* __restrict__ B, double* __restrict__ C,
                                const CellDev* __restrict__ cells, char* smem) {
     using VT = typename SH::VT;
+    if constexpr (CT > 1) {
+        if (2 * (jb.ct_active - jb.c0) <= CT) {
+            any_job<SH, CT / 2>(jb, A, tv, B, C, cells, smem);
+            return;
+        }
+    }
     if (jb.gather) {
-        gather_job<VT, SH::CT, SH::RG, SH::KC, SH::STG>(jb, tv, B, C, cells, smem);
+        gather_job<VT, CT, SH::RG, SH::KC, SH::STG>(jb, tv, B, C, cells, smem);
     } else if constexpr (sizeof(VT) == 4) {
-        gemm_f32_job<SH::TRB, SH::RB, SH::CT, SH::PF, SH::KC>(jb, (const float*)A, (const float*)B, C);
-    } else if constexpr (SH::S == 0) {
-        gemm_split_job<VT, SH::TRB, SH::RB, SH::CT, SH::PF, SH::KC>(
+        gemm_f32_job<SH::TRB, SH::RB, CT, SH::PF, SH::KC>(jb, (const float*)A, (const float*)B, C);
+    } else if constexpr (SH::S == 0 || CT == 1) {
+        gemm_split_job<VT, SH::TRB, SH::RB, CT, 2, SH::KC>(
             jb, (const unsigned short*)A, (const unsigned short*)B, C);
     } else {
-        gemm_split_lds_job<VT, SH::RB, SH::CT, SH::PF, SH::KC, SH::S, SH::RG>(
+        gemm_split_lds_job<VT, SH::RB, CT, SH::PF, SH::KC, SH::S, SH::RG>(
             jb, (const unsigned short*)A, (const unsigned short*)B, C, smem);
     }
 }
@@ -759,6 +769,13 @@ static void with_shape(int form, int ctmax, int variant, F&& fn) {
         SPLIT_SHAPES(bf8_t, 4, 4, 3, G_CAP)
     }
 #undef SPLIT_SHAPES
+}
+
+// Work groups of a product class that a CU holds.
+int gemm_groups_per_cu(int form, int ctmax) {
+    int n = 1;
+    with_shape(form, ctmax, 0, [&](auto sh) { n = decltype(sh)::OCC; });
+    return n;
 }
 
 // Readable shape of a variant.

@@ -72,6 +72,7 @@ void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int c
                  const RTabView& tv, const void* b, double* c, const CellDev* cells, const PqLists* q, int variant);
 void gemm_kernels_init(int form, int ctmax);
 int gemm_job_tiles(int ctmax);
+int gemm_groups_per_cu(int form, int ctmax);
 int gemm_variants(int form, int ctmax);
 std::string gemm_shape(int form, int ctmax, int variant);
 // Offset-table forms (gemm_table.hip): one job per wave, 16 pad columns over a window of
