@@ -210,6 +210,14 @@ static void compute_windows(fbc_ctx* c, const std::vector<double>& rho_cut, int 
             for (int b = 0; b < p.n_b; b += TAB_COLS) tiles.push_back({b, std::min(p.n_b, b + TAB_COLS)});
             for (int i = 0; i < p.n_i; i += TAB_COLS) chunks.push_back({i, std::min(p.n_i, i + TAB_COLS)});
             plan_windows_ranges(g, p.nm, tiles, chunks, c->nz_max / p.nz, rho_cut, w);
+            if (c->opt.table_fp32) {
+                // which modes count as skipping, and so run in FP32, is decided on tiles of 32 pad and
+                // chunks of 8 interface columns: part of what the option computes, whatever the tiles of
+                // the product
+                PlanWindows v;
+                plan_windows(g, p.nm, (int)roundup(p.M, 96), 0, true, 96, c->nz_max / p.nz, rho_cut, v);
+                w.mode_skips.swap(v.mode_skips);
+            }
         } else {
             plan_windows(g, p.nm, p.mp, p.kp, false, rows_tile, c->nz_max / p.nz, rho_cut, w);
         }

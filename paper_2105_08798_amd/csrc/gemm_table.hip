@@ -31,11 +31,16 @@
 #include "kernels.h"
 #include "pq.h"
 
-// One job of one wave over its CT column tiles; F32: the gathered values and f^ rounded to FP32 on FP32 MFMA, summed in FP32 over
-// 8 interface columns and in FP64 across them.  DB: B fragments in flight, in (q, d) steps.
+// One job of one wave over its CT column tiles.  DB: B fragments in flight, in (q, d) steps.
+// F32: the gathered values and f^ rounded to FP32 on FP32 MFMA, summed in FP32 over 8 interface
+// columns and in FP64 across them; their 48 k' run through the MFMAs four at a time in natural order
+// (k' = 6 i + 2 d + part), lane group g the fourth's g-th, so values change lanes through LDS: the
+// records [interface column][pad column][6][2], f^ [k'][RHS column].
+constexpr int F32_REC = 8 * 16 * 12, F32_B = 48 * 16;       // floats; the latter per column tile
+constexpr int f32_lds(int ct) { return 4 * (F32_REC + F32_B * ct); }
 template <int CT, int DB, bool F32>
 __device__ inline void tab_job(const GemmJob& jb, const TabView& tv, const double* __restrict__ B,
-                               double* __restrict__ C, const CellDev* __restrict__ cells) {
+                               double* __restrict__ C, const CellDev* __restrict__ cells, float* lds) {
     static_assert(12 % DB == 0, "the B ring must divide the 12 steps of a chunk");
     const int lane = threadIdx.x & 63, g = lane >> 4;
     const CellDev cd = cells[jb.cell];
@@ -96,46 +101,71 @@ __device__ inline void tab_job(const GemmJob& jb, const TabView& tv, const doubl
             __builtin_amdgcn_sched_barrier(0);
         }
         for (int t = 0; t < n; ++t) {
-            f4_t a32[3][CT];
             const int c3 = chunk_at(t + 3);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if constexpr (F32) {
-                    if ((q & 1) == 0) {
+                    const int il = 4 * (q & 1) + g;
+                    float4* ra = (float4*)(lds + (il * 16 + (lane & 15)) * 12);
+#pragma unroll
+                    for (int e = 0; e < 6; e += 2)
+                        ra[e / 2] = make_float4((float)rec[q][e].x, (float)rec[q][e].y, (float)rec[q][e + 1].x,
+                                                (float)rec[q][e + 1].y);
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        const int step = 3 * q + d, slot = step % DB, sn = step + DB;
+                        float* rb = lds + F32_REC + (6 * il + 2 * d) * 16 + (lane & 15);
+#pragma unroll
+                        for (int x = 0; x < CT; ++x) {
+                            rb[x * F32_B] = (float)bb[slot][x].x;
+                            rb[x * F32_B + 16] = (float)bb[slot][x].y;
+                        }
+                        load_b(slot, sn % 12, sn < 12 ? cur : nxt);
+                    }
+                    if (q & 1) {
+                        __builtin_amdgcn_wave_barrier();        // (one wave: its LDS operations are in order)
+                        f4_t a32[3][CT];
 #pragma unroll
                         for (int c = 0; c < 3; ++c)
 #pragma unroll
                             for (int x = 0; x < CT; ++x) a32[c][x] = (f4_t){0, 0, 0, 0};
-                    }
-                }
 #pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const int step = 3 * q + d, slot = step % DB;
-#pragma unroll
-                    for (int part = 0; part < 2; ++part)
-#pragma unroll
-                        for (int x = 0; x < CT; ++x)
+                        for (int n4 = 0; n4 < 12; ++n4) {
+                            const int kq = 4 * n4 + g, i = kq / 6, e = kq - 6 * i, d = e >> 1;
+                            const float* fa = lds + (i * 16 + (lane & 15)) * 12 + (e & 1);
 #pragma unroll
                             for (int c = 0; c < 3; ++c) {
-                                const double2 r = rec[q][sym_idx(c, d)];
-                                const double av = part ? r.y : r.x, bv = part ? bb[slot][x].y : bb[slot][x].x;
-                                if constexpr (F32)
-                                    a32[c][x] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)av, (float)bv, a32[c][x],
-                                                                                     0, 0, 0);
-                                else
-                                    acc[c][x] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[c][x], 0, 0, 0);
+                                const float av = fa[2 * sym_idx(c, d)];
+#pragma unroll
+                                for (int x = 0; x < CT; ++x)
+                                    a32[c][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                        av, lds[F32_REC + x * F32_B + 64 * n4 + lane], a32[c][x], 0, 0, 0);
                             }
-                    const int sn = step + DB;
-                    load_b(slot, sn % 12, sn < 12 ? cur : nxt);
-                }
-                if constexpr (F32) {
-                    if (q & 1) {
+                        }
+                        __builtin_amdgcn_wave_barrier();
 #pragma unroll
                         for (int c = 0; c < 3; ++c)
 #pragma unroll
                             for (int x = 0; x < CT; ++x)
 #pragma unroll
                                 for (int j = 0; j < 4; ++j) acc[c][x][j] += (double)a32[c][x][j];
+                    }
+                } else {
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        const int step = 3 * q + d, slot = step % DB;
+#pragma unroll
+                        for (int part = 0; part < 2; ++part)
+#pragma unroll
+                            for (int x = 0; x < CT; ++x)
+#pragma unroll
+                                for (int c = 0; c < 3; ++c) {
+                                    const double2 r = rec[q][sym_idx(c, d)];
+                                    acc[c][x] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                                        part ? r.y : r.x, part ? bb[slot][x].y : bb[slot][x].x, acc[c][x], 0, 0, 0);
+                                }
+                        const int sn = step + DB;
+                        load_b(slot, sn % 12, sn < 12 ? cur : nxt);
                     }
                 }
                 load_rec(q, on[q]);
@@ -168,16 +198,16 @@ __device__ inline void tab_job(const GemmJob& jb, const TabView& tv, const doubl
 // column tile, 48 registers, for any count but 8 (64).
 template <int CT, int MIX>
 __device__ inline void tab_any(const GemmJob& jb, const TabView& tv, const double* __restrict__ B,
-                               double* __restrict__ C, const CellDev* __restrict__ cells) {
+                               double* __restrict__ C, const CellDev* __restrict__ cells, float* lds) {
     if constexpr (CT > 1) {
         if (2 * jb.ct_active <= CT) {
-            tab_any<CT / 2, MIX>(jb, tv, B, C, cells);
+            tab_any<CT / 2, MIX>(jb, tv, B, C, cells, lds);
             return;
         }
     }
     constexpr int DB = CT == 8 ? 2 : 12 / CT;
-    if (MIX && jb.prec) tab_job<CT, DB, true>(jb, tv, B, C, cells);
-    else tab_job<CT, DB, false>(jb, tv, B, C, cells);
+    if (MIX && jb.prec) tab_job<CT, DB, true>(jb, tv, B, C, cells, lds);
+    else tab_job<CT, DB, false>(jb, tv, B, C, cells, lds);
 }
 
 // Each wave of a work group (one, or four: variant 1) on its own job; MIX: each job in its
@@ -190,17 +220,19 @@ k_tab(const GemmJob* __restrict__ jobs, int njobs, TabView tv, const double* __r
     if (j >= njobs) return;
     const GemmJob jb = jobs[j];
     if (jb.mb == 0) return;
-    tab_any<CT, MIX>(jb, tv, B, C, cells);
+    extern __shared__ __attribute__((aligned(128))) float tab_lds[];
+    tab_any<CT, MIX>(jb, tv, B, C, cells, tab_lds + (threadIdx.x >> 6) * (f32_lds(CT) / 4));
 }
 
 template <int CT, int MIX>
 __global__ void __launch_bounds__(256, CT <= 2 ? 2 : 1)
 k_tab_pq(const GemmJob* __restrict__ jobs, int njobs, PqLists q, TabView tv, const double* __restrict__ B,
          double* __restrict__ C, const CellDev* __restrict__ cells) {
+    extern __shared__ __attribute__((aligned(128))) float tab_lds[];
     int cur = 0;
     for (int j = pq_next_wave(q, cur); j < njobs; j = pq_next_wave(q, cur)) {
         const GemmJob jb = jobs[j];
-        tab_any<CT, MIX>(jb, tv, B, C, cells);
+        tab_any<CT, MIX>(jb, tv, B, C, cells, tab_lds + (threadIdx.x >> 6) * (f32_lds(CT) / 4));
     }
     pq_done_wave(q);
 }
@@ -217,9 +249,10 @@ void launch_gemm_dtab(hipStream_t st, const GemmJob* jobs, int njobs, int ct, co
         if (q)                                                                                                \
             hipLaunchKernelGGL((k_tab_pq<CT, MIX>),                                                           \
                                dim3(std::min(groups, 4 / waves * pq_groups_of(k_tab_pq<CT, MIX>, 256))),      \
-                               dim3(64 * waves), 0, st, jobs, njobs, *q, tv, b, c, cells);                    \
+                               dim3(64 * waves), MIX * waves * f32_lds(CT), st, jobs, njobs, *q, tv, b, c, cells);                    \
         else                                                                                                  \
-            hipLaunchKernelGGL((k_tab<CT, MIX>), dim3(groups), dim3(64 * waves), 0, st, jobs, njobs, tv, b, c, cells); \
+            hipLaunchKernelGGL((k_tab<CT, MIX>), dim3(groups), dim3(64 * waves), MIX * waves * f32_lds(CT), st, jobs,  \
+                               njobs, tv, b, c, cells);                                                       \
     } while (0)
 #define TAB_CT(CT) do { if (mixed) TAB_CASE(CT, 1); else TAB_CASE(CT, 0); } while (0)
     switch (ct) {
