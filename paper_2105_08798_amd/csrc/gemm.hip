@@ -459,7 +459,6 @@ __device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const v
     const int row0 = 16 * jb.rb0, tile = row0 / JOB_ROWS;
     // the rows in the order used here: row - row0, place of the pad column in the box << 16
     const int32_t* rows = tv.keys + cd.rrow + tile * JOB_ROWS;
-    const bool full = CT != 4 || jb.ct_active - jb.c0 != 3;       // else the last tile holds no RHS
     d4_t acc[RB][CT];
     f4_t ac32[RB][CT];
 #pragma unroll
@@ -560,23 +559,24 @@ __device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const v
                     float4 bb[CT];
 #pragma unroll
                     for (int c = 0; c < CT; ++c) bb[c] = *(const float4*)(bl + (c * 4 + q) * 1024);
+                    float av[4][RB];
 #pragma unroll
                     for (int h = 0; h < 4; ++h) {
                         constexpr int A0 = 32 * PH;
                         const int a = A0 + 8 * q + 2 * h;
                         const int pl = *(const int*)(smem + il4[a % 3] + 4 * (a / 3 - A0 / 3));
-                        float av[RB];
 #pragma unroll
-                        for (int r = 0; r < RB; ++r) av[r] = *(const float*)(smem + base[r][a % 3] + pl);
+                        for (int r = 0; r < RB; ++r) av[h][r] = *(const float*)(smem + base[r][a % 3] + pl);
+                    }
+#pragma unroll
+                    for (int h = 0; h < 4; ++h)
 #pragma unroll
                         for (int c = 0; c < CT; ++c) {
-                            if (c == 3 && !full) continue;
                             const float bv = h == 0 ? bb[c].x : h == 1 ? bb[c].y : h == 2 ? bb[c].z : bb[c].w;
 #pragma unroll
                             for (int r = 0; r < RB; ++r)
-                                ac32[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r], bv, ac32[r][c], 0, 0, 0);
+                                ac32[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[h][r], bv, ac32[r][c], 0, 0, 0);
                         }
-                    }
                 }
             } else {
 #pragma unroll
@@ -603,7 +603,6 @@ __device__ inline void gather_job(const GemmJob& jb, const RTabView& tv, const v
                     }
 #pragma unroll
                     for (int c = 0; c < CT; ++c) {
-                        if (c == 3 && !full) continue;
                         const VT bh = *(const VT*)(bl + (c * 4 + 2 * s) * 1024);
                         const VT bo = *(const VT*)(bl + (c * 4 + 2 * s + 1) * 1024);
 #pragma unroll
@@ -673,9 +672,9 @@ struct Shape {
     static constexpr int WPE = std::max(1, OCC_ * RG_ / 4);      // waves per SIMD
 };
 
-// A job runs the column tiles that hold RHS of its cell, rounded up to a power of two (three of
-// four: the gather jobs leave the fourth out): a cell with few RHS beside one with many, or the
-// second job of five tiles, does not multiply zeros.
+// A job runs the column tiles that hold RHS of its cell, rounded up to a power of two (gather jobs
+// also three): a cell with few RHS beside one with many, or the second job of five tiles, does not
+// multiply zeros.
 template <typename SH, int CT = SH::CT>
 __device__ inline void any_job(const GemmJob& jb, const void* __restrict__ A, const RTabView& tv,
                                const void* __restrict__ B, double* __restrict__ C,
@@ -688,6 +687,12 @@ __device__ inline void any_job(const GemmJob& jb, const void* __restrict__ A, co
         }
     }
     if (jb.gather) {
+        if constexpr (CT == 4) {
+            if (jb.ct_active - jb.c0 == 3) {
+                gather_job<VT, 3, SH::RG, SH::KC, SH::STG>(jb, tv, B, C, cells, smem);
+                return;
+            }
+        }
         gather_job<VT, CT, SH::RG, SH::KC, SH::STG>(jb, tv, B, C, cells, smem);
     } else if constexpr (sizeof(VT) == 4) {
         gemm_f32_job<SH::TRB, SH::RB, CT, SH::PF, SH::KC>(jb, (const float*)A, (const float*)B, C);
