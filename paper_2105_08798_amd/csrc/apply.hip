@@ -197,7 +197,10 @@ struct NfTotal {
     double2* shat;
     int *shat_on, *bexp, *status;
 };
-// One work group of NT threads; lds: 3 Nz complex values and at least 6 NT doubles.
+// Components of the per-layer net force whose line transforms fit into the CU's LDS together: all
+// three, or one at a time (lines of 4096 layers: 64 KiB each).
+__host__ __device__ inline int nf_seqs(int nz) { return 3 * nz * (int)sizeof(double2) <= 160 * 1024 ? 3 : 1; }
+// One work group of NT threads; lds: 6 NT doubles and, with shat, nf_seqs Nz complex values.
 __device__ inline void netforce_total(const NfTotal& a, int r, int nz, int logn, int n_i,
                                       const double2* __restrict__ tw, double2* lds) {
     const double* __restrict__ sums = a.sums;
@@ -228,24 +231,27 @@ __device__ inline void netforce_total(const NfTotal& a, int r, int nz, int logn,
     if (!shat) return;
     // v[0..2] hold the totals in every thread after block_sum
     const double gam = (double)n_i * 0x1p-52;
-    for (int e = threadIdx.x; e < 3 * nz; e += NT) {
-        const int c = e / nz, n0 = e - c * nz;
-        const double sub = project ? v[c] / nz : 0.0;
-        const double* o = sums + ((int64_t)r * nz + n0) * NF_STRIDE;
-        double s = o[c] - sub;
-        if (fabs(s) <= gam * o[3 + c] && isfinite(o[3 + c])) s = 0.0;
-        lds[c * nz + bitrev(n0, logn)] = make_double2(s, 0.0);
-    }
-    __syncthreads();
-    lds_fft(lds, 3, logn, tw, false);
-    const int nm = (nz >> 1) + 1;
+    const int nm = (nz >> 1) + 1, ns = nf_seqs(nz);
     int any = 0;
-    for (int e = threadIdx.x; e < 3 * nm; e += NT) {
-        const int m = e / 3, c = e - 3 * m;
-        double2 z = lds[c * nz + m];
-        if (project && m == 0) z = make_double2(0.0, 0.0);
-        shat[((int64_t)r * nm + m) * 3 + c] = z;
-        any |= (z.x != 0.0 || z.y != 0.0);
+    for (int c0 = 0; c0 < 3; c0 += ns) {
+        for (int e = threadIdx.x; e < ns * nz; e += NT) {
+            const int q = e / nz, n0 = e - q * nz, c = c0 + q;
+            const double sub = project ? (c == 0 ? v[0] : c == 1 ? v[1] : v[2]) / nz : 0.0;
+            const double* o = sums + ((int64_t)r * nz + n0) * NF_STRIDE;
+            double s = o[c] - sub;
+            if (fabs(s) <= gam * o[3 + c] && isfinite(o[3 + c])) s = 0.0;
+            lds[q * nz + bitrev(n0, logn)] = make_double2(s, 0.0);
+        }
+        __syncthreads();
+        lds_fft(lds, ns, logn, tw, false);
+        for (int e = threadIdx.x; e < ns * nm; e += NT) {
+            const int m = e / ns, q = e - ns * m;
+            double2 z = lds[q * nz + m];
+            if (project && m == 0) z = make_double2(0.0, 0.0);
+            shat[((int64_t)r * nm + m) * 3 + c0 + q] = z;
+            any |= (z.x != 0.0 || z.y != 0.0);
+        }
+        __syncthreads();
     }
     any = __syncthreads_or(any);
     if (threadIdx.x == 0) a.shat_on[r] = any;   // 0: s^ = 0 exactly, the compensation adds 0
@@ -257,7 +263,10 @@ __global__ void __launch_bounds__(NT) k_netforce_total(NfTotal a, int nz, int lo
     else relax_alpha(rx, nz, blockIdx.x, (double*)lds);
 }
 
-static size_t nf_lds(int nz) { return std::max((size_t)3 * nz * sizeof(double2), (size_t)6 * NT * sizeof(double)); }
+// LDS of the net-force totals (with or without the line transforms) and of the step factor.
+static size_t nf_lds(int nz, bool transforms) {
+    return std::max(transforms ? (size_t)nf_seqs(nz) * nz * sizeof(double2) : 0, (size_t)6 * NT * sizeof(double));
+}
 
 // ----------------------------------------------------------------------------------
 // rFFT along the line for every (RHS, column component), written straight into the
@@ -557,13 +566,13 @@ void launch_forward(hipStream_t st, int form, const double* f, double* sums, dou
     else if (statistics)
         hipLaunchKernelGGL(k_netforce<false>, dim3(nz, R), dim3(NT), 0, st, f, sums, nz, n_i, check, status, rx);
     if (wide ? totals + relax : totals && (project || bexp)) {
-        hipLaunchKernelGGL(k_netforce_total, dim3(R, totals + (wide ? relax : 0)), dim3(NT), nf_lds(nz), st, nf, nz,
-                           logn, n_i, tw, totals, rx);
+        hipLaunchKernelGGL(k_netforce_total, dim3(R, totals + (wide ? relax : 0)), dim3(NT), nf_lds(nz, totals && shat), st, nf,
+                           nz, logn, n_i, tw, totals, rx);
         totals = 0;
     }
     if (!wide && totals + relax) {
         grid.y += totals + relax;
-        lds = std::max(lds, nf_lds(nz));
+        lds = std::max(lds, nf_lds(nz, totals && shat));
     }
     const double inv_cnt = 1.0 / ((double)n_i * nz);
 #define RF_LAUNCH(FM)                                                                                       \
