@@ -272,6 +272,9 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
     c->d1min = os.d1min;
     c->d2min = os.d2min;
     c->w2 = os.w2;
+    // the products look offsets up by keys of 32 bits (plan_key)
+    if (is_table_form(form) && os.lut.size() > ((size_t)1 << 32))
+        return fail(c, FBC_E_UNSUPPORTED, "column offsets spread over more than 2^32 lattice places");
     const int T = c->nz_max / 2 + 1;
     std::vector<void*> tmp;
     auto talloc = [&](void** ptr, int64_t bytes) -> fbc_status {
@@ -1165,11 +1168,12 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
             cd.push_back(CellDev{(int64_t)keys.size(), (int64_t)keys.size() + nb, 0, 0, 0, 0});
             for (int b = 0; b < nb; ++b) {
                 const int q = std::min(b, p.n_b - 1);
-                keys.push_back((int32_t)(((int64_t)p.cols_b[2 * q] - c->d1min) * c->w2 + p.cols_b[2 * q + 1] - c->d2min));
+                keys.push_back((int32_t)(plan_key(p.cols_b[2 * q], p.cols_b[2 * q + 1], c->w2) -
+                                         plan_key(c->d1min, c->d2min, c->w2)));
             }
             for (int x = 0; x < ni; ++x) {             // [chunk][g][q] holds column 16 chunk + 4 q + g
                 const int q = std::min((x & ~15) + 4 * (x & 3) + ((x >> 2) & 3), p.n_i - 1);
-                keys.push_back((int32_t)((int64_t)p.cols_i[2 * q] * c->w2 + p.cols_i[2 * q + 1]));
+                keys.push_back((int32_t)plan_key(p.cols_i[2 * q], p.cols_i[2 * q + 1], c->w2));
             }
         }
         if ((s = dev_alloc(c, (void**)&c->colkeys, (int64_t)keys.size() * 4)) != FBC_OK) goto fail_out;

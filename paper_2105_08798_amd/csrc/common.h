@@ -135,8 +135,8 @@ __device__ inline T uniform_at(const T* p) {
     return v;
 }
 
-// Per-cell device view used by the offset-table product kernel: the column keys n1 w2 + n2
-// (their differences index the offset lookup), pad columns up to whole tiles of 16 (the last
+// Per-cell device view used by the offset-table product kernel: the column keys (plan_key;
+// their differences index the offset lookup), pad columns up to whole tiles of 16 (the last
 // column repeated), interface columns up to whole chunks of 16 in the order [chunk][g][q].
 struct CellDev {
     int64_t key_b, key_i;    // offsets into TabView::keys

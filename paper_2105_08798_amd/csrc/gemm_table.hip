@@ -58,8 +58,8 @@ __device__ inline void tab_job(const GemmJob& jb, const TabView& tv, const doubl
         // zero by definition and read as the zero record behind the table
         const int o_lim = tv.need ? tv.need[jb.a_off / (6 * tv.n_off)] : 0x7fffffff;
         const int64_t o_zero = tv.zero_rec - (jb.a_off - tv.a_base) / 6;
-        const int kb = tv.keys[cd.key_b + b0 + (lane & 15)];
-        const int32_t* keys = tv.keys + cd.key_i + 4 * g;
+        const uint32_t kb = tv.keys[cd.key_b + b0 + (lane & 15)];
+        const uint32_t* keys = (const uint32_t*)tv.keys + cd.key_i + 4 * g;
         const double2* b = (const double2*)(B + jb.b_off) + bpos(lane);
         auto chunk_at = [&](int t) { return wrap_k(p0 + min(t, n - 1), nch); };
         double2 rec[4][6];
@@ -76,17 +76,19 @@ __device__ inline void tab_job(const GemmJob& jb, const TabView& tv, const doubl
                 bb[slot][x] = b[((int64_t)x * nch + ch) * 768 + step * 64];
         };
         // table offsets of the chunk after the next refill's, and the keys of the one after that
-        int cur = chunk_at(0), nxt = chunk_at(1), key[4], on[4];
+        int cur = chunk_at(0), nxt = chunk_at(1), on[4];
+        uint32_t key[4];
         {
             const int c2 = chunk_at(2);
-            int o[4], k1[4];
+            uint32_t k0[4], k1[4];
+            int o[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                o[q] = keys[16 * cur + q];
+                k0[q] = keys[16 * cur + q];
                 k1[q] = keys[16 * nxt + q];
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) o[q] = tv.lut[kb - o[q]];
+            for (int q = 0; q < 4; ++q) o[q] = tv.lut[kb - k0[q]];
             // the order of the main loop's refills, so that its first pass waits like the others
 #pragma unroll
             for (int q = 0; q < 4; ++q) {

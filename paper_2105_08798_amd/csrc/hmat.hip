@@ -375,7 +375,8 @@ __global__ void __launch_bounds__(NTH, 4) k_hmat_y(const HBlk* __restrict__ blks
     const double2* tab = st.tab + (int64_t)m * st.n_off * 6;
     for (int p0 = 0; p0 < ncol; p0 += 16) {
         const int lc = min(p0 + col, ncol - 1), ib = leaf_cols[c0 + lc];
-        const int bkey = (st.cols_b[2 * ib] - st.d1min) * st.w2 + st.cols_b[2 * ib + 1] - st.d2min;
+        const uint32_t bkey = ((uint32_t)st.cols_b[2 * ib] - (uint32_t)st.d1min) * (uint32_t)st.w2 +
+                              (uint32_t)st.cols_b[2 * ib + 1] - (uint32_t)st.d2min;      // (keys modulo 2^32, plan_key)
         for (int r0 = 0; r0 < io.r_out; r0 += HR) {
             const double2* xm = x + (int64_t)m * 3 * n_i * Rp + r0 + (col & 7);
             d4_t acc[3] = {};
@@ -389,7 +390,7 @@ __global__ void __launch_bounds__(NTH, 4) k_hmat_y(const HBlk* __restrict__ blks
                     const int steps = (b.ns + 3) >> 2;
                     auto key_at = [&](int t) { return sk[min(4 * t + g, b.ns - 1)]; };
                     int2 kc = key_at(wave), kn = key_at(wave + 4);
-                    int o = st.lut[bkey - kc.y];
+                    int o = st.lut[bkey - (uint32_t)kc.y];
                     for (int t = wave; t < steps; t += 4) {
                         double2 a[6], xv[3];
 #pragma unroll
@@ -397,7 +398,7 @@ __global__ void __launch_bounds__(NTH, 4) k_hmat_y(const HBlk* __restrict__ blks
 #pragma unroll
                         for (int d = 0; d < 3; ++d) xv[d] = xm[(int64_t)(3 * kc.x + d) * Rp];
                         kc = kn;
-                        o = st.lut[bkey - kc.y];
+                        o = st.lut[bkey - (uint32_t)kc.y];
                         kn = key_at(t + 8);
                         if (4 * t + g >= b.ns)
                             for (int d = 0; d < 3; ++d) xv[d] = make_double2(0, 0);
@@ -481,7 +482,7 @@ struct fbc_hmat {
     int* lr_ids = nullptr;
     int* d_ids_d = nullptr;
     int32_t *tcols = nullptr, *scols = nullptr, *leaf_cols = nullptr;
-    int2* skeys = nullptr;                // per entry of scols: column, n1 w2 + n2
+    int2* skeys = nullptr;                // per entry of scols: column, its key (plan_key)
     int *leaf_off = nullptr, *contrib_off = nullptr;
     HContrib* contrib = nullptr;
     double2 *U = nullptr, *V = nullptr, *T = nullptr, *D = nullptr;
@@ -562,7 +563,7 @@ extern "C" fbc_status fbc_hmat_create(const fbc_ctx* ctx, const fbc_hmat_opts* o
         scols.insert(scols.end(), ti[q.s].idx.begin(), ti[q.s].idx.end());
         for (int i : ti[q.s].idx) {
             skeys.push_back(i);
-            skeys.push_back(p.cols_i[2 * i] * ctx->w2 + p.cols_i[2 * i + 1]);
+            skeys.push_back((int32_t)plan_key(p.cols_i[2 * i], p.cols_i[2 * i + 1], ctx->w2));
         }
         h->part_stream.push_back(q.kind);
         h->part_stream.push_back(b.nt);

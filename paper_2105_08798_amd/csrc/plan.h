@@ -25,6 +25,13 @@ struct PlanOffsets {
 };
 PlanOffsets plan_offsets(const std::vector<PlanGeom>& cells);
 
+// Key of a column, n1 w2 + n2 modulo 2^32 (columns may lie anywhere, their keys past 32 bits).  A pad
+// column's key less that of (d1min, d2min) and of an interface column is the pair's index in lut,
+// also modulo 2^32: exact for lookups of up to 2^32 entries.
+inline uint32_t plan_key(int32_t n1, int32_t n2, int w2) {
+    return (uint32_t)n1 * (uint32_t)w2 + (uint32_t)n2;
+}
+
 // In-plane distance of column a from column b (a = 1, c = a / sqrt 2).
 double plan_pair_rho(int32_t a1, int32_t a2, int32_t b1, int32_t b2);
 
