@@ -6,6 +6,7 @@
 #include <cstring>
 #include <map>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -14,7 +15,7 @@
 #include "ctx.h"
 #include "plan.h"
 
-int gemm_tile_rows(int form, int ctmax);
+int gemm_tile_rows(int form, int jt);
 extern "C" fbc_status fbc_timing(fbc_ctx* c, int enable);
 extern "C" fbc_status fbc_timing_read(fbc_ctx* c, double* ms, int* n);
 static void drop_relax_graph(fbc_ctx* c);
@@ -469,7 +470,7 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
                 rho_cut[t] = v;
             }
         }
-        const int rows_tile = gemm_tile_rows(form, c->ctmax);
+        const int rows_tile = gemm_tile_rows(form, c->job_tiles);
         compute_windows(c, rho_cut, rows_tile);
         if (!is_table_form(form)) {
             // modes whose rows carry no gauge depend on the offset alone: gathered from the reduced
@@ -478,6 +479,15 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
             // table takes more memory than the blocks it stands for
             const int64_t tile_bytes = chunk_tile_elems(form, rows_tile) * store_elem_bytes(form);
             int64_t blocks = 0;
+            if (c->job_tiles == 8) {               // all blocks stored: where the memory holds them
+                int64_t all = 0;
+                size_t free_b = 0, total_b = 0;
+                for (const CellPlan& p : c->cells) all += std::accumulate(p.win_len.begin(), p.win_len.end(), (int64_t)0) * tile_bytes;
+                if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && all > (int64_t)(free_b / 4 * 3)) {
+                    c->job_tiles = 4;              // (the same tile height)
+                    gemm_kernels_init(form, 4);
+                }
+            }
             for (CellPlan& p : c->cells) {
                 const int sub = rows_tile / JOB_ROWS;
                 PlanBoxes pb;
@@ -487,7 +497,7 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
                 p.gather.assign((size_t)p.nm * p.n_tiles, 0);
                 for (int m = 0; m < p.nm; ++m)
                     for (int tl = 0; tl < p.n_tiles; ++tl)
-                        if (fits[tl] && (p.mode_skips[m] || !row_gauge_active(c))) {
+                        if (c->job_tiles < 8 && fits[tl] && (p.mode_skips[m] || !row_gauge_active(c))) {
                             p.gather[(size_t)m * p.n_tiles + tl] = 1;
                             blocks += p.win_len[(size_t)m * p.n_tiles + tl] * tile_bytes;
                         }
@@ -550,7 +560,7 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
             c->scratch_bytes += tot_rm * 16;
         }
         // compact store: the chunk-tiles of every window, cell after cell
-        const int rows_tile = gemm_tile_rows(form, c->ctmax);
+        const int rows_tile = gemm_tile_rows(form, c->job_tiles);
         const int64_t cte = chunk_tile_elems(form, rows_tile);
         int64_t a_tot = 0, max_reg = 0;
         for (CellPlan& p : c->cells) {
@@ -622,7 +632,7 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
 static void product_stats(fbc_ctx* c) {
     const int form = c->opt.form;
     const bool dt = is_table_form(form);
-    const int rows_tile = dt ? 3 * TAB_COLS : gemm_tile_rows(form, c->ctmax);
+    const int rows_tile = dt ? 3 * TAB_COLS : gemm_tile_rows(form, c->job_tiles);
     const double eb = 4.0;                       // stored bytes per real entry
     const double fb = dt ? 16.0 : 8.0;           // bytes per complex f^
     double bytes = 0, flops = 0, area = 0, kept = 0;
@@ -685,19 +695,19 @@ struct Unit {
     int64_t cost;
 };
 
-// pairs: the jobs of a row tile (contexts of eight column tiles: two) next to each other.
+// pairs: the jobs of a row tile (two where its cell has more column tiles than a job) next to each other.
 static void unit_jobs(const fbc_ctx* c, const Unit& u, int nsplit, bool pairs, std::vector<GemmJob>& out) {
     const int form = c->opt.form;
     const CellPlan& p = c->cells[u.cell];
     const bool dt = is_table_form(form);
-    const int tile_rows = dt ? 3 * TAB_COLS : gemm_tile_rows(form, c->ctmax);
+    const int tile_rows = dt ? 3 * TAB_COLS : gemm_tile_rows(form, c->job_tiles);
     const int tiles = p.mp / tile_rows;
     const int unit_k = dt ? TAB_COLS : 64;
     // In the persistent lists the two jobs of a row tile, which read the same blocks, are taken by
     // groups of one XCD one after the other (256 layers, 64 RHS: 3.56 ms, apart 4.05).  Elsewhere jobs
     // are dealt to the XCDs in turn, and pairs of different length would give half of the XCDs all
     // the long ones (64 layers, 700 / 1500 columns, 48 RHS in FP32: 0.61 ms, apart 0.51).
-    const int step = dt ? p.ctr : gemm_job_tiles(c->ctmax);
+    const int step = dt ? p.ctr : c->job_tiles;
     for (int ca = 0; ca < (pairs ? 1 : p.ctr); ca += step)
         for (int ks = 0; ks < nsplit; ++ks)
             for (int tl = 0; tl < tiles; ++tl) {
@@ -754,7 +764,7 @@ static std::vector<GemmJob> build_jobs(const fbc_ctx* c, int nsplit, int order, 
     for (int ci = 0; ci < (int)c->cells.size(); ++ci) {
         const CellPlan& p = c->cells[ci];
         const int mult = c->nz_max / p.nz;
-        const int64_t tile_rows = dt ? 3 * TAB_COLS : gemm_tile_rows(c->opt.form, c->ctmax);
+        const int64_t tile_rows = dt ? 3 * TAB_COLS : gemm_tile_rows(c->opt.form, c->job_tiles);
         const int64_t unit_k = dt ? 6 * TAB_COLS : 64;
         for (int m = 0; m < p.nm; ++m) {
             int64_t cost = 0;
@@ -902,11 +912,6 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     c->lat = *lat;
     c->sur = opt->surrogate;
     (void)hipGetDevice(&c->device);
-    if (!is_table_form(opt->form)) {
-        int ct = 1;
-        for (int i = 0; i < n_cells; ++i) ct = std::max(ct, (cells[i].n_rhs + 7) / 8);
-        gemm_kernels_init(opt->form, ct);
-    }
     apply_kernels_init();            // dynamic-LDS limits of the long-line transforms, before any capture
     hipStream_t st = (hipStream_t)stream;
     const int form = opt->form;
@@ -916,8 +921,27 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     int ctmax = 1;
     for (int i = 0; i < n_cells; ++i) ctmax = std::max(ctmax, (cells[i].n_rhs + 7) / 8);
     const int ctl = ctmax <= 1 ? 1 : ctmax <= 2 ? 2 : ctmax <= 4 ? 4 : 8;
-    const int rows_tile = gemm_tile_rows(form, ctl);
     c->ctmax = ctl;
+    c->job_tiles = std::min(ctl, 4);
+    // FP32 with more than 56 RHS (and no cell below 49): jobs of eight column tiles, all streamed.  They
+    // are bound by FP32 MFMA, where a gathered block's addresses and LDS traffic come on top, twice for
+    // two jobs of four tiles.  Per call, 64 RHS, streamed / gathered: 256 layers, 2048 / 4096 columns
+    // 9.19 / 9.94 ms, 1024 / 2048 columns 4.12 / 4.43; 1024 layers, 500 / 1000 columns 7.6 / 8.1; 64
+    // layers, 700 / 1400 columns 0.76 / 0.79.  Seven tiles: 4.04 ms as eight, 4.00 as four and three.
+    // (Gathered in jobs of eight: 10.8 ms where streamed ones take 9.4: one group per CU, nothing to hide
+    // the short windows' starts behind.)  Fewer jobs than CUs: of four, so that twice as many CUs
+    // have one (16 layers, 300 / 600 columns, 135 jobs of eight: 114 us both).
+    if (form == FBC_FORM_FP32 && ctmax == 8) {
+        int64_t jobs = 0;
+        bool few = false;
+        for (int i = 0; i < n_cells; ++i) {
+            jobs += (int64_t)(cells[i].nz / 2 + 1) * ((3 * (int64_t)cells[i].n_b + JOB_ROWS - 1) / JOB_ROWS);
+            few = few || cells[i].n_rhs <= 48;
+        }
+        if (!few && jobs >= 256) c->job_tiles = 8;
+    }
+    if (!is_table_form(form)) gemm_kernels_init(form, c->job_tiles);
+    const int rows_tile = gemm_tile_rows(form, c->job_tiles);
     int64_t f_off = 0, u_off = 0, b_off = 0, c_off = 0, w_off = 0;
     int rhs0 = 0;
     int64_t tiles_total = 0;   // (cell, mode, row tile) work items before the K split
@@ -989,11 +1013,11 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
             // Whole call, 1 / 2 / 4 slices: 300 columns, 10 RHS, 2064 jobs 270, 293, 385 us; 240
             // columns, 18 RHS, 1419 jobs 339, 370, 458; 500 columns, 12 RHS, 1560 jobs 256, 238, 296;
             // 777 columns, 13 RHS, 1122 jobs 209, 193, 222; 1213 columns, 28 RHS, 280 jobs 315, 192, 156
-            const int64_t cols = (c->ctmax + gemm_job_tiles(c->ctmax) - 1) / gemm_job_tiles(c->ctmax);
-            const int64_t jobs1 = tiles_total * cols * (gemm_tile_rows(form, c->ctmax) / JOB_ROWS);
+            const int64_t cols = (c->ctmax + c->job_tiles - 1) / c->job_tiles;
+            const int64_t jobs1 = tiles_total * cols * (gemm_tile_rows(form, c->job_tiles) / JOB_ROWS);
             int chunks = 1;
             for (const auto& p : c->cells) chunks = std::max(chunks, p.kp / 64);
-            const int64_t slots = 256 * gemm_groups_per_cu(form, c->ctmax);
+            const int64_t slots = 256 * gemm_groups_per_cu(form, c->job_tiles);
             const int64_t enough = c->ctmax <= 2 && chunks >= 40 ? 2 * slots : slots + slots / 4;
             int r = 1;
             while (r < 4 && jobs1 * r < enough && c->vslices % (2 * r) == 0 && chunks / (2 * r) >= (jobs1 * r < 128 ? 4 : 14))
@@ -1288,7 +1312,7 @@ static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st, bool re
         launch_gemm_dtab(st, c->jobs, c->njobs, c->ctmax, tv, (const double*)c->bfrag, c->cbuf, c->celldev,
                          c->job_order >= 3 ? &c->lists : nullptr, c->opt.table_fp32, c->variant);
     } else
-        launch_gemm(st, form, c->jobs, c->njobs, c->ctmax, c->store, RTabView{c->rtab, c->colkeys, (int)(2 * c->rbox.w), (int)c->rbox.base, (int)(c->rbox.mode_bytes / 64)}, c->bfrag, c->cbuf,
+        launch_gemm(st, form, c->jobs, c->njobs, c->job_tiles, c->store, RTabView{c->rtab, c->colkeys, (int)(2 * c->rbox.w), (int)c->rbox.base, (int)(c->rbox.mode_bytes / 64)}, c->bfrag, c->cbuf,
                     c->celldev, c->job_order >= 3 ? &c->lists : nullptr, c->variant);
     if (tm) {
         (void)hipEventRecord(c->ev[2 * c->n_timed + 1], st);
@@ -1395,7 +1419,7 @@ extern "C" fbc_status fbc_apply_graph(fbc_ctx* c, const double* f, double* u, do
 
 static int n_variants(const fbc_ctx* c) {
     if (c->opt.form == FBC_FORM_DTABLE_FP64 || c->opt.form == FBC_FORM_SURROGATE) return 1;
-    return c->opt.form == FBC_FORM_FP64 ? 2 : gemm_variants(c->opt.form, c->ctmax);
+    return c->opt.form == FBC_FORM_FP64 ? 2 : gemm_variants(c->opt.form, c->job_tiles);
 }
 
 extern "C" fbc_status fbc_autotune(fbc_ctx* c, const double* f, double* w, int reps,
@@ -1821,7 +1845,7 @@ extern "C" fbc_status fbc_get_info(const fbc_ctx* c, fbc_info* info) {
     info->kernel_variant = c->variant;
     info->n_variants = n_variants(c);
     const std::string shape = is_table_form(c->opt.form) ? std::string("offset table, 16 pad columns x 16 interface columns per step and wave, waves=") + (c->variant ? "4" : "1")
-                                                         : gemm_shape(c->opt.form, c->ctmax, c->variant);
+                                                         : gemm_shape(c->opt.form, c->job_tiles, c->variant);
     std::snprintf(info->kernel_shape, sizeof info->kernel_shape, "%s", shape.c_str());
     return FBC_OK;
 }

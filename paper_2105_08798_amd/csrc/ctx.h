@@ -17,6 +17,7 @@ struct fbc_ctx {
     int total_rhs = 0;
     int64_t f_elems = 0, u_elems = 0;
     int ctmax = 1;
+    int job_tiles = 1;              // reduced forms: column tiles of a product job (1, 2, 4 or 8)
     // device buffers (all owned)
     std::vector<void*> allocs;
     void* store = nullptr;          // dense store (FP64 / FP32 / split BF16)

@@ -668,32 +668,32 @@ struct Shape {
     using VT = VT_;
     static constexpr int TRB = TRB_, CT = CT_, RG = RG_, KC = KC_, PF = PF_, S = S_, OCC = OCC_, STG = STG_;
     static constexpr int NTH = 64 * RG_, RB = JOB_ROWS / 16 / RG_;
-    static constexpr int LDS = S_ == 0 ? gather_lds(CT_) : std::max(gather_lds(CT_), 2 * S_ * CT_ * 2048);
+    static constexpr int LDS = CT_ == 8 ? 0 : S_ == 0 ? gather_lds(CT_) : std::max(gather_lds(CT_), 2 * S_ * CT_ * 2048);
     static constexpr int WPE = std::max(1, OCC_ * RG_ / 4);      // waves per SIMD
 };
 
 // A job runs the column tiles that hold RHS of its cell, rounded up to a power of two (gather jobs
-// also three): a cell with few RHS beside one with many, or the second job of five tiles, does not
+// also three; jobs of eight tiles, stream jobs all, hold seven or eight): a cell with few RHS beside one with many, or the second job of five tiles, does not
 // multiply zeros.
 template <typename SH, int CT = SH::CT>
 __device__ inline void any_job(const GemmJob& jb, const void* __restrict__ A, const RTabView& tv,
                                const void* __restrict__ B, double* __restrict__ C,
                                const CellDev* __restrict__ cells, char* smem) {
     using VT = typename SH::VT;
-    if constexpr (CT > 1) {
+    if constexpr (CT > 1 && CT < 8) {
         if (2 * (jb.ct_active - jb.c0) <= CT) {
             any_job<SH, CT / 2>(jb, A, tv, B, C, cells, smem);
             return;
         }
     }
-    if (jb.gather) {
+    if (CT < 8 && jb.gather) {
         if constexpr (CT == 4) {
             if (jb.ct_active - jb.c0 == 3) {
                 gather_job<VT, 3, SH::RG, SH::KC, SH::STG>(jb, tv, B, C, cells, smem);
                 return;
             }
         }
-        gather_job<VT, CT, SH::RG, SH::KC, SH::STG>(jb, tv, B, C, cells, smem);
+        if constexpr (CT < 8) gather_job<VT, CT, SH::RG, SH::KC, SH::STG>(jb, tv, B, C, cells, smem);
     } else if constexpr (sizeof(VT) == 4) {
         gemm_f32_job<SH::TRB, SH::RB, CT, SH::PF, SH::KC>(jb, (const float*)A, (const float*)B, C);
     } else if constexpr (SH::S == 0 || CT == 1) {
@@ -731,39 +731,39 @@ __global__ void __launch_bounds__(SH::NTH, SH::WPE) k_gemm_pq(const GemmJob* __r
 // Rows of a tile (16 per row block): the planner pads rows to whole tiles, K' to a multiple of
 // 64, takes the windows per tile and lays the compact store out in tiles of this height.  256
 // rows at two column tiles, 128 at the others; a job is 128 rows of a tile (JOB_ROWS).
-int gemm_tile_rows(int, int ctmax) { return ctmax == 2 ? 256 : 128; }
+int gemm_tile_rows(int, int jt) { return jt == 2 ? 256 : 128; }
 
-// Kernel variants of a product class (form, column tiles) that the autotuner may choose
-// from.  They share the tile height and the arithmetic order, so every variant gives bitwise
-// the same result: variant 0 is the default; variant 1 changes the depth of the stream jobs'
-// prefetch ring (FP32) or their K steps per barrier (split products with four or eight column
-// tiles; variant 2: half the ring besides).
-int gemm_variants(int form, int ctmax) {
-    if (form == FBC_FORM_SPLIT_FP16 || form == FBC_FORM_SPLIT_BF16) return ctmax <= 2 ? 1 : 3;
+// Kernel variants of a product class (form, column tiles of a job) that the autotuner may choose
+// from (jt: 1, 2, 4, or 8).  They share the tile height and the arithmetic order, so every variant
+// gives bitwise the same result: variant 0 is the default; variant 1 changes the depth of the stream jobs'
+// prefetch ring (FP32) or their K steps per barrier (split products with four column tiles; variant
+// 2: half the ring besides).
+int gemm_variants(int form, int jt) {
+    if (form == FBC_FORM_SPLIT_FP16 || form == FBC_FORM_SPLIT_BF16) return jt <= 2 ? 1 : 3;
     return 2;
 }
-
-// Column tiles of a job: contexts of eight tiles run each row tile as two jobs of four.
-int gemm_job_tiles(int ctmax) { return std::min(ctmax, 4); }
 
 // Calls fn(Shape) for a product class and variant.  FP32 sums: 2 chunks of 64 k' for split FP16
 // (its representation error is ~2^-23, so the FP32 sums must not dominate; 1 chunk at one or
 // two column tiles), 4 for split BF16 and FP32.
 template <typename F>
-static void with_shape(int form, int ctmax, int variant, F&& fn) {
+static void with_shape(int form, int jt, int variant, F&& fn) {
 #define SPLIT_SHAPES(VT, KC12, KC48, OCC2, STG2)                                               \
-    if (ctmax <= 1) fn(Shape<VT, 8, 1, 4, KC12, 4, G_CAP, 2>());                               \
-    else if (ctmax <= 2) fn(Shape<VT, 16, 2, 4, KC12, OCC2, STG2, 2>());                       \
+    if (jt <= 1) fn(Shape<VT, 8, 1, 4, KC12, 4, G_CAP, 2>());                               \
+    else if (jt <= 2) fn(Shape<VT, 16, 2, 4, KC12, OCC2, STG2, 2>());                       \
     else if (variant == 2) fn(Shape<VT, 8, 4, 4, KC48, 2, G_CAP, 2, 1>());                     \
     else if (variant == 1) fn(Shape<VT, 8, 4, 4, KC48, 2, G_CAP, 4, 1>());                     \
     else fn(Shape<VT, 8, 4, 4, KC48, 2, G_CAP, 4, 2>());
     if (form == FBC_FORM_FP32) {
-        if (ctmax <= 1) {
+        if (jt <= 1) {
             if (variant) fn(Shape<float, 8, 1, 4, 4, 4, G_CAP, 2>());
             else fn(Shape<float, 8, 1, 4, 4, 4, G_CAP, 4>());
-        } else if (ctmax <= 2) {
+        } else if (jt <= 2) {
             if (variant) fn(Shape<float, 16, 2, 4, 4, 3, G_CAP, 2>());
             else fn(Shape<float, 16, 2, 4, 4, 3, G_CAP, 4>());
+        } else if (jt > 4) {
+            if (variant) fn(Shape<float, 8, 8, 4, 4, 1, 0, 2>());
+            else fn(Shape<float, 8, 8, 4, 4, 1, 0, 4>());
         } else {
             if (variant) fn(Shape<float, 8, 4, 4, 4, 2, G_CAP, 4>());
             else fn(Shape<float, 8, 4, 4, 4, 2, G_CAP, 2>());
@@ -777,16 +777,16 @@ static void with_shape(int form, int ctmax, int variant, F&& fn) {
 }
 
 // Work groups of a product class that a CU holds.
-int gemm_groups_per_cu(int form, int ctmax) {
+int gemm_groups_per_cu(int form, int jt) {
     int n = 1;
-    with_shape(form, ctmax, 0, [&](auto sh) { n = decltype(sh)::OCC; });
+    with_shape(form, jt, 0, [&](auto sh) { n = decltype(sh)::OCC; });
     return n;
 }
 
 // Readable shape of a variant.
-std::string gemm_shape(int form, int ctmax, int variant) {
+std::string gemm_shape(int form, int jt, int variant) {
     char buf[96];
-    with_shape(form, ctmax, variant, [&](auto sh) {
+    with_shape(form, jt, variant, [&](auto sh) {
         using SH = decltype(sh);
         snprintf(buf, sizeof buf, "%s rows=%d CT=%d waves=%d KC=%d ring=%d S=%d, gather + stream",
                  form == FBC_FORM_FP32 ? "f32" : form == FBC_FORM_SPLIT_FP16 ? "f16" : "bf16", JOB_ROWS, SH::CT,
@@ -797,9 +797,9 @@ std::string gemm_shape(int form, int ctmax, int variant) {
 
 // Raises the dynamic-LDS limit of the product kernels of a class on the current device (call
 // outside stream capture, e.g. at context creation).
-void gemm_kernels_init(int form, int ctmax) {
-    for (int v = 0; v < gemm_variants(form, ctmax); ++v)
-        with_shape(form, ctmax, v, [&](auto sh) {
+void gemm_kernels_init(int form, int jt) {
+    for (int v = 0; v < gemm_variants(form, jt); ++v)
+        with_shape(form, jt, v, [&](auto sh) {
             using SH = decltype(sh);
             (void)hipFuncSetAttribute((const void*)k_gemm<SH>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS);
             (void)hipFuncSetAttribute((const void*)k_gemm_pq<SH>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS);
@@ -807,10 +807,10 @@ void gemm_kernels_init(int form, int ctmax) {
     (void)hipGetLastError();
 }
 
-void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int ctmax, const void* a,
+void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int jt, const void* a,
                  const RTabView& tv, const void* b, double* c, const CellDev* cells, const PqLists* q, int variant) {
     if (njobs <= 0) return;
-    with_shape(form, ctmax, variant, [&](auto sh) {
+    with_shape(form, jt, variant, [&](auto sh) {
         using SH = decltype(sh);
         if (q)
             hipLaunchKernelGGL(k_gemm_pq<SH>, dim3(std::min(njobs, SH::OCC * device_cus())),

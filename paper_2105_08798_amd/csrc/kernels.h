@@ -66,15 +66,14 @@ struct RelaxClamp {
 void launch_forward(hipStream_t st, int form, const double* f, double* sums, double* tot, double2* shat, int* shat_on,
                     bool statistics, double tol, int check, int project, void* bfrag, int R, int nz, int n_i, int kp,
                     int ct, const double2* tw, int* bexp, int* status, const RelaxIn& rx);
-// Reduced forms.  variant: one of gemm_variants(form, ctmax) kernel instantiations (bitwise the
+// Reduced forms.  variant: one of gemm_variants(form, jt) kernel instantiations (bitwise the
 // same result); q != NULL: persistent work-queue kernel on these lists.
-void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int ctmax, const void* a,
+void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int jt, const void* a,
                  const RTabView& tv, const void* b, double* c, const CellDev* cells, const PqLists* q, int variant);
-void gemm_kernels_init(int form, int ctmax);
-int gemm_job_tiles(int ctmax);
-int gemm_groups_per_cu(int form, int ctmax);
-int gemm_variants(int form, int ctmax);
-std::string gemm_shape(int form, int ctmax, int variant);
+void gemm_kernels_init(int form, int jt);
+int gemm_groups_per_cu(int form, int jt);
+int gemm_variants(int form, int jt);
+std::string gemm_shape(int form, int jt, int variant);
 // Offset-table forms (gemm_table.hip): one job per wave, 16 pad columns over a window of
 // interface columns.  q != NULL: persistent work-queue kernel; mixed: jobs carry their precision;
 // variant 1: work groups of four waves instead of one (bitwise the same result).
