@@ -1525,22 +1525,24 @@ extern "C" fbc_status fbc_autotune(fbc_ctx* c, const double* f, double* w, int r
 }
 
 // Key of a tuned configuration: FNV-1a over everything that decides the product's work
-// (form, tolerance, row gauge, torus, cells with their column sets and RHS, column
-// tiles) and the device it ran on.
+// (form, tolerance, row gauge, precision of the table product, torus, cells with their column
+// sets and RHS, column tiles) and the device it ran on.
 static uint64_t tune_key(const fbc_ctx* c) {
     uint64_t h = 1469598103934665603ull;
     auto mix = [&](const void* p, size_t n) {
         const unsigned char* b = (const unsigned char*)p;
         for (size_t i = 0; i < n; ++i) h = (h ^ b[i]) * 1099511628211ull;
     };
-    const int version = 2;
+    const int version = 3;
     mix(&version, sizeof version);
     mix(&c->opt.form, sizeof c->opt.form);
     mix(&c->opt.skip_tol, sizeof c->opt.skip_tol);
     mix(&c->opt.row_gauge, sizeof c->opt.row_gauge);
+    mix(&c->opt.table_fp32, sizeof c->opt.table_fp32);
     mix(&c->opt.bz_m1, sizeof c->opt.bz_m1);
     mix(&c->opt.bz_m2, sizeof c->opt.bz_m2);
     mix(&c->ctmax, sizeof c->ctmax);
+    mix(&c->job_tiles, sizeof c->job_tiles);
     for (const CellPlan& p : c->cells) {
         const int hd[4] = {p.nz, p.n_i, p.n_b, p.R};
         mix(hd, sizeof hd);
