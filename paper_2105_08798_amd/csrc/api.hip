@@ -1009,10 +1009,15 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
             // pipeline a fill (some six chunks of 64 K').  As many slices (a divisor: FP32 sums still
             // end where the slices counted above would, GemmJob::vs) as fill the chip's groups 5/4
             // times, with long jobs of one or two column tiles twice; 14 chunks a job or more, four
-            // where the jobs are fewer than half of the CUs.
+            // where the jobs are fewer than half of the CUs.  Eight slices only where four leave less
+            // than two jobs a CU (few pad columns beside many interface columns).
             // Whole call, 1 / 2 / 4 slices: 300 columns, 10 RHS, 2064 jobs 270, 293, 385 us; 240
             // columns, 18 RHS, 1419 jobs 339, 370, 458; 500 columns, 12 RHS, 1560 jobs 256, 238, 296;
-            // 777 columns, 13 RHS, 1122 jobs 209, 193, 222; 1213 columns, 28 RHS, 280 jobs 315, 192, 156
+            // 777 columns, 13 RHS, 1122 jobs 209, 193, 222; 1213 columns, 28 RHS, 280 jobs 315, 192, 156.
+            // 4 / 8 slices: 2048 / 40 columns, 1 RHS, 9 jobs 57, 42; 2000 / 200, 4 RHS, 85 jobs 84, 72; 800 /
+            // 300, 16 RHS, 72 jobs 65, 62; 2000 / 500, 24 RHS, 60 jobs 139, 104; 800 / 300, 64 RHS, 144
+            // jobs 112, 121; 1500 / 2500, 3 RHS, 295 jobs 83, 88; 1000 / 900, 8 RHS, 110 jobs 50, 51 (eight
+            // of 11 chunks a job)
             const int64_t cols = (c->ctmax + c->job_tiles - 1) / c->job_tiles;
             const int64_t jobs1 = tiles_total * cols * (gemm_tile_rows(form, c->job_tiles) / JOB_ROWS);
             int chunks = 1;
@@ -1020,7 +1025,8 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
             const int64_t slots = 256 * gemm_groups_per_cu(form, c->job_tiles);
             const int64_t enough = c->ctmax <= 2 && chunks >= 40 ? 2 * slots : slots + slots / 4;
             int r = 1;
-            while (r < 4 && jobs1 * r < enough && c->vslices % (2 * r) == 0 && chunks / (2 * r) >= (jobs1 * r < 128 ? 4 : 14))
+            while (r < 8 && jobs1 * r < (r < 4 ? enough : 512) && c->vslices % (2 * r) == 0 &&
+                   chunks / (2 * r) >= (jobs1 * r < 128 ? 4 : r >= 4 && jobs1 * r < 384 ? 9 : 14))
                 r *= 2;
             c->nsplit = r;
         }
