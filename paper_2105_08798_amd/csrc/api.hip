@@ -695,6 +695,17 @@ struct Unit {
     int64_t cost;
 };
 
+// Column tiles of a job of the offset-table products: all of them, for the gathered records serve
+// every one; fewer where the jobs would leave most of the 1024 SIMDs idle (8 layers, 20 / 40 columns,
+// 64 RHS, 15 jobs: 49 us per call, a job for each tile 21; 96 / 192 columns 59 and 36).
+static int tab_job_tiles(const fbc_ctx* c, int nsplit) {
+    int64_t jobs = 0;
+    for (const CellPlan& p : c->cells) jobs += (int64_t)p.nm * p.n_tiles * nsplit;
+    int step = c->ctmax;
+    while (c->opt.form != FBC_FORM_SURROGATE && step > 1 && jobs * (c->ctmax / step) * 2 <= 1024) step /= 2;
+    return step;
+}
+
 // pairs: the jobs of a row tile (two where its cell has more column tiles than a job) next to each other.
 static void unit_jobs(const fbc_ctx* c, const Unit& u, int nsplit, bool pairs, std::vector<GemmJob>& out) {
     const int form = c->opt.form;
@@ -707,7 +718,7 @@ static void unit_jobs(const fbc_ctx* c, const Unit& u, int nsplit, bool pairs, s
     // groups of one XCD one after the other (256 layers, 64 RHS: 3.56 ms, apart 4.05).  Elsewhere jobs
     // are dealt to the XCDs in turn, and pairs of different length would give half of the XCDs all
     // the long ones (64 layers, 700 / 1500 columns, 48 RHS in FP32: 0.61 ms, apart 0.51).
-    const int step = dt ? p.ctr : c->job_tiles;
+    const int step = dt ? tab_job_tiles(c, nsplit) : c->job_tiles;
     for (int ca = 0; ca < (pairs ? 1 : p.ctr); ca += step)
         for (int ks = 0; ks < nsplit; ++ks)
             for (int tl = 0; tl < tiles; ++tl) {
@@ -741,7 +752,10 @@ static void unit_jobs(const fbc_ctx* c, const Unit& u, int nsplit, bool pairs, s
             }
             j.prec = (dt && c->opt.table_fp32 && p.mode_skips[u.m]) ? 1 : 0;
             if (dt) {
-                out.push_back(j);
+                for (j.c0 = ca; j.c0 < (pairs ? p.ctr : ca + 1); j.c0 += step) {
+                    j.ct_active = std::min(p.ctr, j.c0 + step);
+                    out.push_back(j);
+                }
                 continue;
             }
             // JOB_ROWS rows at a time; the store's row blocks of a K step follow one another

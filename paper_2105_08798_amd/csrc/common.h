@@ -88,14 +88,14 @@ struct GemmJob {
     // range is cyclic: indices at or beyond the padded K wrap to its start (windows around
     // the non-negligible blocks of a tile may straddle the end); k0 == k1: empty (zeros)
     int32_t k0, k1;
-    int32_t ct_active;  // column tiles holding RHS of this cell (offset form skips the rest)
+    int32_t ct_active;  // column tiles holding RHS of this cell; offset forms: end of the job's
     int32_t crs;        // output row stride (doubles): the modes of a row are adjacent
     int32_t prec;       // offset forms: 1 = this job on FP32 MFMA (options.table_fp32), 0 = FP64
     // reduced forms: 1 = blocks gathered from the reduced table (a_off: byte offset of its mode),
     // 0 = streamed from the compact store; the (mode, tile)'s window has win_len chunks of 64 k',
     // this job starts at chunk win_a of it, and FP32 sums end where vs equal slices of it do
     int32_t gather, win_len, win_a, vs;
-    int32_t c0;         // reduced forms: first column tile of the job
+    int32_t c0;         // first column tile of the job
 };
 
 // Work lists of a persistent product launch: one list consumed by every work group (the

@@ -60,7 +60,7 @@ __device__ inline void tab_job(const GemmJob& jb, const TabView& tv, const doubl
         const int64_t o_zero = tv.zero_rec - (jb.a_off - tv.a_base) / 6;
         const uint32_t kb = tv.keys[cd.key_b + b0 + (lane & 15)];
         const uint32_t* keys = (const uint32_t*)tv.keys + cd.key_i + 4 * g;
-        const double2* b = (const double2*)(B + jb.b_off) + bpos(lane);
+        const double2* b = (const double2*)(B + jb.b_off) + (int64_t)jb.c0 * nch * 768 + bpos(lane);
         auto chunk_at = [&](int t) { return wrap_k(p0 + min(t, n - 1), nch); };
         double2 rec[4][6];
         auto load_rec = [&](int q, int o) {
@@ -190,19 +190,19 @@ __device__ inline void tab_job(const GemmJob& jb, const TabView& tv, const doubl
             const int bl = b0 + (F32 ? 4 * g + j : 4 * j + g);
 #pragma unroll
             for (int c = 0; c < 3; ++c)
-                C[jb.c_off + ((int64_t)x * mp + 3 * bl + c) * jb.crs + col] = acc[c][x][j];
+                C[jb.c_off + ((int64_t)(jb.c0 + x) * mp + 3 * bl + c) * jb.crs + col] = acc[c][x][j];
         }
 }
 
-// A job runs the column tiles that hold RHS of its cell (jb.ct_active, rounded up to a power
-// of two; the context's count CT is the largest of its cells'), so that a cell with few RHS
-// beside one with many does not multiply zeros.  B fragments in flight: 12 steps of one
-// column tile, 48 registers, for any count but 8 (64).
+// A job runs the column tiles [c0, ct_active) of its cell, rounded up to a power of two; the
+// context's count CT is the largest of its cells', so that a cell with few RHS beside one with many
+// does not multiply zeros.  B fragments in flight: 12 steps of one column tile, 48 registers, for
+// any count but 8 (64).
 template <int CT, int MIX>
 __device__ inline void tab_any(const GemmJob& jb, const TabView& tv, const double* __restrict__ B,
                                double* __restrict__ C, const CellDev* __restrict__ cells, float* lds) {
     if constexpr (CT > 1) {
-        if (2 * jb.ct_active <= CT) {
+        if (2 * (jb.ct_active - jb.c0) <= CT) {
             tab_any<CT / 2, MIX>(jb, tv, B, C, cells, lds);
             return;
         }
