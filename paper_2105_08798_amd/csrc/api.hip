@@ -448,6 +448,7 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
         }
     }
     HIPCHK(c, hipGetLastError());
+    unsigned long long* tab_amax = nullptr;        // largest magnitude per table mode, once it is known
     {
         // distance cut-off per table mode, then the windows of every cell
         std::vector<double> rho_cut(T, INFINITY);
@@ -460,6 +461,7 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
                 cleanup();
                 return s;
             }
+            tab_amax = st2;
             launch_tab_rhocut(st, c->tab, T, n_off, d1_d, d2_d, tau, st2, st2 + T);
             std::vector<unsigned long long> bits(T);
             HIPCHK(c, hipMemcpyAsync(bits.data(), st2 + T, (size_t)T * 8, hipMemcpyDeviceToHost, st));
@@ -580,15 +582,19 @@ static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, 
         }
         if (c->rbox.mode_bytes > 0) {
             const RBox& box = c->rbox;
-            unsigned long long* amax_t;
-            if ((s = dev_alloc(c, (void**)&c->rtab, T * box.mode_bytes)) != FBC_OK ||
-                (s = talloc((void**)&amax_t, (int64_t)T * 8)) != FBC_OK) {
+            if ((s = dev_alloc(c, (void**)&c->rtab, T * box.mode_bytes)) != FBC_OK) {
                 cleanup();
                 return s;
             }
             c->store_bytes += T * box.mode_bytes;
-            launch_tab_absmax(st, c->tab, T, n_off, amax_t);
-            launch_build_rtab(st, form, c->tab, T, n_off, d1_d, d2_d, box, amax_t, c->rtab);
+            if (form == FBC_FORM_SPLIT_FP16 && !tab_amax) {           // (its scales)
+                if ((s = talloc((void**)&tab_amax, (int64_t)T * 8)) != FBC_OK) {
+                    cleanup();
+                    return s;
+                }
+                launch_tab_absmax(st, c->tab, T, n_off, tab_amax);
+            }
+            launch_build_rtab(st, form, c->tab, T, n_off, d1_d, d2_d, box, tab_amax, c->rtab);
             HIPCHK(c, hipGetLastError());
         }
         int64_t* reg_d;
@@ -929,6 +935,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     apply_kernels_init();            // dynamic-LDS limits of the long-line transforms, before any capture
     hipStream_t st = (hipStream_t)stream;
     const int form = opt->form;
+    std::vector<char> col_data;                // column keys on their way to the device
 
     // plan: one column-tile count for the whole context (template of the product kernel),
     // rows padded to whole work-group tiles, K' padded to a multiple of 64
@@ -1220,11 +1227,13 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
                 keys.push_back((int32_t)plan_key(p.cols_i[2 * q], p.cols_i[2 * q + 1], c->w2));
             }
         }
-        if ((s = dev_alloc(c, (void**)&c->colkeys, (int64_t)keys.size() * 4)) != FBC_OK) goto fail_out;
-        if ((s = dev_alloc(c, (void**)&c->celldev, (int64_t)cd.size() * sizeof(CellDev))) != FBC_OK) goto fail_out;
-        HIPCHK(c, hipMemcpyAsync(c->colkeys, keys.data(), keys.size() * 4, hipMemcpyHostToDevice, st));
-        HIPCHK(c, hipMemcpyAsync(c->celldev, cd.data(), cd.size() * sizeof(CellDev), hipMemcpyHostToDevice, st));
-        HIPCHK(c, hipStreamSynchronize(st));
+        const size_t head = cd.size() * sizeof(CellDev);             // both in one allocation
+        col_data.resize(head + keys.size() * 4);
+        std::memcpy(col_data.data(), cd.data(), head);
+        std::memcpy(col_data.data() + head, keys.data(), keys.size() * 4);
+        if ((s = dev_alloc(c, (void**)&c->celldev, (int64_t)col_data.size())) != FBC_OK) goto fail_out;
+        c->colkeys = (int32_t*)(c->celldev + cd.size());
+        HIPCHK(c, hipMemcpyAsync(c->celldev, col_data.data(), col_data.size(), hipMemcpyHostToDevice, st));
     }
     product_stats(c);
     if (form == FBC_FORM_SURROGATE) c->nsplit = 1;     // slices are generated per mode chunk
@@ -1236,7 +1245,9 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     // longest first 3.86; 128 layers, 40 RHS 0.73, 0.79; 646 jobs at 60 RHS 156 us, 146);
     // mode-major chunks consumed by the persistent kernel for the surrogate
     {
-        const int64_t njobs = (int64_t)build_jobs(c, c->nsplit, 2).size();
+        int64_t njobs = 0;
+        for (const CellPlan& p : c->cells)
+            njobs += (int64_t)p.nm * (p.mp / JOB_ROWS) * c->nsplit * ((p.ctr + c->job_tiles - 1) / c->job_tiles);
         const int order = form == FBC_FORM_SURROGATE ? 3 : !is_table_form(form) && c->ctmax > 4 && njobs >= 2048 ? 4 : 2;
         if ((s = upload_jobs(c, c->nsplit, order, st)) != FBC_OK) goto fail_out;
     }

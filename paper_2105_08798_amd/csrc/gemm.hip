@@ -8,8 +8,9 @@
 // Two kinds of jobs share a launch, 128 rows of one (cell, mode) each:
 //  * stream: the tile's blocks are stored (compact store: the K chunks of its window, one
 //    contiguous run in MFMA fragment order, each wave-wide 16-byte load 1 KiB contiguous) and
-//    streamed once from HBM.  Only modes whose rows carry a row gauge take it (the
-//    subtracted mean makes an entry depend on the pad column, not on the offset alone).
+//    streamed once from HBM.  Modes whose rows carry a row gauge take it (the subtracted mean
+//    makes an entry depend on the pad column, not on the offset alone), tiles whose boxes do
+//    not fit, and every mode of FP32 contexts of eight column tiles.
 //  * gather: every other mode reads the table of distinct column offsets in the form's
 //    precision: the records of a K chunk's box of offsets are staged through LDS and read back as
 //    fragments (gather_job).
@@ -432,8 +433,9 @@ typedef unsigned u2_t __attribute__((ext_vector_type(2)));
 // chunk's columns shift them (rows may be permuted freely, the K order may not).  The column and
 // the component of k' depend on the lane only through its group g and the chunk number mod 3, so
 // they come from three per-lane constants each.  Bound by LDS, the vector operations and MFMA about
-// equally (1024 layers, 2048 / 4096 columns, 16 RHS, two column tiles, gathered modes alone: busy
-// 59, 50 and 32 % of 2.8 ms; with 16-byte planes and rows by place 65 % of 3.1).
+// equally (1024 layers, 2048 / 4096 columns, 16 RHS, two column tiles, no row gauge so that every mode
+// is gathered, 4.0 ms: busy 60, 50 and 32 %, 27 % of the LDS time bank conflicts; with 16-byte planes
+// and rows by place the modes that are gathered with the gauge took 3.1 ms, 2.8 now).
 // Bytes of a plane: 16 modulo 64, so that the three pairs of planes that a quad of lanes writes
 // fall into distinct banks.
 constexpr int G_PL = G_CAP * 8 + 16;
@@ -788,9 +790,9 @@ std::string gemm_shape(int form, int jt, int variant) {
     char buf[96];
     with_shape(form, jt, variant, [&](auto sh) {
         using SH = decltype(sh);
-        snprintf(buf, sizeof buf, "%s rows=%d CT=%d waves=%d KC=%d ring=%d S=%d, gather + stream",
+        snprintf(buf, sizeof buf, "%s rows=%d CT=%d waves=%d KC=%d ring=%d S=%d, %s",
                  form == FBC_FORM_FP32 ? "f32" : form == FBC_FORM_SPLIT_FP16 ? "f16" : "bf16", JOB_ROWS, SH::CT,
-                 SH::RG, SH::KC, SH::PF, SH::S);
+                 SH::RG, SH::KC, SH::PF, SH::S, SH::CT == 8 ? "stream" : "gather + stream");
     });
     return buf;
 }
