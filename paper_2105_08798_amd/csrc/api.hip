@@ -201,16 +201,32 @@ static double skip_tolerance(const fbc_options& o) {
                : 1e-16;
 }
 
+// Columns in the order `ord` (empty: as they are).
+static std::vector<int32_t> taken(const std::vector<int32_t>& cols, const std::vector<int32_t>& ord) {
+    if (ord.empty()) return cols;
+    std::vector<int32_t> out;
+    for (int32_t k : ord) out.insert(out.end(), {cols[2 * k], cols[2 * k + 1]});
+    return out;
+}
+
 static void compute_windows(fbc_ctx* c, const std::vector<double>& rho_cut, int rows_tile) {
     const bool dt = is_table_form(c->opt.form);
     for (CellPlan& p : c->cells) {
         PlanWindows w;
         const PlanGeom g{p.n_i, p.n_b, p.cols_i.data(), p.cols_b.data()};
         if (dt) {
+            // Tiles and chunks hold neighbours, also where the caller lists the columns in no such order: the
+            // windows would skip nothing, and a wave's records would share no cache lines.  Columns in
+            // random order, as they come / by angle: 128 layers, 1024 / 2048 columns, 8 RHS 3.95 and 0.96
+            // ms; 32 layers, 301 / 613 columns, 3 RHS 106 and 71 us; below 65536 pairs no gain (8 layers,
+            // 96 / 192 columns 22.2 and 23.6)
+            plan_order(g, p.ord_i, p.ord_b);
+            const std::vector<int32_t> ci = taken(p.cols_i, p.ord_i), cb = taken(p.cols_b, p.ord_b);
             std::vector<PlanRange> tiles, chunks;
             for (int b = 0; b < p.n_b; b += TAB_COLS) tiles.push_back({b, std::min(p.n_b, b + TAB_COLS)});
             for (int i = 0; i < p.n_i; i += TAB_COLS) chunks.push_back({i, std::min(p.n_i, i + TAB_COLS)});
-            plan_windows_ranges(g, p.nm, tiles, chunks, c->nz_max / p.nz, rho_cut, w);
+            plan_windows_ranges(PlanGeom{p.n_i, p.n_b, ci.data(), cb.data()}, p.nm, tiles, chunks, c->nz_max / p.nz,
+                                rho_cut, w);
             if (c->opt.table_fp32) {
                 // which modes count as skipping, and so run in FP32, is decided on tiles of 32 pad and
                 // chunks of 8 interface columns: part of what the option computes, whatever the tiles of
@@ -1164,6 +1180,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         // column keys of the offset-table products and of the gather jobs (see CellDev)
         std::vector<CellDev> cd;
         std::vector<int32_t> keys;
+        std::vector<std::pair<int, int64_t>> place_at;       // cell, where in the keys its places lie
         for (auto& p : c->cells) {
             if (!is_table_form(form)) {
                 CellDev v{};
@@ -1216,15 +1233,24 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
                 continue;
             }
             const int nb = (int)roundup(p.n_b, TAB_COLS), ni = (int)roundup(p.n_i, TAB_COLS);
-            cd.push_back(CellDev{(int64_t)keys.size(), (int64_t)keys.size() + nb, 0, 0, 0, 0});
+            cd.push_back(CellDev{(int64_t)keys.size(), (int64_t)keys.size() + nb, -1, 0, 0, 0, 0});
+            const std::vector<int32_t> ci = taken(p.cols_i, p.ord_i), cb = taken(p.cols_b, p.ord_b);
             for (int b = 0; b < nb; ++b) {
                 const int q = std::min(b, p.n_b - 1);
-                keys.push_back((int32_t)(plan_key(p.cols_b[2 * q], p.cols_b[2 * q + 1], c->w2) -
-                                         plan_key(c->d1min, c->d2min, c->w2)));
+                keys.push_back((int32_t)(plan_key(cb[2 * q], cb[2 * q + 1], c->w2) - plan_key(c->d1min, c->d2min, c->w2)));
             }
             for (int x = 0; x < ni; ++x) {             // [chunk][g][q] holds column 16 chunk + 4 q + g
                 const int q = std::min((x & ~15) + 4 * (x & 3) + ((x >> 2) & 3), p.n_i - 1);
-                keys.push_back((int32_t)plan_key(p.cols_i[2 * q], p.cols_i[2 * q + 1], c->w2));
+                keys.push_back((int32_t)plan_key(ci[2 * q], ci[2 * q + 1], c->w2));
+            }
+            if (!p.ord_b.empty()) {
+                cd.back().order_b = (int64_t)keys.size();
+                for (int b = 0; b < nb; ++b) keys.push_back(b < p.n_b ? p.ord_b[b] : b);
+            }
+            if (!p.ord_i.empty()) {
+                place_at.push_back({(int)(&p - c->cells.data()), (int64_t)keys.size()});
+                keys.resize(keys.size() + p.n_i);
+                for (int i = 0; i < p.n_i; ++i) keys[place_at.back().second + p.ord_i[i]] = i;
             }
         }
         const size_t head = cd.size() * sizeof(CellDev);             // both in one allocation
@@ -1233,6 +1259,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
         std::memcpy(col_data.data() + head, keys.data(), keys.size() * 4);
         if ((s = dev_alloc(c, (void**)&c->celldev, (int64_t)col_data.size())) != FBC_OK) goto fail_out;
         c->colkeys = (int32_t*)(c->celldev + cd.size());
+        for (const auto& a : place_at) c->cells[a.first].place_i = c->colkeys + a.second;
         HIPCHK(c, hipMemcpyAsync(c->celldev, col_data.data(), col_data.size(), hipMemcpyHostToDevice, st));
     }
     product_stats(c);
@@ -1297,7 +1324,7 @@ static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st, bool re
                        comp ? c->shat_on + p.rhs0 : nullptr,
                        c->opt.check_netforce || c->opt.project_netforce || comp || f16, c->opt.netforce_tol,
                        c->opt.check_netforce, c->opt.project_netforce, bm, p.R, p.nz, p.n_i, p.kp, p.ct,
-                       c->tw + p.tw_off, bexp, c->status,
+                       c->tw + p.tw_off, bexp, c->status, p.place_i,
                        relax ? RelaxIn{c->fprev + p.f_off, c->rpart + c->rpart_off[ci], c->alpha + p.rhs0,
                                        c->finf + p.rhs0, c->status + 4, c->ropt.relax, c->ropt.alpha_min}
                              : RelaxIn{});
@@ -1337,7 +1364,7 @@ static void enqueue_forward(fbc_ctx* c, const double* f, hipStream_t st, bool re
     } else if (form == FBC_FORM_DTABLE_FP64 && c->hmat) {
         const CellPlan& p = c->cells[0];          // one cell (checked when attached)
         hmat_enqueue_pipeline(c->hmat, (const double*)c->bfrag + p.b_off, b_mode_elems(form, p), p.kp,
-                              c->cbuf + p.c_off, p.mp, p.nm, p.ct, st);
+                              p.place_i, c->cbuf + p.c_off, p.mp, p.nm, p.ct, st);
     } else if (is_table_form(form)) {
         const TabView tv{c->tab, 0, c->lut, c->colkeys, nullptr, c->n_offsets, 0};
         launch_gemm_dtab(st, c->jobs, c->njobs, c->ctmax, tv, (const double*)c->bfrag, c->cbuf, c->celldev,
@@ -1899,13 +1926,16 @@ extern "C" fbc_status fbc_copy_block_rows(fbc_ctx* c, int cell, int m, int b0, i
     HIPCHK(c, hipMemcpy(tabm.data(), c->tab + (int64_t)m * mult * c->n_offsets * 6, tabm.size() * 16,
                         hipMemcpyDeviceToHost));
     OffsetSet os = offsets_of(c->cells);
+    std::vector<int> at_b(p.n_b), at_i(p.n_i);           // the columns' places in tiles and chunks
+    for (int b = 0; b < p.n_b; ++b) at_b[p.ord_b.empty() ? b : p.ord_b[b]] = b;
+    for (int i = 0; i < p.n_i; ++i) at_i[p.ord_i.empty() ? i : p.ord_i[i]] = i;
     for (int b = b0; b < b1; ++b) {
-        const size_t r = (size_t)m * p.n_tiles + b / TAB_COLS;
+        const size_t r = (size_t)m * p.n_tiles + at_b[b] / TAB_COLS;
         for (int i = 0; i < p.n_i; ++i) {
             const int x = p.cols_b[2 * b] - p.cols_i[2 * i] - os.d1min;
             const int y = p.cols_b[2 * b + 1] - p.cols_i[2 * i + 1] - os.d2min;
             const int64_t o = os.lut[(size_t)x * os.w2 + y];
-            const bool in = !windows || (i / TAB_COLS - p.win_start[r] + p.n_chunks) % p.n_chunks < p.win_len[r];
+            const bool in = !windows || (at_i[i] / TAB_COLS - p.win_start[r] + p.n_chunks) % p.n_chunks < p.win_len[r];
             for (int cc = 0; cc < 3; ++cc)
                 for (int d = 0; d < 3; ++d) {
                     const double2 v = in ? tabm[o * 6 + sym_idx(cc, d)] : make_double2(0.0, 0.0);

@@ -343,7 +343,8 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
                                                   void* __restrict__ bfrag, int nz, int logn,
                                                   int n_i, int kp, int ct, int ltc,
                                                   const double2* __restrict__ tw, double inv_cnt,
-                                                  const int* __restrict__ bexp, int pairs, NfTotal nf, int ny, int totals,
+                                                  const int* __restrict__ bexp, int pairs,
+                                                  const int32_t* __restrict__ place, NfTotal nf, int ny, int totals,
                                                   RelaxIn rx) {
     extern __shared__ double2 lds[];
     if constexpr (NTH == NT)
@@ -446,8 +447,9 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
             }
             if (m == 0 || 2 * m == nz) fi = 0.0;
             double* bm = (double*)bfrag + m * mode_elems;
-            *(double2*)(bm + tab_frag_off(nre, k, nch)) = make_double2(fr, -fi);
-            *(double2*)(bm + tab_frag_off(nim, k, nch)) = make_double2(fi, fr);
+            const int at = place ? 3 * place[k / 3] + k % 3 : k;      // (its place in the product's K order)
+            *(double2*)(bm + tab_frag_off(nre, at, nch)) = make_double2(fr, -fi);
+            *(double2*)(bm + tab_frag_off(nim, at, nch)) = make_double2(fi, fr);
         }
         __syncthreads();        // the next chunk overwrites the LDS sequences
         continue;
@@ -526,7 +528,7 @@ __global__ void __launch_bounds__(NTH) k_line_rfft(const double* __restrict__ f,
 
 void launch_forward(hipStream_t st, int form, const double* f, double* sums, double* tot, double2* shat, int* shat_on,
                     bool statistics, double tol, int check, int project, void* bfrag, int R, int nz, int n_i, int kp,
-                    int ct, const double2* tw, int* bexp, int* status, const RelaxIn& rx) {
+                    int ct, const double2* tw, int* bexp, int* status, const int32_t* place, const RelaxIn& rx) {
     int logn = 0;
     while ((1 << logn) < nz) ++logn;
     const int K = 3 * n_i;
@@ -579,10 +581,10 @@ void launch_forward(hipStream_t st, int form, const double* f, double* sums, dou
     do {                                                                                                    \
         if (wide) {                                                                                         \
             hipLaunchKernelGGL((k_line_rfft<FM, 1024>), grid, dim3(1024), lds, st, f, tot, project, bfrag, nz, logn, \
-                               n_i, kp, ct, ltc, tw, inv_cnt, bexp, pairs, nf, ny, totals, rx);              \
+                               n_i, kp, ct, ltc, tw, inv_cnt, bexp, pairs, place, nf, ny, totals, rx);       \
         } else {                                                                                            \
             hipLaunchKernelGGL((k_line_rfft<FM, NT>), grid, dim3(NT), lds, st, f, tot, project, bfrag, nz, logn, \
-                               n_i, kp, ct, ltc, tw, inv_cnt, bexp, pairs, nf, ny, totals, rx);              \
+                               n_i, kp, ct, ltc, tw, inv_cnt, bexp, pairs, place, nf, ny, totals, rx);       \
         }                                                                                                   \
     } while (0)
     switch (form) {

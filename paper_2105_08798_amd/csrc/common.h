@@ -140,6 +140,7 @@ __device__ inline T uniform_at(const T* p) {
 // column repeated), interface columns up to whole chunks of 16 in the order [chunk][g][q].
 struct CellDev {
     int64_t key_b, key_i;    // offsets into TabView::keys
+    int64_t order_b;         // pad column of each place in the tiles (the same keys), -1: as they come
     // reduced forms, offsets into RTabView::keys: interface columns (n1, n2) in natural order, the last
     // one repeated past the end; per chunk of 64 k' the smallest and largest n1 and the largest n2 of
     // its columns (four ints); per JOB_ROWS rows the smallest n1, the range of n1, the smallest n2
@@ -205,6 +206,10 @@ struct CellPlan {
     int n_tiles = 0, n_chunks = 0;
     std::vector<int32_t> win_start, win_len;   // [nm][n_tiles]
     std::vector<uint8_t> mode_skips;           // [nm]: some chunk of this mode is skipped
+    // offset-table forms: column at each place of the tiles and chunks (plan_order; empty: as they
+    // come), and on the device the place of each interface column (NULL: as they come)
+    std::vector<int32_t> ord_b, ord_i;
+    const int32_t* place_i = nullptr;
     std::vector<uint8_t> gather;               // [nm][n_tiles]: reduced forms: blocks from the reduced table (RTabView)
     // Compact dense store of the tiles that are not gathered: region r = m n_tiles + tl holds the
     // win_len[r] chunk-tiles of that window from chunk-tile reg_pre[r] on (cell-local); n_ct =

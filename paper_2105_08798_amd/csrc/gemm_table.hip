@@ -182,16 +182,21 @@ __device__ inline void tab_job(const GemmJob& jb, const TabView& tv, const doubl
     }
     const int64_t mp = (int64_t)jb.mb * 16;
     const int col = lane & 15;
+    auto put = [&](auto place) {
 #pragma unroll
-    for (int x = 0; x < CT; ++x)
+        for (int x = 0; x < CT; ++x)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            // output rows of the 16x16 MFMAs: FP64 4 j + lane / 16, FP32 4 (lane / 16) + j
-            const int bl = b0 + (F32 ? 4 * g + j : 4 * j + g);
+            for (int j = 0; j < 4; ++j) {
+                // output rows of the 16x16 MFMAs: FP64 4 j + lane / 16, FP32 4 (lane / 16) + j
+                const int bl = place(b0 + (F32 ? 4 * g + j : 4 * j + g));
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-                C[jb.c_off + ((int64_t)(jb.c0 + x) * mp + 3 * bl + c) * jb.crs + col] = acc[c][x][j];
-        }
+                for (int c = 0; c < 3; ++c)
+                    C[jb.c_off + ((int64_t)(jb.c0 + x) * mp + 3 * bl + c) * jb.crs + col] = acc[c][x][j];
+            }
+    };
+    const int order_b = __builtin_amdgcn_readfirstlane((int)cd.order_b);
+    if (order_b < 0) put([](int b) { return b; });
+    else put([&](int b) { return tv.keys[order_b + b]; });
 }
 
 // A job runs the column tiles [c0, ct_active) of its cell, rounded up to a power of two; the

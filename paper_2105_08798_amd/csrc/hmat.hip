@@ -81,6 +81,7 @@ struct HIo {
     const double* bf;      // fragments of mode 0; mode m at + m * bf_mode
     int64_t bf_mode;
     int kp;
+    const int32_t* place;  // CellPlan::place_i of the fragments
     double* rec;           // records of the cell
     int mp, nm;
     int r_out;             // RHS slots written per row: R (plain) or 8 x tiles (records)
@@ -101,7 +102,10 @@ __global__ void __launch_bounds__(NTH) k_hmat_x(HIo io, int n_i, int R, int Rp, 
         double2 v = make_double2(0, 0);
         if (r < R) {
             if constexpr (PIPE)
-                v = make_double2(b[tab_frag_off(16 * tile + j, col, nch)], b[tab_frag_off(16 * tile + j + 8, col, nch)]);
+                {
+                const int k = io.place ? 3 * io.place[col / 3] + col % 3 : col;
+                v = make_double2(b[tab_frag_off(16 * tile + j, k, nch)], b[tab_frag_off(16 * tile + j + 8, k, nch)]);
+            }
             else
                 v = io.x[((int64_t)m * 3 * n_i + col) * R + r];
         }
@@ -764,12 +768,13 @@ extern "C" fbc_status fbc_hmat_apply(fbc_hmat* h, const double* fhat, double* wh
 
 // The product step of a context's apply pipeline (fbc_set_hmat): B fragments in, product
 // records out (one K slice).
-void hmat_enqueue_pipeline(fbc_hmat* h, const double* bfrag, int64_t bf_mode, int kp, double* rec, int mp, int nm,
-                           int ct, hipStream_t st) {
+void hmat_enqueue_pipeline(fbc_hmat* h, const double* bfrag, int64_t bf_mode, int kp, const int32_t* place, double* rec,
+                           int mp, int nm, int ct, hipStream_t st) {
     HIo io{};
     io.bf = bfrag;
     io.bf_mode = bf_mode;
     io.kp = kp;
+    io.place = place;
     io.rec = rec;
     io.mp = mp;
     io.nm = nm;

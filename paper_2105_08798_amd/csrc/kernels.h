@@ -62,10 +62,10 @@ struct RelaxClamp {
     int relax;
 };
 // launch_forward: these (if `statistics`; bexp: also the operand scale of split FP16), then the
-// transforms of f into the product's B fragments.
+// transforms of f into the product's B fragments (place: CellPlan::place_i, offset-table forms).
 void launch_forward(hipStream_t st, int form, const double* f, double* sums, double* tot, double2* shat, int* shat_on,
                     bool statistics, double tol, int check, int project, void* bfrag, int R, int nz, int n_i, int kp,
-                    int ct, const double2* tw, int* bexp, int* status, const RelaxIn& rx);
+                    int ct, const double2* tw, int* bexp, int* status, const int32_t* place, const RelaxIn& rx);
 // Reduced forms.  variant: one of gemm_variants(form, jt) kernel instantiations (bitwise the
 // same result); q != NULL: persistent work-queue kernel on these lists.
 void launch_gemm(hipStream_t st, int form, const GemmJob* jobs, int njobs, int jt, const void* a,
@@ -81,8 +81,8 @@ std::string gemm_shape(int form, int jt, int variant);
 void launch_gemm_dtab(hipStream_t st, const GemmJob* jobs, int njobs, int ct, const TabView& tv, const double* b,
                       double* c, const CellDev* cells, const PqLists* q, int mixed, int variant);
 // H-matrix product step (hmat.hip): B fragments of one FP64 cell in, product records out
-void hmat_enqueue_pipeline(fbc_hmat* h, const double* bfrag, int64_t bf_mode, int kp, double* rec, int mp, int nm,
-                           int ct, hipStream_t st);
+void hmat_enqueue_pipeline(fbc_hmat* h, const double* bfrag, int64_t bf_mode, int kp, const int32_t* place, double* rec,
+                           int mp, int nm, int ct, hipStream_t st);
 const fbc_ctx* hmat_context(const fbc_hmat* h);
 void irfft_shape(int nz, int* tr, int* pp);
 void launch_line_irfft(hipStream_t st, const double* c, double* w, double* wmax_part, int R,

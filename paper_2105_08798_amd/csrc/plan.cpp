@@ -53,6 +53,47 @@ PlanOffsets plan_offsets(const std::vector<PlanGeom>& cells) {
     return o;
 }
 
+void plan_order(const PlanGeom& g, std::vector<int32_t>& ord_i, std::vector<int32_t>& ord_b) {
+    // places relative to the first interface column: the same wherever the cell lies
+    auto place = [&](const int32_t* c, double& x, double& y) {
+        const double d1 = (double)((int64_t)c[0] - g.cols_i[0]), d2 = (double)((int64_t)c[1] - g.cols_i[1]);
+        x = 0.5 * d1;
+        y = (d1 + 2.0 * d2) * (0.5 * M_SQRT1_2);
+    };
+    double x0 = 0.0, y0 = 0.0;
+    for (int k = 0; k < g.n_i; ++k) {
+        double x, y;
+        place(g.cols_i + 2 * k, x, y);
+        x0 += x / g.n_i;
+        y0 += y / g.n_i;
+    }
+    auto order = [&](const int32_t* cols, int n, std::vector<int32_t>& ord) {
+        std::vector<double> x(n), y(n), phi(n), r(n);
+        for (int k = 0; k < n; ++k) {
+            place(cols + 2 * k, x[k], y[k]);
+            phi[k] = std::atan2(y[k] - y0, x[k] - x0);
+            r[k] = std::hypot(x[k] - x0, y[k] - y0);
+        }
+        ord.resize(n);
+        for (int k = 0; k < n; ++k) ord[k] = k;
+        std::sort(ord.begin(), ord.end(), [&](int32_t a, int32_t b) {
+            return phi[a] != phi[b] ? phi[a] < phi[b] : r[a] != r[b] ? r[a] < r[b] : a < b;
+        });
+        double given = 0.0, sorted = 0.0, mean_r = 0.0;
+        for (int k = 0; k < n; ++k) mean_r += r[k] / n;
+        for (int k = 1; k < n; ++k) {
+            given += std::hypot(x[k] - x[k - 1], y[k] - y[k - 1]) / (n - 1);
+            sorted += std::hypot(x[ord[k]] - x[ord[k - 1]], y[ord[k]] - y[ord[k - 1]]) / (n - 1);
+        }
+        if (given <= 0.75 * mean_r || given <= 4.0 * sorted) ord.clear();
+    };
+    ord_i.clear();
+    ord_b.clear();
+    if ((int64_t)g.n_i * g.n_b < 65536) return;
+    order(g.cols_i, g.n_i, ord_i);
+    order(g.cols_b, g.n_b, ord_b);
+}
+
 double plan_pair_rho(int32_t a1, int32_t a2, int32_t b1, int32_t b2) {
     const int d1 = a1 - b1, d2 = a2 - b2;
     const double x = 0.5 * d1, y = (d1 + 2.0 * d2) * (0.5 * M_SQRT1_2);
