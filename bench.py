@@ -64,18 +64,9 @@ def io_bytes(cells, form: str) -> dict:
 
 
 def kernel_matches(form: str, name: str) -> bool:
-    """Whether a profiled kernel name is the product kernel of a form (either launch form:
+    """Whether a profiled kernel is the product kernel of a form's kind (either launch form:
     one work group per job, or the persistent work-queue kernel `..._pq`)."""
-    name = name.replace("_pq<", "<")
-    if form == "fp64":
-        return name.startswith("k_gemm_f64<")
-    if form == "fp32":
-        return name.startswith("k_gemm_f32<")
-    if form == "split_bf16":
-        return name.startswith("k_gemm_split") and "bf16" in name
-    if form == "split_fp16":
-        return name.startswith("k_gemm_split") and "f16x8" in name
-    return name.startswith("k_gemm_dtab<")
+    return name.startswith("k_gemm" if form in ("fp32", "split_bf16", "split_fp16") else "k_tab")
 
 
 def measured_traffic(workload: str, form: str, product_bytes: float, tuned: dict | None):
@@ -273,6 +264,7 @@ def time_form(torch, wl, form: str, steps: int, warmup: int, graph: bool, tune: 
         log(f"{form}: unbalanced forces {extra['unbalanced_ms_per_step']:.3f} ms/step, "
             f"relax step {extra['relax_step_ms']:.3f} ms")
     store_bytes = ctx.info.store_bytes
+    kernel_shape = ctx.info.kernel_shape.decode()
     prod = dict(bytes=ctx.info.product_bytes, flops=ctx.info.product_flops,
                 skipped_fraction=ctx.info.skipped_fraction)
     rc = ctx.sync_status(stream=stream)
@@ -293,7 +285,7 @@ def time_form(torch, wl, form: str, steps: int, warmup: int, graph: bool, tune: 
     ms = 1000.0 * dt / steps
     total_rhs = sum(c.n_rhs for c in wl.cells)
     out = dict(ms_per_step=ms, updates_per_s=total_rhs / (ms / 1000.0), assembly_s=t_asm,
-               store_bytes=int(store_bytes), autotune=tuned,
+               store_bytes=int(store_bytes), autotune=tuned, kernel_shape=kernel_shape,
                gemm_ms=(gemm_ms / n_gemm) if n_gemm else None, gemm_launches_timed=n_gemm,
                graph=bool(graph), surrogate_training=sur_info, product=prod, **extra)
     log(f"{form}: {ms:.3f} ms/step, GEMM {out['gemm_ms']} ms, {out['updates_per_s']:.1f} updates/s")
@@ -388,18 +380,22 @@ def roofline_of(form: str, r: dict) -> dict:
     """Roofline of the product kernel of one form: algorithmic bytes (the stored blocks it
     does not skip, f^ and w^) or flops (8 per complex multiply-add of those blocks) per
     launch over its average launch time, against the roof its arithmetic intensity puts it
-    under."""
+    under.  hbm_frac and mfma_frac (the executed products, three per algorithmic one in the
+    split forms) give both; limits says what holds the reduced forms below them."""
     gm = r["gemm_ms"]
     b, fl = r["product"]["bytes"], r["product"]["flops"]
     gbs = b / (gm * 1e-3) / 1e9
     tfs = fl / (gm * 1e-3) / 1e12
     peak = PEAK_TFLOPS[form]
     mfma_bound = fl * MFMA_PER_ALG.get(form, 1.0) / b > peak * 1e3 / HBM_PEAK_GBS
-    if mfma_bound:
-        return dict(bound="mfma", achieved=tfs, peak=peak, unit="TFLOP/s", frac=tfs / peak,
-                    flops_per_launch=fl, bytes_per_launch=b)
-    return dict(bound="hbm", achieved=gbs, peak=HBM_PEAK_GBS, unit="GB/s", frac=gbs / HBM_PEAK_GBS,
+    both = dict(hbm_frac=gbs / HBM_PEAK_GBS, mfma_frac=tfs * MFMA_PER_ALG.get(form, 1.0) / peak,
                 bytes_per_launch=b, flops_per_launch=fl)
+    if form in ("fp32", "split_bf16", "split_fp16"):
+        both["limits"] = ("FP32 MFMA" if "CT=8" in r["kernel_shape"] else
+                          "gathered modes: LDS, vector operations and MFMA about equally; streamed modes: HBM")
+    if mfma_bound:
+        return dict(bound="mfma", achieved=tfs, peak=peak, unit="TFLOP/s", frac=tfs / peak, **both)
+    return dict(bound="hbm", achieved=gbs, peak=HBM_PEAK_GBS, unit="GB/s", frac=gbs / HBM_PEAK_GBS, **both)
 
 
 def run_workload(torch, args, name: str, forms: list, extras_for=None) -> dict:
@@ -464,9 +460,10 @@ def run_workload(torch, args, name: str, forms: list, extras_for=None) -> dict:
 
 
 # Real-space periodic Green function (fbc_plgf_eval): algorithmic FP64 flops of one
-# continuum evaluation (64 circle nodes x 69 flops: node vector 9, acoustic tensor 24,
-# symmetric inverse 30, accumulation 6; wave sum 36; set-up 48) and of one image term.
-PLGF_FLOPS_KELVIN = 64 * 69 + 36 + 48
+# continuum evaluation (32 circle nodes, half of the 64, x 60 flops: acoustic tensor as a
+# trigonometric polynomial 24, symmetric inverse 30, accumulation 6; set-up 130) and of one
+# image term.
+PLGF_FLOPS_KELVIN = 32 * 60 + 130
 PLGF_FLOPS_IMAGE = 12
 FP64_VECTOR_PEAK = 78.6
 
@@ -551,8 +548,8 @@ def bench_plgf(args, torch) -> dict:
 
 def bench_hmat(args, torch) -> dict:
     """H-matrix form (Appendix C: b_min = 20, gamma = 2, eps = 1e-5) of every line mode of
-    the medium cell, built from an FP64 offset-table context (no dense store); the H-matrix
-    product over all modes against the dense FP64 product of the same cell."""
+    the medium cell, built from an FP64 offset-table context; the H-matrix product over all
+    modes against the FP64 form's product of the same cell."""
     import fbc_workloads as W
     from paper_2105_08798_amd import FBC, HMatrix
     wl = W.make_single("medium")
@@ -580,7 +577,7 @@ def bench_hmat(args, torch) -> dict:
     e1.record(st)
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / args.steps
-    # dense FP64 product of the same cell (its own kernel timing)
+    # the FP64 form's product of the same cell (its own kernel timing)
     ctx = FBC(wl.cells, wl.bz, form="fp64")
     f = torch.from_numpy(c.forces.ravel().copy()).to(dev)
     w = torch.zeros(R * c.nz * c.n_b * 3, dtype=torch.float64, device=dev)
@@ -595,8 +592,8 @@ def bench_hmat(args, torch) -> dict:
     dense_ms, n_d = ctx.timing_read()
     dense_ms = dense_ms / max(n_d, 1)
 
-    # whole fbc_apply steps: dense FP64 store, offset-table product, and the H-matrix
-    # attached as the table context's product step
+    # whole fbc_apply steps: the FP64 form, the offset-table form, and the H-matrix attached as
+    # the table context's product step
     def apply_ms(cx):
         u = torch.zeros(R * c.nz * c.n_b * 3, dtype=torch.float64, device=dev)
         for _ in range(2):
@@ -618,7 +615,7 @@ def bench_hmat(args, torch) -> dict:
     step_ms["dtable_fp64+hmat"], u_h = apply_ms(tab)
     tab.set_hmat(None)
     upd_err = float(np.linalg.norm(u_h - u_dense) / np.linalg.norm(u_dense))
-    log(f"hmat: fbc_apply ms/step {step_ms}; H-matrix update vs dense FP64 update {upd_err:.2e}")
+    log(f"hmat: fbc_apply ms/step {step_ms}; H-matrix update vs FP64 update {upd_err:.2e}")
     info = h.info
     from oracle import green
     yy = y.cpu().numpy()
@@ -631,7 +628,7 @@ def bench_hmat(args, torch) -> dict:
     bytes_ = info.stored_entries * 16 + nm * 3 * (c.n_i + c.n_b) * R * 16
     log(f"hmat: build {t_build:.2f} s, {info.n_blocks} blocks ({info.n_low_rank} low rank), max rank "
         f"{info.max_rank_used}, stored {info.stored_entries / info.dense_entries:.3f} of dense, "
-        f"{ms:.3f} ms per product (dense FP64 product {dense_ms:.3f} ms), errors {errs}")
+        f"{ms:.3f} ms per product (FP64 form's product {dense_ms:.3f} ms), errors {errs}")
     line = {
         "metric": "H-matrix products/s over all line modes (Appendix C form, FP64)",
         "value": 1e3 / ms, "unit": "products/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,

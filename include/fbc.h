@@ -79,8 +79,12 @@ typedef enum {
 typedef enum {
     FBC_FORM_FP64 = 0,        /* FP64: blocks gathered from the table of distinct column
                                  offsets (FBC_FORM_DTABLE_FP64's product), FP64 MFMA         */
-    FBC_FORM_FP32 = 1,        /* dense FP32 complex blocks, FP32 MFMA, FP64 across K chunks   */
-    FBC_FORM_SPLIT_BF16 = 2,  /* dense split-BF16 (hi+lo) blocks, BF16 MFMA with FP32
+    /* The reduced forms (FP32, split BF16, split FP16) read the blocks of a line mode from a
+     * table of column offsets in their precision where its rows carry no gauge (row_gauge)
+     * and the columns come in a neighbourly order (fbc_cell), from stored blocks elsewhere;
+     * FP32 with more than 56 RHS per cell stores all of them.  The result is the same. */
+    FBC_FORM_FP32 = 1,        /* FP32 complex blocks, FP32 MFMA, FP64 across K chunks         */
+    FBC_FORM_SPLIT_BF16 = 2,  /* split-BF16 (hi+lo) blocks, BF16 MFMA with FP32
                                  accumulation inside K chunks and FP64 across them            */
     FBC_FORM_DTABLE_FP64 = 3, /* FP64 table over distinct column offsets (entries depend on
                                  n_b - n_i only), gathered into the operands of FP64 MFMA;
@@ -92,7 +96,7 @@ typedef enum {
                                  function plus a learned correction (Appendix B: exact
                                  near field, continuum far field; bands below); needs
                                  options.surrogate with MLP weights set                    */
-    FBC_FORM_SPLIT_FP16 = 5   /* dense split-FP16 blocks, scaled per line mode by a power of
+    FBC_FORM_SPLIT_FP16 = 5   /* split-FP16 blocks, scaled per line mode by a power of
                                  two (hi = fp16(2^e G), lo = fp16(2^e G - hi): 22 bits at the
                                  bytes of split BF16), forces likewise scaled per call, FP16
                                  MFMA with FP32 accumulation inside K chunks, FP64 across  */
@@ -115,9 +119,14 @@ typedef struct {
     int nz;                  /* layers along the line, power of two in [2, 4096]          */
     int n_i;                 /* interface columns (>= 1)                                   */
     int n_b;                 /* pad columns (>= 1)                                         */
-    int n_rhs;               /* force right-hand sides applied per call, in [1, 65535]     */
+    int n_rhs;               /* force right-hand sides applied per call, in [1, 64]        */
     const int32_t* cols_i;   /* host [n_i][2] (n1, n2); copied, not retained               */
     const int32_t* cols_b;   /* host [n_b][2] (n1, n2); copied, not retained               */
+    /* Any order of the columns is right.  The reduced forms are fastest where columns that
+     * follow one another are neighbours in the plane, as by angle around the core: any 43
+     * pad and 12 interface columns in a row should span a box of at most 384 lattice
+     * offsets, else their blocks are stored and streamed, at the price of memory and time.
+     * The FP64 forms take columns at random or by distance in an order of their own. */
 } fbc_cell;
 
 typedef struct {
@@ -151,6 +160,8 @@ typedef struct {
                                 FP64 across them -- and FP64 MFMA at the modes without
                                 skipping (mode 0 among them: its long-range part carries
                                 the gauge constant); error of the order of the FP32 form's.
+                                Not faster than 0 on MI355X (1024 layers, 4096 / 8192
+                                columns, 16 RHS, learned form: 43.4 against 39.2 ms).
                                 0 (default) = FP64 MFMA everywhere.  FBC_E_ARG for other
                                 values or forms                                           */
 } fbc_options;
@@ -161,8 +172,9 @@ void fbc_default_options(fbc_options* opt);
 
 /* Assembles G^(m) for m = 0..N_z/2 of every cell on the device (Appendix B, discrete
  * Brillouin-zone sum in FP64, then the chosen store), and the plan and scratch buffers.
- * Done once per geometry (Section 3.2: built once, reused).  stream: hipStream_t or
- * NULL.  Synchronises the stream before returning.  On success *out owns everything. */
+ * Done once per geometry (Section 3.2: built once, reused).  FBC_E_UNSUPPORTED for an FP64,
+ * offset-table or surrogate form whose column offsets spread over more than 2^32 lattice
+ * places (their lookup alone would take 16 GiB).  stream: hipStream_t or NULL.  Synchronises the stream before returning.  On success *out owns everything. */
 fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cells, int n_cells,
                           const fbc_options* opt, void* stream, fbc_ctx** out);
 
@@ -449,14 +461,15 @@ fbc_status fbc_mlp_adam_step(fbc_mlp* m, float lr, void* stream);
 fbc_status fbc_mlp_forward(fbc_mlp* m, const float* x, float* y, int n, void* stream);
 /* For callers that cannot allocate device memory (code under HIP graph capture, serving
  * loops, harnesses that forbid hipMalloc): the same forward pass (same kernels, bitwise the
- * result of fbc_mlp_forward) with the layer activations kept in a workspace of 64 MiB that
- * the library holds statically on every GPU it runs on (until the process ends) instead
- * of the network's own workspace; n is not limited by max_batch but by that workspace:
+ * result of fbc_mlp_forward); what it stages, an output that overlaps its input, goes to a
+ * workspace of 64 MiB that the library holds statically on every GPU it runs on (until the
+ * process ends) instead of the network's own; n is not limited by max_batch:
  * n in [1, fbc_mlp_forward_noalloc_max_rows()] (10591 rows), else FBC_E_ARG.  Calls no
  * allocating routine; asynchronous on `stream`.  The network's device must be current
- * (FBC_E_ARG otherwise).  All calls on one GPU share the workspace: calls that overlap on
- * one GPU (other streams, other threads) race; calls ordered on one stream do not.  Every
- * workspace value is written before it is read, so nothing carries over between calls. */
+ * (FBC_E_ARG otherwise).  All calls on one GPU share the workspace: calls with y over x that
+ * overlap on one GPU (other streams, other threads) race; calls ordered on one stream do
+ * not.  Every workspace value is written before it is read, so nothing carries over
+ * between calls. */
 fbc_status fbc_mlp_forward_noalloc(const fbc_mlp* m, const float* x, float* y, int n, void* stream);
 int fbc_mlp_forward_noalloc_max_rows(void);
 /* ------------------------------------------------------------------------------------
@@ -529,7 +542,7 @@ fbc_status fbc_plgf_eval(fbc_plgf* p, const int32_t* disp, int64_t n, int nz, in
  * row of the block first, then the unused row of largest |u_k|; stop when
  * |u_k| |v_k| <= eps ||S_k||_F holds for two consecutive terms); rows and columns of a
  * block follow the tree order (first child's columns, then the second's).  A block that
- * needs more than max_rank terms is applied from the dense store instead.  Paper:
+ * needs more than max_rank terms is applied from the offset table instead.  Paper:
  * b_min = 20, gamma = 2, eps = 1e-5.
  * ------------------------------------------------------------------------------------ */
 typedef struct fbc_hmat fbc_hmat;

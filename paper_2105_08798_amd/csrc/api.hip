@@ -143,7 +143,7 @@ static bool is_table_form(int form) {        // products over the FP64 offset ta
     return form == FBC_FORM_FP64 || form == FBC_FORM_DTABLE_FP64 || form == FBC_FORM_SURROGATE;
 }
 
-// Row gauge: reduced dense forms store G^_bi(m) - mean_i G^_bi(m) (smaller dynamic range
+// Row gauge: reduced forms store G^_bi(m) - mean_i G^_bi(m) (smaller dynamic range
 // before rounding) and add the mean back exactly (FP64) against sum_i f^_i(m).
 static bool is_split16(int form) { return form == FBC_FORM_SPLIT_BF16 || form == FBC_FORM_SPLIT_FP16; }
 
@@ -248,8 +248,8 @@ static void compute_windows(fbc_ctx* c, const std::vector<double>& rho_cut, int 
 
 // Builds the offset table tab[t][o][6] for every line mode t = 0..nz_max/2 of the finest
 // line grid of the context (a cell with Nz layers reads table mode m * nz_max / Nz, the
-// same wavenumber), then either fills the dense stores of every cell and frees the
-// table, or keeps it for the offset-table form.
+// same wavenumber), then either fills the reduced forms' compact store and table and frees
+// it, or keeps it for the offset-table forms.
 static fbc_status assemble_all(fbc_ctx* c, hipStream_t st, const BondTable& bt, double* sn_d,
                                int logL) {
     const int m1 = c->opt.bz_m1, m2 = c->opt.bz_m2;
@@ -1085,7 +1085,7 @@ extern "C" fbc_status fbc_assemble_G(const fbc_lattice* lat, const fbc_cell* cel
     c->f_elems = f_off;
     c->u_elems = u_off;
     fbc_status s;
-    // the dense store is allocated once the negligible-block windows are known (assembly)
+    // the compact store is allocated once the negligible-block windows are known (assembly)
     if ((s = dev_alloc(c, &c->bfrag, b_off * b_elem_bytes(form))) != FBC_OK) goto fail_out;
     if ((s = dev_alloc(c, (void**)&c->cbuf, c_off * 8)) != FBC_OK) goto fail_out;
     if ((s = dev_alloc(c, (void**)&c->wbuf, w_off * 8)) != FBC_OK) goto fail_out;

@@ -71,20 +71,20 @@ __host__ __device__ inline int sym_idx(int c, int d) {
     return (lo == 0) ? (hi == 1 ? 3 : 4) : 5;
 }
 
-// One work item of the per-mode complex product: a tile of 4*RB row blocks of one mode
-// of one cell over one slice of K (the K split keeps enough work items to fill the chip
+// One work item of the per-mode complex product: JOB_ROWS rows (reduced forms) or TAB_COLS pad
+// columns (offset forms) of one mode of one cell over one slice of K (the K split keeps enough work items to fill the chip
 // evenly; the partial products of the slices are summed in fixed order by the inverse
 // line transform).  Offsets are in elements of the respective arrays.
 struct GemmJob {
-    int64_t a_off;   // A store (dense forms) or table mode base (offset form)
+    int64_t a_off;   // compact store or reduced table (reduced forms), table mode base (offset forms)
     int64_t b_off;   // B fragments of this mode
     int64_t c_off;   // output [ct][mp][nm][16] doubles: this mode's record, K slice
     int32_t mb;      // row blocks of the mode (mp / 16)
     int32_t kp;      // padded K' (row stride of the fragment arrays)
     int32_t rb0;     // first row block of this tile
     int32_t ct;      // column tiles (8 RHS each)
-    int32_t cell;    // cell index (offset form)
-    // K' range [k0, k1) (dense forms) or interface columns [k0, k1) (offset forms, multiples of 16); the
+    int32_t cell;    // cell index
+    // K' range [k0, k1) (reduced forms) or interface columns [k0, k1) (offset forms, multiples of 16); the
     // range is cyclic: indices at or beyond the padded K wrap to its start (windows around
     // the non-negligible blocks of a tile may straddle the end); k0 == k1: empty (zeros)
     int32_t k0, k1;
@@ -115,7 +115,7 @@ __host__ __device__ inline int wrap_k(int idx, int n) { return idx >= n ? idx - 
 // B fragments of the offset-table products, in the K order of their kernel (chunks of 16
 // interface columns; column 16 chunk + 4 q + g in lane group g): per column tile and chunk
 // 12 steps (q, d) of 64 units (Re- and Im-part operand), column n's four units of a step
-// adjacent as in the dense forms (bpos).  Element offset of the pair for B column n and
+// adjacent as in the reduced forms (bpos).  Element offset of the pair for B column n and
 // complex column k = 3 i + d; nch chunks.
 __host__ __device__ inline int64_t tab_frag_off(int n, int k, int nch) {
     const int i = k / 3, d = k - 3 * i;
@@ -189,7 +189,7 @@ struct CellPlan {
     int ct;              // column tiles of the B / output layouts (same for every cell)
     int ctr;             // column tiles holding RHS of this cell = ceil(R / 8)
     int64_t f_off, u_off;        // offsets (doubles) into caller's f and u
-    int64_t a_off;               // dense store offset (elements of the store type) of mode 0
+    int64_t a_off;               // compact store offset (elements of the store type) of mode 0
     int64_t b_off;               // B fragments offset (elements) of mode 0
     int64_t c_off;               // GEMM output offset (doubles) of mode 0, K slice 0
     int64_t c_split;             // doubles per K slice of the GEMM output (nm*ct*mp*16)

@@ -20,7 +20,7 @@ struct fbc_ctx {
     int job_tiles = 1;              // reduced forms: column tiles of a product job (1, 2, 4 or 8)
     // device buffers (all owned)
     std::vector<void*> allocs;
-    void* store = nullptr;          // dense store (FP64 / FP32 / split BF16)
+    void* store = nullptr;          // compact store (reduced forms)
     int64_t store_bytes = 0;
     void* bfrag = nullptr;          // GEMM B operand
     double* cbuf = nullptr;         // GEMM output

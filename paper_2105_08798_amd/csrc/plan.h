@@ -3,7 +3,8 @@
 // undefined-behaviour sanitizers, into a CPU check program.
 //  * distinct column offsets n_b - n_i and their dense lookup (Section 3.2: the Green
 //    blocks depend on the offset only);
-//  * negligible-block windows of the dense and offset-table products;
+//  * the order in which offset-table products take columns;
+//  * negligible-block windows of the reduced and offset-table products;
 //  * cluster trees and the block partition of the H-matrix form (Appendix C).
 #pragma once
 #include <cstdint>

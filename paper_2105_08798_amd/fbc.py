@@ -415,7 +415,8 @@ class MLP:
                                                      _stream_handle(stream)))
 
     def forward_noalloc(self, x, y, stream=None):
-        """The same forward pass with the activations in the library's static workspace."""
+        """The same forward pass without allocation: an output over its input is staged in the
+        library's static workspace."""
         import torch
         _lcheck(self._lib, self._lib.fbc_mlp_forward_noalloc(self.handle, _dptr(x, torch.float32),
                                                              _dptr(y, torch.float32), int(x.shape[0]),
