@@ -323,13 +323,13 @@ typedef struct {
     int job_order;             /* work-list order (see fbc_autotune)                      */
     int n_jobs;                /* work groups of the per-mode product launch              */
     double product_bytes;      /* HBM bytes one product launch must read and write: the
-                                  stored blocks of the K chunks it does not skip (dense
-                                  forms) or the table (offset forms), plus f^ and w^    */
+                                  blocks of the K chunks it does not skip (stored ones; the
+                                  table's records of the others), plus f^ and w^        */
     double product_flops;      /* real flops of the blocks it does not skip (8 per
                                   complex multiply-add)                                 */
     double skipped_fraction;   /* fraction of the (row, K) block area skipped             */
     int kernel_variant;        /* product kernel variant in use                           */
-    int n_variants;            /* variants of this context's product (1 for table forms)  */
+    int n_variants;            /* variants of this context's product (1 for forms 3 and 4)  */
     char kernel_shape[96];     /* readable shape of the product kernel in use             */
 } fbc_info;
 fbc_status fbc_get_info(const fbc_ctx* ctx, fbc_info* info);
